@@ -49,7 +49,7 @@ template <int D, bool CAUSAL, bool TAIL>
 __global__ __launch_bounds__(256, 2)
 void attn_fwd_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K, const bf16* __restrict__ V,
                      bf16* __restrict__ O, float* __restrict__ LSE,
-                     int Nq, int Nk, int num_q_tiles, int total_wg, float scale, int hq, int hkv,
+                     int Nq, int Nk, int num_q_tiles, int heads, int head_group, float scale, int hq, int hkv,
                      int n_splits, int tiles_per_split, float* __restrict__ O_part, float* __restrict__ LSE_part)
 {
     using S = FwdShape<D>;
@@ -65,16 +65,14 @@ void attn_fwd_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K, con
     const int l32 = lane & 31;
     const int h = lane >> 5;
 
-    // workgroup -> (head, query tile); heavy (late) query tiles first when causal
+    // workgroup -> (head, query tile), see TileOrder
     // Split over the keys (general-case variant, no mask; used for decode-shaped calls where heads and
     // query tiles alone cannot fill the chip): n_splits workgroups share one query tile, each takes
     // tiles_per_split (even) consecutive key tiles and leaves a normalised fp32 partial O and its LSE.
-    const int logical = xcd_remap(blockIdx.x, total_wg);
-    const int split = (TAIL && !CAUSAL) ? logical % n_splits : 0;
-    const int tile_id = (TAIL && !CAUSAL) ? logical / n_splits : logical;
-    const int bh = tile_id / num_q_tiles;
-    int qt = tile_id % num_q_tiles;
-    if (CAUSAL) qt = num_q_tiles - 1 - qt;
+    const int split = (TAIL && !CAUSAL) ? blockIdx.x % n_splits : 0;
+    const int tile_id = (TAIL && !CAUSAL) ? blockIdx.x / n_splits : blockIdx.x;
+    int bh, qt;
+    tile_of(tile_id, heads, num_q_tiles, head_group, bh, qt);
 
     // grouped-query attention: query head h of a batch entry reads key/value head h / (hq / hkv)
     const size_t head = (size_t)bh * Nq * D;
@@ -275,7 +273,7 @@ void attn_fwd_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K, con
     const float inv = 1.0f / l_tot;
     if (TAIL && !CAUSAL && n_splits > 1) {
         if (my_q < Nq) {
-            const size_t prow = ((size_t)split * (total_wg / n_splits / num_q_tiles) + bh) * Nq + my_q;   // [split][head][query]
+            const size_t prow = ((size_t)split * heads + bh) * Nq + my_q;   // [split][head][query]
             float* Op = O_part + prow * D;
 #pragma unroll
             for (int db = 0; db < D / 32; db++)
@@ -311,7 +309,7 @@ static hipError_t launch_fwd_tt(const void* q, const void* k, const void* v, voi
     const int total = B * H * num_q_tiles * n_splits;
     hipLaunchKernelGGL(kern, dim3(total), dim3(S::kThreads), 0, stream,
                        (const bf16*)q, (const bf16*)k, (const bf16*)v, (bf16*)o, lse,
-                       Nq, Nk, num_q_tiles, total, scale, H, Hkv, n_splits, tiles_per_split, o_part, lse_part);
+                       Nq, Nk, num_q_tiles, B * H, tile_order_heads(B * H, num_q_tiles, CAUSAL), scale, H, Hkv, n_splits, tiles_per_split, o_part, lse_part);
     return hipGetLastError();
 }
 

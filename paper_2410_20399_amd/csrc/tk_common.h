@@ -143,4 +143,18 @@ __device__ __forceinline__ int xcd_remap(int wg, int total) {
     return (total % 8 == 0) ? (wg % 8) * (total / 8) + wg / 8 : wg;
 }
 
+// Order of the (head, tile) work of a launch with one workgroup per tile.  Workgroups are dealt to the 8
+// XCDs round-robin, so with 8 * d heads walked together, head index innermost, every XCD (private L2)
+// works on d consecutive heads at a time; within that group the last tiles, the long ones when causal,
+// come first.  `group` = 8 * d comes from tile_order_heads() on the host.
+__device__ __forceinline__ void tile_of(int wg, int heads, int tiles, int group, int& head, int& tile) {
+    const int per_group = group * tiles;
+    const int g = wg / per_group, r = wg - g * per_group;
+    int in_group = heads - g * group;                   // the last group may be smaller
+    if (in_group > group) in_group = group;
+    const int rank = r / in_group, j = r - rank * in_group;
+    head = g * group + (in_group % 8 == 0 ? (j % 8) * (in_group / 8) + j / 8 : j);
+    tile = tiles - 1 - rank;
+}
+
 }  // namespace tk

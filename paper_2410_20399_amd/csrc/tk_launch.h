@@ -24,6 +24,25 @@ inline hipError_t compute_unit_count(int* cus) {
     return e;
 }
 
+// Heads that tile_of() walks together.  Without a mask all tiles weigh the same: one head per XCD, the best
+// reuse of its L2.  With the causal mask a tile's work grows with its index, and an XCD's 64 resident
+// workgroups (32 compute units x 2) are best given out longest first: d heads per XCD, as many as keep
+// d * tiles within one and a half times that, preferably a divisor of an XCD's share.  (One head after the
+// other gives a compute unit the same tile index of two heads, two long ones or two short ones:
+// B2 H16 N2048 D128 62 -> 50 us, B1 Hq32 Hkv8 N3001 111 -> 89 us; more heads than this and the L2 and the
+// balance at the end both get worse: the first of these 54 us with 6 heads, 56 us with 8.)
+inline int tile_order_heads(int heads, int tiles, bool causal) {
+    const int per_xcd = (heads + 7) / 8;
+    int d = 1;
+    if (causal) {
+        d = 96 / tiles < per_xcd ? 96 / tiles : per_xcd;
+        if (d < 1) d = 1;
+        for (int e = d; 2 * e > d; e--)
+            if (per_xcd % e == 0) { d = e; break; }
+    }
+    return 8 * d < heads ? 8 * d : heads;
+}
+
 // H query heads share Hkv key/value heads in groups of H / Hkv consecutive heads (Hkv == H: plain
 // multi-head attention); Nq queries, Nk keys per head (causal: aligned at their ends, Nq <= Nk).
 // q, o, d_o, dq: [B,H,Nq,D]; k, v, dk, dv: [B,Hkv,Nk,D]; lse, delta: [B,H,Nq].
