@@ -295,9 +295,9 @@ int tk_attn_decode_plan(int B, int Hq, int Hkv, int Nk, int D, int compute_units
  *
  *   a : in,  bf16 [M, K] row-major        b : in, bf16 [K, N] row-major        c : out, bf16 [M, N] row-major
  * M >= 1; N and K positive multiples of 8, so that every row starts on a 16-byte boundary
- * (TK_ERR_BAD_DIM otherwise).  The kernel works on 256 x 256 x 64 tiles; shapes that are not multiples
- * of those run a variant that masks the edge tiles (rows and columns past the end are not stored, the
- * part of the last K step past K contributes zeros).
+ * (TK_ERR_BAD_DIM otherwise).  The tile shape (256 x 256 down to 32 x 64, the small ones also with K split
+ * inside the workgroup) is chosen by M, N and K; rows and columns past the end are not stored, the part of
+ * the last K step past K contributes zeros.
  * No workspace; the result is bit-reproducible (every element is one fixed-order accumulation).
  */
 int tk_gemm(const void* a, const void* b, void* c, int M, int N, int K, void* stream);

@@ -2,250 +2,321 @@
 // appendix as a second workload, and the reference point for what a kernel made of MFMAs and LDS
 // traffic alone sustains on this chip.
 //
-// One workgroup = 4 waves (one per SIMD) = a 256 x 256 tile of C; wave (wm, wn) owns the 128 x 128
-// quadrant and keeps its 16 accumulator blocks (256 registers) for the whole K loop.  A and B are
-// streamed in steps of 64 along K through a two-stage LDS ring filled by direct global->LDS loads:
+// One workgroup computes a TM x TN tile of C with WM x WN waves, each wave a (TM/WM) x (TN/WN) part of
+// it in 16 x 16 accumulator blocks.  A and B are streamed in steps of 64 along K through a ring of
+// kStages LDS stages filled by direct global->LDS loads:
 //
-//   A stage  256 rows x 64 k    (128-byte rows, chunk-swizzled for 16-row same-chunk b128 reads)
-//   B stage  64 k x 256 columns, kept as two 128-column halves (256-byte rows, chunk-swizzled for
-//            the transposing reads that turn k-major rows into "8 consecutive k per lane")
+//   A stage  TM rows x 64 k     (128-byte rows; 16-byte chunks XOR-swizzled for 16-row same-chunk b128 reads)
+//   B stage  64 k x TN columns, as panels of 64 columns (128-byte rows; swizzled for the transposing reads
+//            that turn k-major rows into "8 consecutive k per lane")
 //
-// The products are issued as D^T: v_mfma(B fragment, A fragment), so that a lane owns one ROW of C
-// and stores 4 consecutive columns at a time.  Fragments of k-sub-step t+1 are read from LDS while
-// the 16 MFMAs of sub-step t run; the barrier that frees a stage sits before the last sub-step of
-// a step, whose MFMAs cover the first fragment reads of the next stage.
+// The products are issued as D^T: v_mfma_f32_16x16x32_bf16(B fragment, A fragment), so that a lane owns one
+// ROW of C and stores 4 consecutive columns at a time.  The fragments of one half step (32 k) are read from
+// LDS while the MFMAs of the half step before it run; the barrier that frees a stage sits in the middle of a
+// step, and the load that refills it is issued right behind it.
+//
+// KS > 1: KS groups of WM x WN waves in one workgroup share the K range, group g taking the steps g, g + KS, ...
+// with a ring of its own; the partial sums meet in LDS at the end, always in the same order.
 #include "tk_common.h"
 #include "tk_launch.h"
 
 namespace tk {
 
-struct GemmShape {
-    static constexpr int kThreads = 256;
-    static constexpr int kTileM = 256, kTileN = 256, kTileK = 64;
-    static constexpr int kARowBytes = kTileK * 2;                 // 128
-    static constexpr int kBRowBytes = 128 * 2;                    // one 128-column half
-    static constexpr int kABytes = kTileM * kARowBytes;           // 32 KB
-    static constexpr int kBHalfBytes = kTileK * kBRowBytes;       // 16 KB
-    static constexpr int kStageBytes = kABytes + 2 * kBHalfBytes; // 64 KB
-    static constexpr int kALoads = kABytes / (kThreads * 16);     // 8 per thread
-    static constexpr int kBLoads = kBHalfBytes / (kThreads * 16); // 4 per thread and half
-    static constexpr int kLoadsPerStage = kALoads + 2 * kBLoads;  // 16
-    static constexpr int kSuperM = 8;                             // tile rows walked together (L2 reuse of the B panels)
-};
-
-// sixteen zero bytes: the source of the A chunks that lie beyond K in an edge tile
+// sixteen zero bytes: the source of the chunks of A and the rows of B that lie beyond K
 __device__ __attribute__((aligned(16))) const bf16 g_gemm_zero[8] = {};
 
+__device__ __forceinline__ f32x4 mfma16(bf16x8 a, bf16x8 b, f32x4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+}
+
+// A: 16 lanes read the same chunk of 16 consecutive rows; 128-byte rows alternate between the two halves of the banks
 __device__ __forceinline__ int gemm_swz_a(int row) { return (row >> 1) & 7; }
-__device__ __forceinline__ int gemm_swz_b(int row) { return ((row & 3) << 2) | ((row >> 2) & 3); }
+// B: 32 lanes read 32 bytes of the rows r..r+3 and r+8..r+11 (one transposing read)
+__device__ __forceinline__ int gemm_swz_b(int row) { return (((row >> 1) & 1) | (((row >> 3) & 1) << 1)) << 1; }
 
-// EDGE: the general case (M not a multiple of 256, N not of 256, or K not of 64; N and K multiples of 8
-// so that every row starts on a 16-byte boundary).  The kernel still works on whole 256 x 256 x 64 tiles:
-// rows of A past M fetch row M-1 and columns of B past N fetch the last 8 columns (their results are never
-// stored), the chunks of A and the rows of B past K are fetched from a block of zeros so that they add
-// nothing, and rows / columns past the end are not stored.  The aligned case compiles without any of this.
-template <bool EDGE>
-__global__ __launch_bounds__(256, 1)
+template <int TM, int TN, int WM, int WN, int KS, int STAGES>
+struct GemmTile {
+    static constexpr int kTileM = TM, kTileN = TN, kTileK = 64;
+    static constexpr int kGroupThreads = 64 * WM * WN, kThreads = kGroupThreads * KS;
+    static constexpr int kStages = STAGES;
+    static constexpr int kPartM = TM / WM, kPartN = TN / WN;            // of one wave
+    static constexpr int kBlocksM = kPartM / 16, kBlocksN = kPartN / 16;
+    static constexpr int kABytes = TM * 128, kStageBytes = kABytes + TN * 128;
+    static constexpr int kALoads = TM * 8 / kGroupThreads, kBLoads = TN * 8 / kGroupThreads;    // per thread and step
+    static constexpr int kLoads = kALoads + kBLoads;
+    static constexpr int kLdsBytes = KS * STAGES * kStageBytes;
+    static_assert(TM * 8 % kGroupThreads == 0 && TN * 8 % kGroupThreads == 0 && TN % 64 == 0, "whole loads per thread");
+    static_assert((KS - 1) * TM * TN * 4 <= kLdsBytes && kLdsBytes <= 160 * 1024, "LDS");
+};
+
+// Any M >= 1, N and K multiples of 8 (so that every row starts on a 16-byte boundary).  The kernel works on
+// whole tiles: rows of A past M fetch row M-1 and columns of B past N fetch the last 8 columns (their results
+// are never stored), and in the step that runs past K the chunks of A and the rows of B beyond it are fetched
+// from a block of zeros.  The offsets are clamped once, ahead of the loop; a step that lies within K runs the
+// same instructions whatever the shape.
+template <class S, int WM, int WN, int KS, int WAVES_PER_SIMD>
+__global__ __launch_bounds__(S::kThreads, WAVES_PER_SIMD)
 void gemm_kernel(const bf16* __restrict__ A, const bf16* __restrict__ B, bf16* __restrict__ C,
-                 int M, int N, int K, int tiles_m, int tiles_n)
+                 int M, int N, int K, int tiles_m, int tiles_n, int super_m)
 {
-    using S = GemmShape;
-    __shared__ __attribute__((aligned(1024))) char ring[2 * S::kStageBytes];
+    constexpr int MB = S::kBlocksM, NB = S::kBlocksN;
+    __shared__ __attribute__((aligned(1024))) char lds[S::kLdsBytes];
 
-    const int tid = threadIdx.x;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int lane = tid & 63;
-    const int l32 = lane & 31;
-    const int h = lane >> 5;
-    const int wm = wave >> 1, wn = wave & 1;
+    const int wave_all = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int kg = KS == 1 ? 0 : wave_all / (WM * WN);              // this wave's share of K
+    const int wave = KS == 1 ? wave_all : wave_all % (WM * WN);
+    const int tid = threadIdx.x - kg * S::kGroupThreads;
+    const int lane = threadIdx.x & 63;
+    const int l16 = lane & 15;
+    const int quad = lane >> 4;
+    const int wm = wave / WN, wn = wave % WN;
+    char* const ring = lds + kg * (S::kStages * S::kStageBytes);
 
-    // tile order: XCD-contiguous ids, then groups of kSuperM tile rows walked column by column, so
+    // tile order: XCD-contiguous ids, then groups of super_m tile rows walked column by column, so
     // the workgroups resident on one XCD share a few A and B panels in its L2 (Section 3.3 of the
     // paper makes the same point about block order for its GEMM)
     const int total = tiles_m * tiles_n;
     const int logical = xcd_remap(blockIdx.x, total);
-    const int super_rows = (tiles_m / S::kSuperM) * S::kSuperM;
+    const int super_rows = (tiles_m / super_m) * super_m;
     int tm, tn;
     if (logical < super_rows * tiles_n) {
-        const int grp = logical / (S::kSuperM * tiles_n), in = logical % (S::kSuperM * tiles_n);
-        tm = grp * S::kSuperM + in % S::kSuperM;
-        tn = in / S::kSuperM;
+        const int grp = logical / (super_m * tiles_n), in = logical % (super_m * tiles_n);
+        tm = grp * super_m + in % super_m;
+        tn = in / super_m;
     } else {
         const int rest = tiles_m - super_rows, in = logical - super_rows * tiles_n;
         tm = super_rows + in % rest;
         tn = in / rest;
     }
-    const size_t m0 = (size_t)tm * S::kTileM, n0 = (size_t)tn * S::kTileN;
+    const int m0 = tm * S::kTileM, n0 = tn * S::kTileN;
 
-    // ---- per-thread source offsets (elements) of the direct-to-LDS loads of one stage
-    // A: LDS position s = it*256 + tid holds (row = s / 8, physical chunk = s % 8)
-    // B half t: position s holds (k row = s / 16, physical chunk = s % 16)
-    size_t a_src[S::kALoads], b_src[S::kBLoads];
+    // ---- per-thread source offsets (bytes from the tile's first row / column) of the direct-to-LDS loads of one stage
+    // A: LDS position s = it * threads + tid holds (row = s / 8, physical chunk = s % 8)
+    // B: position s holds (panel = s / 512, k row = s / 8 % 64, physical chunk = s % 8)
+    const bf16* const a_tile = A + (size_t)m0 * K;
+    const bf16* const b_tile = B + n0;
+    uint32_t a_src[S::kALoads], b_src[S::kBLoads];
 #pragma unroll
     for (int it = 0; it < S::kALoads; it++) {
-        const int s = it * S::kThreads + tid, row = s >> 3, pc = s & 7;
-        a_src[it] = (m0 + row) * K + ((pc ^ gemm_swz_a(row)) << 3);
+        const int s = it * S::kGroupThreads + tid, pc = s & 7;
+        int row = s >> 3;
+        const int chunk = pc ^ gemm_swz_a(row);
+        if (row > M - 1 - m0) row = M - 1 - m0;
+        a_src[it] = ((uint32_t)row * (uint32_t)K + chunk * 8) * 2;
     }
 #pragma unroll
     for (int it = 0; it < S::kBLoads; it++) {
-        const int s = it * S::kThreads + tid, row = s >> 4, pc = s & 15;
-        b_src[it] = (size_t)row * N + n0 + ((pc ^ gemm_swz_b(row)) << 3);
+        const int s = it * S::kGroupThreads + tid, row = (s >> 3) & 63, pc = s & 7;
+        int col = (s >> 9) * 64 + ((pc ^ gemm_swz_b(row)) << 3);
+        if (col > N - 8 - n0) col = N - 8 - n0;
+        b_src[it] = ((uint32_t)row * (uint32_t)N + col) * 2;
     }
-    auto issue_stage = [&](int step) {
-        char* base = ring + (step & 1) * S::kStageBytes + wave * 1024;
-        if (!EDGE) {
-            const bf16* a = A + (size_t)step * S::kTileK;
-            const bf16* b = B + (size_t)step * S::kTileK * N;
+    auto issue_stage = [&](int step, int stage_off) {
+        char* base = ring + stage_off + wave * 1024;
+        const int k0 = step * S::kTileK;
+        if (__builtin_expect(k0 + S::kTileK <= K, 1)) {
+            const bf16* a = a_tile + k0;
+            const bf16* b = b_tile + (size_t)k0 * N;
 #pragma unroll
             for (int it = 0; it < S::kALoads; it++)
-                load_global_to_lds16_untracked(a + a_src[it], base + it * (S::kThreads * 16));
+                load_global_to_lds16_sbase_untracked(a, a_src[it], base + it * (S::kGroupThreads * 16));
 #pragma unroll
-            for (int t = 0; t < 2; t++)
-#pragma unroll
-                for (int it = 0; it < S::kBLoads; it++)
-                    load_global_to_lds16_untracked(b + b_src[it] + 128 * t,
-                                                   base + S::kABytes + t * S::kBHalfBytes + it * (S::kThreads * 16));
+            for (int it = 0; it < S::kBLoads; it++)
+                load_global_to_lds16_sbase_untracked(b, b_src[it], base + S::kABytes + it * (S::kGroupThreads * 16));
         } else {
-            const int k0 = step * S::kTileK;
+            const int left = K - k0;            // <= 0: a step of a K share that the others have and this one has not
+            const int at = left > 0 ? k0 : 0;   // (no address past the matrices is formed)
+            const char* a = (const char*)(a_tile + at);
+            const char* b = (const char*)(b_tile + (size_t)at * N);
 #pragma unroll
             for (int it = 0; it < S::kALoads; it++) {
-                const int s = it * S::kThreads + tid, row = s >> 3, pc = s & 7;
-                size_t r = m0 + row;
-                if (r > (size_t)M - 1) r = (size_t)M - 1;
-                const int k = k0 + ((pc ^ gemm_swz_a(row)) << 3);
-                const bf16* src = k < K ? A + r * K + k : g_gemm_zero;
-                load_global_to_lds16_untracked(src, base + it * (S::kThreads * 16));
+                const int s = it * S::kGroupThreads + tid;
+                const int k = ((s & 7) ^ gemm_swz_a(s >> 3)) << 3;
+                load_global_to_lds16_untracked(k < left ? a + a_src[it] : (const char*)g_gemm_zero, base + it * (S::kGroupThreads * 16));
             }
 #pragma unroll
-            for (int t = 0; t < 2; t++)
-#pragma unroll
-                for (int it = 0; it < S::kBLoads; it++) {
-                    const int s = it * S::kThreads + tid, row = s >> 4, pc = s & 15;
-                    const int k = k0 + row;
-                    size_t col = n0 + 128 * t + ((pc ^ gemm_swz_b(row)) << 3);
-                    if (col > (size_t)N - 8) col = (size_t)N - 8;
-                    const bf16* src = k < K ? B + (size_t)k * N + col : g_gemm_zero;
-                    load_global_to_lds16_untracked(src, base + S::kABytes + t * S::kBHalfBytes + it * (S::kThreads * 16));
-                }
+            for (int it = 0; it < S::kBLoads; it++) {
+                const int row = ((it * S::kGroupThreads + tid) >> 3) & 63;
+                load_global_to_lds16_untracked(row < left ? b + b_src[it] : (const char*)g_gemm_zero,
+                                               base + S::kABytes + it * (S::kGroupThreads * 16));
+            }
         }
     };
 
     // ---- per-lane LDS read offsets
-    // A fragment (second MFMA operand: lane <-> row of A, 8 consecutive k): row 32a + l32 of the wave's
-    // 128 rows, logical chunk 2*kb + h
-    const int a_lane = (wm * 128 + l32) * S::kARowBytes + ((h ^ gemm_swz_a(l32)) << 4);
-    // B fragment (first MFMA operand: lane <-> column of B, 8 consecutive k) through transposing
-    // reads: 16-lane group G = lane/16 -> (column half = G%2, k half = G/2 = h); lane j of the group
-    // addresses k row 8h + j/4 (second read: +4), columns 32b + 16*(G%2) + 4*(j%4)
-    const int j16 = lane & 15;
-    const int b_row = 8 * h + (j16 >> 2);
-    const int b_lane = b_row * S::kBRowBytes + (((2 * ((lane >> 4) & 1) + ((j16 & 3) >> 1)) ^ gemm_swz_b(b_row)) << 4) + ((j16 & 1) << 3);
+    // A fragment (second MFMA operand: lane <-> row of A, k = 8 * quad ..+7): row 16a + l16, logical chunk 4 * half + quad
+    const int a_lane = (wm * S::kPartM + l16) * 128 + ((quad ^ gemm_swz_a(l16)) << 4);
+    // B fragment (first MFMA operand: lane <-> column of B, same k) through transposing reads: lane j of a
+    // quad addresses k row 8 * quad + j / 4 (second read: +4), columns 4 * (j % 4) of a 16-column block
+    const int b_row = 8 * quad + (l16 >> 2);
+    const int b_lane = S::kABytes + b_row * 128 + ((((l16 & 3) >> 1) ^ gemm_swz_b(b_row)) << 4) + ((l16 & 1) << 3);
 
-    f32x16 acc[4][4];      // [column block b][row block a]
+    f32x4 acc[NB][MB];
 #pragma unroll
-    for (int b = 0; b < 4; b++)
+    for (int b = 0; b < NB; b++)
 #pragma unroll
-        for (int a = 0; a < 4; a++)
-#pragma unroll
-            for (int r = 0; r < 16; r++) acc[b][a][r] = 0.f;
+        for (int a = 0; a < MB; a++) acc[b][a] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-    bf16x8 af[2][4], bfr[2][4];     // two sets of fragments: one being multiplied, one being read
-    auto read_frags = [&](int set, int step, int kb) {
-        const char* as = ring + (step & 1) * S::kStageBytes;
-        const char* bs = as + S::kABytes + wn * S::kBHalfBytes;
+    bf16x8 af[2][MB], bfr[2][NB];       // two sets of fragments: one being multiplied, one being read
+    auto read_frags = [&](int set, const char* stage, int half) {
 #pragma unroll
-        for (int a = 0; a < 4; a++)
-            af[set][a] = lds_read_b128(as, (a_lane ^ ((2 * kb) << 4)) + a * 32 * S::kARowBytes);
+        for (int a = 0; a < MB; a++) af[set][a] = lds_read_b128(stage, (a_lane ^ (half << 6)) + a * 16 * 128);
 #pragma unroll
-        for (int b = 0; b < 4; b++) {
-            // k rows 16kb + 8h + (0..3) and +4: the +4 flips bit 0 of the swizzle's low field
-            const int row_off = 16 * kb * S::kBRowBytes;
-            const int x0 = (4 * b) << 4, x1 = ((4 * b) ^ 1) << 4;
-            bfr[set][b] = concat(lds_read_tr16(bs, (b_lane ^ x0) + row_off),
-                                 lds_read_tr16(bs, (b_lane ^ x1) + row_off + 4 * S::kBRowBytes));
+        for (int b = 0; b < NB; b++) {
+            const int block = wn * NB + b;      // 16-column block of the tile
+            const int off = (block >> 2) * 8192 + half * 32 * 128, x = b_lane ^ ((block & 3) << 5);
+            bfr[set][b] = concat(lds_read_tr16(stage, x + off), lds_read_tr16(stage, x + off + 4 * 128));
         }
     };
     auto multiply = [&](int set) {
 #pragma unroll
-        for (int b = 0; b < 4; b++)
+        for (int b = 0; b < NB; b++)
 #pragma unroll
-            for (int a = 0; a < 4; a++) acc[b][a] = mfma32(bfr[set][b], af[set][a], acc[b][a]);
+            for (int a = 0; a < MB; a++) acc[b][a] = mfma16(bfr[set][b], af[set][a], acc[b][a]);
     };
-
-    // schedule of one sub-step: the 12 fragment reads go out one per MFMA, ahead of the remaining MFMAs
+    // schedule of one half step: the fragment reads spread over its MFMAs
     auto interleave = [&]() {
+        constexpr int kReads = MB + 2 * NB, kMfmas = MB * NB, kPer = kMfmas / kReads;
+        if constexpr (kPer > 0) {
 #pragma unroll
-        for (int i = 0; i < 12; i++) {
-            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // DS read
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // MFMA
+            for (int i = 0; i < kReads; i++) {
+                __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);      // LDS read
+                __builtin_amdgcn_sched_group_barrier(0x008, kPer, 0);   // MFMA
+            }
+            __builtin_amdgcn_sched_group_barrier(0x008, kMfmas - kPer * kReads, 0);
         }
-        __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);
         __builtin_amdgcn_sched_barrier(0);
     };
 
-    const int n_steps = (K + S::kTileK - 1) / S::kTileK;
-    issue_stage(0);
-    if (n_steps > 1) issue_stage(1);
-    if (n_steps > 1) wait_vmcnt<S::kLoadsPerStage>(); else wait_vmcnt<0>();
+    const int steps_all = (K + S::kTileK - 1) / S::kTileK;
+    const int n_steps = (steps_all + KS - 1) / KS;      // of every group (the last one of some may lie past K)
+#pragma unroll
+    for (int s = 0; s < S::kStages; s++)
+        if (s < n_steps) issue_stage(s * KS + kg, s * S::kStageBytes);
+    if (n_steps >= S::kStages) wait_vmcnt<(S::kStages - 1) * S::kLoads>(); else wait_vmcnt<0>();
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_sched_barrier(0);
-    read_frags(0, 0, 0);
+    read_frags(0, ring, 0);
 
+    int stage = 0;
 #pragma unroll 1
     for (int s = 0; s < n_steps; s++) {
-        // sub-steps 0..2: multiply one set while the next sub-step's fragments are read into the other
-        read_frags(1, s, 1);
+        const int old = stage;
+        read_frags(1, ring + stage, 1);
         multiply(0);
         interleave();
-        read_frags(0, s, 2);
-        multiply(1);
-        interleave();
-        read_frags(1, s, 3);
-        multiply(0);
-        interleave();
-        // Once every wave's last fragment reads of this stage have completed the stage can be refilled;
-        // the next stage (issued one step ago) must have landed before its first fragments are read.
-        __builtin_amdgcn_s_waitcnt(0x0070);      // vmcnt(0) and lgkmcnt(0)
+        stage = stage + S::kStageBytes == S::kStages * S::kStageBytes ? 0 : stage + S::kStageBytes;
+        // Every wave's last reads of this step's stage have completed, so it can be refilled; the next
+        // step's stage (issued kStages - 1 steps ago) must have landed, the newer ones stay in flight.
+        if (s + S::kStages <= n_steps) wait_vmcnt_lds_done<(S::kStages - 2) * S::kLoads>(); else wait_vmcnt_lds_done<0>();
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_sched_barrier(0);
-        if (s + 2 < n_steps) issue_stage(s + 2);
+        if (s + S::kStages < n_steps) issue_stage((s + S::kStages) * KS + kg, old);
         __builtin_amdgcn_sched_barrier(0);
-        if (s + 1 < n_steps) read_frags(0, s + 1, 0);
+        read_frags(0, ring + stage, 0);         // (after the last step: a stage nobody writes, into fragments nobody uses)
         multiply(1);
         interleave();
     }
 
-    // ---- epilogue: lane <-> row of C; register r of block (b, a) <-> column 32b + 8*(r/4) + 4h + r%4
+    if constexpr (KS > 1) {
+        wait_vmcnt_lds_done<0>();
+        __builtin_amdgcn_s_barrier();
+        // partial sums of the groups 1.. : [group][wave][block][lane] x 16 bytes
+        char* part = lds + wave * (NB * MB * 1024) + lane * 16;
+        if (kg > 0) {
 #pragma unroll
-    for (int a = 0; a < 4; a++) {
-        const size_t row = m0 + wm * 128 + 32 * a + l32;
-        if (EDGE && row >= (size_t)M) continue;
-        bf16* crow = C + row * N + n0 + wn * 128;
+            for (int b = 0; b < NB; b++)
 #pragma unroll
-        for (int b = 0; b < 4; b++)
+                for (int a = 0; a < MB; a++)
+                    *(f32x4*)(part + (kg - 1) * (S::kTileM * S::kTileN * 4) + (b * MB + a) * 1024) = acc[b][a];
+        }
+        __syncthreads();
+        if (kg > 0) return;
 #pragma unroll
-            for (int g = 0; g < 4; g++) {
-                const int col = 32 * b + 8 * g + 4 * h;      // within the wave's 128 columns; N is a multiple of 8
-                if (EDGE && n0 + wn * 128 + col >= (size_t)N) continue;
-                bf16x2 lo = cvt2(acc[b][a][4 * g + 0], acc[b][a][4 * g + 1]);
-                bf16x2 hi = cvt2(acc[b][a][4 * g + 2], acc[b][a][4 * g + 3]);
-                *(bf16x4*)(crow + col) = __builtin_shufflevector(lo, hi, 0, 1, 2, 3);
-            }
+        for (int g = 0; g < KS - 1; g++)
+#pragma unroll
+            for (int b = 0; b < NB; b++)
+#pragma unroll
+                for (int a = 0; a < MB; a++)
+                    acc[b][a] += *(const f32x4*)(part + g * (S::kTileM * S::kTileN * 4) + (b * MB + a) * 1024);
+    }
+
+    // ---- epilogue: lane <-> row of C; registers of block (b, a) <-> columns 16b + 4 * quad ..+3 (N is a multiple of 8)
+#pragma unroll
+    for (int a = 0; a < MB; a++) {
+        const size_t row = (size_t)m0 + wm * S::kPartM + 16 * a + l16;
+        if (row >= (size_t)M) continue;
+        bf16* crow = C + row * N;
+#pragma unroll
+        for (int b = 0; b < NB; b++) {
+            const size_t col = (size_t)n0 + wn * S::kPartN + 16 * b + 4 * quad;
+            if (col >= (size_t)N) continue;
+            *(bf16x4*)(crow + col) = __builtin_shufflevector(cvt2(acc[b][a][0], acc[b][a][1]), cvt2(acc[b][a][2], acc[b][a][3]), 0, 1, 2, 3);
+        }
     }
 }
 
+template <int TM, int TN, int WM, int WN, int KS, int STAGES, int WAVES_PER_SIMD>
+static hipError_t launch_tile(const void* a, const void* b, void* c, int M, int N, int K, hipStream_t stream)
+{
+    using S = GemmTile<TM, TN, WM, WN, KS, STAGES>;
+    const int tiles_m = (M + TM - 1) / TM, tiles_n = (N + TN - 1) / TN;
+    constexpr int super_m = TM >= 256 ? 4 : TM >= 128 ? 8 : 16;     // tile rows walked together
+    hipLaunchKernelGGL((gemm_kernel<S, WM, WN, KS, WAVES_PER_SIMD>), dim3(tiles_m * tiles_n), dim3(S::kThreads), 0, stream,
+                       (const bf16*)a, (const bf16*)b, (bf16*)c, M, N, K, tiles_m, tiles_n, super_m);
+    return hipGetLastError();
+}
+
+// The tile shapes, what their steps cost on MI355X, and the choice between them.  A call takes about
+//   3 us + (tiles on the busiest of the compute units) * (steps of a tile / KS) * us per step,
+// and the shape with the smallest sum is taken.  Measured (us per 64-wide k step of one tile; one tile on a unit /
+// several of them after or next to each other), and the time at 8192^3 that follows:
+//   256x256  8 waves   1.50 / 1.57    0.79 ms = 1.39 PFLOP/s (the best rate: least L2 and LDS traffic per flop)
+//   192x256  8 waves   1.15 / 1.25    0.95 ms       64x128  4 waves  0.42 / 0.34   1.46 ms
+//   128x256  8 waves   0.88 / 0.93    0.95 ms       64x64   4 waves  0.25 / 0.24   2.05 ms (L2 bound: 16 KB per 0.5 MFLOP)
+//   256x128  8 waves   0.87 / 0.92    0.94 ms       64x64  K split in 2:  0.43 / 0.53 per two steps
+//   128x192  8 waves   0.76 / 0.735   1.04 ms       32x64  K split in 2:  0.42 / 0.42 per two steps
+//   128x128  8 waves   0.57 / 0.56    1.15 ms       32x64  K split in 4:  0.60 / 0.75 per four steps
+//   128x128  4 waves, two workgroups per compute unit: 0.68 alone, 0.95 for two   1.02 ms
+// (A single 256x256 tile with four waves of 128x128, one per SIMD, took 0.92 ms: nothing filled the gaps of a
+// wave.  With two waves per SIMD and 16x16x32 MFMAs, which move half the accumulator bits per flop of the 32x32x16
+// form, the same LDS ring gives 0.79.)
+struct GemmChoice {
+    hipError_t (*launch)(const void*, const void*, void*, int, int, int, hipStream_t);
+    int tile_m, tile_n, ks;
+    float one, more;        // us per step: the only tile of a compute unit; every tile of several
+};
+static const GemmChoice kGemmChoices[] = {
+    {launch_tile<256, 256, 2, 4, 1, 2, 2>, 256, 256, 1, 1.50f, 1.57f},
+    {launch_tile<192, 256, 2, 4, 1, 2, 2>, 192, 256, 1, 1.15f, 1.25f},
+    {launch_tile<256, 128, 4, 2, 1, 3, 2>, 256, 128, 1, 0.87f, 0.92f},
+    {launch_tile<128, 256, 2, 4, 1, 3, 2>, 128, 256, 1, 0.88f, 0.93f},
+    {launch_tile<128, 192, 2, 4, 1, 3, 2>, 128, 192, 1, 0.76f, 0.735f},
+    {launch_tile<128, 128, 2, 4, 1, 4, 2>, 128, 128, 1, 0.57f, 0.56f},
+    {launch_tile<128, 128, 2, 2, 1, 2, 2>, 128, 128, 1, 0.68f, 0.475f},
+    {launch_tile<64, 128, 2, 2, 1, 3, 2>, 64, 128, 1, 0.42f, 0.34f},
+    {launch_tile<64, 64, 2, 2, 1, 3, 2>, 64, 64, 1, 0.25f, 0.24f},
+    {launch_tile<64, 64, 2, 2, 2, 3, 2>, 64, 64, 2, 0.43f, 0.53f},
+    {launch_tile<32, 64, 2, 2, 2, 4, 2>, 32, 64, 2, 0.42f, 0.42f},
+    {launch_tile<32, 64, 1, 4, 4, 3, 4>, 32, 64, 4, 0.60f, 0.75f},
+};
+
 hipError_t launch_gemm(const void* a, const void* b, void* c, int M, int N, int K, hipStream_t stream)
 {
-    using S = GemmShape;
-    const int tiles_m = (M + S::kTileM - 1) / S::kTileM, tiles_n = (N + S::kTileN - 1) / S::kTileN;
-    const bool edge = M % S::kTileM || N % S::kTileN || K % S::kTileK;
-    if (edge)
-        hipLaunchKernelGGL(gemm_kernel<true>, dim3(tiles_m * tiles_n), dim3(S::kThreads), 0, stream,
-                           (const bf16*)a, (const bf16*)b, (bf16*)c, M, N, K, tiles_m, tiles_n);
-    else
-        hipLaunchKernelGGL(gemm_kernel<false>, dim3(tiles_m * tiles_n), dim3(S::kThreads), 0, stream,
-                           (const bf16*)a, (const bf16*)b, (bf16*)c, M, N, K, tiles_m, tiles_n);
-    return hipGetLastError();
+    int cus = 0;
+    hipError_t e = compute_unit_count(&cus);
+    if (e != hipSuccess) return e;
+    const GemmChoice* best = nullptr;
+    double best_us = 0;
+    for (const GemmChoice& g : kGemmChoices) {
+        const long long tiles = (((long long)M + g.tile_m - 1) / g.tile_m) * (((long long)N + g.tile_n - 1) / g.tile_n);
+        if (tiles > 0x7fffffffLL) continue;
+        const long long rounds = (tiles + cus - 1) / cus;
+        const int steps = (K + 63) / 64, share = (steps + g.ks - 1) / g.ks;
+        const double us = (double)share * (rounds == 1 ? g.one : (double)rounds * g.more);
+        if (!best || us < best_us) { best = &g; best_us = us; }
+    }
+    return best->launch(a, b, c, M, N, K, stream);
 }
 
 }  // namespace tk

@@ -42,7 +42,7 @@ def test_gemm_small_full(attn, M, N, K):
 @pytest.mark.parametrize("M,N,K", [(1, 8, 8), (5, 24, 40), (255, 264, 72), (257, 248, 200), (300, 520, 1000), (1000, 1000, 1000),
                                    (256, 256, 56), (513, 256, 64), (256, 776, 128)])
 def test_gemm_edge_tiles(attn, M, N, K):
-    """Shapes that are not multiples of the 256 x 256 x 64 tile: every element against the oracle, and the
+    """Shapes that are not multiples of any tile: every element against the oracle, and the
     memory after C untouched (rows and columns past the end are masked, not clipped by luck)."""
     a, b = make(M, N, K, 1840 + M + N + K)
     print(f"launch gemm edge M{M} N{N} K{K}", flush=True)
@@ -79,3 +79,25 @@ def test_gemm_full_size_sampled_and_reproducible(attn):
     attn.gemm(ad, bd, out=c3)
     torch.cuda.synchronize()
     assert torch.equal(c3, c1)
+
+
+# One or two sizes for each tile shape the launcher chooses from (256x256 .. 32x64, K split in 2 and in 4): ragged
+# rows and columns, a K that ends inside a step, fewer steps than ring stages, K shares of unequal length.
+@pytest.mark.parametrize("M,N,K", [(3101, 3888, 72), (2731, 5000, 328), (2657, 3416, 200), (3352, 3288, 24), (1488, 4040, 264),
+                                   (1351, 5488, 392), (2455, 1808, 328), (863, 5192, 72), (1425, 1464, 456), (1974, 1152, 8),
+                                   (1641, 4944, 200), (1010, 1104, 136), (805, 8, 24), (238, 16, 24), (2068, 200, 72),
+                                   (599, 840, 584), (97, 48, 96), (22, 216, 328), (1, 320, 256), (59, 24, 424), (14, 352, 1096)])
+def test_gemm_every_tile_shape(attn, M, N, K):
+    g = torch.Generator(device="cuda").manual_seed(M + N + K)
+    a = torch.randn(M, K, generator=g, device="cuda", dtype=torch.bfloat16)
+    b = torch.randn(K, N, generator=g, device="cuda", dtype=torch.bfloat16)
+    print(f"launch gemm M{M} N{N} K{K}", flush=True)
+    guard = 4096
+    buf = torch.full((M * N + guard,), 77.0, dtype=torch.bfloat16, device="cuda")
+    attn.gemm(a, b, out=buf[:M * N].view(M, N))
+    torch.cuda.synchronize()
+    assert bool((buf[M * N:] == 77.0).all()), "wrote past the end of C"
+    ref = a.cpu().double().numpy() @ b.cpu().double().numpy()
+    err = np.abs(buf[:M * N].view(M, N).cpu().double().numpy() - ref)
+    assert np.isfinite(err).all()
+    assert (err <= tol(ref, K)).all(), float((err - tol(ref, K)).max())

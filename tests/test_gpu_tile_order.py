@@ -9,10 +9,9 @@ import math
 import pytest
 import torch
 
-pytestmark = pytest.mark.gpu
+from paper_2410_20399_amd import attn
 
-if torch.cuda.is_available():
-    from paper_2410_20399_amd import attn
+pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("causal", [True, False])
