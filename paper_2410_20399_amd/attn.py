@@ -2,7 +2,9 @@
 
 The functions named ``tk_*`` take torch CUDA tensors (used purely as device
 buffers) and forward pointers, sizes and the current HIP stream to the
-shared library; every step of the computation runs in the HIP kernels.
+shared library; the convenience functions below them (``attn_fwd`` and so on)
+check their tensors, allocate the outputs and make the same calls from C++
+(csrc/binding.cpp).  Every step of the computation runs in the HIP kernels.
 There is no fallback: if the library is missing, loading raises.
 """
 import ctypes
@@ -29,6 +31,7 @@ EXPORTS = ("tk_attn_fwd", "tk_attn_bwd", "tk_attn_bwd_workspace_bytes", "tk_attn
            "tk_attn_bwd_spill_workspace_bytes", "tk_attn_bwd_ds_bytes", "tk_attn_bwd_dkdv_ds", "tk_attn_bwd_dq_from_ds", "tk_rotary", "tk_gemm", "tk_mfma_probe", "tk_status_string", "tk_attn_version")
 
 _lib = None
+_binding = None
 
 
 class TkAttnError(RuntimeError):
@@ -106,6 +109,16 @@ def load_library(path: str = LIB_PATH) -> ctypes.CDLL:
     return lib
 
 
+def _native():
+    """The C++ side of the convenience functions."""
+    global _binding
+    if _binding is None:
+        load_library()
+        from . import _binding as module
+        _binding = module
+    return _binding
+
+
 def status_string(status: int) -> str:
     return load_library().tk_status_string(int(status)).decode()
 
@@ -124,16 +137,22 @@ def _stream(stream):
     return ctypes.c_void_p(stream.cuda_stream)
 
 
+def _raw(stream):
+    return None if stream is None else stream.cuda_stream
+
+
+def _checked(result, where: str):
+    """The outputs of a native call, or the error its status stands for."""
+    if type(result) is int:
+        raise TkAttnError(result, where)
+    return result
+
+
 def _check_bf16(name, t, shape=None):
     if not (t.is_cuda and t.dtype == torch.bfloat16 and t.is_contiguous()):
         raise ValueError(f"{name} must be a contiguous CUDA bf16 tensor")
     if shape is not None and tuple(t.shape) != tuple(shape):
         raise ValueError(f"{name} has shape {tuple(t.shape)}, expected {tuple(shape)}")
-
-
-def _check_f32(name, t, shape):
-    if not (t.is_cuda and t.dtype == torch.float32 and t.is_contiguous() and tuple(t.shape) == tuple(shape)):
-        raise ValueError(f"{name} must be a contiguous CUDA fp32 tensor of shape {tuple(shape)}")
 
 
 # ------------------------------------------------------------------ the C ABI, same names
@@ -269,21 +288,8 @@ def tk_mfma_probe(operands, sink, workgroups, iters, stream=None) -> int:
 # ------------------------------------------------------------------ convenience: allocate outputs, raise on error
 def attn_fwd(q, k, v, causal: bool, scale: float, out=None, stream=None):
     """q, k, v: CUDA bf16 [B,H,N,D]. Returns (o bf16 [B,H,N,D], lse fp32 [B,H,N])."""
-    _check_bf16("q", q)
-    B, H, N, D = q.shape
-    _check_bf16("k", k, q.shape)
-    _check_bf16("v", v, q.shape)
-    if out is None:
-        o = torch.empty_like(q)
-        lse = torch.empty((B, H, N), dtype=torch.float32, device=q.device)
-    else:
-        o, lse = out
-        _check_bf16("o", o, q.shape)
-        _check_f32("lse", lse, (B, H, N))
-    rc = tk_attn_fwd(q, k, v, o, lse, B, H, N, D, causal, scale, stream)
-    if rc != TK_OK:
-        raise TkAttnError(rc, "tk_attn_fwd")
-    return o, lse
+    o, lse = (None, None) if out is None else out
+    return _checked(_native().fwd(q, k, v, causal, scale, _raw(stream), True, True, o, lse), "tk_attn_fwd")
 
 
 SPILL_WORKSPACE_LIMIT = 24 << 30     # largest dS workspace the convenience wrappers allocate by themselves
@@ -305,22 +311,11 @@ def alloc_bwd_workspace(B, H, N, D, device="cuda", spill=None, Nk=None):
 
 def attn_bwd(q, k, v, o, d_o, lse, causal: bool, scale: float, workspace=None, out=None, stream=None):
     """Returns (dq, dk, dv) bf16 [B,H,N,D]; o and lse must come from attn_fwd on the same inputs."""
-    _check_bf16("q", q)
-    B, H, N, D = q.shape
-    for name, t in (("k", k), ("v", v), ("o", o), ("d_o", d_o)):
-        _check_bf16(name, t, q.shape)
-    _check_f32("lse", lse, (B, H, N))
     if workspace is None:
-        workspace = alloc_bwd_workspace(B, H, N, D, q.device)
-    if out is None:
-        dq, dk, dv = torch.empty_like(q), torch.empty_like(q), torch.empty_like(q)
-    else:
-        dq, dk, dv = out
-    rc = tk_attn_bwd(q, k, v, o, d_o, lse, dq, dk, dv, B, H, N, D, causal, scale,
-                     workspace, workspace.numel() * workspace.element_size(), stream)
-    if rc != TK_OK:
-        raise TkAttnError(rc, "tk_attn_bwd")
-    return dq, dk, dv
+        _check_bf16("q", q)
+        workspace = alloc_bwd_workspace(*q.shape, q.device)
+    dq, dk, dv = (None, None, None) if out is None else out
+    return _checked(_native().bwd(q, k, v, o, d_o, lse, causal, scale, workspace, _raw(stream), True, True, dq, dk, dv), "tk_attn_bwd")
 
 
 def attn_bwd_delta(o, d_o, stream=None):
@@ -336,118 +331,43 @@ def attn_bwd_delta(o, d_o, stream=None):
 
 def gqa_fwd(q, k, v, causal: bool, scale: float, stream=None):
     """Grouped-query forward: q bf16 [B,Hq,N,D], k, v bf16 [B,Hkv,N,D]. Returns (o [B,Hq,N,D], lse [B,Hq,N])."""
-    _check_bf16("q", q)
-    B, Hq, N, D = q.shape
-    Hkv = k.shape[1]
-    _check_bf16("k", k, (B, Hkv, N, D))
-    _check_bf16("v", v, (B, Hkv, N, D))
-    o = torch.empty_like(q)
-    lse = torch.empty((B, Hq, N), dtype=torch.float32, device=q.device)
-    rc = tk_attn_fwd_gqa(q, k, v, o, lse, B, Hq, Hkv, N, D, causal, scale, stream)
-    if rc != TK_OK:
-        raise TkAttnError(rc, "tk_attn_fwd_gqa")
-    return o, lse
+    return _checked(_native().fwd(q, k, v, causal, scale, _raw(stream), False, True, None, None), "tk_attn_fwd_gqa")
 
 
 def gqa_bwd(q, k, v, o, d_o, lse, causal: bool, scale: float, workspace=None, stream=None):
     """Grouped-query backward. Returns (dq [B,Hq,N,D], dk, dv [B,Hkv,N,D]) bf16."""
-    _check_bf16("q", q)
-    B, Hq, N, D = q.shape
-    Hkv = k.shape[1]
-    _check_bf16("k", k, (B, Hkv, N, D))
-    _check_bf16("v", v, (B, Hkv, N, D))
-    _check_bf16("o", o, q.shape)
-    _check_bf16("d_o", d_o, q.shape)
-    _check_f32("lse", lse, (B, Hq, N))
     if workspace is None:
-        workspace = alloc_bwd_workspace(B, Hq, N, D, q.device)
-    dq, dk, dv = torch.empty_like(q), torch.empty_like(k), torch.empty_like(v)
-    rc = tk_attn_bwd_gqa(q, k, v, o, d_o, lse, dq, dk, dv, B, Hq, Hkv, N, D, causal, scale,
-                         workspace, workspace.numel() * workspace.element_size(), stream)
-    if rc != TK_OK:
-        raise TkAttnError(rc, "tk_attn_bwd_gqa")
-    return dq, dk, dv
+        _check_bf16("q", q)
+        workspace = alloc_bwd_workspace(*q.shape, q.device)
+    return _checked(_native().bwd(q, k, v, o, d_o, lse, causal, scale, workspace, _raw(stream), False, True, None, None, None),
+                    "tk_attn_bwd_gqa")
 
 
 def rect_fwd(q, k, v, causal: bool, scale: float, stream=None):
     """Forward with Nq queries and Nk keys: q bf16 [B,Hq,Nq,D], k, v bf16 [B,Hkv,Nk,D].
     Returns (o [B,Hq,Nq,D], lse [B,Hq,Nq]).  Causal: query i sees keys j <= i + (Nk - Nq)."""
-    _check_bf16("q", q)
-    B, Hq, Nq, D = q.shape
-    Hkv, Nk = k.shape[1], k.shape[2]
-    _check_bf16("k", k, (B, Hkv, Nk, D))
-    _check_bf16("v", v, (B, Hkv, Nk, D))
-    o = torch.empty_like(q)
-    lse = torch.empty((B, Hq, Nq), dtype=torch.float32, device=q.device)
-    rc = tk_attn_fwd_rect(q, k, v, o, lse, B, Hq, Hkv, Nq, Nk, D, causal, scale, stream)
-    if rc != TK_OK:
-        raise TkAttnError(rc, "tk_attn_fwd_rect")
-    return o, lse
+    return _checked(_native().fwd(q, k, v, causal, scale, _raw(stream), False, False, None, None), "tk_attn_fwd_rect")
 
 
 def rect_bwd(q, k, v, o, d_o, lse, causal: bool, scale: float, workspace=None, stream=None):
     """Backward of rect_fwd. Returns (dq [B,Hq,Nq,D], dk, dv [B,Hkv,Nk,D]) bf16."""
-    _check_bf16("q", q)
-    B, Hq, Nq, D = q.shape
-    Hkv, Nk = k.shape[1], k.shape[2]
-    _check_bf16("k", k, (B, Hkv, Nk, D))
-    _check_bf16("v", v, (B, Hkv, Nk, D))
-    _check_bf16("o", o, q.shape)
-    _check_bf16("d_o", d_o, q.shape)
-    _check_f32("lse", lse, (B, Hq, Nq))
     if workspace is None:
-        workspace = alloc_bwd_workspace(B, Hq, Nq, D, q.device, Nk=Nk)
-    dq, dk, dv = torch.empty_like(q), torch.empty_like(k), torch.empty_like(v)
-    rc = tk_attn_bwd_rect(q, k, v, o, d_o, lse, dq, dk, dv, B, Hq, Hkv, Nq, Nk, D, causal, scale,
-                          workspace, workspace.numel() * workspace.element_size(), stream)
-    if rc != TK_OK:
-        raise TkAttnError(rc, "tk_attn_bwd_rect")
-    return dq, dk, dv
+        _check_bf16("q", q)
+        workspace = alloc_bwd_workspace(*q.shape, q.device, Nk=k.shape[2])
+    return _checked(_native().bwd(q, k, v, o, d_o, lse, causal, scale, workspace, _raw(stream), False, False, None, None, None),
+                    "tk_attn_bwd_rect")
 
 
 def decode(q, k, v, scale: float, workspace=None, stream=None):
     """One query per head: q bf16 [B,Hq,1,D], k, v bf16 [B,Hkv,Nk,D]. Returns (o [B,Hq,1,D], lse [B,Hq,1])."""
-    _check_bf16("q", q)
-    B, Hq, one, D = q.shape
-    if one != 1:
-        raise ValueError("decode takes exactly one query per head")
-    Hkv, Nk = k.shape[1], k.shape[2]
-    _check_bf16("k", k, (B, Hkv, Nk, D))
-    _check_bf16("v", v, (B, Hkv, Nk, D))
-    if workspace is None:
-        workspace = torch.empty(max(tk_attn_decode_workspace_bytes(B, Hq, Hkv, Nk, D), 16), dtype=torch.uint8, device=q.device)
-    o = torch.empty_like(q)
-    lse = torch.empty((B, Hq, 1), dtype=torch.float32, device=q.device)
-    rc = tk_attn_decode(q, k, v, o, lse, B, Hq, Hkv, Nk, D, scale, workspace, workspace.numel() * workspace.element_size(), stream)
-    if rc != TK_OK:
-        raise TkAttnError(rc, "tk_attn_decode")
-    return o, lse
+    return _checked(_native().decode(q, k, v, scale, workspace, _raw(stream)), "tk_attn_decode")
 
 
 def rotary(x, sin_table, cos_table, out=None, stream=None):
     """Rotary positional encoding: x bf16 [B,H,N,D], sin/cos bf16 [N, D/2]. Returns o (out=x works in place)."""
-    _check_bf16("x", x)
-    B, H, N, D = x.shape
-    _check_bf16("sin_table", sin_table, (N, D // 2))
-    _check_bf16("cos_table", cos_table, (N, D // 2))
-    o = torch.empty_like(x) if out is None else out
-    _check_bf16("o", o, x.shape)
-    rc = tk_rotary(x, sin_table, cos_table, o, B, H, N, D, stream)
-    if rc != TK_OK:
-        raise TkAttnError(rc, "tk_rotary")
-    return o
+    return _checked(_native().rotary(x, sin_table, cos_table, out, _raw(stream)), "tk_rotary")
 
 
 def gemm(a, b, out=None, stream=None):
     """C = A B: a bf16 [M,K], b bf16 [K,N] -> c bf16 [M,N] (N and K multiples of 8)."""
-    if a.dtype != torch.bfloat16 or b.dtype != torch.bfloat16 or a.dim() != 2 or b.dim() != 2:
-        raise ValueError("a, b must be 2-D bf16 tensors")
-    if not (a.is_cuda and b.is_cuda and a.is_contiguous() and b.is_contiguous()) or a.shape[1] != b.shape[0]:
-        raise ValueError("a [M,K], b [K,N] must be contiguous CUDA tensors")
-    M, K = a.shape
-    N = b.shape[1]
-    c = torch.empty((M, N), dtype=torch.bfloat16, device=a.device) if out is None else out
-    rc = tk_gemm(a, b, c, M, N, K, stream)
-    if rc != TK_OK:
-        raise TkAttnError(rc, "tk_gemm")
-    return c
+    return _checked(_native().gemm(a, b, out, _raw(stream)), "tk_gemm")

@@ -1,0 +1,272 @@
+// Python side of the convenience functions in attn.py: check the tensors, allocate the outputs, find the
+// stream, call the C ABI.  No arithmetic of the method.
+//
+// A small call is bound by what happens on the host: through ctypes and torch's Python functions a forward
+// took 12.5 us (5 of them to find the current stream, 4 to marshal the arguments), longer than its kernel.
+// Every function here takes the positional arguments its wrapper in attn.py passes, raises ValueError for
+// tensors that do not fit, and returns either the outputs or the negative status of the C call.
+#include <Python.h>
+
+#include <ATen/ATen.h>
+#include <ATen/core/LegacyTypeDispatch.h>
+#include <c10/hip/HIPStream.h>
+#include <torch/csrc/autograd/python_variable.h>
+
+#include <exception>
+#include <initializer_list>
+
+#include "../../include/tk_attn.h"
+
+namespace {
+
+struct Raised {};       // a Python exception is set
+
+[[noreturn]] void value_error(const char* format, const char* name) {
+    PyErr_Format(PyExc_ValueError, format, name);
+    throw Raised();
+}
+
+const at::Tensor& tensor(PyObject* o, const char* name) {
+    if (!THPVariable_Check(o)) {
+        PyErr_Format(PyExc_TypeError, "%s must be a tensor", name);
+        throw Raised();
+    }
+    return THPVariable_Unpack(o);
+}
+
+const at::Tensor& typed(PyObject* o, const char* name, at::ScalarType type, const char* type_name) {
+    const at::Tensor& t = tensor(o, name);
+    if (!(t.is_cuda() && t.scalar_type() == type && t.is_contiguous())) {
+        PyErr_Format(PyExc_ValueError, "%s must be a contiguous CUDA %s tensor", name, type_name);
+        throw Raised();
+    }
+    return t;
+}
+
+void shape(const at::Tensor& t, const char* name, std::initializer_list<int64_t> want) {
+    if (t.sizes() != at::IntArrayRef(want)) {
+        PyObject* text = PyUnicode_FromString("");
+        for (int64_t n : want) {
+            PyObject* more = PyUnicode_FromFormat("%U%s%lld", text, PyUnicode_GetLength(text) ? ", " : "", (long long)n);
+            Py_DECREF(text);
+            text = more;
+        }
+        PyErr_Format(PyExc_ValueError, "%s has another shape than the expected (%U)", name, text);
+        Py_DECREF(text);
+        throw Raised();
+    }
+}
+
+const at::Tensor& bf16(PyObject* o, const char* name) { return typed(o, name, at::kBFloat16, "bf16"); }
+
+const at::Tensor& bf16(PyObject* o, const char* name, std::initializer_list<int64_t> want) {
+    const at::Tensor& t = bf16(o, name);
+    shape(t, name, want);
+    return t;
+}
+
+const at::Tensor& f32(PyObject* o, const char* name, std::initializer_list<int64_t> want) {
+    const at::Tensor& t = typed(o, name, at::kFloat, "fp32");
+    shape(t, name, want);
+    return t;
+}
+
+void rank(const at::Tensor& t, const char* name, int64_t want) {
+    if (t.dim() != want) value_error("%s has the wrong number of dimensions", name);
+}
+
+bool truth(PyObject* o) {
+    const int v = PyObject_IsTrue(o);
+    if (v < 0) throw Raised();
+    return v != 0;
+}
+
+float number(PyObject* o) {
+    const double v = PyFloat_AsDouble(o);
+    if (v == -1.0 && PyErr_Occurred()) throw Raised();
+    return (float)v;
+}
+
+// the raw stream an int names, or the current stream of the current device
+void* stream_of(PyObject* o) {
+    if (o == Py_None) return (void*)c10::hip::getCurrentHIPStream().stream();
+    void* s = PyLong_AsVoidPtr(o);
+    if (PyErr_Occurred()) throw Raised();
+    return s;
+}
+
+PyObject* status(int rc) { return PyLong_FromLong(rc); }
+
+PyObject* give(std::initializer_list<const at::Tensor*> outs) {
+    PyObject* tuple = PyTuple_New((Py_ssize_t)outs.size());
+    if (!tuple) throw Raised();
+    Py_ssize_t i = 0;
+    for (const at::Tensor* t : outs) {
+        PyObject* o = THPVariable_Wrap(*t);
+        if (!o) { Py_DECREF(tuple); throw Raised(); }
+        PyTuple_SET_ITEM(tuple, i++, o);
+    }
+    return tuple;
+}
+
+struct Sizes {
+    int B, Hq, Hkv, Nq, Nk, D;
+};
+
+// q [B,Hq,Nq,D], k and v [B,Hkv,Nk,D]; same_heads / same_length: the calls that do not take others
+Sizes qkv(PyObject* const* a, bool same_heads, bool same_length) {
+    const at::Tensor& q = bf16(a[0], "q");
+    rank(q, "q", 4);
+    const at::Tensor& k = bf16(a[1], "k");
+    rank(k, "k", 4);
+    const int64_t B = q.size(0), Hq = q.size(1), Nq = q.size(2), D = q.size(3);
+    const int64_t Hkv = same_heads ? Hq : k.size(1), Nk = same_length ? Nq : k.size(2);
+    shape(k, "k", {B, Hkv, Nk, D});
+    bf16(a[2], "v", {B, Hkv, Nk, D});
+    for (int64_t n : {B, Hq, Hkv, Nq, Nk, D})
+        if (n > 0x7fffffff) value_error("%s has a dimension beyond 31 bits", "q, k or v");
+    return {(int)B, (int)Hq, (int)Hkv, (int)Nq, (int)Nk, (int)D};
+}
+
+// fwd(q, k, v, causal, scale, stream, same_heads, same_length, o, lse): o and lse None, or where to write
+PyObject* fwd(PyObject* const* a) {
+    const Sizes s = qkv(a, truth(a[6]), truth(a[7]));
+    const at::Tensor& q = THPVariable_Unpack(a[0]);
+    const bool causal = truth(a[3]);
+    const float scale = number(a[4]);
+    void* stream = stream_of(a[5]);
+    at::Tensor o, lse;
+    if (a[8] == Py_None) {
+        at::AutoDispatchBelowADInplaceOrView plain;
+        o = at::empty(q.sizes(), q.options());
+        lse = at::empty({s.B, s.Hq, s.Nq}, q.options().dtype(at::kFloat));
+    } else {
+        o = bf16(a[8], "o", {s.B, s.Hq, s.Nq, s.D});
+        lse = f32(a[9], "lse", {s.B, s.Hq, s.Nq});
+    }
+    const int rc = tk_attn_fwd_rect(q.data_ptr(), THPVariable_Unpack(a[1]).data_ptr(), THPVariable_Unpack(a[2]).data_ptr(),
+                                    o.data_ptr(), (float*)lse.data_ptr(), s.B, s.Hq, s.Hkv, s.Nq, s.Nk, s.D, causal, scale, stream);
+    return rc != TK_OK ? status(rc) : give({&o, &lse});
+}
+
+// bwd(q, k, v, o, d_o, lse, causal, scale, workspace, stream, same_heads, same_length, dq, dk, dv): dq, dk, dv None or where to write
+PyObject* bwd(PyObject* const* a) {
+    const Sizes s = qkv(a, truth(a[10]), truth(a[11]));
+    const at::Tensor &q = THPVariable_Unpack(a[0]), &k = THPVariable_Unpack(a[1]), &v = THPVariable_Unpack(a[2]);
+    const at::Tensor& o = bf16(a[3], "o", {s.B, s.Hq, s.Nq, s.D});
+    const at::Tensor& d_o = bf16(a[4], "d_o", {s.B, s.Hq, s.Nq, s.D});
+    const at::Tensor& lse = f32(a[5], "lse", {s.B, s.Hq, s.Nq});
+    const bool causal = truth(a[6]);
+    const float scale = number(a[7]);
+    const at::Tensor& workspace = tensor(a[8], "workspace");
+    void* stream = stream_of(a[9]);
+    at::Tensor dq, dk, dv;
+    if (a[12] == Py_None) {
+        at::AutoDispatchBelowADInplaceOrView plain;
+        dq = at::empty(q.sizes(), q.options());
+        dk = at::empty(k.sizes(), k.options());
+        dv = at::empty(k.sizes(), k.options());
+    } else {
+        dq = tensor(a[12], "dq");
+        dk = tensor(a[13], "dk");
+        dv = tensor(a[14], "dv");
+    }
+    const int rc = tk_attn_bwd_rect(q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(), d_o.data_ptr(), (const float*)lse.data_ptr(),
+                                    dq.data_ptr(), dk.data_ptr(), dv.data_ptr(), s.B, s.Hq, s.Hkv, s.Nq, s.Nk, s.D, causal, scale,
+                                    workspace.data_ptr(), (size_t)workspace.numel() * workspace.element_size(), stream);
+    return rc != TK_OK ? status(rc) : give({&dq, &dk, &dv});
+}
+
+// decode(q, k, v, scale, workspace or None, stream)
+PyObject* decode(PyObject* const* a) {
+    const at::Tensor& q = bf16(a[0], "q");
+    rank(q, "q", 4);
+    if (q.size(2) != 1) value_error("%s takes exactly one query per head", "decode");
+    const Sizes s = qkv(a, false, false);
+    const float scale = number(a[3]);
+    void* stream = stream_of(a[5]);
+    at::AutoDispatchBelowADInplaceOrView plain;
+    at::Tensor workspace;
+    if (a[4] == Py_None) {
+        size_t n = tk_attn_decode_workspace_bytes(s.B, s.Hq, s.Hkv, s.Nk, s.D);
+        workspace = at::empty({(int64_t)(n < 16 ? 16 : n)}, q.options().dtype(at::kByte));
+    } else {
+        workspace = tensor(a[4], "workspace");
+    }
+    const at::Tensor o = at::empty(q.sizes(), q.options());
+    const at::Tensor lse = at::empty({s.B, s.Hq, 1}, q.options().dtype(at::kFloat));
+    const int rc = tk_attn_decode(q.data_ptr(), THPVariable_Unpack(a[1]).data_ptr(), THPVariable_Unpack(a[2]).data_ptr(),
+                                  o.data_ptr(), (float*)lse.data_ptr(), s.B, s.Hq, s.Hkv, s.Nk, s.D, scale,
+                                  workspace.data_ptr(), (size_t)workspace.numel() * workspace.element_size(), stream);
+    return rc != TK_OK ? status(rc) : give({&o, &lse});
+}
+
+// rotary(x, sin_table, cos_table, out or None, stream)
+PyObject* rotary(PyObject* const* a) {
+    const at::Tensor& x = bf16(a[0], "x");
+    rank(x, "x", 4);
+    const int64_t B = x.size(0), H = x.size(1), N = x.size(2), D = x.size(3);
+    const at::Tensor& sn = bf16(a[1], "sin_table", {N, D / 2});
+    const at::Tensor& cs = bf16(a[2], "cos_table", {N, D / 2});
+    at::Tensor o;
+    if (a[3] == Py_None) {
+        at::AutoDispatchBelowADInplaceOrView plain;
+        o = at::empty(x.sizes(), x.options());
+    } else {
+        o = bf16(a[3], "o", {B, H, N, D});
+    }
+    const int rc = tk_rotary(x.data_ptr(), sn.data_ptr(), cs.data_ptr(), o.data_ptr(), (int)B, (int)H, (int)N, (int)D, stream_of(a[4]));
+    return rc != TK_OK ? status(rc) : THPVariable_Wrap(o);
+}
+
+// gemm(a, b, out or None, stream)
+PyObject* gemm(PyObject* const* args) {
+    const at::Tensor &a = tensor(args[0], "a"), &b = tensor(args[1], "b");
+    if (a.scalar_type() != at::kBFloat16 || b.scalar_type() != at::kBFloat16 || a.dim() != 2 || b.dim() != 2)
+        value_error("%s must be 2-D bf16 tensors", "a, b");
+    if (!(a.is_cuda() && b.is_cuda() && a.is_contiguous() && b.is_contiguous()) || a.size(1) != b.size(0))
+        value_error("%s must be contiguous CUDA tensors", "a [M,K], b [K,N]");
+    const int64_t M = a.size(0), K = a.size(1), N = b.size(1);
+    at::Tensor c;
+    if (args[2] == Py_None) {
+        at::AutoDispatchBelowADInplaceOrView plain;
+        c = at::empty({M, N}, a.options());
+    } else {
+        c = tensor(args[2], "out");
+    }
+    const int rc = tk_gemm(a.data_ptr(), b.data_ptr(), c.data_ptr(), (int)M, (int)N, (int)K, stream_of(args[3]));
+    return rc != TK_OK ? status(rc) : THPVariable_Wrap(c);
+}
+
+template <PyObject* (*F)(PyObject* const*), int N>
+PyObject* entry(PyObject*, PyObject* const* args, Py_ssize_t n) {
+    if (n != N) {
+        PyErr_Format(PyExc_TypeError, "%d arguments expected, %zd given", N, n);
+        return nullptr;
+    }
+    try {
+        return F(args);
+    } catch (const Raised&) {
+    } catch (const c10::OutOfMemoryError& e) {
+        PyObject* torch = PyImport_ImportModule("torch");
+        PyObject* type = torch ? PyObject_GetAttrString(torch, "OutOfMemoryError") : nullptr;
+        if (type) PyErr_SetString(type, e.what_without_backtrace());
+        Py_XDECREF(type);
+        Py_XDECREF(torch);
+    } catch (const std::exception& e) {
+        PyErr_SetString(PyExc_RuntimeError, e.what());
+    }
+    return nullptr;
+}
+
+#define TK_ENTRY(name, n) {#name, (PyCFunction)(void (*)(void))entry<name, n>, METH_FASTCALL, nullptr}
+PyMethodDef kMethods[] = {
+    TK_ENTRY(fwd, 10), TK_ENTRY(bwd, 15), TK_ENTRY(decode, 6), TK_ENTRY(rotary, 5), TK_ENTRY(gemm, 4),
+    {nullptr, nullptr, 0, nullptr},
+};
+PyModuleDef kModule = {PyModuleDef_HEAD_INIT, "_binding", "tensor checks, output allocation and dispatch to the C ABI", -1, kMethods,
+                       nullptr, nullptr, nullptr, nullptr};
+
+}  // namespace
+
+PyMODINIT_FUNC PyInit__binding(void) { return PyModule_Create(&kModule); }

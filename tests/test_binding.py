@@ -1,0 +1,69 @@
+"""The convenience functions of attn.py: what they refuse, and that they honour out= and stream=."""
+import math
+
+import pytest
+import torch
+
+from paper_2410_20399_amd import attn
+
+
+def test_tensors_that_are_not_on_the_gpu_are_refused():
+    x = torch.zeros(1, 2, 128, 64, dtype=torch.bfloat16)
+    with pytest.raises(ValueError):
+        attn.attn_fwd(x, x, x, False, 1.0)
+    with pytest.raises(ValueError):
+        attn.gemm(x[0, 0], x[0, 0].t())
+    with pytest.raises(TypeError):
+        attn.rotary(None, x, x)
+
+
+def tensors(B, H, N, D, n=3):
+    g = torch.Generator(device="cuda").manual_seed(N)
+    return [torch.randn(B, H, N, D, generator=g, device="cuda", dtype=torch.bfloat16) for _ in range(n)]
+
+
+@pytest.mark.gpu
+def test_wrong_shapes_types_and_dimensions():
+    q, k, v = tensors(2, 4, 128, 64)
+    for bad in (k[:, :2].contiguous(), k[:, :, :64].contiguous(), k.float(), k.transpose(2, 3)):
+        with pytest.raises(ValueError):
+            attn.attn_fwd(q, bad, v, False, 0.125)
+        with pytest.raises(ValueError):
+            attn.attn_fwd(q, k, bad, False, 0.125)
+    with pytest.raises(ValueError):
+        attn.gqa_fwd(q, k[:, :2, :64].contiguous(), v[:, :2, :64].contiguous(), False, 0.125)
+    with pytest.raises(ValueError):
+        attn.decode(q, k, v, 0.125)
+    o, lse = attn.attn_fwd(q, k, v, False, 0.125)
+    with pytest.raises(ValueError):
+        attn.attn_bwd(q, k, v, o, o, lse[:1].contiguous(), False, 0.125)
+    with pytest.raises(attn.TkAttnError):
+        attn.attn_fwd(q[..., :32].contiguous(), k[..., :32].contiguous(), v[..., :32].contiguous(), False, 0.125)
+    with pytest.raises(attn.TkAttnError):
+        attn.attn_bwd(q, k, v, o, o, lse, False, 0.125, workspace=torch.empty(16, dtype=torch.uint8, device="cuda"))
+    with pytest.raises(attn.TkAttnError):
+        attn.gemm(torch.zeros(8, 12, dtype=torch.bfloat16, device="cuda"), torch.zeros(12, 8, dtype=torch.bfloat16, device="cuda"))
+
+
+@pytest.mark.gpu
+def test_out_and_stream_are_honoured():
+    B, H, N, D = 1, 2, 300, 128
+    q, k, v, d_o = tensors(B, H, N, D, 4)
+    scale = 1 / math.sqrt(D)
+    o, lse = attn.attn_fwd(q, k, v, True, scale)
+    grads = attn.attn_bwd(q, k, v, o, d_o, lse, True, scale)
+    torch.cuda.synchronize()
+    side = torch.cuda.Stream()
+    o2, lse2 = torch.empty_like(o), torch.empty_like(lse)
+    grads2 = tuple(torch.empty_like(q) for _ in range(3))
+    workspace = attn.alloc_bwd_workspace(B, H, N, D)
+    torch.cuda.synchronize()
+    assert attn.attn_fwd(q, k, v, True, scale, out=(o2, lse2), stream=side)[0].data_ptr() == o2.data_ptr()
+    attn.attn_bwd(q, k, v, o2, d_o, lse2, True, scale, workspace=workspace, out=grads2, stream=side)
+    side.synchronize()          # (nothing else is waited for: the work was on this stream)
+    assert torch.equal(o, o2) and torch.equal(lse, lse2)
+    assert all(torch.equal(a, b) for a, b in zip(grads, grads2))
+    with torch.cuda.stream(side):
+        o3, _ = attn.attn_fwd(q, k, v, True, scale)
+    side.synchronize()
+    assert torch.equal(o, o3)
