@@ -249,6 +249,23 @@ int tk_attn_fwd_rect(const void* q, const void* k, const void* v,
                      int B, int Hq, int Hkv, int Nq, int Nk, int D, int causal, float scale,
                      void* stream);
 
+/*
+ * tk_attn_fwd_rect for callers that can hand over device scratch.  With fewer queries than keys and too few
+ * (head, 128-query tile) pairs to fill the chip - a chunk of a prompt against a long history - the keys are
+ * split over more workgroups, which leave fp32 partial (O, LSE) pairs in the scratch, and merged.  Results equal
+ * tk_attn_fwd_rect's up to fp32 rounding order of the merge, and are bit-reproducible.
+ *
+ *   scratch : device memory of tk_attn_fwd_scratch_bytes(...) bytes, 16-byte aligned; contents on entry are
+ *             ignored.  NULL or less than that many bytes: the call is tk_attn_fwd_rect.
+ * tk_attn_fwd_scratch_bytes returns 0 where the call would not split (on the current device) or would be rejected.
+ */
+size_t tk_attn_fwd_scratch_bytes(int B, int Hq, int Hkv, int Nq, int Nk, int D, int causal);
+
+int tk_attn_fwd_rect_scratch(const void* q, const void* k, const void* v,
+                             void* o, float* lse,
+                             int B, int Hq, int Hkv, int Nq, int Nk, int D, int causal, float scale,
+                             void* scratch, size_t scratch_bytes, void* stream);
+
 int tk_attn_bwd_rect(const void* q, const void* k, const void* v,
                      const void* o, const void* d_o, const float* lse,
                      void* dq, void* dk, void* dv,

@@ -45,7 +45,11 @@ template <int D> __device__ __forceinline__ int swizzle_v(int row) {
 // 128); the aligned square case compiles without any of the tail code.  With the causal mask the
 // sequences are aligned at their ends: query i sees keys j <= i + (Nk - Nq); the host has checked
 // Nq <= Nk for that case, so every query sees key 0.
-template <int D, bool CAUSAL, bool TAIL>
+//
+// SPLIT (implies TAIL): n_splits workgroups share one query tile, each takes tiles_per_split (even)
+// consecutive key tiles and leaves a normalised fp32 partial O and its LSE for the merge kernel below.  For
+// calls whose heads and query tiles alone cannot fill the chip: decoding, a chunk of a prompt against a long history.
+template <int D, bool CAUSAL, bool TAIL, bool SPLIT>
 __global__ __launch_bounds__(256, 2)
 void attn_fwd_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K, const bf16* __restrict__ V,
                      bf16* __restrict__ O, float* __restrict__ LSE,
@@ -65,14 +69,9 @@ void attn_fwd_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K, con
     const int l32 = lane & 31;
     const int h = lane >> 5;
 
-    // workgroup -> (head, query tile), see TileOrder
-    // Split over the keys (general-case variant, no mask; used for decode-shaped calls where heads and
-    // query tiles alone cannot fill the chip): n_splits workgroups share one query tile, each takes
-    // tiles_per_split (even) consecutive key tiles and leaves a normalised fp32 partial O and its LSE.
-    const int split = (TAIL && !CAUSAL) ? blockIdx.x % n_splits : 0;
-    const int tile_id = (TAIL && !CAUSAL) ? blockIdx.x / n_splits : blockIdx.x;
-    int bh, qt;
-    tile_of(tile_id, heads, num_q_tiles, head_group, bh, qt);
+    int bh, qt, split = 0;
+    if (SPLIT) split_of(blockIdx.x, gridDim.x, hq / hkv, num_q_tiles, n_splits, bh, split, qt);
+    else tile_of(blockIdx.x, heads, num_q_tiles, head_group, bh, qt);
 
     // grouped-query attention: query head h of a batch entry reads key/value head h / (hq / hkv)
     const size_t head = (size_t)bh * Nq * D;
@@ -154,6 +153,10 @@ void attn_fwd_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K, con
     float m_run = -INFINITY;   // running max of raw scores (shared by both half-waves)
     float l_run = 0.f;         // running sum, partial: this lane's 32 of the 64 keys per tile
 
+    // A split of a causal call may hold no key that a row sees: its maximum stays -inf, and its exponents are
+    // then taken against 0, so that P = 2^-inf = 0.  (Without a split every row sees key 0.)
+    auto finite_max = [&](float m) { return SPLIT && CAUSAL && m == -INFINITY ? 0.f : m; };
+
     auto compute_tile = [&](int stage, int tile) {
         const int j0 = tile * S::kTileKV;
         if (CAUSAL && j0 > q0 + 31 + off) return;    // every key of the tile is masked for this wave
@@ -199,7 +202,7 @@ void attn_fwd_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K, con
         const bool raise = (mx - m_run) * c > kMaxSlack;          // true on the first tile (m_run = -inf)
         if (__builtin_amdgcn_ballot_w64(raise) != 0) {
             const float m_new = __builtin_fmaxf(m_run, mx);
-            const float corr = __builtin_amdgcn_exp2f((m_run - m_new) * c);
+            const float corr = __builtin_amdgcn_exp2f((m_run - finite_max(m_new)) * c);
             m_run = m_new;
             l_run *= corr;
 #pragma unroll
@@ -207,7 +210,7 @@ void attn_fwd_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K, con
 #pragma unroll
                 for (int r = 0; r < 16; r++) o_acc[db][r] *= corr;
         }
-        const float mc = m_run * c;
+        const float mc = finite_max(m_run) * c;
         // P = 2^(S*c - m*c), partial row sums
         float psum = 0.f;
 #pragma unroll
@@ -250,11 +253,11 @@ void attn_fwd_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K, con
     }
 
     int t_begin = 0;
-    if (TAIL && !CAUSAL && n_splits > 1) {
+    if (SPLIT) {
         t_begin = split * tiles_per_split;
         if (t_begin + tiles_per_split < n_tiles) n_tiles = t_begin + tiles_per_split;
     }
-    issue_tile(0, t_begin);
+    if (!SPLIT || t_begin < n_tiles) issue_tile(0, t_begin);     // (causal: a split may lie wholly beyond the tile's last key)
     wait_vmcnt<0>();
     __syncthreads();
     for (int t = t_begin; t < n_tiles; t += 2) {
@@ -270,8 +273,8 @@ void attn_fwd_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K, con
 
     // ---- epilogue
     const float l_tot = half_sum(l_run);
-    const float inv = 1.0f / l_tot;
-    if (TAIL && !CAUSAL && n_splits > 1) {
+    const float inv = SPLIT && CAUSAL && l_tot == 0.f ? 0.f : 1.0f / l_tot;     // (no visible key in this split: O = 0, LSE = -inf)
+    if (SPLIT) {
         if (my_q < Nq) {
             const size_t prow = ((size_t)split * heads + bh) * Nq + my_q;   // [split][head][query]
             float* Op = O_part + prow * D;
@@ -298,13 +301,13 @@ void attn_fwd_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K, con
     }
 }
 
-template <int D, bool CAUSAL, bool TAIL>
+template <int D, bool CAUSAL, bool TAIL, bool SPLIT>
 static hipError_t launch_fwd_tt(const void* q, const void* k, const void* v, void* o, float* lse,
                                 int B, int H, int Hkv, int Nq, int Nk, float scale, hipStream_t stream,
                                 int n_splits = 1, int tiles_per_split = 0, float* o_part = nullptr, float* lse_part = nullptr)
 {
     using S = FwdShape<D>;
-    auto kern = attn_fwd_kernel<D, CAUSAL, TAIL>;
+    auto kern = attn_fwd_kernel<D, CAUSAL, TAIL, SPLIT>;
     const int num_q_tiles = (Nq + S::kTileQ - 1) / S::kTileQ;
     const int total = B * H * num_q_tiles * n_splits;
     hipLaunchKernelGGL(kern, dim3(total), dim3(S::kThreads), 0, stream,
@@ -318,8 +321,8 @@ static hipError_t launch_fwd_t(const void* q, const void* k, const void* v, void
                                int B, int H, int Hkv, int Nq, int Nk, float scale, hipStream_t stream)
 {
     using S = FwdShape<D>;
-    return (Nq != Nk || Nq % S::kTileQ) ? launch_fwd_tt<D, CAUSAL, true>(q, k, v, o, lse, B, H, Hkv, Nq, Nk, scale, stream)
-                                        : launch_fwd_tt<D, CAUSAL, false>(q, k, v, o, lse, B, H, Hkv, Nq, Nk, scale, stream);
+    return (Nq != Nk || Nq % S::kTileQ) ? launch_fwd_tt<D, CAUSAL, true, false>(q, k, v, o, lse, B, H, Hkv, Nq, Nk, scale, stream)
+                                        : launch_fwd_tt<D, CAUSAL, false, false>(q, k, v, o, lse, B, H, Hkv, Nq, Nk, scale, stream);
 }
 
 hipError_t launch_attn_fwd(const void* q, const void* k, const void* v, void* o, float* lse,
@@ -361,17 +364,17 @@ void attn_fwd_combine_kernel(const float* __restrict__ O_part, const float* __re
     if (col == 0) LSE[row] = m + __builtin_logf(wsum);
 }
 
-// Non-causal forward with the keys split n_splits ways (n_splits >= 2, every split holds at least one
-// key: (n_splits - 1) * tiles_per_split * 64 < Nk, tiles_per_split even).  o_part: fp32
-// [n_splits][B*H][Nq][D], lse_part: fp32 [n_splits][B*H][Nq].
+// Forward with the keys split n_splits ways (n_splits >= 2, every split holds at least one key:
+// (n_splits - 1) * tiles_per_split * 64 < Nk, tiles_per_split even).  o_part: fp32 [n_splits][B*H][Nq][D],
+// lse_part: fp32 [n_splits][B*H][Nq].
 hipError_t launch_attn_fwd_splitk(const void* q, const void* k, const void* v, void* o, float* lse,
                                   float* o_part, float* lse_part,
-                                  int B, int H, int Hkv, int Nq, int Nk, int D, float scale,
+                                  int B, int H, int Hkv, int Nq, int Nk, int D, int causal, float scale,
                                   int n_splits, int tiles_per_split, hipStream_t stream)
 {
-    hipError_t e = D == 128
-        ? launch_fwd_tt<128, false, true>(q, k, v, o, lse, B, H, Hkv, Nq, Nk, scale, stream, n_splits, tiles_per_split, o_part, lse_part)
-        : launch_fwd_tt<64, false, true>(q, k, v, o, lse, B, H, Hkv, Nq, Nk, scale, stream, n_splits, tiles_per_split, o_part, lse_part);
+    auto launch = D == 128 ? (causal ? launch_fwd_tt<128, true, true, true> : launch_fwd_tt<128, false, true, true>)
+                           : (causal ? launch_fwd_tt<64, true, true, true> : launch_fwd_tt<64, false, true, true>);
+    hipError_t e = launch(q, k, v, o, lse, B, H, Hkv, Nq, Nk, scale, stream, n_splits, tiles_per_split, o_part, lse_part);
     if (e != hipSuccess) return e;
     const size_t rows = (size_t)B * H * Nq;
     if (D == 128) {

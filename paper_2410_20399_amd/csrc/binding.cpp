@@ -95,6 +95,28 @@ void* stream_of(PyObject* o) {
     return s;
 }
 
+// Makes `stream` the current one for a while.  Scratch that a call takes and gives back must come from the pool of
+// the stream it runs on: only there is the memory's next use ordered behind this one, and this one behind its last.
+class OnStream {
+public:
+    explicit OnStream(void* stream) : before_(c10::hip::getCurrentHIPStream()), changed_(stream != (void*)before_.stream()) {
+        if (changed_) c10::hip::setCurrentHIPStream(c10::hip::getStreamFromExternal((hipStream_t)stream, before_.device_index()));
+    }
+    ~OnStream() { if (changed_) c10::hip::setCurrentHIPStream(before_); }
+    OnStream(const OnStream&) = delete;
+    OnStream& operator=(const OnStream&) = delete;
+
+private:
+    c10::hip::HIPStream before_;
+    bool changed_;
+};
+
+at::Tensor scratch_on(void* stream, size_t bytes, const at::Tensor& like) {
+    at::AutoDispatchBelowADInplaceOrView plain;
+    OnStream on(stream);
+    return at::empty({(int64_t)bytes}, like.options().dtype(at::kByte));
+}
+
 PyObject* status(int rc) { return PyLong_FromLong(rc); }
 
 PyObject* give(std::initializer_list<const at::Tensor*> outs) {
@@ -144,8 +166,12 @@ PyObject* fwd(PyObject* const* a) {
         o = bf16(a[8], "o", {s.B, s.Hq, s.Nq, s.D});
         lse = f32(a[9], "lse", {s.B, s.Hq, s.Nq});
     }
-    const int rc = tk_attn_fwd_rect(q.data_ptr(), THPVariable_Unpack(a[1]).data_ptr(), THPVariable_Unpack(a[2]).data_ptr(),
-                                    o.data_ptr(), (float*)lse.data_ptr(), s.B, s.Hq, s.Hkv, s.Nq, s.Nk, s.D, causal, scale, stream);
+    const size_t n = s.Nq < s.Nk ? tk_attn_fwd_scratch_bytes(s.B, s.Hq, s.Hkv, s.Nq, s.Nk, s.D, causal) : 0;
+    at::Tensor scratch;
+    if (n) scratch = scratch_on(stream, n, q);
+    const int rc = tk_attn_fwd_rect_scratch(q.data_ptr(), THPVariable_Unpack(a[1]).data_ptr(), THPVariable_Unpack(a[2]).data_ptr(),
+                                            o.data_ptr(), (float*)lse.data_ptr(), s.B, s.Hq, s.Hkv, s.Nq, s.Nk, s.D, causal, scale,
+                                            n ? scratch.data_ptr() : nullptr, n, stream);
     return rc != TK_OK ? status(rc) : give({&o, &lse});
 }
 
@@ -189,7 +215,7 @@ PyObject* decode(PyObject* const* a) {
     at::Tensor workspace;
     if (a[4] == Py_None) {
         size_t n = tk_attn_decode_workspace_bytes(s.B, s.Hq, s.Hkv, s.Nk, s.D);
-        workspace = at::empty({(int64_t)(n < 16 ? 16 : n)}, q.options().dtype(at::kByte));
+        workspace = scratch_on(stream, n < 16 ? 16 : n, q);
     } else {
         workspace = tensor(a[4], "workspace");
     }

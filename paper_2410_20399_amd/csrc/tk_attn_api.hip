@@ -120,6 +120,34 @@ DecodePlan plan_decode(int B, int Hq, int Hkv, int Nk, int compute_units)
     return p;
 }
 
+// Few queries against a longer history: the heads and 128-query tiles alone leave compute units idle.  The split
+// aims at the two workgroups per compute unit that are resident at once at D = 128.  Whole call, us (unsplit, then
+// 1, 2, 3, 4 per compute unit): B1 Hq32 Hkv8 Nq512 Nk8192 D128 163, 98, 84, 89, 92; Hq64 of the same 186, 164, 146,
+// 154, 155; B1 Hq8 Hkv2 Nq700 Nk9000 D64 120, 37, 34, 38, 38.  A split holds at least 8 64-key tiles: with 16
+// B2 Hq8 Hkv2 Nq100 Nk2100 takes 28 instead of 21 us (18 with 4), but with 4 B1 H16 Nq512 Nk2048 D64 23 instead of 18.5.
+constexpr int kFwdSplitWgPerCu = 2;
+constexpr int kFwdSplitMinTiles = 8;
+
+struct FwdPlan {
+    int n_splits, tiles_per_split;
+};
+
+// Nq < Nk only: with equal lengths a head's bits do not depend on how many heads the call has.
+FwdPlan plan_fwd(int B, int Hq, int Nq, int Nk, int compute_units)
+{
+    const long long base = (long long)B * Hq * ((Nq + kTileN - 1) / kTileN);
+    const int tiles = (Nk + 63) / 64;
+    long long want = Nq < Nk ? (long long)kFwdSplitWgPerCu * compute_units / base : 1;
+    if (want > tiles / kFwdSplitMinTiles) want = tiles / kFwdSplitMinTiles;
+    if (want < 1) want = 1;
+    int per = (int)((tiles + want - 1) / want);
+    per += per & 1;                                   // the kernel walks the tiles in pairs
+    return {(tiles + per - 1) / per, per};            // no split is empty
+}
+
+// fp32 partial O and partial LSE of a split forward, each padded to 256 bytes
+size_t fwd_part_bytes(int n_splits, size_t rows, int D) { return ((size_t)n_splits * rows * D * sizeof(float) + 255) & ~(size_t)255; }
+
 }  // namespace
 
 extern "C" {
@@ -132,6 +160,36 @@ int tk_attn_fwd_rect(const void* q, const void* k, const void* v, void* o, float
     if (!aligned16(q) || !aligned16(k) || !aligned16(v) || !aligned16(o) || !aligned16(lse)) return TK_ERR_MISALIGNED;
     if (int rc = check_scale(scale)) return rc;
     hipError_t e = tk::launch_attn_fwd(q, k, v, o, lse, B, Hq, Hkv, Nq, Nk, D, causal != 0, scale, (hipStream_t)stream);
+    return e == hipSuccess ? TK_OK : TK_ERR_LAUNCH;
+}
+
+size_t tk_attn_fwd_scratch_bytes(int B, int Hq, int Hkv, int Nq, int Nk, int D, int causal)
+{
+    if (check_lengths(B, Hq, Hkv, Nq, Nk, D, causal) != TK_OK || Nq >= Nk) return 0;
+    int cus = 0;
+    if (tk::compute_unit_count(&cus) != hipSuccess || cus < 1) return 0;
+    const FwdPlan p = plan_fwd(B, Hq, Nq, Nk, cus);
+    if (p.n_splits == 1) return 0;
+    const size_t rows = (size_t)B * Hq * Nq;
+    return fwd_part_bytes(p.n_splits, rows, D) + fwd_part_bytes(p.n_splits, rows, 1);
+}
+
+int tk_attn_fwd_rect_scratch(const void* q, const void* k, const void* v, void* o, float* lse,
+                             int B, int Hq, int Hkv, int Nq, int Nk, int D, int causal, float scale,
+                             void* scratch, size_t scratch_bytes, void* stream)
+{
+    const size_t need = scratch ? tk_attn_fwd_scratch_bytes(B, Hq, Hkv, Nq, Nk, D, causal) : 0;
+    if (need == 0 || scratch_bytes < need)
+        return tk_attn_fwd_rect(q, k, v, o, lse, B, Hq, Hkv, Nq, Nk, D, causal, scale, stream);
+    if (!q || !k || !v || !o || !lse) return TK_ERR_NULL_PTR;
+    if (!aligned16(q) || !aligned16(k) || !aligned16(v) || !aligned16(o) || !aligned16(lse) || !aligned16(scratch)) return TK_ERR_MISALIGNED;
+    if (int rc = check_scale(scale)) return rc;
+    int cus = 0;
+    if (tk::compute_unit_count(&cus) != hipSuccess) return TK_ERR_LAUNCH;
+    const FwdPlan p = plan_fwd(B, Hq, Nq, Nk, cus);
+    float* lse_part = (float*)((char*)scratch + fwd_part_bytes(p.n_splits, (size_t)B * Hq * Nq, D));
+    hipError_t e = tk::launch_attn_fwd_splitk(q, k, v, o, lse, (float*)scratch, lse_part, B, Hq, Hkv, Nq, Nk, D, causal != 0, scale,
+                                              p.n_splits, p.tiles_per_split, (hipStream_t)stream);
     return e == hipSuccess ? TK_OK : TK_ERR_LAUNCH;
 }
 
@@ -192,7 +250,7 @@ int tk_attn_decode(const void* q, const void* k, const void* v, void* o, float* 
         const size_t rows = (size_t)B * Hq;
         float* o_part = (float*)workspace;
         float* lse_part = (float*)((char*)workspace + (((size_t)decode_max_splits(B, Hq, Hkv) * rows * D * sizeof(float) + 255) & ~(size_t)255));
-        e = tk::launch_attn_fwd_splitk(q, k, v, o, lse, o_part, lse_part, p.b, p.h, p.hkv, p.nq, Nk, D, scale,
+        e = tk::launch_attn_fwd_splitk(q, k, v, o, lse, o_part, lse_part, p.b, p.h, p.hkv, p.nq, Nk, D, 0, scale,
                                        p.n_splits, p.tiles_per_split, (hipStream_t)stream);
     }
     return e == hipSuccess ? TK_OK : TK_ERR_LAUNCH;

@@ -49,12 +49,11 @@ inline int tile_order_heads(int heads, int tiles, bool causal) {
 hipError_t launch_attn_fwd(const void* q, const void* k, const void* v, void* o, float* lse,
                            int B, int H, int Hkv, int Nq, int Nk, int D, int causal, float scale, hipStream_t stream);
 
-// The same forward, non-causal, with the keys split n_splits (>= 2) ways and a merge kernel behind it
-// (decode-shaped calls).  o_part: fp32 [n_splits][B*H][Nq][D]; lse_part: fp32 [n_splits][B*H][Nq];
+// The same forward with the keys split n_splits (>= 2) ways and a merge kernel behind it.  o_part: fp32 [n_splits][B*H][Nq][D]; lse_part: fp32 [n_splits][B*H][Nq];
 // tiles_per_split: even number of 64-key tiles per split, (n_splits - 1) * tiles_per_split * 64 < Nk.
 hipError_t launch_attn_fwd_splitk(const void* q, const void* k, const void* v, void* o, float* lse,
                                   float* o_part, float* lse_part,
-                                  int B, int H, int Hkv, int Nq, int Nk, int D, float scale,
+                                  int B, int H, int Hkv, int Nq, int Nk, int D, int causal, float scale,
                                   int n_splits, int tiles_per_split, hipStream_t stream);
 
 // Delta_i = sum_d dO_id O_id
