@@ -160,14 +160,16 @@ __device__ __forceinline__ void split_of(int wg, int total, int group, int tiles
 // Order of the (head, tile) work of a launch with one workgroup per tile.  Workgroups are dealt to the 8
 // XCDs round-robin, so with 8 * d heads walked together, head index innermost, every XCD (private L2)
 // works on d consecutive heads at a time; within that group the last tiles, the long ones when causal,
-// come first.  `group` = 8 * d comes from tile_order_heads() on the host.
+// come first.  `group` = 8 * d (or all heads) comes from tile_order_heads() on the host.  XCD x walks the heads
+// x * heads/8 and following, as xcd_remap() deals them to the backward kernels, which find in their L2 what the
+// forward left there.
 __device__ __forceinline__ void tile_of(int wg, int heads, int tiles, int group, int& head, int& tile) {
     const int per_group = group * tiles;
     const int g = wg / per_group, r = wg - g * per_group;
     int in_group = heads - g * group;                   // the last group may be smaller
     if (in_group > group) in_group = group;
     const int rank = r / in_group, j = r - rank * in_group;
-    head = g * group + (in_group % 8 == 0 ? (j % 8) * (in_group / 8) + j / 8 : j);
+    head = heads % 8 == 0 ? (j % 8) * (heads / 8) + g * (group / 8) + j / 8 : g * group + j;
     tile = tiles - 1 - rank;
 }
 
