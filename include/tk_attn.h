@@ -110,7 +110,9 @@ size_t tk_attn_bwd_workspace_bytes(int B, int H, int N, int D);
 /*
  * Bytes of workspace from which tk_attn_bwd / _gqa / _rect take the faster form that stores dS:
  * Delta plus one 2 KB block per (query head, 128-key tile, 32-query block, 32 keys), i.e. about
- * 2 * B * Hq * Nq * Nk bytes (8.6 GB for B*Hq = 256, Nq = Nk = 4096).  0 if the shape is invalid.
+ * 2 * B * Hq * Nq * Nk bytes (8.6 GB for B*Hq = 256, Nq = Nk = 4096), and for small problems 8 * B * Hq * Nk * D
+ * bytes for partial sums of dK and dV, with which grouped heads are split over more workgroups.  0 if the shape is
+ * invalid.
  */
 size_t tk_attn_bwd_spill_workspace_bytes(int B, int Hq, int Nq, int Nk, int D);
 
@@ -174,7 +176,7 @@ int tk_attn_bwd_dq(const void* q, const void* k, const void* v, const void* d_o,
  *
  *   q, o, d_o, dq : bf16 [B, Hq, N, D]        k, v, dk, dv : bf16 [B, Hkv, N, D]
  *   lse, delta    : fp32 [B, Hq, N]
- *   dk, dv are summed over the query heads of each group (in fp32, inside one workgroup: no atomics).
+ *   dk, dv are summed over the query heads of each group (in fp32 and in a fixed order: no atomics).
  *   workspace for tk_attn_bwd_gqa: tk_attn_bwd_workspace_bytes(B, Hq, N, D) bytes.
  * TK_ERR_BAD_DIM also covers Hkv < 1, Hkv > Hq and Hq % Hkv != 0.
  */
@@ -272,6 +274,28 @@ int tk_attn_bwd_rect(const void* q, const void* k, const void* v,
                      int B, int Hq, int Hkv, int Nq, int Nk, int D, int causal, float scale,
                      void* workspace, size_t workspace_bytes,
                      void* stream);
+
+/*
+ * tk_attn_bwd_rect for callers that can hand over device scratch besides the workspace.  With a Delta-only
+ * workspace, grouped heads and too few key tiles to fill the chip, the query heads of each group are split over
+ * several workgroups, which leave fp32 partial sums of dK and dV in the scratch, added up in a fixed order.  (A
+ * workspace of tk_attn_bwd_spill_workspace_bytes holds the room for this itself.)  Results equal tk_attn_bwd_rect's
+ * up to fp32 summation order and are bit-reproducible.
+ *
+ *   scratch : device memory of tk_attn_bwd_scratch_bytes(...) bytes, 16-byte aligned; contents on entry are
+ *             ignored.  NULL or less than that many bytes: the call is tk_attn_bwd_rect.
+ * tk_attn_bwd_scratch_bytes returns 0 where the call, with a workspace of workspace_bytes, has no use for it (on the
+ * current device) or would be rejected.
+ */
+size_t tk_attn_bwd_scratch_bytes(int B, int Hq, int Hkv, int Nq, int Nk, int D, int causal, size_t workspace_bytes);
+
+int tk_attn_bwd_rect_scratch(const void* q, const void* k, const void* v,
+                             const void* o, const void* d_o, const float* lse,
+                             void* dq, void* dk, void* dv,
+                             int B, int Hq, int Hkv, int Nq, int Nk, int D, int causal, float scale,
+                             void* workspace, size_t workspace_bytes,
+                             void* scratch, size_t scratch_bytes,
+                             void* stream);
 
 /*
  * Decode-shaped forward: ONE query per head against Nk keys (the Nq = 1 case of tk_attn_fwd_rect,

@@ -26,7 +26,7 @@ TK_ERR_SCRATCH_LIMIT = -7
 
 EXPORTS = ("tk_attn_fwd", "tk_attn_bwd", "tk_attn_bwd_workspace_bytes", "tk_attn_bwd_delta",
            "tk_attn_bwd_dkdv", "tk_attn_bwd_dq", "tk_attn_fwd_gqa", "tk_attn_bwd_gqa", "tk_attn_bwd_dkdv_gqa",
-           "tk_attn_bwd_dq_gqa", "tk_attn_bwd_dq_delta", "tk_attn_fwd_rect", "tk_attn_fwd_rect_scratch", "tk_attn_fwd_scratch_bytes", "tk_attn_bwd_rect", "tk_attn_decode",
+           "tk_attn_bwd_dq_gqa", "tk_attn_bwd_dq_delta", "tk_attn_fwd_rect", "tk_attn_fwd_rect_scratch", "tk_attn_fwd_scratch_bytes", "tk_attn_bwd_rect", "tk_attn_bwd_rect_scratch", "tk_attn_bwd_scratch_bytes", "tk_attn_decode",
            "tk_attn_decode_workspace_bytes", "tk_attn_decode_plan", "tk_attn_bwd_noalloc", "tk_attn_bwd_noalloc_max_rows",
            "tk_attn_bwd_spill_workspace_bytes", "tk_attn_bwd_ds_bytes", "tk_attn_bwd_dkdv_ds", "tk_attn_bwd_dq_from_ds", "tk_rotary", "tk_gemm", "tk_mfma_probe", "tk_status_string", "tk_attn_version")
 
@@ -93,6 +93,10 @@ def load_library(path: str = LIB_PATH) -> ctypes.CDLL:
     lib.tk_attn_fwd_rect_scratch.restype = i
     lib.tk_attn_bwd_rect.argtypes = [vp, vp, vp, vp, vp, fp, vp, vp, vp, i, i, i, i, i, i, i, f, vp, sz, vp]
     lib.tk_attn_bwd_rect.restype = i
+    lib.tk_attn_bwd_scratch_bytes.argtypes = [i, i, i, i, i, i, i, sz]
+    lib.tk_attn_bwd_scratch_bytes.restype = sz
+    lib.tk_attn_bwd_rect_scratch.argtypes = [vp, vp, vp, vp, vp, fp, vp, vp, vp, i, i, i, i, i, i, i, f, vp, sz, vp, sz, vp]
+    lib.tk_attn_bwd_rect_scratch.restype = i
     lib.tk_attn_decode.argtypes = [vp, vp, vp, vp, fp, i, i, i, i, i, f, vp, sz, vp]
     lib.tk_attn_decode.restype = i
     lib.tk_attn_decode_plan.argtypes = [i, i, i, i, i, i, ctypes.POINTER(ctypes.c_int)]
@@ -256,6 +260,18 @@ def tk_attn_bwd_rect(q, k, v, o, d_o, lse, dq, dk, dv, B, Hq, Hkv, Nq, Nk, D, ca
     return load_library().tk_attn_bwd_rect(_ptr(q), _ptr(k), _ptr(v), _ptr(o), _ptr(d_o), _ptr(lse), _ptr(dq),
                                            _ptr(dk), _ptr(dv), B, Hq, Hkv, Nq, Nk, D, int(bool(causal)), float(scale),
                                            _ptr(workspace), int(workspace_bytes), _stream(stream))
+
+
+def tk_attn_bwd_scratch_bytes(B, Hq, Hkv, Nq, Nk, D, causal, workspace_bytes) -> int:
+    return int(load_library().tk_attn_bwd_scratch_bytes(B, Hq, Hkv, Nq, Nk, D, int(bool(causal)), int(workspace_bytes)))
+
+
+def tk_attn_bwd_rect_scratch(q, k, v, o, d_o, lse, dq, dk, dv, B, Hq, Hkv, Nq, Nk, D, causal, scale, workspace,
+                             workspace_bytes, scratch, scratch_bytes, stream=None) -> int:
+    return load_library().tk_attn_bwd_rect_scratch(_ptr(q), _ptr(k), _ptr(v), _ptr(o), _ptr(d_o), _ptr(lse), _ptr(dq),
+                                                   _ptr(dk), _ptr(dv), B, Hq, Hkv, Nq, Nk, D, int(bool(causal)), float(scale),
+                                                   _ptr(workspace), int(workspace_bytes), _ptr(scratch), int(scratch_bytes),
+                                                   _stream(stream))
 
 
 def tk_attn_decode_workspace_bytes(B, Hq, Hkv, Nk, D) -> int:

@@ -131,13 +131,18 @@ template <int D> __device__ __forceinline__ int swz(int row) {
 // h = lane / 32) holds in half s the queries 16s + 8g + 4h + t (g = 0..1, t = 0..3) of the block, at
 // element 4g + t.  Block (query head, key tile kt, query block qb, wave w) sits at
 // (((head * num_kv_tiles + kt) * n_qb + qb) * 4 + w) * 2048 bytes.  Masked pairs and padding rows hold 0.
-template <int D, bool CAUSAL, bool TAIL, bool SPILL>
+//
+// SPLIT (implies TAIL): the query heads of a group are dealt to n_splits workgroups, each of which leaves fp32
+// sums over its own heads in Part ([n_splits][2: dK, dV][B * hkv][Nk][D], unscaled) for attn_bwd_dkdv_sum_kernel.
+// For launches with fewer units than compute units: a unit's time is the length of its query stream, 1.2 us a
+// block of 32 queries, whether the other compute units are idle or not.
+template <int D, bool CAUSAL, bool TAIL, bool SPILL, bool SPLIT>
 __global__ __launch_bounds__(256, D == 64 ? 2 : 1)
 void attn_bwd_dkdv_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K, const bf16* __restrict__ V,
                           const bf16* __restrict__ dO, const float* __restrict__ LSE, const float* __restrict__ Delta,
                           bf16* __restrict__ dK, bf16* __restrict__ dV,
                           int Nq, int Nk, int num_kv_tiles, int total_units, float scale, int hq, int hkv,
-                          char* __restrict__ DS, int n_qb)
+                          char* __restrict__ DS, int n_qb, int n_splits, float* __restrict__ Part)
 {
     using S = DkdvShape<D>;
     __shared__ __attribute__((aligned(1024))) char ring[S::kStages * S::kStageBytes];
@@ -158,10 +163,11 @@ void attn_bwd_dkdv_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K
     // Grouped-query attention: a key/value head is shared by `group` consecutive query heads, and a
     // pass streams the query blocks of all of them, one head after the other, into the same dK, dV
     // accumulators.  bh below counts key/value heads.
-    const int group = hq / hkv;
+    const int heads_per_kv = hq / hkv;
+    const int group = SPLIT ? heads_per_kv / n_splits : heads_per_kv;      // query heads of a pass
     const int units = CAUSAL ? (num_kv_tiles + 1) / 2 : num_kv_tiles;
-    auto q_head_row = [&](int bh) {         // first row of the first query head of key/value head bh
-        return (size_t)((bh / hkv) * hq + (bh % hkv) * group) * Nq;
+    auto q_head_row = [&](int bh, int split) {         // first row of the first query head of a pass of key/value head bh
+        return (size_t)((bh / hkv) * hq + (bh % hkv) * heads_per_kv + split * group) * Nq;
     };
     // The query blocks of a pass: blocks of 32 rows from pass_ibegin(kt) on, per query head of the
     // group; an even count (the loops below take two blocks per trip), of which the first
@@ -177,10 +183,12 @@ void attn_bwd_dkdv_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K
     auto pass_nblocks = [&](int ibegin) {
         return TAIL ? 2 * ((Nq - ibegin + 2 * S::kTileQ - 1) / (2 * S::kTileQ)) : (Nq - ibegin) / S::kTileQ;
     };
-    auto pass_tile = [&](int vu, int half, int& bh, int& kt) {
+    auto pass_tile = [&](int vu, int half, int& bh, int& kt, int& split) {
         const int logical = xcd_remap(vu, total_units);
         bh = logical / units;
         const int unit = logical % units;
+        split = 0;
+        if (SPLIT) { split = bh % n_splits; bh /= n_splits; }      // (the units of a split, which read the same queries, are neighbours)
         kt = half == 0 ? unit : num_kv_tiles - 1 - unit;
     };
     // the pass after (vu, half) in this workgroup's walk; vu >= total_units means "none"
@@ -222,10 +230,10 @@ void attn_bwd_dkdv_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K
         p_left = p_nblocks;
     };
     auto producer_open = [&]() __attribute__((always_inline)) {            // set the cursor to the first block of pass (p_vu, p_half)
-        int bh, kt;
-        pass_tile(p_vu, p_half, bh, kt);
+        int bh, kt, split;
+        pass_tile(p_vu, p_half, bh, kt, split);
         p_ibegin = pass_ibegin(kt);
-        p_head_row = q_head_row(bh);
+        p_head_row = q_head_row(bh, split);
         p_nblocks = pass_nblocks(p_ibegin);
         p_g = 0;
         producer_head();
@@ -319,8 +327,8 @@ void attn_bwd_dkdv_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K
     int c_stage = 0;                        // byte offset of the ring stage of the next block to consume ...
     int c_stage1 = S::kStageBytes, c_stage2 = 2 * S::kStageBytes;      // ... and of the two blocks after it (D = 128)
     {
-        int bh, kt;
-        pass_tile(c_vu, c_half, bh, kt);
+        int bh, kt, split;
+        pass_tile(c_vu, c_half, bh, kt, split);
         producer_open();
 #pragma unroll
         for (int b = 0; b < S::kAhead; b++) issue_next();
@@ -329,8 +337,8 @@ void attn_bwd_dkdv_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K
 
 #pragma unroll 1
     while (c_vu < total_units) {
-    int bh, kt;
-    pass_tile(c_vu, c_half, bh, kt);
+    int bh, kt, split;
+    pass_tile(c_vu, c_half, bh, kt, split);
     const size_t head = (size_t)bh * Nk * D;       // of the key/value head
     const int j0 = kt * S::kTileKV;
     const int jw0 = j0 + wave * 32;                // first key of this wave
@@ -365,7 +373,7 @@ void attn_bwd_dkdv_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K
 
     // register r of a score block <-> query i0 + 8*(r/4) + 4h + r%4, lane <-> key my_j
     const bool pad_key = TAIL && SPILL && my_j >= Nk;    // a padding key was computed from the last real row: its dS must not reach dQ
-    auto q_head_of = [&](int g) { return (size_t)(bh / hkv) * hq + (size_t)(bh % hkv) * group + g; };
+    auto q_head_of = [&](int g) { return (size_t)(bh / hkv) * hq + (size_t)(bh % hkv) * heads_per_kv + split * group + g; };
 
     if constexpr (S::kPipe) {
     // ------------------------------------------------------------------------------------------
@@ -700,9 +708,23 @@ void attn_bwd_dkdv_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K
     // products and its stores run (S and dP are done with the old fragments).
     next_pass(c_vu, c_half);
     if (c_vu < total_units) {
-        int nbh, nkt;
-        pass_tile(c_vu, c_half, nbh, nkt);
+        int nbh, nkt, nsplit;
+        pass_tile(c_vu, c_half, nbh, nkt, nsplit);
         load_kv(nbh, nkt);
+    }
+    if (SPLIT) {            // fp32 sums, 16 bytes per lane straight from the accumulators
+        if (my_j < Nk) {
+            const size_t kv_floats = (size_t)(total_units / (units * n_splits)) * Nk * D;     // of all key/value heads
+            float* dst = Part + (size_t)split * 2 * kv_floats + head + (size_t)my_j * D + 4 * h;
+#pragma unroll
+            for (int db = 0; db < D / 32; db++)
+#pragma unroll
+                for (int g = 0; g < 4; g++) {
+                    *(f32x4*)(dst + 32 * db + 8 * g) = f32x4{dk_acc[db][4 * g], dk_acc[db][4 * g + 1], dk_acc[db][4 * g + 2], dk_acc[db][4 * g + 3]};
+                    *(f32x4*)(dst + kv_floats + 32 * db + 8 * g) = f32x4{dv_acc[db][4 * g], dv_acc[db][4 * g + 1], dv_acc[db][4 * g + 2], dv_acc[db][4 * g + 3]};
+                }
+        }
+        continue;
     }
     // ---- epilogue.  In accumulator layout a lane holds 4 consecutive columns of ONE key row
     // (lane <-> key my_j, register r of block db <-> column 32db + 8*(r/4) + 4h + r%4), so storing
@@ -735,49 +757,71 @@ void attn_bwd_dkdv_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K
     wait_vmcnt<0>();      // the spare prefetches of the last blocks must not outlive the workgroup's LDS
 }
 
-template <int D, bool CAUSAL, bool TAIL, bool SPILL>
+// dK = scale * sum of the n_splits partial sums, dV likewise without the scale; blockIdx.y: 0 dK, 1 dV.  n4: groups of four elements of one tensor.
+__global__ __launch_bounds__(256)
+void attn_bwd_dkdv_sum_kernel(const float* __restrict__ Part, bf16* __restrict__ dK, bf16* __restrict__ dV, size_t n4, int n_splits, float scale)
+{
+    const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
+    if (i >= n4) return;
+    const f32x4* src = (const f32x4*)Part + (size_t)blockIdx.y * n4 + i;
+    f32x4 acc = src[0];
+#pragma unroll 4
+    for (int s = 1; s < n_splits; s++) acc += src[(size_t)s * 2 * n4];
+    const float mul = blockIdx.y == 0 ? scale : 1.0f;
+    const bf16x2 lo = cvt2(acc[0] * mul, acc[1] * mul), hi = cvt2(acc[2] * mul, acc[3] * mul);
+    *(bf16x4*)((blockIdx.y == 0 ? dK : dV) + 4 * i) = __builtin_shufflevector(lo, hi, 0, 1, 2, 3);
+}
+
+template <int D, bool CAUSAL, bool TAIL, bool SPILL, bool SPLIT>
 static hipError_t launch_dkdv_tt(const void* q, const void* k, const void* v, const void* d_o,
                                  const float* lse, const float* delta, void* dk, void* dv,
-                                 int B, int H, int Hkv, int Nq, int Nk, float scale, hipStream_t stream, void* ds)
+                                 int B, int H, int Hkv, int Nq, int Nk, float scale, hipStream_t stream, void* ds,
+                                 int n_splits, float* part)
 {
     using S = DkdvShape<D>;
     const int num_kv_tiles = (Nk + S::kTileKV - 1) / S::kTileKV;
-    const int total_units = B * Hkv * (CAUSAL ? (num_kv_tiles + 1) / 2 : num_kv_tiles);
+    const int total_units = B * Hkv * n_splits * (CAUSAL ? (num_kv_tiles + 1) / 2 : num_kv_tiles);
     int cus = 0;
     hipError_t e = compute_unit_count(&cus);
     if (e != hipSuccess) return e;
     const int resident = cus * (D == 64 ? 2 : 1);               // as many workgroups as fit at once
     const int grid = total_units < resident ? total_units : resident;
-    hipLaunchKernelGGL((attn_bwd_dkdv_kernel<D, CAUSAL, TAIL, SPILL>), dim3(grid), dim3(S::kThreads), 0, stream,
+    hipLaunchKernelGGL((attn_bwd_dkdv_kernel<D, CAUSAL, TAIL, SPILL, SPLIT>), dim3(grid), dim3(S::kThreads), 0, stream,
                        (const bf16*)q, (const bf16*)k, (const bf16*)v, (const bf16*)d_o, lse, delta,
                        (bf16*)dk, (bf16*)dv, Nq, Nk, num_kv_tiles, total_units, scale, H, Hkv,
-                       (char*)ds, ds_query_blocks(Nq));
+                       (char*)ds, ds_query_blocks(Nq), n_splits, part);
+    if (SPLIT) {
+        const size_t n4 = (size_t)B * Hkv * Nk * D / 4;
+        hipLaunchKernelGGL(attn_bwd_dkdv_sum_kernel, dim3((unsigned)((n4 + 255) / 256), 2), dim3(256), 0, stream,
+                           part, (bf16*)dk, (bf16*)dv, n4, n_splits, scale);
+    }
     return hipGetLastError();
 }
 
 template <int D, bool CAUSAL>
 static hipError_t launch_dkdv_t(const void* q, const void* k, const void* v, const void* d_o,
                                 const float* lse, const float* delta, void* dk, void* dv,
-                                int B, int H, int Hkv, int Nq, int Nk, float scale, hipStream_t stream, void* ds)
+                                int B, int H, int Hkv, int Nq, int Nk, float scale, hipStream_t stream, void* ds,
+                                int n_splits, float* part)
 {
     using S = DkdvShape<D>;
     const bool tail = Nq != Nk || Nk % S::kTileKV;
-    if (ds) return tail ? launch_dkdv_tt<D, CAUSAL, true, true>(q, k, v, d_o, lse, delta, dk, dv, B, H, Hkv, Nq, Nk, scale, stream, ds)
-                        : launch_dkdv_tt<D, CAUSAL, false, true>(q, k, v, d_o, lse, delta, dk, dv, B, H, Hkv, Nq, Nk, scale, stream, ds);
-    return tail ? launch_dkdv_tt<D, CAUSAL, true, false>(q, k, v, d_o, lse, delta, dk, dv, B, H, Hkv, Nq, Nk, scale, stream, ds)
-                : launch_dkdv_tt<D, CAUSAL, false, false>(q, k, v, d_o, lse, delta, dk, dv, B, H, Hkv, Nq, Nk, scale, stream, ds);
+    auto launch = part ? (ds ? launch_dkdv_tt<D, CAUSAL, true, true, true> : launch_dkdv_tt<D, CAUSAL, true, false, true>)
+                : tail ? (ds ? launch_dkdv_tt<D, CAUSAL, true, true, false> : launch_dkdv_tt<D, CAUSAL, true, false, false>)
+                       : (ds ? launch_dkdv_tt<D, CAUSAL, false, true, false> : launch_dkdv_tt<D, CAUSAL, false, false, false>);
+    return launch(q, k, v, d_o, lse, delta, dk, dv, B, H, Hkv, Nq, Nk, scale, stream, ds, part ? n_splits : 1, part);
 }
 
-// ds != nullptr: the kernel also stores its dS blocks there (ds_spill_bytes(...) bytes) for launch_attn_bwd_dq_from_ds
+// ds != nullptr: the kernel also stores its dS blocks there (ds_spill_bytes(...) bytes) for launch_attn_bwd_dq_from_ds.
+// part != nullptr: the query heads of a group are split n_splits ways (dkdv_splits()), partial sums in part.
 hipError_t launch_attn_bwd_dkdv(const void* q, const void* k, const void* v, const void* d_o,
                                 const float* lse, const float* delta, void* dk, void* dv,
                                 int B, int H, int Hkv, int Nq, int Nk, int D, int causal, float scale, hipStream_t stream,
-                                void* ds)
+                                void* ds, int n_splits, float* part)
 {
-    if (D == 128) return causal ? launch_dkdv_t<128, true>(q, k, v, d_o, lse, delta, dk, dv, B, H, Hkv, Nq, Nk, scale, stream, ds)
-                                : launch_dkdv_t<128, false>(q, k, v, d_o, lse, delta, dk, dv, B, H, Hkv, Nq, Nk, scale, stream, ds);
-    return causal ? launch_dkdv_t<64, true>(q, k, v, d_o, lse, delta, dk, dv, B, H, Hkv, Nq, Nk, scale, stream, ds)
-                  : launch_dkdv_t<64, false>(q, k, v, d_o, lse, delta, dk, dv, B, H, Hkv, Nq, Nk, scale, stream, ds);
+    auto launch = D == 128 ? (causal ? launch_dkdv_t<128, true> : launch_dkdv_t<128, false>)
+                           : (causal ? launch_dkdv_t<64, true> : launch_dkdv_t<64, false>);
+    return launch(q, k, v, d_o, lse, delta, dk, dv, B, H, Hkv, Nq, Nk, scale, stream, ds, n_splits, part);
 }
 
 // ------------------------------------------------------------------------------------------

@@ -197,9 +197,13 @@ PyObject* bwd(PyObject* const* a) {
         dk = tensor(a[13], "dk");
         dv = tensor(a[14], "dv");
     }
-    const int rc = tk_attn_bwd_rect(q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(), d_o.data_ptr(), (const float*)lse.data_ptr(),
-                                    dq.data_ptr(), dk.data_ptr(), dv.data_ptr(), s.B, s.Hq, s.Hkv, s.Nq, s.Nk, s.D, causal, scale,
-                                    workspace.data_ptr(), (size_t)workspace.numel() * workspace.element_size(), stream);
+    const size_t workspace_bytes = (size_t)workspace.numel() * workspace.element_size();
+    const size_t n = s.Hq != s.Hkv ? tk_attn_bwd_scratch_bytes(s.B, s.Hq, s.Hkv, s.Nq, s.Nk, s.D, causal, workspace_bytes) : 0;
+    at::Tensor scratch;
+    if (n) scratch = scratch_on(stream, n, q);
+    const int rc = tk_attn_bwd_rect_scratch(q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(), d_o.data_ptr(), (const float*)lse.data_ptr(),
+                                            dq.data_ptr(), dk.data_ptr(), dv.data_ptr(), s.B, s.Hq, s.Hkv, s.Nq, s.Nk, s.D, causal, scale,
+                                            workspace.data_ptr(), workspace_bytes, n ? scratch.data_ptr() : nullptr, n, stream);
     return rc != TK_OK ? status(rc) : give({&dq, &dk, &dv});
 }
 

@@ -120,6 +120,28 @@ DecodePlan plan_decode(int B, int Hq, int Hkv, int Nk, int compute_units)
     return p;
 }
 
+// The dS buffer of the storing backward ends with room for the partial sums of a split dK/dV kernel.  It is sized
+// without the number of key/value heads (n_splits * Hkv <= Hq) and of the device, so it is there wherever a split may
+// happen: up to 256 compute units with two workgroups each, and dS no larger than 4 GiB (with more the room would be
+// large for the rare call, few key tiles under very many query heads, that could use it).
+constexpr int kDkdvMaxWorkgroups = 512;
+
+size_t dkdv_part_room(int B, int Hq, int Nq, int Nk, int D)
+{
+    const long long units = (long long)B * (((Nk + 127) / 128 + 1) / 2);
+    if (Hq == 1 || Nq < 256 || 2 * units > kDkdvMaxWorkgroups || tk::ds_spill_bytes(B, Hq, Nq, Nk) > ((size_t)4 << 30)) return 0;
+    return tk::dkdv_part_bytes(B, Hq, Nk, D, 1);
+}
+
+// how the dK/dV kernel of a storing backward splits, given that room
+int dkdv_splits_storing(int B, int Hq, int Hkv, int Nq, int Nk, int D, int causal)
+{
+    int cus = 0;
+    if (dkdv_part_room(B, Hq, Nq, Nk, D) == 0 || tk::compute_unit_count(&cus) != hipSuccess) return 1;
+    if (cus > kDkdvMaxWorkgroups / 2) cus = kDkdvMaxWorkgroups / 2;
+    return tk::dkdv_splits(B, Hq, Hkv, Nq, Nk, D, causal != 0, cus);
+}
+
 // Few queries against a longer history: the heads and 128-query tiles alone leave compute units idle.  The split
 // aims at the two workgroups per compute unit that are resident at once at D = 128.  Whole call, us (unsplit, then
 // 1, 2, 3, 4 per compute unit): B1 Hq32 Hkv8 Nq512 Nk8192 D128 163, 98, 84, 89, 92; Hq64 of the same 186, 164, 146,
@@ -265,13 +287,13 @@ size_t tk_attn_bwd_workspace_bytes(int B, int H, int N, int D)
 size_t tk_attn_bwd_spill_workspace_bytes(int B, int Hq, int Nq, int Nk, int D)
 {
     if (check_lengths(B, Hq, Hq, Nq, Nk, D, 0) != TK_OK) return 0;
-    return delta_bytes(B, Hq, Nq) + tk::ds_spill_bytes(B, Hq, Nq, Nk);
+    return delta_bytes(B, Hq, Nq) + tk_attn_bwd_ds_bytes(B, Hq, Nq, Nk, D);
 }
 
 size_t tk_attn_bwd_ds_bytes(int B, int Hq, int Nq, int Nk, int D)
 {
     if (check_lengths(B, Hq, Hq, Nq, Nk, D, 0) != TK_OK) return 0;
-    return tk::ds_spill_bytes(B, Hq, Nq, Nk);
+    return tk::ds_spill_bytes(B, Hq, Nq, Nk) + dkdv_part_room(B, Hq, Nq, Nk, D);
 }
 
 int tk_attn_bwd_dkdv_ds(const void* q, const void* k, const void* v, const void* d_o,
@@ -284,8 +306,10 @@ int tk_attn_bwd_dkdv_ds(const void* q, const void* k, const void* v, const void*
         !aligned16(delta) || !aligned16(dk) || !aligned16(dv) || !aligned16(ds))
         return TK_ERR_MISALIGNED;
     if (int rc = check_scale(scale)) return rc;
+    const int n_splits = dkdv_splits_storing(B, Hq, Hkv, N, N, D, causal);
+    float* part = n_splits > 1 ? (float*)((char*)ds + tk::ds_spill_bytes(B, Hq, N, N)) : nullptr;
     hipError_t e = tk::launch_attn_bwd_dkdv(q, k, v, d_o, lse, delta, dk, dv, B, Hq, Hkv, N, N, D, causal != 0, scale,
-                                            (hipStream_t)stream, ds);
+                                            (hipStream_t)stream, ds, n_splits, part);
     return e == hipSuccess ? TK_OK : TK_ERR_LAUNCH;
 }
 
@@ -371,27 +395,41 @@ int tk_attn_bwd_dq(const void* q, const void* k, const void* v, const void* d_o,
     return tk_attn_bwd_dq_gqa(q, k, v, d_o, lse, delta, dq, B, H, H, N, D, causal, scale, stream);
 }
 
-int tk_attn_bwd_rect(const void* q, const void* k, const void* v, const void* o, const void* d_o, const float* lse,
-                     void* dq, void* dk, void* dv,
-                     int B, int Hq, int Hkv, int Nq, int Nk, int D, int causal, float scale,
-                     void* workspace, size_t workspace_bytes, void* stream)
+size_t tk_attn_bwd_scratch_bytes(int B, int Hq, int Hkv, int Nq, int Nk, int D, int causal, size_t workspace_bytes)
+{
+    if (check_lengths(B, Hq, Hkv, Nq, Nk, D, causal) != TK_OK || Hq == Hkv) return 0;
+    if (workspace_bytes >= delta_bytes(B, Hq, Nq) + tk::ds_spill_bytes(B, Hq, Nq, Nk)) return 0;
+    int cus = 0;
+    if (tk::compute_unit_count(&cus) != hipSuccess) return 0;
+    const int n_splits = tk::dkdv_splits(B, Hq, Hkv, Nq, Nk, D, causal != 0, cus);
+    return n_splits > 1 ? tk::dkdv_part_bytes(B, Hkv, Nk, D, n_splits) : 0;
+}
+
+int tk_attn_bwd_rect_scratch(const void* q, const void* k, const void* v, const void* o, const void* d_o, const float* lse,
+                             void* dq, void* dk, void* dv,
+                             int B, int Hq, int Hkv, int Nq, int Nk, int D, int causal, float scale,
+                             void* workspace, size_t workspace_bytes, void* scratch, size_t scratch_bytes, void* stream)
 {
     if (!q || !k || !v || !o || !d_o || !lse || !dq || !dk || !dv || !workspace) return TK_ERR_NULL_PTR;
     if (int rc = check_lengths(B, Hq, Hkv, Nq, Nk, D, causal)) return rc;
     if (!aligned16(q) || !aligned16(k) || !aligned16(v) || !aligned16(o) || !aligned16(d_o) || !aligned16(lse) ||
-        !aligned16(dq) || !aligned16(dk) || !aligned16(dv) || !aligned16(workspace))
+        !aligned16(dq) || !aligned16(dk) || !aligned16(dv) || !aligned16(workspace) || !aligned16(scratch))
         return TK_ERR_MISALIGNED;
     if (int rc = check_scale(scale)) return rc;
     if (workspace_bytes < tk_attn_bwd_workspace_bytes(B, Hq, Nq, D)) return TK_ERR_WORKSPACE_TOO_SMALL;
 
     hipStream_t s = (hipStream_t)stream;
     float* delta = (float*)workspace;
-    if (workspace_bytes >= tk_attn_bwd_spill_workspace_bytes(B, Hq, Nq, Nk, D)) {
+    if (workspace_bytes >= delta_bytes(B, Hq, Nq) + tk::ds_spill_bytes(B, Hq, Nq, Nk)) {
         // Large workspace: 10*D flops per (query, key) pair instead of 14*D.  Delta on its own, then dK/dV,
         // which also leaves its bf16 dS blocks behind Delta in the workspace, then dQ = scale * dS K from them.
-        void* ds = (char*)workspace + delta_bytes(B, Hq, Nq);
+        // (A workspace with room for dS but not for partial sums behind it runs unsplit.)
+        char* ds = (char*)workspace + delta_bytes(B, Hq, Nq);
+        const bool room = workspace_bytes >= tk_attn_bwd_spill_workspace_bytes(B, Hq, Nq, Nk, D);
+        const int n_splits = room ? dkdv_splits_storing(B, Hq, Hkv, Nq, Nk, D, causal) : 1;
+        float* part = n_splits > 1 ? (float*)(ds + tk::ds_spill_bytes(B, Hq, Nq, Nk)) : nullptr;
         if (tk::launch_attn_bwd_delta(o, d_o, delta, B, Hq, Nq, D, s) != hipSuccess) return TK_ERR_LAUNCH;
-        if (tk::launch_attn_bwd_dkdv(q, k, v, d_o, lse, delta, dk, dv, B, Hq, Hkv, Nq, Nk, D, causal != 0, scale, s, ds) != hipSuccess)
+        if (tk::launch_attn_bwd_dkdv(q, k, v, d_o, lse, delta, dk, dv, B, Hq, Hkv, Nq, Nk, D, causal != 0, scale, s, ds, n_splits, part) != hipSuccess)
             return TK_ERR_LAUNCH;
         if (tk::launch_attn_bwd_dq_from_ds(k, ds, dq, B, Hq, Hkv, Nq, Nk, D, causal != 0, scale, s) != hipSuccess)
             return TK_ERR_LAUNCH;
@@ -403,9 +441,22 @@ int tk_attn_bwd_rect(const void* q, const void* k, const void* v, const void* o,
     if (tk::launch_attn_bwd_dq(q, k, v, d_o, lse, nullptr, dq, B, Hq, Hkv, Nq, Nk, D, causal != 0, scale, s, o, delta) != hipSuccess)
         return TK_ERR_LAUNCH;
     // 2. dK, dV per key tile of every key/value head, with that Delta
-    if (tk::launch_attn_bwd_dkdv(q, k, v, d_o, lse, delta, dk, dv, B, Hq, Hkv, Nq, Nk, D, causal != 0, scale, s) != hipSuccess)
+    const size_t need = scratch ? tk_attn_bwd_scratch_bytes(B, Hq, Hkv, Nq, Nk, D, causal, workspace_bytes) : 0;
+    const bool split = need > 0 && scratch_bytes >= need;
+    const int n_splits = split ? (int)(need / tk::dkdv_part_bytes(B, Hkv, Nk, D, 1)) : 1;
+    if (tk::launch_attn_bwd_dkdv(q, k, v, d_o, lse, delta, dk, dv, B, Hq, Hkv, Nq, Nk, D, causal != 0, scale, s, nullptr, n_splits,
+                                 split ? (float*)scratch : nullptr) != hipSuccess)
         return TK_ERR_LAUNCH;
     return TK_OK;
+}
+
+int tk_attn_bwd_rect(const void* q, const void* k, const void* v, const void* o, const void* d_o, const float* lse,
+                     void* dq, void* dk, void* dv,
+                     int B, int Hq, int Hkv, int Nq, int Nk, int D, int causal, float scale,
+                     void* workspace, size_t workspace_bytes, void* stream)
+{
+    return tk_attn_bwd_rect_scratch(q, k, v, o, d_o, lse, dq, dk, dv, B, Hq, Hkv, Nq, Nk, D, causal, scale,
+                                    workspace, workspace_bytes, nullptr, 0, stream);
 }
 
 int tk_attn_bwd_gqa(const void* q, const void* k, const void* v, const void* o, const void* d_o, const float* lse,

@@ -68,11 +68,32 @@ inline size_t ds_spill_bytes(int B, int H, int Nq, int Nk) {
     return (size_t)B * H * (size_t)((Nk + 127) / 128) * (size_t)ds_query_blocks(Nq) * 8192;
 }
 
+// Ways to split the query heads of a group over workgroups of the dK/dV kernel: the largest divisor of the group with
+// which the units still fit the compute units at once, 1 = no split.  (With more units than that the split only adds
+// the traffic of the partial sums.)  Fewer than 256 queries are not split: the stream of a unit is then short next to
+// the launch of the kernel that adds up.  Whole backward, us, unsplit and split: B2 Hq16 Hkv4 N1001 D128 causal 219,
+// 112; B1 Hq32 Hkv8 N4096 642, 579 (two ways); B1 Hq64 Hkv1 N3000 6956, 686; B1 Hq8 Hkv1 N300 148, 53; at D = 64
+// B1 Hq32 Hkv8 N2048 204, 111.
+inline int dkdv_splits(int B, int H, int Hkv, int Nq, int Nk, int D, bool causal, int compute_units) {
+    const int tiles = (Nk + 127) / 128, group = H / Hkv;
+    const long long units = (long long)B * Hkv * (causal ? (tiles + 1) / 2 : tiles);
+    const long long resident = (long long)compute_units * (D == 64 ? 2 : 1);
+    if (Nq < 256) return 1;
+    for (int s = group; s > 1; s--)
+        if (group % s == 0 && units * s <= resident) return s;
+    return 1;
+}
+// fp32 partial sums of dK and dV
+inline size_t dkdv_part_bytes(int B, int Hkv, int Nk, int D, int n_splits) {
+    return (size_t)n_splits * 2 * B * Hkv * Nk * D * sizeof(float);
+}
+
 // dK, dV (key-tile parallel).  ds != nullptr: also store the dS blocks there (ds_spill_bytes(B, H, Nq, Nk) bytes).
+// part != nullptr: n_splits = dkdv_splits(...) > 1 ways, partial sums in part (dkdv_part_bytes(...) bytes).
 hipError_t launch_attn_bwd_dkdv(const void* q, const void* k, const void* v, const void* d_o,
                                 const float* lse, const float* delta, void* dk, void* dv,
                                 int B, int H, int Hkv, int Nq, int Nk, int D, int causal, float scale, hipStream_t stream,
-                                void* ds = nullptr);
+                                void* ds = nullptr, int n_splits = 1, float* part = nullptr);
 
 // dQ = scale * dS K from the blocks a launch_attn_bwd_dkdv call with the same shape arguments stored
 hipError_t launch_attn_bwd_dq_from_ds(const void* k, const void* ds, void* dq,
