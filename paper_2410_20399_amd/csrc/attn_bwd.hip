@@ -1284,6 +1284,10 @@ void attn_bwd_dq_from_ds_kernel(const bf16* __restrict__ K, const char* __restri
         step(set3, t + 3);
     }
     wait_vmcnt<0>();          // the redirected loads of the last steps must not outlive this pass (LDS, registers)
+    // Nobody uses what the last of them bring, but their registers have to stay taken until they are here: the compiler
+    // would give them to the epilogue's row numbers and accumulators, which a late load then overwrites.
+#pragma unroll
+    for (int n = 0; n < 4; n++) { claim_loaded(set0[n]); claim_loaded(set1[n]); claim_loaded(set2[n]); claim_loaded(set3[n]); }
     __builtin_amdgcn_s_barrier();
 
     if (!TAIL || my_q < Nq) {
