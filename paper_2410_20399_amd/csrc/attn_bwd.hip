@@ -1088,11 +1088,11 @@ hipError_t launch_attn_bwd_dq(const void* q, const void* k, const void* v, const
 // ------------------------------------------------------------------------------------------
 // kernel 4: dQ from the dS blocks that kernel 2 stored
 // ------------------------------------------------------------------------------------------
-template <int D>
+template <int D, int WAVES>
 struct DqDsShape {
-    static constexpr int kWaves = 8;
-    static constexpr int kThreads = 512;
-    static constexpr int kTileQ = 256;                  // queries per workgroup (32 per wave)
+    static constexpr int kWaves = WAVES;
+    static constexpr int kThreads = 64 * kWaves;
+    static constexpr int kTileQ = 32 * kWaves;          // queries per workgroup (32 per wave)
     static constexpr int kTileKV = 64;                  // keys per step
     static constexpr int kRowBytes = D * 2;
     static constexpr int kChunksPerRow = D / 8;
@@ -1130,13 +1130,17 @@ __device__ __forceinline__ void claim_loaded(bf16x8& r) { asm volatile("" : "+v"
 // 16 lanes: every bank once).  No mask code: kernel 2 stored zeros for masked pairs, padding queries and
 // padding keys; a wave does not compute on tiles that lie wholly beyond its diagonal, which kernel 2 may not
 // have written: its loads of such tiles are redirected to its last real tile.
-template <int D, bool CAUSAL, bool TAIL>
-__global__ __launch_bounds__(512, 1)
+//
+// Four waves instead of eight (a tile of 128 queries) where the launch then still fits the compute units at once:
+// the time of a step on a compute unit is that of its waves' LDS reads.  Whole backward, causal D128: B2 Hq16 Hkv4
+// N1001 112 -> 100 us, B1 H16 N4096 269 -> 248, B4 H16 N1024 99 -> 91.
+template <int D, bool CAUSAL, bool TAIL, int WAVES>
+__global__ __launch_bounds__(64 * WAVES, 1)
 void attn_bwd_dq_from_ds_kernel(const bf16* __restrict__ K, const char* __restrict__ DS, bf16* __restrict__ dQ,
                                 int Nq, int Nk, int num_q_tiles, int total_wg, float scale, int hq, int hkv,
                                 int num_kv_tiles, int n_qb)
 {
-    using S = DqDsShape<D>;
+    using S = DqDsShape<D, WAVES>;
     __shared__ __attribute__((aligned(1024))) char smem[S::kLdsBytes];
     char* const kring = smem;
     const int tid = threadIdx.x;
@@ -1304,12 +1308,12 @@ void attn_bwd_dq_from_ds_kernel(const bf16* __restrict__ K, const char* __restri
     }   // pass
 }
 
-template <int D, bool CAUSAL, bool TAIL>
+template <int D, bool CAUSAL, bool TAIL, int WAVES>
 static hipError_t launch_dq_from_ds_tt(const void* k, const void* ds, void* dq,
                                        int B, int H, int Hkv, int Nq, int Nk, float scale, hipStream_t stream)
 {
-    using S = DqDsShape<D>;
-    auto kern = attn_bwd_dq_from_ds_kernel<D, CAUSAL, TAIL>;
+    using S = DqDsShape<D, WAVES>;
+    auto kern = attn_bwd_dq_from_ds_kernel<D, CAUSAL, TAIL, WAVES>;
     const int num_q_tiles = (Nq + S::kTileQ - 1) / S::kTileQ;
     const int num_kv_tiles = (Nk + 127) / 128;
     const int total = B * H * (CAUSAL ? (num_q_tiles + 1) / 2 : num_q_tiles);
@@ -1319,22 +1323,26 @@ static hipError_t launch_dq_from_ds_tt(const void* k, const void* ds, void* dq,
     return hipGetLastError();
 }
 
-template <int D>
+template <int D, bool CAUSAL>
 static hipError_t launch_dq_from_ds_t(const void* k, const void* ds, void* dq,
-                                      int B, int H, int Hkv, int Nq, int Nk, int causal, float scale, hipStream_t stream)
+                                      int B, int H, int Hkv, int Nq, int Nk, float scale, hipStream_t stream)
 {
-    const bool tail = Nq != Nk || Nq % 256;
-    if (causal) return tail ? launch_dq_from_ds_tt<D, true, true>(k, ds, dq, B, H, Hkv, Nq, Nk, scale, stream)
-                            : launch_dq_from_ds_tt<D, true, false>(k, ds, dq, B, H, Hkv, Nq, Nk, scale, stream);
-    return tail ? launch_dq_from_ds_tt<D, false, true>(k, ds, dq, B, H, Hkv, Nq, Nk, scale, stream)
-                : launch_dq_from_ds_tt<D, false, false>(k, ds, dq, B, H, Hkv, Nq, Nk, scale, stream);
+    int cus = 0;
+    hipError_t e = compute_unit_count(&cus);
+    if (e != hipSuccess) return e;
+    const int tiles = (Nq + 127) / 128;
+    const long long small = (long long)B * H * (CAUSAL ? (tiles + 1) / 2 : tiles);      // workgroups of four waves
+    auto launch = small <= cus               ? launch_dq_from_ds_tt<D, CAUSAL, true, 4>
+                : (Nq != Nk || Nq % 256) ? launch_dq_from_ds_tt<D, CAUSAL, true, 8> : launch_dq_from_ds_tt<D, CAUSAL, false, 8>;
+    return launch(k, ds, dq, B, H, Hkv, Nq, Nk, scale, stream);
 }
 
 hipError_t launch_attn_bwd_dq_from_ds(const void* k, const void* ds, void* dq,
                                       int B, int H, int Hkv, int Nq, int Nk, int D, int causal, float scale, hipStream_t stream)
 {
-    return D == 128 ? launch_dq_from_ds_t<128>(k, ds, dq, B, H, Hkv, Nq, Nk, causal, scale, stream)
-                    : launch_dq_from_ds_t<64>(k, ds, dq, B, H, Hkv, Nq, Nk, causal, scale, stream);
+    auto launch = D == 128 ? (causal ? launch_dq_from_ds_t<128, true> : launch_dq_from_ds_t<128, false>)
+                           : (causal ? launch_dq_from_ds_t<64, true> : launch_dq_from_ds_t<64, false>);
+    return launch(k, ds, dq, B, H, Hkv, Nq, Nk, scale, stream);
 }
 
 }  // namespace tk
