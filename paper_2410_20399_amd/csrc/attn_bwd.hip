@@ -142,7 +142,7 @@ void attn_bwd_dkdv_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K
                           const bf16* __restrict__ dO, const float* __restrict__ LSE, const float* __restrict__ Delta,
                           bf16* __restrict__ dK, bf16* __restrict__ dV,
                           int Nq, int Nk, int num_kv_tiles, int total_units, float scale, int hq, int hkv,
-                          char* __restrict__ DS, int n_qb, int n_splits, float* __restrict__ Part)
+                          char* __restrict__ DS, int n_qb, int pair_tiles, int n_splits, float* __restrict__ Part)
 {
     using S = DkdvShape<D>;
     __shared__ __attribute__((aligned(1024))) char ring[S::kStages * S::kStageBytes];
@@ -159,13 +159,14 @@ void attn_bwd_dkdv_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K
 
     // Work unit: one key tile, or, when causal, the pair (u, last - u): tile u loops over the
     // query blocks from its diagonal on, so the pairs carry (nearly) the same work and the static
-    // schedule is balanced.  A "pass" is one key tile; (vu, half) names the pass `half` of unit vu.
+    // schedule is balanced.  (Not paired where every tile can have a workgroup of its own, see pair_tiles().)  A "pass" is one key tile; (vu, half) names the pass `half` of unit vu.
     // Grouped-query attention: a key/value head is shared by `group` consecutive query heads, and a
     // pass streams the query blocks of all of them, one head after the other, into the same dK, dV
     // accumulators.  bh below counts key/value heads.
     const int heads_per_kv = hq / hkv;
     const int group = SPLIT ? heads_per_kv / n_splits : heads_per_kv;      // query heads of a pass
-    const int units = CAUSAL ? (num_kv_tiles + 1) / 2 : num_kv_tiles;
+    const bool paired = CAUSAL && (!TAIL || pair_tiles);
+    const int units = paired ? (num_kv_tiles + 1) / 2 : num_kv_tiles;
     auto q_head_row = [&](int bh, int split) {         // first row of the first query head of a pass of key/value head bh
         return (size_t)((bh / hkv) * hq + (bh % hkv) * heads_per_kv + split * group) * Nq;
     };
@@ -193,7 +194,7 @@ void attn_bwd_dkdv_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K
     };
     // the pass after (vu, half) in this workgroup's walk; vu >= total_units means "none"
     auto next_pass = [&](int& vu, int& half) {
-        if (CAUSAL && half == 0) {
+        if (paired && half == 0) {
             const int unit = xcd_remap(vu, total_units) % units;
             if (num_kv_tiles - 1 - unit != unit) { half = 1; return; }   // (odd tile count: the middle tile has no partner)
         }
@@ -776,20 +777,16 @@ template <int D, bool CAUSAL, bool TAIL, bool SPILL, bool SPLIT>
 static hipError_t launch_dkdv_tt(const void* q, const void* k, const void* v, const void* d_o,
                                  const float* lse, const float* delta, void* dk, void* dv,
                                  int B, int H, int Hkv, int Nq, int Nk, float scale, hipStream_t stream, void* ds,
-                                 int n_splits, float* part)
+                                 int resident, bool paired, int n_splits, float* part)
 {
     using S = DkdvShape<D>;
     const int num_kv_tiles = (Nk + S::kTileKV - 1) / S::kTileKV;
-    const int total_units = B * Hkv * n_splits * (CAUSAL ? (num_kv_tiles + 1) / 2 : num_kv_tiles);
-    int cus = 0;
-    hipError_t e = compute_unit_count(&cus);
-    if (e != hipSuccess) return e;
-    const int resident = cus * (D == 64 ? 2 : 1);               // as many workgroups as fit at once
+    const int total_units = B * Hkv * n_splits * (CAUSAL && paired ? (num_kv_tiles + 1) / 2 : num_kv_tiles);
     const int grid = total_units < resident ? total_units : resident;
     hipLaunchKernelGGL((attn_bwd_dkdv_kernel<D, CAUSAL, TAIL, SPILL, SPLIT>), dim3(grid), dim3(S::kThreads), 0, stream,
                        (const bf16*)q, (const bf16*)k, (const bf16*)v, (const bf16*)d_o, lse, delta,
                        (bf16*)dk, (bf16*)dv, Nq, Nk, num_kv_tiles, total_units, scale, H, Hkv,
-                       (char*)ds, ds_query_blocks(Nq), n_splits, part);
+                       (char*)ds, ds_query_blocks(Nq), paired, n_splits, part);
     if (SPLIT) {
         const size_t n4 = (size_t)B * Hkv * Nk * D / 4;
         hipLaunchKernelGGL(attn_bwd_dkdv_sum_kernel, dim3((unsigned)((n4 + 255) / 256), 2), dim3(256), 0, stream,
@@ -805,11 +802,17 @@ static hipError_t launch_dkdv_t(const void* q, const void* k, const void* v, con
                                 int n_splits, float* part)
 {
     using S = DkdvShape<D>;
-    const bool tail = Nq != Nk || Nk % S::kTileKV;
+    int cus = 0;
+    hipError_t e = compute_unit_count(&cus);
+    if (e != hipSuccess) return e;
+    const int resident = cus * (D == 64 ? 2 : 1);               // as many workgroups as fit at once
+    if (!part) n_splits = 1;
+    const bool paired = CAUSAL && pair_tiles((long long)B * Hkv * n_splits, (Nk + S::kTileKV - 1) / S::kTileKV, cus);
+    const bool tail = Nq != Nk || Nk % S::kTileKV || paired != CAUSAL;
     auto launch = part ? (ds ? launch_dkdv_tt<D, CAUSAL, true, true, true> : launch_dkdv_tt<D, CAUSAL, true, false, true>)
                 : tail ? (ds ? launch_dkdv_tt<D, CAUSAL, true, true, false> : launch_dkdv_tt<D, CAUSAL, true, false, false>)
                        : (ds ? launch_dkdv_tt<D, CAUSAL, false, true, false> : launch_dkdv_tt<D, CAUSAL, false, false, false>);
-    return launch(q, k, v, d_o, lse, delta, dk, dv, B, H, Hkv, Nq, Nk, scale, stream, ds, part ? n_splits : 1, part);
+    return launch(q, k, v, d_o, lse, delta, dk, dv, B, H, Hkv, Nq, Nk, scale, stream, ds, resident, paired, n_splits, part);
 }
 
 // ds != nullptr: the kernel also stores its dS blocks there (ds_spill_bytes(...) bytes) for launch_attn_bwd_dq_from_ds.
@@ -848,7 +851,7 @@ __global__ __launch_bounds__(256, 2)
 void attn_bwd_dq_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K, const bf16* __restrict__ V,
                         const bf16* __restrict__ dO, const float* __restrict__ LSE, const float* __restrict__ Delta,
                         bf16* __restrict__ dQ, int Nq, int Nk, int num_q_tiles, int total_wg, float scale, int hq, int hkv,
-                        const bf16* __restrict__ O, float* __restrict__ DeltaOut)
+                        const bf16* __restrict__ O, float* __restrict__ DeltaOut, int pair_tiles)
 {
     using S = DqShape<D>;
     __shared__ __attribute__((aligned(1024))) char stage0[S::kStageBytes];
@@ -863,7 +866,8 @@ void attn_bwd_dq_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K, 
     // Work unit: one query tile, or, when causal, the pair (last - u, u): tile t streams the keys up
     // to its diagonal, so the pairs carry (nearly) the same work and the launch is balanced.
     // Nq queries, Nk keys; TAIL and the causal alignment as in the kernels above.
-    const int units = CAUSAL ? (num_q_tiles + 1) / 2 : num_q_tiles;
+    const bool paired = CAUSAL && (!TAIL || pair_tiles);
+    const int units = paired ? (num_q_tiles + 1) / 2 : num_q_tiles;
     const int logical = xcd_remap(blockIdx.x, total_wg);
     const int bh = logical / units;
     const int unit = logical % units;
@@ -874,7 +878,7 @@ void attn_bwd_dq_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K, 
     const bf16* Kh = K + kv_head;
     const bf16* Vh = V + kv_head;
 #pragma unroll 1
-    for (int pass = 0; pass < (CAUSAL ? 2 : 1); pass++) {
+    for (int pass = 0; pass < (paired ? 2 : 1); pass++) {
     const int qt = pass == 0 ? num_q_tiles - 1 - unit : unit;
     if (pass == 1 && qt == num_q_tiles - 1 - unit) break;   // odd tile count: the middle tile has no partner
     const int q0 = qt * S::kTileQ + wave * 32;
@@ -1048,14 +1052,14 @@ template <int D, bool CAUSAL, bool TAIL, bool FUSED>
 static hipError_t launch_dq_tt(const void* q, const void* k, const void* v, const void* d_o,
                                const float* lse, const float* delta, void* dq,
                                int B, int H, int Hkv, int Nq, int Nk, float scale, hipStream_t stream,
-                               const void* o, float* delta_out)
+                               const void* o, float* delta_out, bool paired)
 {
     using S = DqShape<D>;
     const int num_q_tiles = (Nq + S::kTileQ - 1) / S::kTileQ;
-    const int total = B * H * (CAUSAL ? (num_q_tiles + 1) / 2 : num_q_tiles);
+    const int total = B * H * (paired ? (num_q_tiles + 1) / 2 : num_q_tiles);
     hipLaunchKernelGGL((attn_bwd_dq_kernel<D, CAUSAL, TAIL, FUSED>), dim3(total), dim3(S::kThreads), 0, stream,
                        (const bf16*)q, (const bf16*)k, (const bf16*)v, (const bf16*)d_o, lse, delta,
-                       (bf16*)dq, Nq, Nk, num_q_tiles, total, scale, H, Hkv, (const bf16*)o, delta_out);
+                       (bf16*)dq, Nq, Nk, num_q_tiles, total, scale, H, Hkv, (const bf16*)o, delta_out, paired);
     return hipGetLastError();
 }
 
@@ -1066,11 +1070,14 @@ static hipError_t launch_dq_t(const void* q, const void* k, const void* v, const
                               const void* o, float* delta_out)
 {
     using S = DqShape<D>;
-    const bool tail = Nq != Nk || Nq % S::kTileQ;
-    if (o) return tail ? launch_dq_tt<D, CAUSAL, true, true>(q, k, v, d_o, lse, delta, dq, B, H, Hkv, Nq, Nk, scale, stream, o, delta_out)
-                       : launch_dq_tt<D, CAUSAL, false, true>(q, k, v, d_o, lse, delta, dq, B, H, Hkv, Nq, Nk, scale, stream, o, delta_out);
-    return tail ? launch_dq_tt<D, CAUSAL, true, false>(q, k, v, d_o, lse, delta, dq, B, H, Hkv, Nq, Nk, scale, stream, o, delta_out)
-                : launch_dq_tt<D, CAUSAL, false, false>(q, k, v, d_o, lse, delta, dq, B, H, Hkv, Nq, Nk, scale, stream, o, delta_out);
+    int cus = 0;
+    hipError_t e = compute_unit_count(&cus);
+    if (e != hipSuccess) return e;
+    const bool paired = CAUSAL && pair_tiles((long long)B * H, (Nq + S::kTileQ - 1) / S::kTileQ, cus);
+    const bool tail = Nq != Nk || Nq % S::kTileQ || paired != CAUSAL;
+    auto launch = o ? (tail ? launch_dq_tt<D, CAUSAL, true, true> : launch_dq_tt<D, CAUSAL, false, true>)
+                    : (tail ? launch_dq_tt<D, CAUSAL, true, false> : launch_dq_tt<D, CAUSAL, false, false>);
+    return launch(q, k, v, d_o, lse, delta, dq, B, H, Hkv, Nq, Nk, scale, stream, o, delta_out, paired);
 }
 
 // o != nullptr: Delta is computed from o and d_o inside the kernel and written to delta_out (delta is not read).
@@ -1138,7 +1145,7 @@ template <int D, bool CAUSAL, bool TAIL, int WAVES>
 __global__ __launch_bounds__(64 * WAVES, 1)
 void attn_bwd_dq_from_ds_kernel(const bf16* __restrict__ K, const char* __restrict__ DS, bf16* __restrict__ dQ,
                                 int Nq, int Nk, int num_q_tiles, int total_wg, float scale, int hq, int hkv,
-                                int num_kv_tiles, int n_qb)
+                                int num_kv_tiles, int n_qb, int pair_tiles)
 {
     using S = DqDsShape<D, WAVES>;
     __shared__ __attribute__((aligned(1024))) char smem[S::kLdsBytes];
@@ -1150,7 +1157,8 @@ void attn_bwd_dq_from_ds_kernel(const bf16* __restrict__ K, const char* __restri
     const int h = lane >> 5;
     char* const dsbuf = smem + S::kKStages * S::kKTileBytes + wave * (2 * S::kDsTileBytes);   // two buffers of this wave
 
-    const int units = CAUSAL ? (num_q_tiles + 1) / 2 : num_q_tiles;
+    const bool paired = CAUSAL && (!TAIL || pair_tiles);
+    const int units = paired ? (num_q_tiles + 1) / 2 : num_q_tiles;
     const int logical = xcd_remap(blockIdx.x, total_wg);
     const int bh = logical / units;                  // query head
     const int unit = logical % units;
@@ -1180,7 +1188,7 @@ void attn_bwd_dq_from_ds_kernel(const bf16* __restrict__ K, const char* __restri
     const int ds_lane = (4 * h + (j16 >> 2)) * 64 + ((lane >> 4) & 1) * 32 + (j16 & 1) * 16 + ((j16 & 3) >> 1) * 8;
 
 #pragma unroll 1
-    for (int pass = 0; pass < (CAUSAL ? 2 : 1); pass++) {
+    for (int pass = 0; pass < (paired ? 2 : 1); pass++) {
     const int qt = pass == 0 ? num_q_tiles - 1 - unit : unit;
     if (pass == 1 && qt == num_q_tiles - 1 - unit) break;   // odd tile count: the middle tile has no partner
     const int q0 = qt * S::kTileQ + wave * 32;
@@ -1310,16 +1318,16 @@ void attn_bwd_dq_from_ds_kernel(const bf16* __restrict__ K, const char* __restri
 
 template <int D, bool CAUSAL, bool TAIL, int WAVES>
 static hipError_t launch_dq_from_ds_tt(const void* k, const void* ds, void* dq,
-                                       int B, int H, int Hkv, int Nq, int Nk, float scale, hipStream_t stream)
+                                       int B, int H, int Hkv, int Nq, int Nk, float scale, hipStream_t stream, bool paired)
 {
     using S = DqDsShape<D, WAVES>;
     auto kern = attn_bwd_dq_from_ds_kernel<D, CAUSAL, TAIL, WAVES>;
     const int num_q_tiles = (Nq + S::kTileQ - 1) / S::kTileQ;
     const int num_kv_tiles = (Nk + 127) / 128;
-    const int total = B * H * (CAUSAL ? (num_q_tiles + 1) / 2 : num_q_tiles);
+    const int total = B * H * (paired ? (num_q_tiles + 1) / 2 : num_q_tiles);
     hipLaunchKernelGGL(kern, dim3(total), dim3(S::kThreads), 0, stream,
                        (const bf16*)k, (const char*)ds, (bf16*)dq, Nq, Nk, num_q_tiles, total, scale, H, Hkv,
-                       num_kv_tiles, ds_query_blocks(Nq));
+                       num_kv_tiles, ds_query_blocks(Nq), paired);
     return hipGetLastError();
 }
 
@@ -1334,7 +1342,7 @@ static hipError_t launch_dq_from_ds_t(const void* k, const void* ds, void* dq,
     const long long small = (long long)B * H * (CAUSAL ? (tiles + 1) / 2 : tiles);      // workgroups of four waves
     auto launch = small <= cus               ? launch_dq_from_ds_tt<D, CAUSAL, true, 4>
                 : (Nq != Nk || Nq % 256) ? launch_dq_from_ds_tt<D, CAUSAL, true, 8> : launch_dq_from_ds_tt<D, CAUSAL, false, 8>;
-    return launch(k, ds, dq, B, H, Hkv, Nq, Nk, scale, stream);
+    return launch(k, ds, dq, B, H, Hkv, Nq, Nk, scale, stream, CAUSAL && (small > cus || pair_tiles((long long)B * H, tiles, cus)));
 }
 
 hipError_t launch_attn_bwd_dq_from_ds(const void* k, const void* ds, void* dq,

@@ -88,6 +88,13 @@ inline size_t dkdv_part_bytes(int B, int Hkv, int Nk, int D, int n_splits) {
     return (size_t)n_splits * 2 * B * Hkv * Nk * D * sizeof(float);
 }
 
+// Whether the tiles of a causal backward launch are paired, long with short, for equal work per workgroup: not where
+// each has a compute unit of its own without: the longest tile alone is then the shorter way, by one tile in `tiles`
+// and a start-up.  Whole backward, us, paired and not: B2 Hq16 Hkv4 N1001 D128 100, 84; B2 H12 N700 D64 47, 37; but with
+// 32 tiles B1 H8 N4096 D128 201, 224 (half the compute units hold a higher clock) and with two workgroups to a compute
+// unit, two long ones or two short ones, B1 H16 N4096 D64 173, 227.
+inline bool pair_tiles(long long heads, int tiles, int compute_units) { return heads * tiles > compute_units || tiles > 16; }
+
 // dK, dV (key-tile parallel).  ds != nullptr: also store the dS blocks there (ds_spill_bytes(B, H, Nq, Nk) bytes).
 // part != nullptr: n_splits = dkdv_splits(...) > 1 ways, partial sums in part (dkdv_part_bytes(...) bytes).
 hipError_t launch_attn_bwd_dkdv(const void* q, const void* k, const void* v, const void* d_o,
