@@ -339,29 +339,65 @@ hipError_t launch_attn_fwd(const void* q, const void* k, const void* v, void* o,
 // ------------------------------------------------------------------------------------------
 // O = sum_s w_s O_s / sum_s w_s with w_s = exp(LSE_s - max_s LSE_s), LSE = max + ln sum_s w_s: the
 // partials are softmax results over disjoint key ranges, each normalised by its own sum.
-template <int D>
+//
+// Bound by latency: a decode call has few rows and up to 256 splits, and one lane group walking all splits of a row,
+// its loads one behind the other, took longer than the attention itself.  So D / 4 lanes (four columns each) form one
+// of PARTS groups that walk a row's splits side by side, and join through LDS; the maximum is found with one LSE per
+// lane.  More than four splits take eight groups: whole decode call, B1 Hq16 Hkv2 Nk32000 D128 (125 splits) 63 -> 15
+// us, Hq32 Hkv8 Nk8192 (32) 25 -> 11, Nk2000 (8) 13.7 -> 11.0.  Few splits of many rows (a chunk of a prompt) are
+// bound by the bytes, and take one.
+template <int D, int PARTS>
 __global__ __launch_bounds__(256)
 void attn_fwd_combine_kernel(const float* __restrict__ O_part, const float* __restrict__ LSE_part,
                              bf16* __restrict__ O, float* __restrict__ LSE, size_t rows, int n_splits)
 {
     constexpr int kLanesPerRow = D / 4;                 // one float4 per lane
-    const size_t row = (size_t)blockIdx.x * (256 / kLanesPerRow) + threadIdx.x / kLanesPerRow;
-    if (row >= rows) return;
-    const int col = (threadIdx.x % kLanesPerRow) * 4;
-    float m = -INFINITY;
-    for (int s = 0; s < n_splits; s++) m = __builtin_fmaxf(m, LSE_part[(size_t)s * rows + row]);
-    float wsum = 0.f;
+    constexpr int kRows = 256 / (kLanesPerRow * PARTS);
+    __shared__ f32x4 acc_of[PARTS][kRows][kLanesPerRow];
+    __shared__ float w_of[PARTS][kRows];
+    const int lane = threadIdx.x % kLanesPerRow, part = threadIdx.x / kLanesPerRow % PARTS, r = threadIdx.x / (kLanesPerRow * PARTS);
+    const size_t row = (size_t)blockIdx.x * kRows + r;
+    const bool live = row < rows;
+    const int col = lane * 4;
+    float m = -INFINITY, wsum = 0.f;
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-    for (int s = 0; s < n_splits; s++) {
-        const float w = __builtin_expf(LSE_part[(size_t)s * rows + row] - m);
-        const f32x4 v = *(const f32x4*)(O_part + ((size_t)s * rows + row) * D + col);
-        wsum += w;
-        acc += v * w;
+    if (live) {
+        // the maximum over all splits: a row's lanes fetch one LSE each
+        for (int s = lane; s < n_splits; s += kLanesPerRow) m = __builtin_fmaxf(m, LSE_part[(size_t)s * rows + row]);
+#pragma unroll
+        for (int off = kLanesPerRow / 2; off >= 1; off >>= 1) m = __builtin_fmaxf(m, __shfl_xor(m, off));
+#pragma unroll 4
+        for (int s = part; s < n_splits; s += PARTS) {
+            const float w = __builtin_expf(LSE_part[(size_t)s * rows + row] - m);
+            const f32x4 v = *(const f32x4*)(O_part + ((size_t)s * rows + row) * D + col);
+            wsum += w;
+            acc += v * w;
+        }
     }
+    if (PARTS > 1) {
+        acc_of[part][r][lane] = acc;
+        if (lane == 0) w_of[part][r] = wsum;
+        __syncthreads();
+        if (part != 0) return;
+#pragma unroll
+        for (int p = 1; p < PARTS; p++) {
+            acc += acc_of[p][r][lane];
+            wsum += w_of[p][r];
+        }
+    }
+    if (!live) return;
     const float inv = 1.0f / wsum;
     bf16x2 lo = cvt2(acc[0] * inv, acc[1] * inv), hi = cvt2(acc[2] * inv, acc[3] * inv);
     *(bf16x4*)(O + row * D + col) = __builtin_shufflevector(lo, hi, 0, 1, 2, 3);
     if (col == 0) LSE[row] = m + __builtin_logf(wsum);
+}
+
+template <int D, int PARTS>
+static void launch_combine(const float* o_part, const float* lse_part, void* o, float* lse, size_t rows, int n_splits, hipStream_t stream)
+{
+    constexpr int kRows = 256 / (D / 4 * PARTS);
+    hipLaunchKernelGGL((attn_fwd_combine_kernel<D, PARTS>), dim3((unsigned)((rows + kRows - 1) / kRows)), dim3(256), 0, stream,
+                       o_part, lse_part, (bf16*)o, lse, rows, n_splits);
 }
 
 // Forward with the keys split n_splits ways (n_splits >= 2, every split holds at least one key:
@@ -377,13 +413,9 @@ hipError_t launch_attn_fwd_splitk(const void* q, const void* k, const void* v, v
     hipError_t e = launch(q, k, v, o, lse, B, H, Hkv, Nq, Nk, scale, stream, n_splits, tiles_per_split, o_part, lse_part);
     if (e != hipSuccess) return e;
     const size_t rows = (size_t)B * H * Nq;
-    if (D == 128) {
-        const unsigned grid = (unsigned)((rows + 7) / 8);
-        hipLaunchKernelGGL((attn_fwd_combine_kernel<128>), dim3(grid), dim3(256), 0, stream, o_part, lse_part, (bf16*)o, lse, rows, n_splits);
-    } else {
-        const unsigned grid = (unsigned)((rows + 15) / 16);
-        hipLaunchKernelGGL((attn_fwd_combine_kernel<64>), dim3(grid), dim3(256), 0, stream, o_part, lse_part, (bf16*)o, lse, rows, n_splits);
-    }
+    auto combine = D == 128 ? (n_splits > 4 ? launch_combine<128, 8> : launch_combine<128, 1>)
+                            : (n_splits > 4 ? launch_combine<64, 8> : launch_combine<64, 1>);
+    combine(o_part, lse_part, o, lse, rows, n_splits, stream);
     return hipGetLastError();
 }
 
