@@ -335,6 +335,196 @@ hipError_t launch_attn_fwd(const void* q, const void* k, const void* v, void* o,
 }
 
 // ------------------------------------------------------------------------------------------
+// decode: up to 32 query rows per key/value head
+// ------------------------------------------------------------------------------------------
+// The forward kernel gives a workgroup's rows to its waves, 32 each; with one query for each head of a group only the
+// first wave has any, and a 64-key tile takes it about a microsecond.  Here all four waves hold the same rows and share
+// the keys: a trip is two tiles, wave w takes 32 keys of tile w / 2, and the waves' (O, max, sum) are joined through
+// LDS at the end.  A split has few tiles, so what counts is how soon they are here: four are requested before the
+// first is waited for.  That takes the LDS of a whole compute unit, so it is for launches of at most one workgroup
+// each; beyond that the calls are bound by the bytes, and the forward kernel's two workgroups keep more of them in
+// flight.  Decode call, this kernel against the forward kernel, us: B1 Hq32 Hkv8 Nk2000 D128 9.6, 10.4; Nk500 9.4, 10.3;
+// B4 Hq16 Hkv2 Nk5000 D64 8.9, 10.7; but (two stages) B16 Hq32 Hkv8 Nk8192 98, 94, B1 Hq64 Hkv8 Nk65536 48, 46.
+// O_part == nullptr (one split): the result itself, bf16.  Grid: heads * n_splits, the splits of a head next to each other.
+template <int D>
+__global__ __launch_bounds__(256, 1)
+void attn_decode_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K, const bf16* __restrict__ V,
+                        bf16* __restrict__ O, float* __restrict__ LSE, int rows, int Nk, int heads, float scale,
+                        int n_splits, int tiles_per_split, float* __restrict__ O_part, float* __restrict__ LSE_part)
+{
+    using S = FwdShape<D>;
+    constexpr int kStages = 4;
+    __shared__ __attribute__((aligned(1024))) char smem[kStages * S::kStageBytes];
+    __shared__ __attribute__((aligned(1024))) char q_smem[32 * S::kRowBytes];
+    __shared__ float stat[2][S::kWaves][32];             // maximum and sum of each wave and row
+
+    const int tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lane = tid & 63;
+    const int l32 = lane & 31;
+    const int h = lane >> 5;
+    const int split = blockIdx.x % n_splits, head = blockIdx.x / n_splits;
+    const bf16* Kh = K + (size_t)head * Nk * D;
+    const bf16* Vh = V + (size_t)head * Nk * D;
+    const float c = scale * kLog2e;
+
+    const int n_all = 2 * ((Nk + 2 * S::kTileKV - 1) / (2 * S::kTileKV));       // tiles of the head, an even count
+    const int t_begin = split * tiles_per_split;
+    const int t_end = t_begin + tiles_per_split < n_all ? t_begin + tiles_per_split : n_all;
+
+    // tiles go to LDS as in the forward kernel; rows past the last key fetch it again (they are masked below)
+    auto issue_tile = [&](int tile) {
+        char* base = smem + (tile - t_begin) % kStages * S::kStageBytes + wave * 1024;
+#pragma unroll
+        for (int it = 0; it < S::kLoadsPerTile; it++) {
+            const int s = it * S::kThreads + tid, r = s / S::kChunksPerRow, pc = s % S::kChunksPerRow;
+            const int row = tile * S::kTileKV + r < Nk ? tile * S::kTileKV + r : Nk - 1;
+            load_global_to_lds16_untracked(Kh + (size_t)row * D + (pc ^ swizzle_k<D>(r)) * 8, base + it * (S::kThreads * 16));
+            load_global_to_lds16_untracked(Vh + (size_t)row * D + (pc ^ swizzle_v<D>(r)) * 8, base + S::kTileBytes + it * (S::kThreads * 16));
+        }
+    };
+
+    // the query rows travel to LDS as well, ahead of the tiles: loads that the compiler tracks would wait for all of them
+#pragma unroll
+    for (int it = 0; it < 32 * S::kChunksPerRow / S::kThreads; it++) {
+        const int s = it * S::kThreads + tid, r = s / S::kChunksPerRow, pc = s % S::kChunksPerRow;
+        const size_t row = (size_t)head * rows + (r < rows ? r : rows - 1);
+        load_global_to_lds16_untracked(Q + row * D + (pc ^ swizzle_k<D>(r)) * 8, q_smem + wave * 1024 + it * (S::kThreads * 16));
+    }
+#pragma unroll
+    for (int n = 0; n < kStages; n++)
+        if (n < 2 || t_begin + n < t_end) issue_tile(t_begin + n);
+
+    const int my_tile = wave >> 1, key0 = 32 * (wave & 1);       // of a trip's two tiles; first key within the tile
+    const int k_lane = l32 * S::kRowBytes + ((h ^ swizzle_k<D>(l32)) << 4);
+    const int j16 = lane & 15;
+    const int v_row = 4 * h + (j16 >> 2);
+    const int v_chunk = 2 * ((lane >> 4) & 1) + ((j16 & 3) >> 1);
+    const int v_lane = v_row * S::kRowBytes + ((v_chunk ^ swizzle_v<D>(v_row)) << 4) + ((j16 & 1) << 3);
+
+    f32x16 o_acc[D / 32];
+#pragma unroll
+    for (int db = 0; db < D / 32; db++)
+#pragma unroll
+        for (int r = 0; r < 16; r++) o_acc[db][r] = 0.f;
+    float m_run = -INFINITY, l_run = 0.f;
+    auto finite_max = [](float m) { return m == -INFINITY ? 0.f : m; };        // (exponents of a row without a finite score are taken against 0)
+
+    bf16x8 qf[D / 16];
+    auto compute_block = [&](const char* ks, int j0) {           // 32 keys from j0 on; ks: their K rows
+        const char* vs = ks + S::kTileBytes;
+        f32x16 s;
+#pragma unroll
+        for (int r = 0; r < 16; r++) s[r] = 0.f;
+#pragma unroll
+        for (int kb = 0; kb < D / 16; kb++) s = mfma32(lds_read_b128(ks, k_lane ^ ((2 * kb) << 4)), qf[kb], s);
+        if (j0 + 32 > Nk) {
+#pragma unroll
+            for (int r = 0; r < 16; r++)
+                if (j0 + 8 * (r >> 2) + 4 * h + (r & 3) >= Nk) s[r] = -INFINITY;
+        }
+        float mx = s[0];
+#pragma unroll
+        for (int r = 1; r < 16; r++) mx = __builtin_fmaxf(mx, s[r]);
+        const float m_new = __builtin_fmaxf(m_run, half_max(mx));
+        const float corr = __builtin_amdgcn_exp2f((m_run - finite_max(m_new)) * c);
+        m_run = m_new;
+        const float mc = finite_max(m_run) * c;
+        float psum = 0.f;
+#pragma unroll
+        for (int r = 0; r < 16; r++) {
+            s[r] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[r], c, -mc));
+            psum += s[r];
+        }
+        l_run = l_run * corr + psum;
+#pragma unroll
+        for (int db = 0; db < D / 32; db++)
+#pragma unroll
+            for (int r = 0; r < 16; r++) o_acc[db][r] *= corr;
+#pragma unroll
+        for (int kk = 0; kk < 2; kk++) {
+            const int r0 = 8 * kk;
+            const bf16x8 pb = cvt8(s[r0 + 0], s[r0 + 1], s[r0 + 2], s[r0 + 3], s[r0 + 4], s[r0 + 5], s[r0 + 6], s[r0 + 7]);
+#pragma unroll
+            for (int db = 0; db < D / 32; db++) {
+                const int row_off = 16 * kk * S::kRowBytes;
+                const bf16x4 v0 = lds_read_tr16(vs, (v_lane ^ ((4 * db) << 4)) + row_off);
+                const bf16x4 v1 = lds_read_tr16(vs, (v_lane ^ (((4 * db) ^ 2) << 4)) + row_off + 8 * S::kRowBytes);
+                o_acc[db] = mfma32(concat(v0, v1), pb, o_acc[db]);
+            }
+        }
+    };
+
+    // The tiles of trip t are here, and visible to all waves.  (In order: the next trip's two tiles may still be on
+    // their way, if there is a next trip.)
+    auto wait_trip = [&](int t) {
+        if (t + 2 < t_end) wait_vmcnt<2 * 2 * S::kLoadsPerTile>();
+        else wait_vmcnt<0>();
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+        asm volatile("" : : : "memory");
+    };
+    wait_trip(t_begin);
+#pragma unroll
+    for (int kb = 0; kb < D / 16; kb++) qf[kb] = lds_read_b128(q_smem, k_lane ^ ((2 * kb) << 4));
+    for (int t = t_begin; t < t_end; t += 2) {
+        if (t > t_begin) wait_trip(t);
+        const int j0 = (t + my_tile) * S::kTileKV + key0;
+        if (j0 < Nk) compute_block(smem + (t + my_tile - t_begin) % kStages * S::kStageBytes + key0 * S::kRowBytes, j0);
+        if (t + kStages < t_end) {
+            wait_vmcnt_lds_done<63>();      // nobody reads these stages any more
+            __builtin_amdgcn_s_barrier();
+            __builtin_amdgcn_sched_barrier(0);
+            issue_tile(t + kStages);
+            issue_tile(t + kStages + 1);
+        }
+    }
+
+    // ---- join the waves: wave w forms the result of accumulator registers w * kRegs and following
+    const float l_wave = half_sum(l_run);
+    __syncthreads();
+    float* mine = (float*)smem + wave * (D / 2 * 64);            // [register][lane]
+#pragma unroll
+    for (int db = 0; db < D / 32; db++)
+#pragma unroll
+        for (int r = 0; r < 16; r++) mine[(db * 16 + r) * 64 + lane] = o_acc[db][r];
+    if (h == 0) { stat[0][wave][l32] = m_run; stat[1][wave][l32] = l_wave; }
+    __syncthreads();
+    float m = -INFINITY, l = 0.f, f[S::kWaves];
+#pragma unroll
+    for (int w = 0; w < S::kWaves; w++) m = __builtin_fmaxf(m, stat[0][w][l32]);
+#pragma unroll
+    for (int w = 0; w < S::kWaves; w++) {
+        f[w] = __builtin_amdgcn_exp2f((stat[0][w][l32] - finite_max(m)) * c);
+        l += stat[1][w][l32] * f[w];
+    }
+    if (l32 >= rows) return;
+    const float inv = 1.0f / l;
+    constexpr int kRegs = D / 8;
+    const size_t row = (size_t)head * rows + l32;
+    const size_t part_row = (size_t)split * heads * rows + row;
+#pragma unroll
+    for (int g = 0; g < kRegs / 4; g++) {
+        const int reg = wave * kRegs + 4 * g;
+        float v[4];
+#pragma unroll
+        for (int e = 0; e < 4; e++) {
+            v[e] = 0.f;
+#pragma unroll
+            for (int w = 0; w < S::kWaves; w++) v[e] += ((const float*)smem)[w * (D / 2 * 64) + (reg + e) * 64 + lane] * f[w];
+            v[e] *= inv;
+        }
+        const int col = 32 * (reg / 16) + 8 * (reg % 16 / 4) + 4 * h;
+        if (O_part) *(f32x4*)(O_part + part_row * D + col) = f32x4{v[0], v[1], v[2], v[3]};
+        else *(bf16x4*)(O + row * D + col) = __builtin_shufflevector(cvt2(v[0], v[1]), cvt2(v[2], v[3]), 0, 1, 2, 3);
+    }
+    if (wave == 0 && h == 0) {
+        const float lse = m * scale + __builtin_logf(l);
+        if (O_part) LSE_part[part_row] = lse; else LSE[row] = lse;
+    }
+}
+
+// ------------------------------------------------------------------------------------------
 // merge of the partial results of a split over the keys
 // ------------------------------------------------------------------------------------------
 // O = sum_s w_s O_s / sum_s w_s with w_s = exp(LSE_s - max_s LSE_s), LSE = max + ln sum_s w_s: the
@@ -400,6 +590,13 @@ static void launch_combine(const float* o_part, const float* lse_part, void* o, 
                        o_part, lse_part, (bf16*)o, lse, rows, n_splits);
 }
 
+static void combine(const float* o_part, const float* lse_part, void* o, float* lse, size_t rows, int D, int n_splits, hipStream_t stream)
+{
+    auto launch = D == 128 ? (n_splits > 4 ? launch_combine<128, 8> : launch_combine<128, 1>)
+                           : (n_splits > 4 ? launch_combine<64, 8> : launch_combine<64, 1>);
+    launch(o_part, lse_part, o, lse, rows, n_splits, stream);
+}
+
 // Forward with the keys split n_splits ways (n_splits >= 2, every split holds at least one key:
 // (n_splits - 1) * tiles_per_split * 64 < Nk, tiles_per_split even).  o_part: fp32 [n_splits][B*H][Nq][D],
 // lse_part: fp32 [n_splits][B*H][Nq].
@@ -412,10 +609,25 @@ hipError_t launch_attn_fwd_splitk(const void* q, const void* k, const void* v, v
                            : (causal ? launch_fwd_tt<64, true, true, true> : launch_fwd_tt<64, false, true, true>);
     hipError_t e = launch(q, k, v, o, lse, B, H, Hkv, Nq, Nk, scale, stream, n_splits, tiles_per_split, o_part, lse_part);
     if (e != hipSuccess) return e;
-    const size_t rows = (size_t)B * H * Nq;
-    auto combine = D == 128 ? (n_splits > 4 ? launch_combine<128, 8> : launch_combine<128, 1>)
-                            : (n_splits > 4 ? launch_combine<64, 8> : launch_combine<64, 1>);
-    combine(o_part, lse_part, o, lse, rows, n_splits, stream);
+    combine(o_part, lse_part, o, lse, (size_t)B * H * Nq, D, n_splits, stream);
+    return hipGetLastError();
+}
+
+template <int D>
+static void launch_decode_t(const void* q, const void* k, const void* v, void* o, float* lse, float* o_part, float* lse_part,
+                            int heads, int rows, int Nk, float scale, int n_splits, int tiles_per_split, hipStream_t stream)
+{
+    hipLaunchKernelGGL((attn_decode_kernel<D>), dim3((unsigned)(heads * n_splits)), dim3(256), 0, stream,
+                       (const bf16*)q, (const bf16*)k, (const bf16*)v, (bf16*)o, lse, rows, Nk, heads, scale,
+                       n_splits, tiles_per_split, n_splits > 1 ? o_part : nullptr, lse_part);
+}
+
+hipError_t launch_attn_decode(const void* q, const void* k, const void* v, void* o, float* lse, float* o_part, float* lse_part,
+                              int heads, int rows, int Nk, int D, float scale, int n_splits, int tiles_per_split, hipStream_t stream)
+{
+    auto launch = D == 128 ? launch_decode_t<128> : launch_decode_t<64>;
+    launch(q, k, v, o, lse, o_part, lse_part, heads, rows, Nk, scale, n_splits, tiles_per_split, stream);
+    if (n_splits > 1) combine(o_part, lse_part, o, lse, (size_t)heads * rows, D, n_splits, stream);
     return hipGetLastError();
 }
 

@@ -265,16 +265,17 @@ int tk_attn_decode(const void* q, const void* k, const void* v, void* o, float* 
     int cus = 0;
     if (tk::compute_unit_count(&cus) != hipSuccess || cus < 1) return TK_ERR_LAUNCH;
     const DecodePlan p = plan_decode(B, Hq, Hkv, Nk, cus);
+    const size_t rows = (size_t)B * Hq;
+    float* o_part = (float*)workspace;
+    float* lse_part = (float*)((char*)workspace + (((size_t)decode_max_splits(B, Hq, Hkv) * rows * D * sizeof(float) + 255) & ~(size_t)255));
     hipError_t e;
-    if (p.n_splits == 1) {
+    if (p.nq <= tk::kDecodeRows && p.h == p.hkv && (long long)p.b * p.h * p.n_splits <= cus)     // (see attn_decode_kernel)
+        e = tk::launch_attn_decode(q, k, v, o, lse, o_part, lse_part, p.b * p.h, p.nq, Nk, D, scale, p.n_splits, p.tiles_per_split, (hipStream_t)stream);
+    else if (p.n_splits == 1)
         e = tk::launch_attn_fwd(q, k, v, o, lse, p.b, p.h, p.hkv, p.nq, Nk, D, 0, scale, (hipStream_t)stream);
-    } else {
-        const size_t rows = (size_t)B * Hq;
-        float* o_part = (float*)workspace;
-        float* lse_part = (float*)((char*)workspace + (((size_t)decode_max_splits(B, Hq, Hkv) * rows * D * sizeof(float) + 255) & ~(size_t)255));
+    else
         e = tk::launch_attn_fwd_splitk(q, k, v, o, lse, o_part, lse_part, p.b, p.h, p.hkv, p.nq, Nk, D, 0, scale,
                                        p.n_splits, p.tiles_per_split, (hipStream_t)stream);
-    }
     return e == hipSuccess ? TK_OK : TK_ERR_LAUNCH;
 }
 

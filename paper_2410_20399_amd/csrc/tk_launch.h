@@ -56,6 +56,12 @@ hipError_t launch_attn_fwd_splitk(const void* q, const void* k, const void* v, v
                                   int B, int H, int Hkv, int Nq, int Nk, int D, int causal, float scale,
                                   int n_splits, int tiles_per_split, hipStream_t stream);
 
+// Decoding on a launch of at most one workgroup a compute unit: `rows` (<= kDecodeRows) query rows for each of `heads` key/value heads, the keys split n_splits (>= 1) ways as
+// above.  q, o: [heads, rows, D]; k, v: [heads, Nk, D]; lse: [heads, rows].
+constexpr int kDecodeRows = 32;
+hipError_t launch_attn_decode(const void* q, const void* k, const void* v, void* o, float* lse, float* o_part, float* lse_part,
+                              int heads, int rows, int Nk, int D, float scale, int n_splits, int tiles_per_split, hipStream_t stream);
+
 // Delta_i = sum_d dO_id O_id
 hipError_t launch_attn_bwd_delta(const void* o, const void* d_o, float* delta,
                                  int B, int H, int N, int D, hipStream_t stream);
