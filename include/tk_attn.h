@@ -276,10 +276,11 @@ int tk_attn_bwd_rect(const void* q, const void* k, const void* v,
                      void* stream);
 
 /*
- * tk_attn_bwd_rect for callers that can hand over device scratch besides the workspace.  With a Delta-only
- * workspace, grouped heads and too few key tiles to fill the chip, the query heads of each group are split over
- * several workgroups, which leave fp32 partial sums of dK and dV in the scratch, added up in a fixed order.  (A
- * workspace of tk_attn_bwd_spill_workspace_bytes holds the room for this itself.)  Results equal tk_attn_bwd_rect's
+ * tk_attn_bwd_rect for callers that can hand over device scratch besides the workspace.  With too few key tiles to
+ * fill the chip the queries of a key tile are split over several workgroups - the query heads of a group, and without
+ * a mask and with Nq != Nk the queries of a head - which leave fp32 partial sums of dK and dV in the scratch, added up
+ * in a fixed order.  (A workspace of tk_attn_bwd_spill_workspace_bytes holds the room for a split of the heads itself.)
+ * Results equal tk_attn_bwd_rect's
  * up to fp32 summation order and are bit-reproducible.
  *
  *   scratch : device memory of tk_attn_bwd_scratch_bytes(...) bytes, 16-byte aligned; contents on entry are

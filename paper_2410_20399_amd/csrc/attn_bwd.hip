@@ -132,8 +132,9 @@ template <int D> __device__ __forceinline__ int swz(int row) {
 // element 4g + t.  Block (query head, key tile kt, query block qb, wave w) sits at
 // (((head * num_kv_tiles + kt) * n_qb + qb) * 4 + w) * 2048 bytes.  Masked pairs and padding rows hold 0.
 //
-// SPLIT (implies TAIL): the query heads of a group are dealt to n_splits workgroups, each of which leaves fp32
-// sums over its own heads in Part ([n_splits][2: dK, dV][B * hkv][Nk][D], unscaled) for attn_bwd_dkdv_sum_kernel.
+// SPLIT (implies TAIL): the queries are dealt to n_splits workgroups - the query heads of a group to
+// n_splits / q_splits and, without a mask, the blocks of a head to q_splits - each of which leaves fp32
+// sums over its own in Part ([n_splits][2: dK, dV][B * hkv][Nk][D], unscaled) for attn_bwd_dkdv_sum_kernel.
 // For launches with fewer units than compute units: a unit's time is the length of its query stream, 1.2 us a
 // block of 32 queries, whether the other compute units are idle or not.
 template <int D, bool CAUSAL, bool TAIL, bool SPILL, bool SPLIT>
@@ -142,7 +143,8 @@ void attn_bwd_dkdv_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K
                           const bf16* __restrict__ dO, const float* __restrict__ LSE, const float* __restrict__ Delta,
                           bf16* __restrict__ dK, bf16* __restrict__ dV,
                           int Nq, int Nk, int num_kv_tiles, int total_units, float scale, int hq, int hkv,
-                          char* __restrict__ DS, int n_qb, int pair_tiles, int n_splits, float* __restrict__ Part)
+                          char* __restrict__ DS, int n_qb, int pair_tiles, int n_splits, int q_splits,
+                          float* __restrict__ Part)
 {
     using S = DkdvShape<D>;
     __shared__ __attribute__((aligned(1024))) char ring[S::kStages * S::kStageBytes];
@@ -164,25 +166,28 @@ void attn_bwd_dkdv_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K
     // pass streams the query blocks of all of them, one head after the other, into the same dK, dV
     // accumulators.  bh below counts key/value heads.
     const int heads_per_kv = hq / hkv;
-    const int group = SPLIT ? heads_per_kv / n_splits : heads_per_kv;      // query heads of a pass
+    const int group = SPLIT ? heads_per_kv / (n_splits / q_splits) : heads_per_kv;      // query heads of a pass
     const bool paired = CAUSAL && (!TAIL || pair_tiles);
     const int units = paired ? (num_kv_tiles + 1) / 2 : num_kv_tiles;
     auto q_head_row = [&](int bh, int split) {         // first row of the first query head of a pass of key/value head bh
-        return (size_t)((bh / hkv) * hq + (bh % hkv) * heads_per_kv + split * group) * Nq;
+        return (size_t)((bh / hkv) * hq + (bh % hkv) * heads_per_kv + (SPLIT ? split / q_splits * group : 0)) * Nq;
     };
     // The query blocks of a pass: blocks of 32 rows from pass_ibegin(kt) on, per query head of the
     // group; an even count (the loops below take two blocks per trip), of which the first
     // `n_masked` may touch the diagonal.  General case: the first query that sees a key of the tile
     // is j0 - off, rounded down to a block boundary; rows past Nq are padding.
     const int off = TAIL ? Nk - Nq : 0;
-    auto pass_ibegin = [&](int kt) {
+    const int q_chunk = SPLIT && !CAUSAL ? dkdv_q_chunk(Nq, q_splits) : 0;      // blocks of a head in one split
+    auto pass_ibegin = [&](int kt, int split) {
+        if (SPLIT && !CAUSAL) return split % q_splits * q_chunk * S::kTileQ;
         if (!CAUSAL) return 0;
         if (!TAIL) return kt * S::kTileKV;
         const int first = kt * S::kTileKV - off;
         return first > 0 ? first & ~(S::kTileQ - 1) : 0;
     };
     auto pass_nblocks = [&](int ibegin) {
-        return TAIL ? 2 * ((Nq - ibegin + 2 * S::kTileQ - 1) / (2 * S::kTileQ)) : (Nq - ibegin) / S::kTileQ;
+        const int n = TAIL ? 2 * ((Nq - ibegin + 2 * S::kTileQ - 1) / (2 * S::kTileQ)) : (Nq - ibegin) / S::kTileQ;
+        return SPLIT && !CAUSAL && n > q_chunk ? q_chunk : n;
     };
     auto pass_tile = [&](int vu, int half, int& bh, int& kt, int& split) {
         const int logical = xcd_remap(vu, total_units);
@@ -233,7 +238,7 @@ void attn_bwd_dkdv_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K
     auto producer_open = [&]() __attribute__((always_inline)) {            // set the cursor to the first block of pass (p_vu, p_half)
         int bh, kt, split;
         pass_tile(p_vu, p_half, bh, kt, split);
-        p_ibegin = pass_ibegin(kt);
+        p_ibegin = pass_ibegin(kt, split);
         p_head_row = q_head_row(bh, split);
         p_nblocks = pass_nblocks(p_ibegin);
         p_g = 0;
@@ -344,7 +349,7 @@ void attn_bwd_dkdv_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K
     const int j0 = kt * S::kTileKV;
     const int jw0 = j0 + wave * 32;                // first key of this wave
     const int my_j = jw0 + l32;
-    const int i_begin = pass_ibegin(kt);
+    const int i_begin = pass_ibegin(kt, split);
     const int n_blocks = pass_nblocks(i_begin);           // per query head of the group
     // blocks that may hold a masked (query, key) pair: rows below j0 + 127 - off, i.e. four blocks
     // from i_begin when that is the tile's own first row, up to five when off is not a multiple of 32
@@ -374,7 +379,7 @@ void attn_bwd_dkdv_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K
 
     // register r of a score block <-> query i0 + 8*(r/4) + 4h + r%4, lane <-> key my_j
     const bool pad_key = TAIL && SPILL && my_j >= Nk;    // a padding key was computed from the last real row: its dS must not reach dQ
-    auto q_head_of = [&](int g) { return (size_t)(bh / hkv) * hq + (size_t)(bh % hkv) * heads_per_kv + split * group + g; };
+    auto q_head_of = [&](int g) { return (size_t)(bh / hkv) * hq + (size_t)(bh % hkv) * heads_per_kv + (SPLIT ? split / q_splits * group : 0) + g; };
 
     if constexpr (S::kPipe) {
     // ------------------------------------------------------------------------------------------
@@ -777,7 +782,7 @@ template <int D, bool CAUSAL, bool TAIL, bool SPILL, bool SPLIT>
 static hipError_t launch_dkdv_tt(const void* q, const void* k, const void* v, const void* d_o,
                                  const float* lse, const float* delta, void* dk, void* dv,
                                  int B, int H, int Hkv, int Nq, int Nk, float scale, hipStream_t stream, void* ds,
-                                 int resident, bool paired, int n_splits, float* part)
+                                 int resident, bool paired, int n_splits, int q_splits, float* part)
 {
     using S = DkdvShape<D>;
     const int num_kv_tiles = (Nk + S::kTileKV - 1) / S::kTileKV;
@@ -786,7 +791,7 @@ static hipError_t launch_dkdv_tt(const void* q, const void* k, const void* v, co
     hipLaunchKernelGGL((attn_bwd_dkdv_kernel<D, CAUSAL, TAIL, SPILL, SPLIT>), dim3(grid), dim3(S::kThreads), 0, stream,
                        (const bf16*)q, (const bf16*)k, (const bf16*)v, (const bf16*)d_o, lse, delta,
                        (bf16*)dk, (bf16*)dv, Nq, Nk, num_kv_tiles, total_units, scale, H, Hkv,
-                       (char*)ds, ds_query_blocks(Nq), paired, n_splits, part);
+                       (char*)ds, ds_query_blocks(Nq), paired, n_splits, q_splits, part);
     if (SPLIT) {
         const size_t n4 = (size_t)B * Hkv * Nk * D / 4;
         hipLaunchKernelGGL(attn_bwd_dkdv_sum_kernel, dim3((unsigned)((n4 + 255) / 256), 2), dim3(256), 0, stream,
@@ -799,32 +804,32 @@ template <int D, bool CAUSAL>
 static hipError_t launch_dkdv_t(const void* q, const void* k, const void* v, const void* d_o,
                                 const float* lse, const float* delta, void* dk, void* dv,
                                 int B, int H, int Hkv, int Nq, int Nk, float scale, hipStream_t stream, void* ds,
-                                int n_splits, float* part)
+                                int n_splits, int q_splits, float* part)
 {
     using S = DkdvShape<D>;
     int cus = 0;
     hipError_t e = compute_unit_count(&cus);
     if (e != hipSuccess) return e;
     const int resident = cus * (D == 64 ? 2 : 1);               // as many workgroups as fit at once
-    if (!part) n_splits = 1;
+    if (!part) n_splits = q_splits = 1;
     const bool paired = CAUSAL && pair_tiles((long long)B * Hkv * n_splits, (Nk + S::kTileKV - 1) / S::kTileKV, cus);
     const bool tail = Nq != Nk || Nk % S::kTileKV || paired != CAUSAL;
     auto launch = part ? (ds ? launch_dkdv_tt<D, CAUSAL, true, true, true> : launch_dkdv_tt<D, CAUSAL, true, false, true>)
                 : tail ? (ds ? launch_dkdv_tt<D, CAUSAL, true, true, false> : launch_dkdv_tt<D, CAUSAL, true, false, false>)
                        : (ds ? launch_dkdv_tt<D, CAUSAL, false, true, false> : launch_dkdv_tt<D, CAUSAL, false, false, false>);
-    return launch(q, k, v, d_o, lse, delta, dk, dv, B, H, Hkv, Nq, Nk, scale, stream, ds, resident, paired, n_splits, part);
+    return launch(q, k, v, d_o, lse, delta, dk, dv, B, H, Hkv, Nq, Nk, scale, stream, ds, resident, paired, n_splits, q_splits, part);
 }
 
 // ds != nullptr: the kernel also stores its dS blocks there (ds_spill_bytes(...) bytes) for launch_attn_bwd_dq_from_ds.
-// part != nullptr: the query heads of a group are split n_splits ways (dkdv_splits()), partial sums in part.
+// part != nullptr: the queries are split n_splits ways (dkdv_splits()), partial sums in part.
 hipError_t launch_attn_bwd_dkdv(const void* q, const void* k, const void* v, const void* d_o,
                                 const float* lse, const float* delta, void* dk, void* dv,
                                 int B, int H, int Hkv, int Nq, int Nk, int D, int causal, float scale, hipStream_t stream,
-                                void* ds, int n_splits, float* part)
+                                void* ds, int n_splits, int q_splits, float* part)
 {
     auto launch = D == 128 ? (causal ? launch_dkdv_t<128, true> : launch_dkdv_t<128, false>)
                            : (causal ? launch_dkdv_t<64, true> : launch_dkdv_t<64, false>);
-    return launch(q, k, v, d_o, lse, delta, dk, dv, B, H, Hkv, Nq, Nk, scale, stream, ds, n_splits, part);
+    return launch(q, k, v, d_o, lse, delta, dk, dv, B, H, Hkv, Nq, Nk, scale, stream, ds, n_splits, q_splits, part);
 }
 
 // ------------------------------------------------------------------------------------------

@@ -198,7 +198,7 @@ PyObject* bwd(PyObject* const* a) {
         dv = tensor(a[14], "dv");
     }
     const size_t workspace_bytes = (size_t)workspace.numel() * workspace.element_size();
-    const size_t n = s.Hq != s.Hkv ? tk_attn_bwd_scratch_bytes(s.B, s.Hq, s.Hkv, s.Nq, s.Nk, s.D, causal, workspace_bytes) : 0;
+    const size_t n = s.Hq != s.Hkv || s.Nq != s.Nk ? tk_attn_bwd_scratch_bytes(s.B, s.Hq, s.Hkv, s.Nq, s.Nk, s.D, causal, workspace_bytes) : 0;
     at::Tensor scratch;
     if (n) scratch = scratch_on(stream, n, q);
     const int rc = tk_attn_bwd_rect_scratch(q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(), d_o.data_ptr(), (const float*)lse.data_ptr(),

@@ -133,13 +133,24 @@ size_t dkdv_part_room(int B, int Hq, int Nq, int Nk, int D)
     return tk::dkdv_part_bytes(B, Hq, Nk, D, 1);
 }
 
-// how the dK/dV kernel of a storing backward splits, given that room
+// how the dK/dV kernel of a storing backward splits, given that room (the query heads only: it has no more)
 int dkdv_splits_storing(int B, int Hq, int Hkv, int Nq, int Nk, int D, int causal)
 {
     int cus = 0;
     if (dkdv_part_room(B, Hq, Nq, Nk, D) == 0 || tk::compute_unit_count(&cus) != hipSuccess) return 1;
     if (cus > kDkdvMaxWorkgroups / 2) cus = kDkdvMaxWorkgroups / 2;
-    return tk::dkdv_splits(B, Hq, Hkv, Nq, Nk, D, causal != 0, cus);
+    const tk::DkdvSplits p = tk::dkdv_splits(B, Hq, Hkv, Nq, Nk, D, causal != 0, cus);
+    return p.n_splits / p.q_splits;
+}
+
+// how it splits with scratch for it
+tk::DkdvSplits dkdv_splits_scratch(int B, int Hq, int Hkv, int Nq, int Nk, int D, int causal, size_t workspace_bytes)
+{
+    int cus = 0;
+    if (tk::compute_unit_count(&cus) != hipSuccess) return {1, 1};
+    const tk::DkdvSplits p = tk::dkdv_splits(B, Hq, Hkv, Nq, Nk, D, causal != 0, cus);
+    const bool storing = workspace_bytes >= delta_bytes(B, Hq, Nq) + tk::ds_spill_bytes(B, Hq, Nq, Nk);
+    return storing && p.q_splits == 1 ? tk::DkdvSplits{1, 1} : p;      // (heads alone: the workspace has room)
 }
 
 // Few queries against a longer history: the heads and 128-query tiles alone leave compute units idle.  The split
@@ -310,7 +321,7 @@ int tk_attn_bwd_dkdv_ds(const void* q, const void* k, const void* v, const void*
     const int n_splits = dkdv_splits_storing(B, Hq, Hkv, N, N, D, causal);
     float* part = n_splits > 1 ? (float*)((char*)ds + tk::ds_spill_bytes(B, Hq, N, N)) : nullptr;
     hipError_t e = tk::launch_attn_bwd_dkdv(q, k, v, d_o, lse, delta, dk, dv, B, Hq, Hkv, N, N, D, causal != 0, scale,
-                                            (hipStream_t)stream, ds, n_splits, part);
+                                            (hipStream_t)stream, ds, n_splits, 1, part);
     return e == hipSuccess ? TK_OK : TK_ERR_LAUNCH;
 }
 
@@ -398,11 +409,8 @@ int tk_attn_bwd_dq(const void* q, const void* k, const void* v, const void* d_o,
 
 size_t tk_attn_bwd_scratch_bytes(int B, int Hq, int Hkv, int Nq, int Nk, int D, int causal, size_t workspace_bytes)
 {
-    if (check_lengths(B, Hq, Hkv, Nq, Nk, D, causal) != TK_OK || Hq == Hkv) return 0;
-    if (workspace_bytes >= delta_bytes(B, Hq, Nq) + tk::ds_spill_bytes(B, Hq, Nq, Nk)) return 0;
-    int cus = 0;
-    if (tk::compute_unit_count(&cus) != hipSuccess) return 0;
-    const int n_splits = tk::dkdv_splits(B, Hq, Hkv, Nq, Nk, D, causal != 0, cus);
+    if (check_lengths(B, Hq, Hkv, Nq, Nk, D, causal) != TK_OK || (Hq == Hkv && Nq == Nk)) return 0;
+    const int n_splits = dkdv_splits_scratch(B, Hq, Hkv, Nq, Nk, D, causal, workspace_bytes).n_splits;
     return n_splits > 1 ? tk::dkdv_part_bytes(B, Hkv, Nk, D, n_splits) : 0;
 }
 
@@ -421,16 +429,22 @@ int tk_attn_bwd_rect_scratch(const void* q, const void* k, const void* v, const 
 
     hipStream_t s = (hipStream_t)stream;
     float* delta = (float*)workspace;
+    const size_t need = scratch ? tk_attn_bwd_scratch_bytes(B, Hq, Hkv, Nq, Nk, D, causal, workspace_bytes) : 0;
+    const bool split = need > 0 && scratch_bytes >= need;
+    const tk::DkdvSplits by_scratch = split ? dkdv_splits_scratch(B, Hq, Hkv, Nq, Nk, D, causal, workspace_bytes) : tk::DkdvSplits{1, 1};
     if (workspace_bytes >= delta_bytes(B, Hq, Nq) + tk::ds_spill_bytes(B, Hq, Nq, Nk)) {
         // Large workspace: 10*D flops per (query, key) pair instead of 14*D.  Delta on its own, then dK/dV,
         // which also leaves its bf16 dS blocks behind Delta in the workspace, then dQ = scale * dS K from them.
         // (A workspace with room for dS but not for partial sums behind it runs unsplit.)
         char* ds = (char*)workspace + delta_bytes(B, Hq, Nq);
-        const bool room = workspace_bytes >= tk_attn_bwd_spill_workspace_bytes(B, Hq, Nq, Nk, D);
-        const int n_splits = room ? dkdv_splits_storing(B, Hq, Hkv, Nq, Nk, D, causal) : 1;
-        float* part = n_splits > 1 ? (float*)(ds + tk::ds_spill_bytes(B, Hq, Nq, Nk)) : nullptr;
+        tk::DkdvSplits p = by_scratch;
+        float* part = split ? (float*)scratch : nullptr;
+        if (!split && workspace_bytes >= tk_attn_bwd_spill_workspace_bytes(B, Hq, Nq, Nk, D)) {
+            p = {dkdv_splits_storing(B, Hq, Hkv, Nq, Nk, D, causal), 1};
+            if (p.n_splits > 1) part = (float*)(ds + tk::ds_spill_bytes(B, Hq, Nq, Nk));
+        }
         if (tk::launch_attn_bwd_delta(o, d_o, delta, B, Hq, Nq, D, s) != hipSuccess) return TK_ERR_LAUNCH;
-        if (tk::launch_attn_bwd_dkdv(q, k, v, d_o, lse, delta, dk, dv, B, Hq, Hkv, Nq, Nk, D, causal != 0, scale, s, ds, n_splits, part) != hipSuccess)
+        if (tk::launch_attn_bwd_dkdv(q, k, v, d_o, lse, delta, dk, dv, B, Hq, Hkv, Nq, Nk, D, causal != 0, scale, s, ds, p.n_splits, p.q_splits, part) != hipSuccess)
             return TK_ERR_LAUNCH;
         if (tk::launch_attn_bwd_dq_from_ds(k, ds, dq, B, Hq, Hkv, Nq, Nk, D, causal != 0, scale, s) != hipSuccess)
             return TK_ERR_LAUNCH;
@@ -442,11 +456,8 @@ int tk_attn_bwd_rect_scratch(const void* q, const void* k, const void* v, const 
     if (tk::launch_attn_bwd_dq(q, k, v, d_o, lse, nullptr, dq, B, Hq, Hkv, Nq, Nk, D, causal != 0, scale, s, o, delta) != hipSuccess)
         return TK_ERR_LAUNCH;
     // 2. dK, dV per key tile of every key/value head, with that Delta
-    const size_t need = scratch ? tk_attn_bwd_scratch_bytes(B, Hq, Hkv, Nq, Nk, D, causal, workspace_bytes) : 0;
-    const bool split = need > 0 && scratch_bytes >= need;
-    const int n_splits = split ? (int)(need / tk::dkdv_part_bytes(B, Hkv, Nk, D, 1)) : 1;
-    if (tk::launch_attn_bwd_dkdv(q, k, v, d_o, lse, delta, dk, dv, B, Hq, Hkv, Nq, Nk, D, causal != 0, scale, s, nullptr, n_splits,
-                                 split ? (float*)scratch : nullptr) != hipSuccess)
+    if (tk::launch_attn_bwd_dkdv(q, k, v, d_o, lse, delta, dk, dv, B, Hq, Hkv, Nq, Nk, D, causal != 0, scale, s, nullptr,
+                                 by_scratch.n_splits, by_scratch.q_splits, split ? (float*)scratch : nullptr) != hipSuccess)
         return TK_ERR_LAUNCH;
     return TK_OK;
 }

@@ -74,20 +74,37 @@ inline size_t ds_spill_bytes(int B, int H, int Nq, int Nk) {
     return (size_t)B * H * (size_t)((Nk + 127) / 128) * (size_t)ds_query_blocks(Nq) * 8192;
 }
 
-// Ways to split the query heads of a group over workgroups of the dK/dV kernel: the largest divisor of the group with
-// which the units still fit the compute units at once, 1 = no split.  (With more units than that the split only adds
-// the traffic of the partial sums.)  Fewer than 256 queries are not split: the stream of a unit is then short next to
-// the launch of the kernel that adds up.  Whole backward, us, unsplit and split: B2 Hq16 Hkv4 N1001 D128 causal 219,
-// 112; B1 Hq32 Hkv8 N4096 642, 579 (two ways); B1 Hq64 Hkv1 N3000 6956, 686; B1 Hq8 Hkv1 N300 148, 53; at D = 64
-// B1 Hq32 Hkv8 N2048 204, 111.
-inline int dkdv_splits(int B, int H, int Hkv, int Nq, int Nk, int D, bool causal, int compute_units) {
+// Ways to split the queries of a key tile over workgroups of the dK/dV kernel, as far as the units still fit the compute
+// units at once (with more units the split only adds the traffic of the partial sums): n_splits in all, of which
+// q_splits share the query blocks of a head and n_splits / q_splits the query heads of a group.
+//   Heads: the largest divisor of the group that fits.  Fewer than 256 queries are not split: the stream of a unit is
+// then short next to the launch of the kernel that adds up.  Whole backward, us, unsplit and split: B2 Hq16 Hkv4 N1001
+// D128 causal 219, 112; B1 Hq32 Hkv8 N4096 642, 579 (two ways); B1 Hq64 Hkv1 N3000 6956, 686; B1 Hq8 Hkv1 N300 148, 53;
+// at D = 64 B1 Hq32 Hkv8 N2048 204, 111.
+//   Blocks: with other numbers of queries than keys and no mask (with equal lengths and no groups a head's bits do not
+// depend on the number of heads; with a mask the late key tiles have few blocks), down to 512 queries, and only to one
+// workgroup a compute unit.  Backward, us: B1 H4 Nq4096 Nk64 D64 91, 22; B1 H8 Nq3000 Nk200 D128 128, 42; but with two
+// workgroups to some compute units B4 H16 Nq1000 Nk300 D64 47, 53, and with 150 queries each B2 H16 Nq300 Nk128 20, 25.
+struct DkdvSplits {
+    int n_splits, q_splits;
+};
+// blocks of a head in one of q_splits parts, an even number; the last part may be shorter
+__host__ __device__ inline int dkdv_q_chunk(int Nq, int q_splits) { return 2 * (((Nq + 63) / 64 + q_splits - 1) / q_splits); }
+inline DkdvSplits dkdv_splits(int B, int H, int Hkv, int Nq, int Nk, int D, bool causal, int compute_units) {
     const int tiles = (Nk + 127) / 128, group = H / Hkv;
     const long long units = (long long)B * Hkv * (causal ? (tiles + 1) / 2 : tiles);
     const long long resident = (long long)compute_units * (D == 64 ? 2 : 1);
-    if (Nq < 256) return 1;
-    for (int s = group; s > 1; s--)
-        if (group % s == 0 && units * s <= resident) return s;
-    return 1;
+    if (Nq < 256) return {1, 1};
+    int heads = group;
+    while (heads > 1 && (group % heads || units * heads > resident)) heads--;
+    int blocks = 1;
+    if (!causal && Nq != Nk) {
+        const long long fit = compute_units / (units * heads), most = Nq / 512, ways = fit < most ? fit : most;
+        blocks = ways < 1 ? 1 : (int)ways;
+        const int pairs = (Nq + 63) / 64, chunk = dkdv_q_chunk(Nq, blocks) / 2;
+        blocks = (pairs + chunk - 1) / chunk;           // no part is empty
+    }
+    return {heads * blocks, blocks};
 }
 // fp32 partial sums of dK and dV
 inline size_t dkdv_part_bytes(int B, int Hkv, int Nk, int D, int n_splits) {
@@ -102,11 +119,11 @@ inline size_t dkdv_part_bytes(int B, int Hkv, int Nk, int D, int n_splits) {
 inline bool pair_tiles(long long heads, int tiles, int compute_units) { return heads * tiles > compute_units || tiles > 16; }
 
 // dK, dV (key-tile parallel).  ds != nullptr: also store the dS blocks there (ds_spill_bytes(B, H, Nq, Nk) bytes).
-// part != nullptr: n_splits = dkdv_splits(...) > 1 ways, partial sums in part (dkdv_part_bytes(...) bytes).
+// part != nullptr: n_splits > 1 ways (dkdv_splits(...)), partial sums in part (dkdv_part_bytes(...) bytes).
 hipError_t launch_attn_bwd_dkdv(const void* q, const void* k, const void* v, const void* d_o,
                                 const float* lse, const float* delta, void* dk, void* dv,
                                 int B, int H, int Hkv, int Nq, int Nk, int D, int causal, float scale, hipStream_t stream,
-                                void* ds = nullptr, int n_splits = 1, float* part = nullptr);
+                                void* ds = nullptr, int n_splits = 1, int q_splits = 1, float* part = nullptr);
 
 // dQ = scale * dS K from the blocks a launch_attn_bwd_dkdv call with the same shape arguments stored
 hipError_t launch_attn_bwd_dq_from_ds(const void* k, const void* ds, void* dq,
