@@ -71,7 +71,12 @@ void attn_fwd_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K, con
 
     int bh, qt, split = 0;
     if (SPLIT) split_of(blockIdx.x, gridDim.x, hq / hkv, num_q_tiles, n_splits, bh, split, qt);
-    else tile_of(blockIdx.x, heads, num_q_tiles, head_group, bh, qt);
+    else if (CAUSAL) tile_of(blockIdx.x, heads, num_q_tiles, head_group, bh, qt);
+    else {              // all tiles weigh the same: head after head, contiguous on an XCD
+        const int id = xcd_remap(blockIdx.x, gridDim.x);
+        bh = id / num_q_tiles;
+        qt = id - bh * num_q_tiles;
+    }
 
     // grouped-query attention: query head h of a batch entry reads key/value head h / (hq / hkv)
     const size_t head = (size_t)bh * Nq * D;
@@ -253,6 +258,9 @@ void attn_fwd_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K, con
     }
 
     int t_begin = 0;
+    // (With a known start the compiler keeps a 64-bit address per lane and load and advances each by a vector addition;
+    // with an unknown one the tile's address stays scalar: B16 H16 N1000 D64 without a mask 88.9 against 87.5 us.)
+    if (TAIL && !CAUSAL && !SPLIT) asm volatile("" : "+s"(t_begin));
     if (SPLIT) {
         t_begin = split * tiles_per_split;
         if (t_begin + tiles_per_split < n_tiles) n_tiles = t_begin + tiles_per_split;
