@@ -20,6 +20,8 @@
 #include "tk_common.h"
 #include "tk_launch.h"
 
+#include <type_traits>
+
 namespace tk {
 
 // sixteen zero bytes: the source of the chunks of A and the rows of B that lie beyond K
@@ -54,7 +56,10 @@ struct GemmTile {
 // are never stored), and in the step that runs past K the chunks of A and the rows of B beyond it are fetched
 // from a block of zeros.  The offsets are clamped once, ahead of the loop; a step that lies within K runs the
 // same instructions whatever the shape.
-template <class S, int WM, int WN, int KS, int WAVES_PER_SIMD>
+//
+// WIDE: lane offsets in 64 bits, for matrices whose rows within one tile lie 4 GiB or more apart (gemm_fits_32_bits).
+// Otherwise an offset is a 32-bit register next to a scalar base, which saves a 64-bit vector addition per load.
+template <class S, int WM, int WN, int KS, int WAVES_PER_SIMD, bool WIDE>
 __global__ __launch_bounds__(S::kThreads, WAVES_PER_SIMD)
 void gemm_kernel(const bf16* __restrict__ A, const bf16* __restrict__ B, bf16* __restrict__ C,
                  int M, int N, int K, int tiles_m, int tiles_n, int super_m)
@@ -95,34 +100,39 @@ void gemm_kernel(const bf16* __restrict__ A, const bf16* __restrict__ B, bf16* _
     // B: position s holds (panel = s / 512, k row = s / 8 % 64, physical chunk = s % 8)
     const bf16* const a_tile = A + (size_t)m0 * K;
     const bf16* const b_tile = B + n0;
-    uint32_t a_src[S::kALoads], b_src[S::kBLoads];
+    using Offset = std::conditional_t<WIDE, uint64_t, uint32_t>;
+    Offset a_src[S::kALoads], b_src[S::kBLoads];
 #pragma unroll
     for (int it = 0; it < S::kALoads; it++) {
         const int s = it * S::kGroupThreads + tid, pc = s & 7;
         int row = s >> 3;
         const int chunk = pc ^ gemm_swz_a(row);
         if (row > M - 1 - m0) row = M - 1 - m0;
-        a_src[it] = ((uint32_t)row * (uint32_t)K + chunk * 8) * 2;
+        a_src[it] = ((Offset)row * (Offset)K + chunk * 8) * 2;
     }
 #pragma unroll
     for (int it = 0; it < S::kBLoads; it++) {
         const int s = it * S::kGroupThreads + tid, row = (s >> 3) & 63, pc = s & 7;
         int col = (s >> 9) * 64 + ((pc ^ gemm_swz_b(row)) << 3);
         if (col > N - 8 - n0) col = N - 8 - n0;
-        b_src[it] = ((uint32_t)row * (uint32_t)N + col) * 2;
+        b_src[it] = ((Offset)row * (Offset)N + col) * 2;
     }
+    auto load = [&](const bf16* base, Offset off, char* dst) {
+        if constexpr (WIDE) load_global_to_lds16_untracked((const char*)base + off, dst);
+        else load_global_to_lds16_sbase_untracked(base, off, dst);
+    };
     auto issue_stage = [&](int step, int stage_off) {
         char* base = ring + stage_off + wave * 1024;
         const int k0 = step * S::kTileK;
-        if (__builtin_expect(k0 + S::kTileK <= K, 1)) {
+        if (__builtin_expect(K - k0 >= S::kTileK, 1)) {
             const bf16* a = a_tile + k0;
             const bf16* b = b_tile + (size_t)k0 * N;
 #pragma unroll
             for (int it = 0; it < S::kALoads; it++)
-                load_global_to_lds16_sbase_untracked(a, a_src[it], base + it * (S::kGroupThreads * 16));
+                load(a, a_src[it], base + it * (S::kGroupThreads * 16));
 #pragma unroll
             for (int it = 0; it < S::kBLoads; it++)
-                load_global_to_lds16_sbase_untracked(b, b_src[it], base + S::kABytes + it * (S::kGroupThreads * 16));
+                load(b, b_src[it], base + S::kABytes + it * (S::kGroupThreads * 16));
         } else {
             const int left = K - k0;            // <= 0: a step of a K share that the others have and this one has not
             const int at = left > 0 ? k0 : 0;   // (no address past the matrices is formed)
@@ -256,13 +266,13 @@ void gemm_kernel(const bf16* __restrict__ A, const bf16* __restrict__ B, bf16* _
     }
 }
 
-template <int TM, int TN, int WM, int WN, int KS, int STAGES, int WAVES_PER_SIMD>
+template <int TM, int TN, int WM, int WN, int KS, int STAGES, int WAVES_PER_SIMD, bool WIDE = false>
 static hipError_t launch_tile(const void* a, const void* b, void* c, int M, int N, int K, hipStream_t stream)
 {
     using S = GemmTile<TM, TN, WM, WN, KS, STAGES>;
     const int tiles_m = (M + TM - 1) / TM, tiles_n = (N + TN - 1) / TN;
     constexpr int super_m = TM >= 256 ? 4 : TM >= 128 ? 8 : 16;     // tile rows walked together
-    hipLaunchKernelGGL((gemm_kernel<S, WM, WN, KS, WAVES_PER_SIMD>), dim3(tiles_m * tiles_n), dim3(S::kThreads), 0, stream,
+    hipLaunchKernelGGL((gemm_kernel<S, WM, WN, KS, WAVES_PER_SIMD, WIDE>), dim3(tiles_m * tiles_n), dim3(S::kThreads), 0, stream,
                        (const bf16*)a, (const bf16*)b, (bf16*)c, M, N, K, tiles_m, tiles_n, super_m);
     return hipGetLastError();
 }
@@ -281,25 +291,40 @@ static hipError_t launch_tile(const void* a, const void* b, void* c, int M, int 
 // (A single 256x256 tile with four waves of 128x128, one per SIMD, took 0.92 ms: nothing filled the gaps of a
 // wave.  With two waves per SIMD and 16x16x32 MFMAs, which move half the accumulator bits per flop of the 32x32x16
 // form, the same LDS ring gives 0.79.)
+// The last three have 64-bit lane offsets and are only considered where a shape of the same rows needs them (128x256 with
+// four waves: few enough threads for the widest N): M1 N34200008 K72 1.76 ms, M250 N34500008 K64 7.0, M300 N35000000 K128
+// 15.1, M32 N8 K69400008 456.
 struct GemmChoice {
     hipError_t (*launch)(const void*, const void*, void*, int, int, int, hipStream_t);
-    int tile_m, tile_n, ks;
+    int threads, tile_m, tile_n, ks;
     float one, more;        // us per step: the only tile of a compute unit; every tile of several
+    bool wide;              // 64-bit lane offsets
 };
 static const GemmChoice kGemmChoices[] = {
-    {launch_tile<256, 256, 2, 4, 1, 2, 2>, 256, 256, 1, 1.50f, 1.57f},
-    {launch_tile<192, 256, 2, 4, 1, 2, 2>, 192, 256, 1, 1.15f, 1.25f},
-    {launch_tile<256, 128, 4, 2, 1, 3, 2>, 256, 128, 1, 0.87f, 0.92f},
-    {launch_tile<128, 256, 2, 4, 1, 3, 2>, 128, 256, 1, 0.88f, 0.93f},
-    {launch_tile<128, 192, 2, 4, 1, 3, 2>, 128, 192, 1, 0.76f, 0.735f},
-    {launch_tile<128, 128, 2, 4, 1, 4, 2>, 128, 128, 1, 0.57f, 0.56f},
-    {launch_tile<128, 128, 2, 2, 1, 2, 2>, 128, 128, 1, 0.68f, 0.475f},
-    {launch_tile<64, 128, 2, 2, 1, 3, 2>, 64, 128, 1, 0.42f, 0.34f},
-    {launch_tile<64, 64, 2, 2, 1, 3, 2>, 64, 64, 1, 0.25f, 0.24f},
-    {launch_tile<64, 64, 2, 2, 2, 3, 2>, 64, 64, 2, 0.43f, 0.53f},
-    {launch_tile<32, 64, 2, 2, 2, 4, 2>, 32, 64, 2, 0.42f, 0.42f},
-    {launch_tile<32, 64, 1, 4, 4, 3, 4>, 32, 64, 4, 0.60f, 0.75f},
+    {launch_tile<256, 256, 2, 4, 1, 2, 2>, 512, 256, 256, 1, 1.50f, 1.57f, false},
+    {launch_tile<192, 256, 2, 4, 1, 2, 2>, 512, 192, 256, 1, 1.15f, 1.25f, false},
+    {launch_tile<256, 128, 4, 2, 1, 3, 2>, 512, 256, 128, 1, 0.87f, 0.92f, false},
+    {launch_tile<128, 256, 2, 4, 1, 3, 2>, 512, 128, 256, 1, 0.88f, 0.93f, false},
+    {launch_tile<128, 192, 2, 4, 1, 3, 2>, 512, 128, 192, 1, 0.76f, 0.735f, false},
+    {launch_tile<128, 128, 2, 4, 1, 4, 2>, 512, 128, 128, 1, 0.57f, 0.56f, false},
+    {launch_tile<128, 128, 2, 2, 1, 2, 2>, 256, 128, 128, 1, 0.68f, 0.475f, false},
+    {launch_tile<64, 128, 2, 2, 1, 3, 2>, 256, 64, 128, 1, 0.42f, 0.34f, false},
+    {launch_tile<64, 64, 2, 2, 1, 3, 2>, 256, 64, 64, 1, 0.25f, 0.24f, false},
+    {launch_tile<64, 64, 2, 2, 2, 3, 2>, 512, 64, 64, 2, 0.43f, 0.53f, false},
+    {launch_tile<32, 64, 2, 2, 2, 4, 2>, 512, 32, 64, 2, 0.42f, 0.42f, false},
+    {launch_tile<32, 64, 1, 4, 4, 3, 4>, 1024, 32, 64, 4, 0.60f, 0.75f, false},
+    {launch_tile<256, 256, 2, 4, 1, 2, 2, true>, 512, 256, 256, 1, 1.50f, 1.57f, true},
+    {launch_tile<128, 256, 2, 2, 1, 3, 1, true>, 256, 128, 256, 1, 1.01f, 1.02f, true},
+    {launch_tile<64, 128, 2, 2, 1, 3, 2, true>, 256, 64, 128, 1, 0.42f, 0.34f, true},
 };
+
+// Whether every lane offset within a tile of tile_m rows is below 4 GiB: the last row of A that the tile fetches, and the
+// last of the up to 64 rows of B in a step.  (A: from K = 8.4 million with 256 rows; B: from N = 34 million with K >= 64.)
+static bool gemm_fits_32_bits(int tile_m, int M, int N, int K)
+{
+    const long long a_rows = tile_m < M ? tile_m : M, b_rows = K < 64 ? K : 64;
+    return a_rows * K * 2 <= 0xffffffffLL && b_rows * N * 2 <= 0xffffffffLL;
+}
 
 hipError_t launch_gemm(const void* a, const void* b, void* c, int M, int N, int K, hipStream_t stream)
 {
@@ -310,13 +335,15 @@ hipError_t launch_gemm(const void* a, const void* b, void* c, int M, int N, int 
     double best_us = 0;
     for (const GemmChoice& g : kGemmChoices) {
         const long long tiles = (((long long)M + g.tile_m - 1) / g.tile_m) * (((long long)N + g.tile_n - 1) / g.tile_n);
-        if (tiles > 0x7fffffffLL) continue;
+        if (tiles * g.threads > 0xffffffffLL) continue;                             // the threads of a launch are counted in 32 bits
+        if (g.ks > 1 && K > 0x7fffffff - 64 * g.ks) continue;                       // (the steps of the last share would leave the range of an int)
+        if (gemm_fits_32_bits(g.tile_m, M, N, K) == g.wide) continue;               // (wide: only where the offsets need it)
         const long long rounds = (tiles + cus - 1) / cus;
         const int steps = (K + 63) / 64, share = (steps + g.ks - 1) / g.ks;
         const double us = (double)share * (rounds == 1 ? g.one : (double)rounds * g.more);
         if (!best || us < best_us) { best = &g; best_us = us; }
     }
-    return best->launch(a, b, c, M, N, K, stream);
+    return best ? best->launch(a, b, c, M, N, K, stream) : hipErrorInvalidValue;
 }
 
 }  // namespace tk

@@ -3,6 +3,8 @@
 Tolerance: fp32 accumulation of K bf16 products and one rounding to bf16.  Per element the error
 is at most half a bf16 ulp of the result (2^-8 |ref|) plus the fp32 accumulation error, bounded
 here by K * 2^-24 * sum_k |a_ik b_kj| <= K * 2^-24 * (a generous 4 * sqrt(K)) for unit-variance data."""
+import math
+
 import numpy as np
 import pytest
 import torch
@@ -101,3 +103,28 @@ def test_gemm_every_tile_shape(attn, M, N, K):
     err = np.abs(buf[:M * N].view(M, N).cpu().double().numpy() - ref)
     assert np.isfinite(err).all()
     assert (err <= tol(ref, K)).all(), float((err - tol(ref, K)).max())
+
+
+# Matrices whose rows within one tile lie up to and beyond 4 GiB apart: wide B (a step has 64 of its rows) and long rows
+# of A, on both sides of the line, where the lanes' offsets no longer fit 32 bits.
+@pytest.mark.parametrize("M,N,K", [(16, 20_000_000, 64), (1, 33_554_432, 64), (1, 34_200_008, 72), (40, 36_000_008, 64), (250, 34_500_008, 64), (300, 35_000_000, 128),
+                                   (32, 8, 40_000_000), (32, 8, 69_400_008), (200, 72, 34_000_000)])
+def test_gemm_offsets_beyond_32_bits(attn, M, N, K):
+    g = torch.Generator(device="cuda").manual_seed(M + N + K)
+    a = torch.empty(M, K, device="cuda", dtype=torch.bfloat16).normal_(generator=g)
+    b = torch.empty(K, N, device="cuda", dtype=torch.bfloat16).normal_(generator=g)
+    print(f"launch gemm M{M} N{N} K{K}", flush=True)
+    c = attn.gemm(a, b)
+    torch.cuda.synchronize()
+    cols = torch.arange(N)
+    if N > 1600:
+        cols = torch.cat([cols[:300], torch.randint(N, (1000,), generator=torch.Generator().manual_seed(N)), cols[-300:]])
+    cols = cols.cuda()
+    ref = torch.zeros(M, len(cols), device="cuda", dtype=torch.float64)
+    for k0 in range(0, K, 1 << 20):
+        ref += a[:, k0:k0 + (1 << 20)].double() @ b[k0:k0 + (1 << 20), cols].double()
+    err = (c[:, cols].double() - ref).abs()
+    # half a bf16 ulp, and the fp32 sums: up to K roundings of partial sums of the size sqrt(k), which add up like a random
+    # walk to less than 0.3 * 2^-24 * K (rms)
+    bound = 2.0 ** -8 * ref.abs() + 2.0 ** -24 * K + 1e-5 * math.sqrt(K)
+    assert bool((err <= bound).all()), float((err - bound).max())
