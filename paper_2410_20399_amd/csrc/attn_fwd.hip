@@ -158,9 +158,10 @@ void attn_fwd_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K, con
     float m_run = -INFINITY;   // running max of raw scores (shared by both half-waves)
     float l_run = 0.f;         // running sum, partial: this lane's 32 of the 64 keys per tile
 
-    // A split of a causal call may hold no key that a row sees: its maximum stays -inf, and its exponents are
-    // then taken against 0, so that P = 2^-inf = 0.  (Without a split every row sees key 0.)
-    auto finite_max = [&](float m) { return SPLIT && CAUSAL && m == -INFINITY ? 0.f : m; };
+    // A split may hold no key that a row sees - beyond its diagonal, or with scores of -inf that the caller masks keys
+    // with: its maximum stays -inf, and its exponents are then taken against 0, so that P = 2^-inf = 0.  (Without a split
+    // every row sees key 0 under the causal mask, and a row that begins with a tile of -inf is NaN.)
+    auto finite_max = [&](float m) { return SPLIT && m == -INFINITY ? 0.f : m; };
 
     auto compute_tile = [&](int stage, int tile) {
         const int j0 = tile * S::kTileKV;
@@ -282,7 +283,7 @@ void attn_fwd_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K, con
 
     // ---- epilogue
     const float l_tot = half_sum(l_run);
-    const float inv = SPLIT && CAUSAL && l_tot == 0.f ? 0.f : 1.0f / l_tot;     // (no visible key in this split: O = 0, LSE = -inf)
+    const float inv = SPLIT && l_tot == 0.f ? 0.f : 1.0f / l_tot;     // (no visible key in this split: O = 0, LSE = -inf)
     if (SPLIT) {
         if (my_q < Nq) {
             const size_t prow = ((size_t)split * heads + bh) * Nq + my_q;   // [split][head][query]
@@ -508,7 +509,7 @@ void attn_decode_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K, 
         l += stat[1][w][l32] * f[w];
     }
     if (l32 >= rows) return;
-    const float inv = 1.0f / l;
+    const float inv = O_part && l == 0.f ? 0.f : 1.0f / l;      // (no visible key in this split: O = 0, LSE = -inf)
     constexpr int kRegs = D / 8;
     const size_t row = (size_t)head * rows + l32;
     const size_t part_row = (size_t)split * heads * rows + row;

@@ -58,3 +58,34 @@ def test_calls_that_are_not_split():
     for shape in ((1, 1, 1, 4096, 4096, 128, True), (1, 1, 1, 5000, 4096, 128, False), (1, 64, 64, 1024, 4096, 128, True),
                   (1, 2, 2, 100, 900, 64, True), (1, 2, 2, 4096, 100, 64, True), (1, 2, 2, 1, 4096, 96, False)):
         assert attn.tk_attn_fwd_scratch_bytes(*shape) == 0, shape
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("B,Hq,Hkv,Nq,Nk,causal", [(2, 4, 2, 130, 4100, False), (2, 2, 2, 200, 3000, True), (1, 8, 2, 1, 2500, False),
+                                                   (2, 8, 2, 1, 9000, False), (40, 8, 4, 1, 4000, False)])
+def test_masked_keys(B, Hq, Hkv, Nq, Nk, D, causal):
+    """Keys that the caller masks with scores of -inf (one column of K holds the mask, the same column of Q ones): whole
+    splits without a visible key add nothing.  One query: decode, on its own kernel and on the forward's."""
+    g = torch.Generator().manual_seed(Nq + Nk + D)
+    q, k, v = (torch.randn(B, h, n, D, generator=g).to(torch.bfloat16) for h, n in ((Hq, Nq), (Hkv, Nk), (Hkv, Nk)))
+    q[..., D - 1] = 1.0
+    k[..., D - 1] = 0.0
+    for b in range(B):
+        k[b, :, 300 + 77 * b:, D - 1] = float("-inf")        # the padding of a shorter sequence
+    k[:, :, 70:200, D - 1] = float("-inf")                  # and whole tiles in between
+    scale = 1 / math.sqrt(D)
+    print(f"launch masked B{B} Hq{Hq} Hkv{Hkv} Nq{Nq} Nk{Nk} D{D} causal={causal}", flush=True)
+    if Nq == 1:
+        o, lse = attn.decode(q.cuda(), k.cuda(), v.cuda(), scale)
+    else:
+        assert attn.tk_attn_fwd_scratch_bytes(B, Hq, Hkv, Nq, Nk, D, causal) > 0, "this shape is meant to be split"
+        o, lse = attn.rect_fwd(q.cuda(), k.cuda(), v.cuda(), causal, scale)
+    torch.cuda.synchronize()
+    b = B - 1                                               # (the rows of one entry: the oracle walks every key in fp64)
+    o_ref, lse_ref = orc.rect_fwd(*(t[b:b + 1].double().numpy() for t in (q, k, v)), causal, scale)
+    assert np.isfinite(o_ref).all()
+    for e in range(B):
+        assert bool(torch.isfinite(o[e]).all()) and bool(torch.isfinite(lse[e]).all()), e
+    err = np.abs(o[b:b + 1].double().cpu().numpy() - o_ref)
+    assert err.max() <= 2e-2 and err.mean() <= 2e-3, (err.max(), err.mean())
+    assert np.abs(lse[b:b + 1].double().cpu().numpy() - lse_ref).max() <= 1e-3
