@@ -210,6 +210,9 @@ int tk_attn_bwd_dq_delta(const void* q, const void* k, const void* v, const void
  * written to ds (tk_attn_bwd_ds_bytes(B, Hq, N, N, D) bytes, 16-byte aligned, need not be cleared), then
  * dQ = scale * dS K from those blocks (k: the same keys; the same B, Hq, Hkv, N, D, causal as the call
  * that wrote ds).  The block layout is private to the two kernels.
+ * tk_attn_bwd_ds_bytes never grows as a size shrinks: a buffer for the largest shape serves the smaller ones.  It holds
+ * the dS blocks and room for partial sums of dK and dV; a call never writes more of it than a workspace of
+ * tk_attn_bwd_spill_workspace_bytes for the same shape has behind its Delta.
  */
 size_t tk_attn_bwd_ds_bytes(int B, int Hq, int Nq, int Nk, int D);
 

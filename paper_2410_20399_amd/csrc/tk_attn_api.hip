@@ -133,6 +133,16 @@ size_t dkdv_part_room(int B, int Hq, int Nq, int Nk, int D)
     return tk::dkdv_part_bytes(B, Hq, Nk, D, 1);
 }
 
+// The same for a dS buffer whose size the call is not told (tk_attn_bwd_dkdv_ds): enough for this shape and every smaller
+// one, since a program may keep the buffer of its largest shape.  dkdv_part_room() is no such bound: it falls to 0 where
+// a shape grows out of the range that splits.  Within that range B * Nk <= kDkdvMaxWorkgroups / 2 pairs of 128-key tiles.
+size_t dkdv_part_room_upto(int B, int Hq, int Nq, int Nk, int D)
+{
+    if (Hq == 1 || Nq < 256) return 0;
+    const long long most = (long long)(kDkdvMaxWorkgroups / 2) * 256, keys = (long long)B * Nk;
+    return tk::dkdv_part_bytes(1, Hq, (int)(keys < most ? keys : most), D, 1);
+}
+
 // how the dK/dV kernel of a storing backward splits, given that room (the query heads only: it has no more)
 int dkdv_splits_storing(int B, int Hq, int Hkv, int Nq, int Nk, int D, int causal)
 {
@@ -299,13 +309,13 @@ size_t tk_attn_bwd_workspace_bytes(int B, int H, int N, int D)
 size_t tk_attn_bwd_spill_workspace_bytes(int B, int Hq, int Nq, int Nk, int D)
 {
     if (check_lengths(B, Hq, Hq, Nq, Nk, D, 0) != TK_OK) return 0;
-    return delta_bytes(B, Hq, Nq) + tk_attn_bwd_ds_bytes(B, Hq, Nq, Nk, D);
+    return delta_bytes(B, Hq, Nq) + tk::ds_spill_bytes(B, Hq, Nq, Nk) + dkdv_part_room(B, Hq, Nq, Nk, D);
 }
 
 size_t tk_attn_bwd_ds_bytes(int B, int Hq, int Nq, int Nk, int D)
 {
     if (check_lengths(B, Hq, Hq, Nq, Nk, D, 0) != TK_OK) return 0;
-    return tk::ds_spill_bytes(B, Hq, Nq, Nk) + dkdv_part_room(B, Hq, Nq, Nk, D);
+    return tk::ds_spill_bytes(B, Hq, Nq, Nk) + dkdv_part_room_upto(B, Hq, Nq, Nk, D);
 }
 
 int tk_attn_bwd_dkdv_ds(const void* q, const void* k, const void* v, const void* d_o,

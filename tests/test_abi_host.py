@@ -327,3 +327,24 @@ def test_product_path_does_not_import_the_oracle():
             if f.endswith((".py", ".hip", ".h", ".cpp")):
                 text = open(os.path.join(dirpath, f)).read()
                 assert "oracle" not in text.lower() or f == "workloads.py", f
+
+
+def test_ds_buffer_of_the_largest_shape_serves_the_smaller_ones(lib):
+    """tk_attn_bwd_dkdv_ds is not told the size of its buffer, so the size must not grow when a shape shrinks; and it
+    covers what the call writes: the part of a spill workspace behind Delta."""
+    import random
+    rng = random.Random(7)
+
+    def need(B, Hq, N, D):
+        return lib.tk_attn_bwd_spill_workspace_bytes(B, Hq, N, N, D) - lib.tk_attn_bwd_workspace_bytes(B, Hq, N, D)
+
+    assert need(128, 2, 256, 128) <= lib.tk_attn_bwd_ds_bytes(257, 2, 256, 256, 128)
+    for _ in range(20000):
+        large = [rng.randint(1, 300), rng.choice([1, 2, 4, 8, 32, 64]), rng.randint(1, 4096)]
+        small = [rng.randint(1, n) for n in large]
+        for i in range(3):
+            if rng.random() < 0.5:
+                small[i] = large[i]
+        D = rng.choice([64, 128])
+        room = lib.tk_attn_bwd_ds_bytes(large[0], large[1], large[2], large[2], 128)
+        assert need(*small, D) <= lib.tk_attn_bwd_ds_bytes(small[0], small[1], small[2], small[2], D) <= room, (large, small, D)
