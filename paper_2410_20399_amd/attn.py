@@ -324,27 +324,35 @@ def attn_fwd(q, k, v, causal: bool, scale: float, out=None, stream=None):
 SPILL_WORKSPACE_LIMIT = 24 << 30     # largest dS workspace the convenience wrappers allocate by themselves
 
 
-def alloc_bwd_workspace(B, H, N, D, device="cuda", spill=None, Nk=None):
-    """Backward workspace.  spill=True: large enough for the form that stores dS (about 2*B*H*N*Nk bytes);
-    spill=False: Delta only; spill=None: the large one where it pays - at D = 128 (the stored dS costs the same
-    bytes at every D while the recomputation it replaces shrinks with D: at D = 64 the storing form measured 25 %
-    slower than the recomputing one) - and if it stays under SPILL_WORKSPACE_LIMIT."""
+def _bwd_workspace_bytes(B, H, N, D, spill=None, Nk=None) -> int:
     small = tk_attn_bwd_workspace_bytes(B, H, N, D)
     if small == 0:
         raise TkAttnError(TK_ERR_BAD_DIM, "tk_attn_bwd_workspace_bytes")
     big = tk_attn_bwd_spill_workspace_bytes(B, H, N, N if Nk is None else Nk, D)
     if spill is None:
         spill = D == 128 and 0 < big <= SPILL_WORKSPACE_LIMIT
-    return torch.empty(big if spill else small, dtype=torch.uint8, device=device)
+    return big if spill else small
+
+
+def alloc_bwd_workspace(B, H, N, D, device="cuda", spill=None, Nk=None):
+    """Backward workspace.  spill=True: large enough for the form that stores dS (about 2*B*H*N*Nk bytes);
+    spill=False: Delta only; spill=None: the large one where it pays - at D = 128 (the stored dS costs the same
+    bytes at every D while the recomputation it replaces shrinks with D: at D = 64 the storing form measured 25 %
+    slower than the recomputing one) - and if it stays under SPILL_WORKSPACE_LIMIT."""
+    return torch.empty(_bwd_workspace_bytes(B, H, N, D, spill, Nk), dtype=torch.uint8, device=device)
+
+
+def _own_workspace(q, Nk=None) -> int:
+    """Bytes of workspace that a backward call takes by itself, from the pool of the stream it runs on, and gives back."""
+    _check_bf16("q", q)
+    return _bwd_workspace_bytes(*q.shape, Nk=Nk)
 
 
 def attn_bwd(q, k, v, o, d_o, lse, causal: bool, scale: float, workspace=None, out=None, stream=None):
     """Returns (dq, dk, dv) bf16 [B,H,N,D]; o and lse must come from attn_fwd on the same inputs."""
-    if workspace is None:
-        _check_bf16("q", q)
-        workspace = alloc_bwd_workspace(*q.shape, q.device)
+    own = _own_workspace(q) if workspace is None else 0
     dq, dk, dv = (None, None, None) if out is None else out
-    return _checked(_native().bwd(q, k, v, o, d_o, lse, causal, scale, workspace, _raw(stream), True, True, dq, dk, dv), "tk_attn_bwd")
+    return _checked(_native().bwd(q, k, v, o, d_o, lse, causal, scale, workspace, own, _raw(stream), True, True, dq, dk, dv), "tk_attn_bwd")
 
 
 def attn_bwd_delta(o, d_o, stream=None):
@@ -365,10 +373,8 @@ def gqa_fwd(q, k, v, causal: bool, scale: float, stream=None):
 
 def gqa_bwd(q, k, v, o, d_o, lse, causal: bool, scale: float, workspace=None, stream=None):
     """Grouped-query backward. Returns (dq [B,Hq,N,D], dk, dv [B,Hkv,N,D]) bf16."""
-    if workspace is None:
-        _check_bf16("q", q)
-        workspace = alloc_bwd_workspace(*q.shape, q.device)
-    return _checked(_native().bwd(q, k, v, o, d_o, lse, causal, scale, workspace, _raw(stream), False, True, None, None, None),
+    own = _own_workspace(q) if workspace is None else 0
+    return _checked(_native().bwd(q, k, v, o, d_o, lse, causal, scale, workspace, own, _raw(stream), False, True, None, None, None),
                     "tk_attn_bwd_gqa")
 
 
@@ -380,10 +386,8 @@ def rect_fwd(q, k, v, causal: bool, scale: float, stream=None):
 
 def rect_bwd(q, k, v, o, d_o, lse, causal: bool, scale: float, workspace=None, stream=None):
     """Backward of rect_fwd. Returns (dq [B,Hq,Nq,D], dk, dv [B,Hkv,Nk,D]) bf16."""
-    if workspace is None:
-        _check_bf16("q", q)
-        workspace = alloc_bwd_workspace(*q.shape, q.device, Nk=k.shape[2])
-    return _checked(_native().bwd(q, k, v, o, d_o, lse, causal, scale, workspace, _raw(stream), False, False, None, None, None),
+    own = _own_workspace(q, k.shape[2]) if workspace is None else 0
+    return _checked(_native().bwd(q, k, v, o, d_o, lse, causal, scale, workspace, own, _raw(stream), False, False, None, None, None),
                     "tk_attn_bwd_rect")
 
 

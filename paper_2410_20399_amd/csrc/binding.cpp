@@ -175,27 +175,35 @@ PyObject* fwd(PyObject* const* a) {
     return rc != TK_OK ? status(rc) : give({&o, &lse});
 }
 
-// bwd(q, k, v, o, d_o, lse, causal, scale, workspace, stream, same_heads, same_length, dq, dk, dv): dq, dk, dv None or where to write
+// bwd(q, k, v, o, d_o, lse, causal, scale, workspace, own_bytes, stream, same_heads, same_length, dq, dk, dv): workspace None: the call takes
+// own_bytes and gives them back; dq, dk, dv None or where to write
 PyObject* bwd(PyObject* const* a) {
-    const Sizes s = qkv(a, truth(a[10]), truth(a[11]));
+    const Sizes s = qkv(a, truth(a[11]), truth(a[12]));
     const at::Tensor &q = THPVariable_Unpack(a[0]), &k = THPVariable_Unpack(a[1]), &v = THPVariable_Unpack(a[2]);
     const at::Tensor& o = bf16(a[3], "o", {s.B, s.Hq, s.Nq, s.D});
     const at::Tensor& d_o = bf16(a[4], "d_o", {s.B, s.Hq, s.Nq, s.D});
     const at::Tensor& lse = f32(a[5], "lse", {s.B, s.Hq, s.Nq});
     const bool causal = truth(a[6]);
     const float scale = number(a[7]);
-    const at::Tensor& workspace = tensor(a[8], "workspace");
-    void* stream = stream_of(a[9]);
+    const size_t own_bytes = PyLong_AsSize_t(a[9]);
+    if (PyErr_Occurred()) throw Raised();
+    void* stream = stream_of(a[10]);
+    at::Tensor workspace;
+    if (a[8] == Py_None) {
+        workspace = scratch_on(stream, own_bytes, q);
+    } else {
+        workspace = tensor(a[8], "workspace");
+    }
     at::Tensor dq, dk, dv;
-    if (a[12] == Py_None) {
+    if (a[13] == Py_None) {
         at::AutoDispatchBelowADInplaceOrView plain;
         dq = at::empty(q.sizes(), q.options());
         dk = at::empty(k.sizes(), k.options());
         dv = at::empty(k.sizes(), k.options());
     } else {
-        dq = tensor(a[12], "dq");
-        dk = tensor(a[13], "dk");
-        dv = tensor(a[14], "dv");
+        dq = tensor(a[13], "dq");
+        dk = tensor(a[14], "dk");
+        dv = tensor(a[15], "dv");
     }
     const size_t workspace_bytes = (size_t)workspace.numel() * workspace.element_size();
     const size_t n = s.Hq != s.Hkv || s.Nq != s.Nk ? tk_attn_bwd_scratch_bytes(s.B, s.Hq, s.Hkv, s.Nq, s.Nk, s.D, causal, workspace_bytes) : 0;
@@ -291,7 +299,7 @@ PyObject* entry(PyObject*, PyObject* const* args, Py_ssize_t n) {
 
 #define TK_ENTRY(name, n) {#name, (PyCFunction)(void (*)(void))entry<name, n>, METH_FASTCALL, nullptr}
 PyMethodDef kMethods[] = {
-    TK_ENTRY(fwd, 10), TK_ENTRY(bwd, 15), TK_ENTRY(decode, 6), TK_ENTRY(rotary, 5), TK_ENTRY(gemm, 4),
+    TK_ENTRY(fwd, 10), TK_ENTRY(bwd, 16), TK_ENTRY(decode, 6), TK_ENTRY(rotary, 5), TK_ENTRY(gemm, 4),
     {nullptr, nullptr, 0, nullptr},
 };
 PyModuleDef kModule = {PyModuleDef_HEAD_INIT, "_binding", "tensor checks, output allocation and dispatch to the C ABI", -1, kMethods,

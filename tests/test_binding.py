@@ -67,3 +67,34 @@ def test_out_and_stream_are_honoured():
         o3, _ = attn.attn_fwd(q, k, v, True, scale)
     side.synchronize()
     assert torch.equal(o, o3)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("D", [64, 128])
+def test_own_workspace_belongs_to_the_stream_of_the_call(D):
+    """A backward call without a workspace, on a stream that is still busy: what the current stream allocates right after
+    the call is not the memory that the call has yet to write."""
+    B, H, N = 1, 4, 1024
+    q, k, v, d_o = tensors(B, H, N, D, 4)
+    scale = 1 / math.sqrt(D)
+    o, lse = attn.attn_fwd(q, k, v, True, scale)
+    want = attn.attn_bwd(q, k, v, o, d_o, lse, True, scale)
+    n = attn.alloc_bwd_workspace(B, H, N, D).numel()
+    a = torch.randn(8192, 8192, device="cuda", dtype=torch.bfloat16)
+    c = torch.empty_like(a)
+    side = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    for call in (lambda: attn.attn_bwd(q, k, v, o, d_o, lse, True, scale, stream=side),
+                 lambda: attn.gqa_bwd(q, k, v, o, d_o, lse, True, scale, stream=side),
+                 lambda: attn.rect_bwd(q, k, v, o, d_o, lse, True, scale, stream=side)):
+        for _ in range(20):
+            attn.gemm(a, a, out=c, stream=side)         # (about 16 ms, which the backward waits behind)
+        got = call()
+        junk = [torch.full((n,), 0x5A, dtype=torch.uint8, device="cuda") for _ in range(4)]
+        torch.cuda.current_stream().synchronize()
+        assert not side.query(), "the other stream was to be busy until here"
+        side.synchronize()
+        assert all(bool((t == 0x5A).all()) for t in junk), "the call wrote memory that was no longer its own"
+        assert all(torch.equal(x, y) for x, y in zip(got, want))
+        del junk
