@@ -345,7 +345,8 @@ def alloc_bwd_workspace(B, H, N, D, device="cuda", spill=None, Nk=None):
 def _own_workspace(q, Nk=None) -> int:
     """Bytes of workspace that a backward call takes by itself, from the pool of the stream it runs on, and gives back."""
     _check_bf16("q", q)
-    return _bwd_workspace_bytes(*q.shape, Nk=Nk)
+    B, H, N, D = q.shape
+    return _bwd_workspace_bytes(B, H, N, D, Nk=Nk)
 
 
 def attn_bwd(q, k, v, o, d_o, lse, causal: bool, scale: float, workspace=None, out=None, stream=None):

@@ -98,3 +98,13 @@ def test_own_workspace_belongs_to_the_stream_of_the_call(D):
         assert all(bool((t == 0x5A).all()) for t in junk), "the call wrote memory that was no longer its own"
         assert all(torch.equal(x, y) for x, y in zip(got, want))
         del junk
+
+
+@pytest.mark.gpu
+def test_backward_refuses_q_of_another_rank():
+    q, k, v = tensors(2, 4, 128, 64)
+    o, lse = attn.attn_fwd(q, k, v, False, 0.125)
+    for bad in (q[0].contiguous(), q[None].contiguous()):
+        for f in (attn.attn_bwd, attn.gqa_bwd, attn.rect_bwd):
+            with pytest.raises(ValueError):
+                f(bad, k, v, o, o, lse, False, 0.125)
