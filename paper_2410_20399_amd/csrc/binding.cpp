@@ -95,12 +95,12 @@ void* stream_of(PyObject* o) {
     return s;
 }
 
-// Makes `stream` the current one for a while.  Scratch that a call takes and gives back must come from the pool of
-// the stream it runs on: only there is the memory's next use ordered behind this one, and this one behind its last.
+// Makes `stream` the current one of `device` for a while.  Scratch that a call takes and gives back must come from the
+// pool of the stream it runs on: only there is the memory's next use ordered behind this one, and this one behind its last.
 class OnStream {
 public:
-    explicit OnStream(void* stream) : before_(c10::hip::getCurrentHIPStream()), changed_(stream != (void*)before_.stream()) {
-        if (changed_) c10::hip::setCurrentHIPStream(c10::hip::getStreamFromExternal((hipStream_t)stream, before_.device_index()));
+    OnStream(void* stream, c10::DeviceIndex device) : before_(c10::hip::getCurrentHIPStream(device)), changed_(stream != (void*)before_.stream()) {
+        if (changed_) c10::hip::setCurrentHIPStream(c10::hip::getStreamFromExternal((hipStream_t)stream, device));
     }
     ~OnStream() { if (changed_) c10::hip::setCurrentHIPStream(before_); }
     OnStream(const OnStream&) = delete;
@@ -111,10 +111,13 @@ private:
     bool changed_;
 };
 
-at::Tensor scratch_on(void* stream, size_t bytes, const at::Tensor& like) {
+// `given`: the stream argument, None for the current stream.  The device is that of the stream: the current one, or with
+// a stream of the caller's the one its tensors are on, which need not be the current.
+at::Tensor scratch_on(void* stream, PyObject* given, size_t bytes, const at::Tensor& like) {
     at::AutoDispatchBelowADInplaceOrView plain;
-    OnStream on(stream);
-    return at::empty({(int64_t)bytes}, like.options().dtype(at::kByte));
+    const c10::DeviceIndex device = given == Py_None ? c10::hip::current_device() : like.device().index();
+    OnStream on(stream, device);
+    return at::empty({(int64_t)bytes}, like.options().dtype(at::kByte).device(at::kCUDA, device));
 }
 
 PyObject* status(int rc) { return PyLong_FromLong(rc); }
@@ -168,7 +171,7 @@ PyObject* fwd(PyObject* const* a) {
     }
     const size_t n = s.Nq < s.Nk ? tk_attn_fwd_scratch_bytes(s.B, s.Hq, s.Hkv, s.Nq, s.Nk, s.D, causal) : 0;
     at::Tensor scratch;
-    if (n) scratch = scratch_on(stream, n, q);
+    if (n) scratch = scratch_on(stream, a[5], n, q);
     const int rc = tk_attn_fwd_rect_scratch(q.data_ptr(), THPVariable_Unpack(a[1]).data_ptr(), THPVariable_Unpack(a[2]).data_ptr(),
                                             o.data_ptr(), (float*)lse.data_ptr(), s.B, s.Hq, s.Hkv, s.Nq, s.Nk, s.D, causal, scale,
                                             n ? scratch.data_ptr() : nullptr, n, stream);
@@ -190,7 +193,7 @@ PyObject* bwd(PyObject* const* a) {
     void* stream = stream_of(a[10]);
     at::Tensor workspace;
     if (a[8] == Py_None) {
-        workspace = scratch_on(stream, own_bytes, q);
+        workspace = scratch_on(stream, a[10], own_bytes, q);
     } else {
         workspace = tensor(a[8], "workspace");
     }
@@ -208,7 +211,7 @@ PyObject* bwd(PyObject* const* a) {
     const size_t workspace_bytes = (size_t)workspace.numel() * workspace.element_size();
     const size_t n = s.Hq != s.Hkv || s.Nq != s.Nk ? tk_attn_bwd_scratch_bytes(s.B, s.Hq, s.Hkv, s.Nq, s.Nk, s.D, causal, workspace_bytes) : 0;
     at::Tensor scratch;
-    if (n) scratch = scratch_on(stream, n, q);
+    if (n) scratch = scratch_on(stream, a[10], n, q);
     const int rc = tk_attn_bwd_rect_scratch(q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(), d_o.data_ptr(), (const float*)lse.data_ptr(),
                                             dq.data_ptr(), dk.data_ptr(), dv.data_ptr(), s.B, s.Hq, s.Hkv, s.Nq, s.Nk, s.D, causal, scale,
                                             workspace.data_ptr(), workspace_bytes, n ? scratch.data_ptr() : nullptr, n, stream);
@@ -227,7 +230,7 @@ PyObject* decode(PyObject* const* a) {
     at::Tensor workspace;
     if (a[4] == Py_None) {
         size_t n = tk_attn_decode_workspace_bytes(s.B, s.Hq, s.Hkv, s.Nk, s.D);
-        workspace = scratch_on(stream, n < 16 ? 16 : n, q);
+        workspace = scratch_on(stream, a[5], n < 16 ? 16 : n, q);
     } else {
         workspace = tensor(a[4], "workspace");
     }

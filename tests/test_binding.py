@@ -101,6 +101,32 @@ def test_own_workspace_belongs_to_the_stream_of_the_call(D):
 
 
 @pytest.mark.gpu
+@pytest.mark.skipif(torch.cuda.device_count() < 2, reason="needs a device that is not the current one")
+def test_scratch_belongs_to_the_stream_of_another_device():
+    """The tensors and the stream are the second device's, the first is the current one."""
+    with torch.cuda.device(1):
+        g = torch.Generator(device="cuda").manual_seed(3)
+        q, d_o = (torch.randn(1, 8, 512, 128, generator=g, device="cuda", dtype=torch.bfloat16) for _ in range(2))
+        k, v = (torch.randn(1, 2, 4096, 128, generator=g, device="cuda", dtype=torch.bfloat16) for _ in range(2))
+        o, lse = attn.rect_fwd(q, k, v, True, 0.1)
+        want = (o, lse, *attn.rect_bwd(q, k, v, o, d_o, lse, True, 0.1))
+        a = torch.randn(8192, 8192, device="cuda", dtype=torch.bfloat16)
+        c = torch.empty_like(a)
+        side = torch.cuda.Stream()
+        torch.cuda.synchronize()
+        torch.cuda.empty_cache()
+    for call in (lambda: attn.rect_fwd(q, k, v, True, 0.1, stream=side), lambda: attn.rect_bwd(q, k, v, o, d_o, lse, True, 0.1, stream=side)):
+        for _ in range(20):
+            attn.gemm(a, a, out=c, stream=side)
+        got = call()
+        junk = [torch.full((n << 20,), 0x5A, dtype=torch.uint8, device="cuda:1") for n in (1, 4, 16, 64)]
+        torch.cuda.current_stream(1).synchronize()
+        side.synchronize()
+        assert all(bool((t == 0x5A).all()) for t in junk)
+        assert all(torch.equal(x, y) for x, y in zip(got, want[:2] if len(got) == 2 else want[2:]))
+
+
+@pytest.mark.gpu
 def test_backward_refuses_q_of_another_rank():
     q, k, v = tensors(2, 4, 128, 64)
     o, lse = attn.attn_fwd(q, k, v, False, 0.125)
