@@ -317,8 +317,7 @@ def tk_mfma_probe(operands, sink, workgroups, iters, stream=None) -> int:
 # ------------------------------------------------------------------ convenience: allocate outputs, raise on error
 def attn_fwd(q, k, v, causal: bool, scale: float, out=None, stream=None):
     """q, k, v: CUDA bf16 [B,H,N,D]. Returns (o bf16 [B,H,N,D], lse fp32 [B,H,N])."""
-    o, lse = (None, None) if out is None else out
-    return _checked(_native().fwd(q, k, v, causal, scale, _raw(stream), True, True, o, lse), "tk_attn_fwd")
+    return _checked(_native().fwd(q, k, v, causal, scale, _raw(stream), True, True, out), "tk_attn_fwd")
 
 
 SPILL_WORKSPACE_LIMIT = 24 << 30     # largest dS workspace the convenience wrappers allocate by themselves
@@ -352,8 +351,7 @@ def _own_workspace(q, Nk=None) -> int:
 def attn_bwd(q, k, v, o, d_o, lse, causal: bool, scale: float, workspace=None, out=None, stream=None):
     """Returns (dq, dk, dv) bf16 [B,H,N,D]; o and lse must come from attn_fwd on the same inputs."""
     own = _own_workspace(q) if workspace is None else 0
-    dq, dk, dv = (None, None, None) if out is None else out
-    return _checked(_native().bwd(q, k, v, o, d_o, lse, causal, scale, workspace, own, _raw(stream), True, True, dq, dk, dv), "tk_attn_bwd")
+    return _checked(_native().bwd(q, k, v, o, d_o, lse, causal, scale, workspace, own, _raw(stream), True, True, out), "tk_attn_bwd")
 
 
 def attn_bwd_delta(o, d_o, stream=None):
@@ -369,26 +367,26 @@ def attn_bwd_delta(o, d_o, stream=None):
 
 def gqa_fwd(q, k, v, causal: bool, scale: float, stream=None):
     """Grouped-query forward: q bf16 [B,Hq,N,D], k, v bf16 [B,Hkv,N,D]. Returns (o [B,Hq,N,D], lse [B,Hq,N])."""
-    return _checked(_native().fwd(q, k, v, causal, scale, _raw(stream), False, True, None, None), "tk_attn_fwd_gqa")
+    return _checked(_native().fwd(q, k, v, causal, scale, _raw(stream), False, True, None), "tk_attn_fwd_gqa")
 
 
 def gqa_bwd(q, k, v, o, d_o, lse, causal: bool, scale: float, workspace=None, stream=None):
     """Grouped-query backward. Returns (dq [B,Hq,N,D], dk, dv [B,Hkv,N,D]) bf16."""
     own = _own_workspace(q) if workspace is None else 0
-    return _checked(_native().bwd(q, k, v, o, d_o, lse, causal, scale, workspace, own, _raw(stream), False, True, None, None, None),
+    return _checked(_native().bwd(q, k, v, o, d_o, lse, causal, scale, workspace, own, _raw(stream), False, True, None),
                     "tk_attn_bwd_gqa")
 
 
 def rect_fwd(q, k, v, causal: bool, scale: float, stream=None):
     """Forward with Nq queries and Nk keys: q bf16 [B,Hq,Nq,D], k, v bf16 [B,Hkv,Nk,D].
     Returns (o [B,Hq,Nq,D], lse [B,Hq,Nq]).  Causal: query i sees keys j <= i + (Nk - Nq)."""
-    return _checked(_native().fwd(q, k, v, causal, scale, _raw(stream), False, False, None, None), "tk_attn_fwd_rect")
+    return _checked(_native().fwd(q, k, v, causal, scale, _raw(stream), False, False, None), "tk_attn_fwd_rect")
 
 
 def rect_bwd(q, k, v, o, d_o, lse, causal: bool, scale: float, workspace=None, stream=None):
     """Backward of rect_fwd. Returns (dq [B,Hq,Nq,D], dk, dv [B,Hkv,Nk,D]) bf16."""
     own = _own_workspace(q, k.shape[2]) if workspace is None else 0
-    return _checked(_native().bwd(q, k, v, o, d_o, lse, causal, scale, workspace, own, _raw(stream), False, False, None, None, None),
+    return _checked(_native().bwd(q, k, v, o, d_o, lse, causal, scale, workspace, own, _raw(stream), False, False, None),
                     "tk_attn_bwd_rect")
 
 

@@ -75,6 +75,39 @@ void rank(const at::Tensor& t, const char* name, int64_t want) {
     if (t.dim() != want) value_error("%s has the wrong number of dimensions", name);
 }
 
+// a size as the C ABI takes it
+int narrow(int64_t n, const char* name) {
+    if (n > 0x7fffffff) value_error("%s has a dimension beyond 31 bits", name);
+    return (int)n;
+}
+
+// memory that the call may write from end to end
+const at::Tensor& buffer(PyObject* o, const char* name) {
+    const at::Tensor& t = tensor(o, name);
+    if (!(t.is_cuda() && t.is_contiguous())) value_error("%s must be a contiguous CUDA tensor", name);
+    return t;
+}
+
+// the tensors of out=
+class Outputs {
+public:
+    Outputs(PyObject* out, Py_ssize_t n) : items_(PySequence_Fast(out, "out must be a sequence of tensors")) {
+        if (!items_) throw Raised();
+        if (PySequence_Fast_GET_SIZE(items_) != n) {
+            Py_DECREF(items_);
+            PyErr_Format(PyExc_ValueError, "out must hold %zd tensors", n);
+            throw Raised();
+        }
+    }
+    ~Outputs() { Py_DECREF(items_); }
+    Outputs(const Outputs&) = delete;
+    Outputs& operator=(const Outputs&) = delete;
+    PyObject* operator[](Py_ssize_t i) const { return PySequence_Fast_GET_ITEM(items_, i); }
+
+private:
+    PyObject* items_;
+};
+
 bool truth(PyObject* o) {
     const int v = PyObject_IsTrue(o);
     if (v < 0) throw Raised();
@@ -148,12 +181,10 @@ Sizes qkv(PyObject* const* a, bool same_heads, bool same_length) {
     const int64_t Hkv = same_heads ? Hq : k.size(1), Nk = same_length ? Nq : k.size(2);
     shape(k, "k", {B, Hkv, Nk, D});
     bf16(a[2], "v", {B, Hkv, Nk, D});
-    for (int64_t n : {B, Hq, Hkv, Nq, Nk, D})
-        if (n > 0x7fffffff) value_error("%s has a dimension beyond 31 bits", "q, k or v");
-    return {(int)B, (int)Hq, (int)Hkv, (int)Nq, (int)Nk, (int)D};
+    return {narrow(B, "q"), narrow(Hq, "q"), narrow(Hkv, "k"), narrow(Nq, "q"), narrow(Nk, "k"), narrow(D, "q")};
 }
 
-// fwd(q, k, v, causal, scale, stream, same_heads, same_length, o, lse): o and lse None, or where to write
+// fwd(q, k, v, causal, scale, stream, same_heads, same_length, out): out None, or (o, lse) to write to
 PyObject* fwd(PyObject* const* a) {
     const Sizes s = qkv(a, truth(a[6]), truth(a[7]));
     const at::Tensor& q = THPVariable_Unpack(a[0]);
@@ -166,8 +197,9 @@ PyObject* fwd(PyObject* const* a) {
         o = at::empty(q.sizes(), q.options());
         lse = at::empty({s.B, s.Hq, s.Nq}, q.options().dtype(at::kFloat));
     } else {
-        o = bf16(a[8], "o", {s.B, s.Hq, s.Nq, s.D});
-        lse = f32(a[9], "lse", {s.B, s.Hq, s.Nq});
+        const Outputs out(a[8], 2);
+        o = bf16(out[0], "o", {s.B, s.Hq, s.Nq, s.D});
+        lse = f32(out[1], "lse", {s.B, s.Hq, s.Nq});
     }
     const size_t n = s.Nq < s.Nk ? tk_attn_fwd_scratch_bytes(s.B, s.Hq, s.Hkv, s.Nq, s.Nk, s.D, causal) : 0;
     at::Tensor scratch;
@@ -178,8 +210,8 @@ PyObject* fwd(PyObject* const* a) {
     return rc != TK_OK ? status(rc) : give({&o, &lse});
 }
 
-// bwd(q, k, v, o, d_o, lse, causal, scale, workspace, own_bytes, stream, same_heads, same_length, dq, dk, dv): workspace None: the call takes
-// own_bytes and gives them back; dq, dk, dv None or where to write
+// bwd(q, k, v, o, d_o, lse, causal, scale, workspace, own_bytes, stream, same_heads, same_length, out): workspace None: the
+// call takes own_bytes and gives them back; out None, or (dq, dk, dv) to write to
 PyObject* bwd(PyObject* const* a) {
     const Sizes s = qkv(a, truth(a[11]), truth(a[12]));
     const at::Tensor &q = THPVariable_Unpack(a[0]), &k = THPVariable_Unpack(a[1]), &v = THPVariable_Unpack(a[2]);
@@ -195,7 +227,7 @@ PyObject* bwd(PyObject* const* a) {
     if (a[8] == Py_None) {
         workspace = scratch_on(stream, a[10], own_bytes, q);
     } else {
-        workspace = tensor(a[8], "workspace");
+        workspace = buffer(a[8], "workspace");
     }
     at::Tensor dq, dk, dv;
     if (a[13] == Py_None) {
@@ -204,9 +236,10 @@ PyObject* bwd(PyObject* const* a) {
         dk = at::empty(k.sizes(), k.options());
         dv = at::empty(k.sizes(), k.options());
     } else {
-        dq = tensor(a[13], "dq");
-        dk = tensor(a[14], "dk");
-        dv = tensor(a[15], "dv");
+        const Outputs out(a[13], 3);
+        dq = bf16(out[0], "dq", {s.B, s.Hq, s.Nq, s.D});
+        dk = bf16(out[1], "dk", {s.B, s.Hkv, s.Nk, s.D});
+        dv = bf16(out[2], "dv", {s.B, s.Hkv, s.Nk, s.D});
     }
     const size_t workspace_bytes = (size_t)workspace.numel() * workspace.element_size();
     const size_t n = s.Hq != s.Hkv || s.Nq != s.Nk ? tk_attn_bwd_scratch_bytes(s.B, s.Hq, s.Hkv, s.Nq, s.Nk, s.D, causal, workspace_bytes) : 0;
@@ -232,7 +265,7 @@ PyObject* decode(PyObject* const* a) {
         size_t n = tk_attn_decode_workspace_bytes(s.B, s.Hq, s.Hkv, s.Nk, s.D);
         workspace = scratch_on(stream, a[5], n < 16 ? 16 : n, q);
     } else {
-        workspace = tensor(a[4], "workspace");
+        workspace = buffer(a[4], "workspace");
     }
     const at::Tensor o = at::empty(q.sizes(), q.options());
     const at::Tensor lse = at::empty({s.B, s.Hq, 1}, q.options().dtype(at::kFloat));
@@ -256,7 +289,7 @@ PyObject* rotary(PyObject* const* a) {
     } else {
         o = bf16(a[3], "o", {B, H, N, D});
     }
-    const int rc = tk_rotary(x.data_ptr(), sn.data_ptr(), cs.data_ptr(), o.data_ptr(), (int)B, (int)H, (int)N, (int)D, stream_of(a[4]));
+    const int rc = tk_rotary(x.data_ptr(), sn.data_ptr(), cs.data_ptr(), o.data_ptr(), narrow(B, "x"), narrow(H, "x"), narrow(N, "x"), narrow(D, "x"), stream_of(a[4]));
     return rc != TK_OK ? status(rc) : THPVariable_Wrap(o);
 }
 
@@ -273,9 +306,9 @@ PyObject* gemm(PyObject* const* args) {
         at::AutoDispatchBelowADInplaceOrView plain;
         c = at::empty({M, N}, a.options());
     } else {
-        c = tensor(args[2], "out");
+        c = bf16(args[2], "out", {M, N});
     }
-    const int rc = tk_gemm(a.data_ptr(), b.data_ptr(), c.data_ptr(), (int)M, (int)N, (int)K, stream_of(args[3]));
+    const int rc = tk_gemm(a.data_ptr(), b.data_ptr(), c.data_ptr(), narrow(M, "a"), narrow(N, "b"), narrow(K, "a"), stream_of(args[3]));
     return rc != TK_OK ? status(rc) : THPVariable_Wrap(c);
 }
 
@@ -302,7 +335,7 @@ PyObject* entry(PyObject*, PyObject* const* args, Py_ssize_t n) {
 
 #define TK_ENTRY(name, n) {#name, (PyCFunction)(void (*)(void))entry<name, n>, METH_FASTCALL, nullptr}
 PyMethodDef kMethods[] = {
-    TK_ENTRY(fwd, 10), TK_ENTRY(bwd, 16), TK_ENTRY(decode, 6), TK_ENTRY(rotary, 5), TK_ENTRY(gemm, 4),
+    TK_ENTRY(fwd, 9), TK_ENTRY(bwd, 14), TK_ENTRY(decode, 6), TK_ENTRY(rotary, 5), TK_ENTRY(gemm, 4),
     {nullptr, nullptr, 0, nullptr},
 };
 PyModuleDef kModule = {PyModuleDef_HEAD_INIT, "_binding", "tensor checks, output allocation and dispatch to the C ABI", -1, kMethods,

@@ -134,3 +134,43 @@ def test_backward_refuses_q_of_another_rank():
         for f in (attn.attn_bwd, attn.gqa_bwd, attn.rect_bwd):
             with pytest.raises(ValueError):
                 f(bad, k, v, o, o, lse, False, 0.125)
+
+
+@pytest.mark.gpu
+def test_outputs_and_workspaces_that_do_not_fit_are_refused():
+    """Whatever the kernels would write to is looked at before anything is launched."""
+    q, k, v, d_o = tensors(1, 4, 256, 64, 4)
+    o, lse = attn.attn_fwd(q, k, v, False, 0.125)
+    workspace = attn.alloc_bwd_workspace(1, 4, 256, 64)
+    new = lambda *shape: torch.empty(shape, dtype=torch.bfloat16, device="cuda")
+    wrong = (new(1, 4, 255, 64), new(1, 4, 256, 64).float(), new(1, 4, 256, 64).cpu(), new(1, 4, 64, 256).transpose(2, 3), new(4 * 256 * 64))
+    for bad in wrong:
+        for i in range(3):
+            out = [torch.empty_like(q) for _ in range(3)]
+            out[i] = bad
+            with pytest.raises(ValueError):
+                attn.attn_bwd(q, k, v, o, d_o, lse, False, 0.125, workspace=workspace, out=out)
+        with pytest.raises(ValueError):
+            attn.attn_fwd(q, k, v, False, 0.125, out=(bad, lse))
+        with pytest.raises(ValueError):
+            attn.rotary(q, new(256, 32), new(256, 32), out=bad)
+    for out in ((None, None, None), (None, torch.empty_like(k), torch.empty_like(v)), (torch.empty_like(q), None, None), 3):
+        with pytest.raises((TypeError, attn.TkAttnError)):
+            attn.attn_bwd(q, k, v, o, d_o, lse, False, 0.125, workspace=workspace, out=out)
+    for out in ((None, None), (None, lse), (o, None)):
+        with pytest.raises((TypeError, AttributeError)):
+            attn.attn_fwd(q, k, v, False, 0.125, out=out)
+    for out in ((o,), (o, lse, lse)):
+        with pytest.raises(ValueError):
+            attn.attn_fwd(q, k, v, False, 0.125, out=out)
+    for bad in (workspace.cpu(), workspace[::2], torch.zeros(1, dtype=torch.uint8, device="cuda").expand(1 << 20), torch.zeros(1 << 20, dtype=torch.uint8)):
+        with pytest.raises(ValueError):
+            attn.attn_bwd(q, k, v, o, d_o, lse, False, 0.125, workspace=bad)
+        with pytest.raises(ValueError):
+            attn.decode(q[:, :, :1].contiguous(), k, v, 0.125, workspace=bad)
+    with pytest.raises(TypeError):
+        attn.attn_bwd(q, k, v, o, d_o, lse, False, 0.125, workspace=1 << 20)
+    a, b = new(16, 64), new(64, 24)
+    for bad in (new(16, 23), new(24, 16), new(16, 24).float(), new(16, 24).cpu(), new(24, 16).t(), new(15, 24), new(16 * 24)):
+        with pytest.raises(ValueError):
+            attn.gemm(a, b, out=bad)
