@@ -121,8 +121,9 @@ def _native():
     """The C++ side of the convenience functions."""
     global _binding
     if _binding is None:
-        load_library()
+        library = load_library()
         from . import _binding as module
+        module.bind(library._handle)
         _binding = module
     return _binding
 

@@ -55,7 +55,6 @@ def _build_binding() -> None:
          "-I" + os.path.join(root, "include"), "-I" + os.path.join(root, "include", "torch", "csrc", "api", "include"),
          "-I/opt/rocm/include", "-I" + sysconfig.get_paths()["include"],
          os.path.join(CSRC, "binding.cpp"), "-o", BINDING,
-         "-L" + HERE, "-ltk_attn", "-Wl,-rpath,$ORIGIN",
          "-L" + os.path.join(root, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"],
         check=True)
 

@@ -12,6 +12,8 @@
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/autograd/python_variable.h>
 
+#include <dlfcn.h>
+
 #include <exception>
 #include <initializer_list>
 
@@ -20,6 +22,17 @@
 namespace {
 
 struct Raised {};       // a Python exception is set
+
+// The functions of the library that load_library() in attn.py opened, which need not be the one next to this module.
+#define TK_FUNCTIONS(F) \
+    F(tk_attn_fwd_scratch_bytes) F(tk_attn_fwd_rect_scratch) F(tk_attn_bwd_scratch_bytes) F(tk_attn_bwd_rect_scratch) \
+    F(tk_attn_decode_workspace_bytes) F(tk_attn_decode) F(tk_rotary) F(tk_gemm)
+struct Library {
+#define TK_MEMBER(name) decltype(&::name) name = nullptr;
+    TK_FUNCTIONS(TK_MEMBER)
+#undef TK_MEMBER
+    bool bound = false;
+} lib;
 
 [[noreturn]] void value_error(const char* format, const char* name) {
     PyErr_Format(PyExc_ValueError, format, name);
@@ -201,10 +214,10 @@ PyObject* fwd(PyObject* const* a) {
         o = bf16(out[0], "o", {s.B, s.Hq, s.Nq, s.D});
         lse = f32(out[1], "lse", {s.B, s.Hq, s.Nq});
     }
-    const size_t n = s.Nq < s.Nk ? tk_attn_fwd_scratch_bytes(s.B, s.Hq, s.Hkv, s.Nq, s.Nk, s.D, causal) : 0;
+    const size_t n = s.Nq < s.Nk ? lib.tk_attn_fwd_scratch_bytes(s.B, s.Hq, s.Hkv, s.Nq, s.Nk, s.D, causal) : 0;
     at::Tensor scratch;
     if (n) scratch = scratch_on(stream, a[5], n, q);
-    const int rc = tk_attn_fwd_rect_scratch(q.data_ptr(), THPVariable_Unpack(a[1]).data_ptr(), THPVariable_Unpack(a[2]).data_ptr(),
+    const int rc = lib.tk_attn_fwd_rect_scratch(q.data_ptr(), THPVariable_Unpack(a[1]).data_ptr(), THPVariable_Unpack(a[2]).data_ptr(),
                                             o.data_ptr(), (float*)lse.data_ptr(), s.B, s.Hq, s.Hkv, s.Nq, s.Nk, s.D, causal, scale,
                                             n ? scratch.data_ptr() : nullptr, n, stream);
     return rc != TK_OK ? status(rc) : give({&o, &lse});
@@ -242,10 +255,10 @@ PyObject* bwd(PyObject* const* a) {
         dv = bf16(out[2], "dv", {s.B, s.Hkv, s.Nk, s.D});
     }
     const size_t workspace_bytes = (size_t)workspace.numel() * workspace.element_size();
-    const size_t n = s.Hq != s.Hkv || s.Nq != s.Nk ? tk_attn_bwd_scratch_bytes(s.B, s.Hq, s.Hkv, s.Nq, s.Nk, s.D, causal, workspace_bytes) : 0;
+    const size_t n = s.Hq != s.Hkv || s.Nq != s.Nk ? lib.tk_attn_bwd_scratch_bytes(s.B, s.Hq, s.Hkv, s.Nq, s.Nk, s.D, causal, workspace_bytes) : 0;
     at::Tensor scratch;
     if (n) scratch = scratch_on(stream, a[10], n, q);
-    const int rc = tk_attn_bwd_rect_scratch(q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(), d_o.data_ptr(), (const float*)lse.data_ptr(),
+    const int rc = lib.tk_attn_bwd_rect_scratch(q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(), d_o.data_ptr(), (const float*)lse.data_ptr(),
                                             dq.data_ptr(), dk.data_ptr(), dv.data_ptr(), s.B, s.Hq, s.Hkv, s.Nq, s.Nk, s.D, causal, scale,
                                             workspace.data_ptr(), workspace_bytes, n ? scratch.data_ptr() : nullptr, n, stream);
     return rc != TK_OK ? status(rc) : give({&dq, &dk, &dv});
@@ -262,14 +275,14 @@ PyObject* decode(PyObject* const* a) {
     at::AutoDispatchBelowADInplaceOrView plain;
     at::Tensor workspace;
     if (a[4] == Py_None) {
-        size_t n = tk_attn_decode_workspace_bytes(s.B, s.Hq, s.Hkv, s.Nk, s.D);
+        size_t n = lib.tk_attn_decode_workspace_bytes(s.B, s.Hq, s.Hkv, s.Nk, s.D);
         workspace = scratch_on(stream, a[5], n < 16 ? 16 : n, q);
     } else {
         workspace = buffer(a[4], "workspace");
     }
     const at::Tensor o = at::empty(q.sizes(), q.options());
     const at::Tensor lse = at::empty({s.B, s.Hq, 1}, q.options().dtype(at::kFloat));
-    const int rc = tk_attn_decode(q.data_ptr(), THPVariable_Unpack(a[1]).data_ptr(), THPVariable_Unpack(a[2]).data_ptr(),
+    const int rc = lib.tk_attn_decode(q.data_ptr(), THPVariable_Unpack(a[1]).data_ptr(), THPVariable_Unpack(a[2]).data_ptr(),
                                   o.data_ptr(), (float*)lse.data_ptr(), s.B, s.Hq, s.Hkv, s.Nk, s.D, scale,
                                   workspace.data_ptr(), (size_t)workspace.numel() * workspace.element_size(), stream);
     return rc != TK_OK ? status(rc) : give({&o, &lse});
@@ -289,7 +302,7 @@ PyObject* rotary(PyObject* const* a) {
     } else {
         o = bf16(a[3], "o", {B, H, N, D});
     }
-    const int rc = tk_rotary(x.data_ptr(), sn.data_ptr(), cs.data_ptr(), o.data_ptr(), narrow(B, "x"), narrow(H, "x"), narrow(N, "x"), narrow(D, "x"), stream_of(a[4]));
+    const int rc = lib.tk_rotary(x.data_ptr(), sn.data_ptr(), cs.data_ptr(), o.data_ptr(), narrow(B, "x"), narrow(H, "x"), narrow(N, "x"), narrow(D, "x"), stream_of(a[4]));
     return rc != TK_OK ? status(rc) : THPVariable_Wrap(o);
 }
 
@@ -308,7 +321,7 @@ PyObject* gemm(PyObject* const* args) {
     } else {
         c = bf16(args[2], "out", {M, N});
     }
-    const int rc = tk_gemm(a.data_ptr(), b.data_ptr(), c.data_ptr(), narrow(M, "a"), narrow(N, "b"), narrow(K, "a"), stream_of(args[3]));
+    const int rc = lib.tk_gemm(a.data_ptr(), b.data_ptr(), c.data_ptr(), narrow(M, "a"), narrow(N, "b"), narrow(K, "a"), stream_of(args[3]));
     return rc != TK_OK ? status(rc) : THPVariable_Wrap(c);
 }
 
@@ -316,6 +329,10 @@ template <PyObject* (*F)(PyObject* const*), int N>
 PyObject* entry(PyObject*, PyObject* const* args, Py_ssize_t n) {
     if (n != N) {
         PyErr_Format(PyExc_TypeError, "%d arguments expected, %zd given", N, n);
+        return nullptr;
+    }
+    if (!lib.bound) {
+        PyErr_SetString(PyExc_RuntimeError, "no library is bound");
         return nullptr;
     }
     try {
@@ -333,8 +350,26 @@ PyObject* entry(PyObject*, PyObject* const* args, Py_ssize_t n) {
     return nullptr;
 }
 
+// bind(handle): the dlopen handle of the library whose functions are called from now on
+PyObject* bind(PyObject*, PyObject* handle) {
+    void* const h = PyLong_AsVoidPtr(handle);
+    if (PyErr_Occurred()) return nullptr;
+    Library found;
+#define TK_FIND(name) \
+    if (!(found.name = (decltype(found.name))dlsym(h, #name))) { \
+        PyErr_SetString(PyExc_AttributeError, "the library has no " #name); \
+        return nullptr; \
+    }
+    TK_FUNCTIONS(TK_FIND)
+#undef TK_FIND
+    found.bound = true;
+    lib = found;
+    Py_RETURN_NONE;
+}
+
 #define TK_ENTRY(name, n) {#name, (PyCFunction)(void (*)(void))entry<name, n>, METH_FASTCALL, nullptr}
 PyMethodDef kMethods[] = {
+    {"bind", bind, METH_O, nullptr},
     TK_ENTRY(fwd, 9), TK_ENTRY(bwd, 14), TK_ENTRY(decode, 6), TK_ENTRY(rotary, 5), TK_ENTRY(gemm, 4),
     {nullptr, nullptr, 0, nullptr},
 };

@@ -1,5 +1,8 @@
 """The convenience functions of attn.py: what they refuse, and that they honour out= and stream=."""
 import math
+import os
+import subprocess
+import sys
 
 import pytest
 import torch
@@ -15,6 +18,42 @@ def test_tensors_that_are_not_on_the_gpu_are_refused():
         attn.gemm(x[0, 0], x[0, 0].t())
     with pytest.raises(TypeError):
         attn.rotary(None, x, x)
+
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+# A library that stands in for the real one, and tensors without memory: the way from Python into the library, on the CPU.
+STAND_IN = """
+import sys, threading, time
+import torch
+from torch._subclasses.fake_tensor import FakeTensorMode
+from paper_2410_20399_amd import attn
+attn.load_library(sys.argv[1])
+class Stream:
+    cuda_stream = 0
+with FakeTensorMode():
+    a, b, c = (torch.empty(s, dtype=torch.bfloat16, device="cuda") for s in ((16, 64), (64, 24), (16, 24)))
+"""
+
+
+@pytest.fixture(scope="module")
+def stand_in(tmp_path_factory):
+    folder = tmp_path_factory.mktemp("stand_in")
+    source, library = str(folder / "lib.c"), str(folder / "lib.so")
+    with open(source, "w") as f:
+        f.write("#include <unistd.h>\n")
+        for name in attn.EXPORTS:
+            f.write("int %s() { return 0; }\n" % name if name != "tk_gemm" else "int tk_gemm() { usleep(400000); return 0; }\n")
+    subprocess.run(["gcc", "-shared", "-fPIC", source, "-o", library], check=True)
+
+    def run(program):
+        subprocess.run([sys.executable, "-c", STAND_IN + program, library], check=True, cwd=ROOT, timeout=120)
+    return run
+
+
+def test_the_library_that_was_loaded_is_the_one_that_is_called(stand_in):
+    # (the real library refuses the missing memory)
+    stand_in("assert attn.gemm(a, b, out=c, stream=Stream()) is not None\n")
 
 
 def tensors(B, H, N, D, n=3):
