@@ -134,12 +134,29 @@ float number(PyObject* o) {
 }
 
 // the raw stream an int names, or the current stream of the current device
-void* stream_of(PyObject* o) {
-    if (o == Py_None) return (void*)c10::hip::getCurrentHIPStream().stream();
+struct Stream {
+    void* raw;
+    bool given;
+};
+Stream stream_of(PyObject* o) {
+    if (o == Py_None) return {(void*)c10::hip::getCurrentHIPStream().stream(), false};
     void* s = PyLong_AsVoidPtr(o);
     if (PyErr_Occurred()) throw Raised();
-    return s;
+    return {s, true};
 }
+
+// The interpreter lock is released while this lives: an allocation may wait for the device and a launch for room in the
+// stream's queue, possibly behind a host callback that needs the lock itself.  No Python object is touched meanwhile.
+class Unlocked {
+public:
+    Unlocked() : state_(PyEval_SaveThread()) {}
+    ~Unlocked() { PyEval_RestoreThread(state_); }
+    Unlocked(const Unlocked&) = delete;
+    Unlocked& operator=(const Unlocked&) = delete;
+
+private:
+    PyThreadState* state_;
+};
 
 // Makes `stream` the current one of `device` for a while.  Scratch that a call takes and gives back must come from the
 // pool of the stream it runs on: only there is the memory's next use ordered behind this one, and this one behind its last.
@@ -157,12 +174,12 @@ private:
     bool changed_;
 };
 
-// `given`: the stream argument, None for the current stream.  The device is that of the stream: the current one, or with
-// a stream of the caller's the one its tensors are on, which need not be the current.
-at::Tensor scratch_on(void* stream, PyObject* given, size_t bytes, const at::Tensor& like) {
+// The device is that of the stream: the current one, or with a stream of the caller's the one its tensors are on, which
+// need not be the current.
+at::Tensor scratch_on(Stream stream, size_t bytes, const at::Tensor& like) {
     at::AutoDispatchBelowADInplaceOrView plain;
-    const c10::DeviceIndex device = given == Py_None ? c10::hip::current_device() : like.device().index();
-    OnStream on(stream, device);
+    const c10::DeviceIndex device = stream.given ? like.device().index() : c10::hip::current_device();
+    OnStream on(stream.raw, device);
     return at::empty({(int64_t)bytes}, like.options().dtype(at::kByte).device(at::kCUDA, device));
 }
 
@@ -200,26 +217,30 @@ Sizes qkv(PyObject* const* a, bool same_heads, bool same_length) {
 // fwd(q, k, v, causal, scale, stream, same_heads, same_length, out): out None, or (o, lse) to write to
 PyObject* fwd(PyObject* const* a) {
     const Sizes s = qkv(a, truth(a[6]), truth(a[7]));
-    const at::Tensor& q = THPVariable_Unpack(a[0]);
+    const at::Tensor &q = THPVariable_Unpack(a[0]), &k = THPVariable_Unpack(a[1]), &v = THPVariable_Unpack(a[2]);
     const bool causal = truth(a[3]);
     const float scale = number(a[4]);
-    void* stream = stream_of(a[5]);
+    const Stream stream = stream_of(a[5]);
     at::Tensor o, lse;
-    if (a[8] == Py_None) {
-        at::AutoDispatchBelowADInplaceOrView plain;
-        o = at::empty(q.sizes(), q.options());
-        lse = at::empty({s.B, s.Hq, s.Nq}, q.options().dtype(at::kFloat));
-    } else {
+    if (a[8] != Py_None) {
         const Outputs out(a[8], 2);
         o = bf16(out[0], "o", {s.B, s.Hq, s.Nq, s.D});
         lse = f32(out[1], "lse", {s.B, s.Hq, s.Nq});
     }
-    const size_t n = s.Nq < s.Nk ? lib.tk_attn_fwd_scratch_bytes(s.B, s.Hq, s.Hkv, s.Nq, s.Nk, s.D, causal) : 0;
-    at::Tensor scratch;
-    if (n) scratch = scratch_on(stream, a[5], n, q);
-    const int rc = lib.tk_attn_fwd_rect_scratch(q.data_ptr(), THPVariable_Unpack(a[1]).data_ptr(), THPVariable_Unpack(a[2]).data_ptr(),
-                                            o.data_ptr(), (float*)lse.data_ptr(), s.B, s.Hq, s.Hkv, s.Nq, s.Nk, s.D, causal, scale,
-                                            n ? scratch.data_ptr() : nullptr, n, stream);
+    int rc;
+    {
+        Unlocked unlocked;
+        if (!o.defined()) {
+            at::AutoDispatchBelowADInplaceOrView plain;
+            o = at::empty(q.sizes(), q.options());
+            lse = at::empty({s.B, s.Hq, s.Nq}, q.options().dtype(at::kFloat));
+        }
+        const size_t n = s.Nq < s.Nk ? lib.tk_attn_fwd_scratch_bytes(s.B, s.Hq, s.Hkv, s.Nq, s.Nk, s.D, causal) : 0;
+        at::Tensor scratch;
+        if (n) scratch = scratch_on(stream, n, q);
+        rc = lib.tk_attn_fwd_rect_scratch(q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(), (float*)lse.data_ptr(),
+                                          s.B, s.Hq, s.Hkv, s.Nq, s.Nk, s.D, causal, scale, n ? scratch.data_ptr() : nullptr, n, stream.raw);
+    }
     return rc != TK_OK ? status(rc) : give({&o, &lse});
 }
 
@@ -233,34 +254,36 @@ PyObject* bwd(PyObject* const* a) {
     const at::Tensor& lse = f32(a[5], "lse", {s.B, s.Hq, s.Nq});
     const bool causal = truth(a[6]);
     const float scale = number(a[7]);
+    at::Tensor workspace;
+    if (a[8] != Py_None) workspace = buffer(a[8], "workspace");
     const size_t own_bytes = PyLong_AsSize_t(a[9]);
     if (PyErr_Occurred()) throw Raised();
-    void* stream = stream_of(a[10]);
-    at::Tensor workspace;
-    if (a[8] == Py_None) {
-        workspace = scratch_on(stream, a[10], own_bytes, q);
-    } else {
-        workspace = buffer(a[8], "workspace");
-    }
+    const Stream stream = stream_of(a[10]);
     at::Tensor dq, dk, dv;
-    if (a[13] == Py_None) {
-        at::AutoDispatchBelowADInplaceOrView plain;
-        dq = at::empty(q.sizes(), q.options());
-        dk = at::empty(k.sizes(), k.options());
-        dv = at::empty(k.sizes(), k.options());
-    } else {
+    if (a[13] != Py_None) {
         const Outputs out(a[13], 3);
         dq = bf16(out[0], "dq", {s.B, s.Hq, s.Nq, s.D});
         dk = bf16(out[1], "dk", {s.B, s.Hkv, s.Nk, s.D});
         dv = bf16(out[2], "dv", {s.B, s.Hkv, s.Nk, s.D});
     }
-    const size_t workspace_bytes = (size_t)workspace.numel() * workspace.element_size();
-    const size_t n = s.Hq != s.Hkv || s.Nq != s.Nk ? lib.tk_attn_bwd_scratch_bytes(s.B, s.Hq, s.Hkv, s.Nq, s.Nk, s.D, causal, workspace_bytes) : 0;
-    at::Tensor scratch;
-    if (n) scratch = scratch_on(stream, a[10], n, q);
-    const int rc = lib.tk_attn_bwd_rect_scratch(q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(), d_o.data_ptr(), (const float*)lse.data_ptr(),
-                                            dq.data_ptr(), dk.data_ptr(), dv.data_ptr(), s.B, s.Hq, s.Hkv, s.Nq, s.Nk, s.D, causal, scale,
-                                            workspace.data_ptr(), workspace_bytes, n ? scratch.data_ptr() : nullptr, n, stream);
+    int rc;
+    {
+        Unlocked unlocked;
+        if (!workspace.defined()) workspace = scratch_on(stream, own_bytes, q);
+        if (!dq.defined()) {
+            at::AutoDispatchBelowADInplaceOrView plain;
+            dq = at::empty(q.sizes(), q.options());
+            dk = at::empty(k.sizes(), k.options());
+            dv = at::empty(k.sizes(), k.options());
+        }
+        const size_t workspace_bytes = (size_t)workspace.numel() * workspace.element_size();
+        const size_t n = s.Hq != s.Hkv || s.Nq != s.Nk ? lib.tk_attn_bwd_scratch_bytes(s.B, s.Hq, s.Hkv, s.Nq, s.Nk, s.D, causal, workspace_bytes) : 0;
+        at::Tensor scratch;
+        if (n) scratch = scratch_on(stream, n, q);
+        rc = lib.tk_attn_bwd_rect_scratch(q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(), d_o.data_ptr(), (const float*)lse.data_ptr(),
+                                          dq.data_ptr(), dk.data_ptr(), dv.data_ptr(), s.B, s.Hq, s.Hkv, s.Nq, s.Nk, s.D, causal, scale,
+                                          workspace.data_ptr(), workspace_bytes, n ? scratch.data_ptr() : nullptr, n, stream.raw);
+    }
     return rc != TK_OK ? status(rc) : give({&dq, &dk, &dv});
 }
 
@@ -270,21 +293,26 @@ PyObject* decode(PyObject* const* a) {
     rank(q, "q", 4);
     if (q.size(2) != 1) value_error("%s takes exactly one query per head", "decode");
     const Sizes s = qkv(a, false, false);
+    const at::Tensor &k = THPVariable_Unpack(a[1]), &v = THPVariable_Unpack(a[2]);
     const float scale = number(a[3]);
-    void* stream = stream_of(a[5]);
-    at::AutoDispatchBelowADInplaceOrView plain;
     at::Tensor workspace;
-    if (a[4] == Py_None) {
-        size_t n = lib.tk_attn_decode_workspace_bytes(s.B, s.Hq, s.Hkv, s.Nk, s.D);
-        workspace = scratch_on(stream, a[5], n < 16 ? 16 : n, q);
-    } else {
-        workspace = buffer(a[4], "workspace");
+    if (a[4] != Py_None) workspace = buffer(a[4], "workspace");
+    const Stream stream = stream_of(a[5]);
+    at::Tensor o, lse;
+    int rc;
+    {
+        Unlocked unlocked;
+        at::AutoDispatchBelowADInplaceOrView plain;
+        if (!workspace.defined()) {
+            const size_t n = lib.tk_attn_decode_workspace_bytes(s.B, s.Hq, s.Hkv, s.Nk, s.D);
+            workspace = scratch_on(stream, n < 16 ? 16 : n, q);
+        }
+        o = at::empty(q.sizes(), q.options());
+        lse = at::empty({s.B, s.Hq, 1}, q.options().dtype(at::kFloat));
+        rc = lib.tk_attn_decode(q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(), (float*)lse.data_ptr(),
+                                s.B, s.Hq, s.Hkv, s.Nk, s.D, scale, workspace.data_ptr(),
+                                (size_t)workspace.numel() * workspace.element_size(), stream.raw);
     }
-    const at::Tensor o = at::empty(q.sizes(), q.options());
-    const at::Tensor lse = at::empty({s.B, s.Hq, 1}, q.options().dtype(at::kFloat));
-    const int rc = lib.tk_attn_decode(q.data_ptr(), THPVariable_Unpack(a[1]).data_ptr(), THPVariable_Unpack(a[2]).data_ptr(),
-                                  o.data_ptr(), (float*)lse.data_ptr(), s.B, s.Hq, s.Hkv, s.Nk, s.D, scale,
-                                  workspace.data_ptr(), (size_t)workspace.numel() * workspace.element_size(), stream);
     return rc != TK_OK ? status(rc) : give({&o, &lse});
 }
 
@@ -292,17 +320,22 @@ PyObject* decode(PyObject* const* a) {
 PyObject* rotary(PyObject* const* a) {
     const at::Tensor& x = bf16(a[0], "x");
     rank(x, "x", 4);
-    const int64_t B = x.size(0), H = x.size(1), N = x.size(2), D = x.size(3);
+    const int64_t N = x.size(2), D = x.size(3);
     const at::Tensor& sn = bf16(a[1], "sin_table", {N, D / 2});
     const at::Tensor& cs = bf16(a[2], "cos_table", {N, D / 2});
+    const int B = narrow(x.size(0), "x"), H = narrow(x.size(1), "x"), n = narrow(N, "x"), d = narrow(D, "x");
     at::Tensor o;
-    if (a[3] == Py_None) {
-        at::AutoDispatchBelowADInplaceOrView plain;
-        o = at::empty(x.sizes(), x.options());
-    } else {
-        o = bf16(a[3], "o", {B, H, N, D});
+    if (a[3] != Py_None) o = bf16(a[3], "o", {B, H, N, D});
+    const Stream stream = stream_of(a[4]);
+    int rc;
+    {
+        Unlocked unlocked;
+        if (!o.defined()) {
+            at::AutoDispatchBelowADInplaceOrView plain;
+            o = at::empty(x.sizes(), x.options());
+        }
+        rc = lib.tk_rotary(x.data_ptr(), sn.data_ptr(), cs.data_ptr(), o.data_ptr(), B, H, n, d, stream.raw);
     }
-    const int rc = lib.tk_rotary(x.data_ptr(), sn.data_ptr(), cs.data_ptr(), o.data_ptr(), narrow(B, "x"), narrow(H, "x"), narrow(N, "x"), narrow(D, "x"), stream_of(a[4]));
     return rc != TK_OK ? status(rc) : THPVariable_Wrap(o);
 }
 
@@ -313,15 +346,19 @@ PyObject* gemm(PyObject* const* args) {
         value_error("%s must be 2-D bf16 tensors", "a, b");
     if (!(a.is_cuda() && b.is_cuda() && a.is_contiguous() && b.is_contiguous()) || a.size(1) != b.size(0))
         value_error("%s must be contiguous CUDA tensors", "a [M,K], b [K,N]");
-    const int64_t M = a.size(0), K = a.size(1), N = b.size(1);
+    const int M = narrow(a.size(0), "a"), K = narrow(a.size(1), "a"), N = narrow(b.size(1), "b");
     at::Tensor c;
-    if (args[2] == Py_None) {
-        at::AutoDispatchBelowADInplaceOrView plain;
-        c = at::empty({M, N}, a.options());
-    } else {
-        c = bf16(args[2], "out", {M, N});
+    if (args[2] != Py_None) c = bf16(args[2], "out", {M, N});
+    const Stream stream = stream_of(args[3]);
+    int rc;
+    {
+        Unlocked unlocked;
+        if (!c.defined()) {
+            at::AutoDispatchBelowADInplaceOrView plain;
+            c = at::empty({M, N}, a.options());
+        }
+        rc = lib.tk_gemm(a.data_ptr(), b.data_ptr(), c.data_ptr(), M, N, K, stream.raw);
     }
-    const int rc = lib.tk_gemm(a.data_ptr(), b.data_ptr(), c.data_ptr(), narrow(M, "a"), narrow(N, "b"), narrow(K, "a"), stream_of(args[3]));
     return rc != TK_OK ? status(rc) : THPVariable_Wrap(c);
 }
 

@@ -56,6 +56,23 @@ def test_the_library_that_was_loaded_is_the_one_that_is_called(stand_in):
     stand_in("assert attn.gemm(a, b, out=c, stream=Stream()) is not None\n")
 
 
+def test_other_threads_run_while_a_call_is_in_the_library(stand_in):
+    # (the stand-in stays in tk_gemm for 0.4 s, as a launch on a full queue does)
+    stand_in("""
+attn.gemm(a, b, out=c, stream=Stream())
+awake = []
+def wake():
+    time.sleep(0.05)
+    awake.append(time.monotonic())
+thread = threading.Thread(target=wake)
+thread.start()
+attn.gemm(a, b, out=c, stream=Stream())
+back = time.monotonic()
+thread.join()
+assert awake[0] < back - 0.1, (awake[0], back)
+""")
+
+
 def tensors(B, H, N, D, n=3):
     g = torch.Generator(device="cuda").manual_seed(N)
     return [torch.randn(B, H, N, D, generator=g, device="cuda", dtype=torch.bfloat16) for _ in range(n)]
