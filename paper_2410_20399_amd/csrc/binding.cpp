@@ -183,6 +183,17 @@ at::Tensor scratch_on(Stream stream, size_t bytes, const at::Tensor& like) {
     return at::empty({(int64_t)bytes}, like.options().dtype(at::kByte).device(at::kCUDA, device));
 }
 
+// Scratch that only makes a call faster: where there is no memory for it the call does without (n becomes 0).
+at::Tensor optional_scratch(Stream stream, size_t& n, const at::Tensor& like) {
+    if (n == 0) return {};
+    try {
+        return scratch_on(stream, n, like);
+    } catch (const c10::OutOfMemoryError&) {
+        n = 0;
+        return {};
+    }
+}
+
 PyObject* status(int rc) { return PyLong_FromLong(rc); }
 
 PyObject* give(std::initializer_list<const at::Tensor*> outs) {
@@ -235,9 +246,8 @@ PyObject* fwd(PyObject* const* a) {
             o = at::empty(q.sizes(), q.options());
             lse = at::empty({s.B, s.Hq, s.Nq}, q.options().dtype(at::kFloat));
         }
-        const size_t n = s.Nq < s.Nk ? lib.tk_attn_fwd_scratch_bytes(s.B, s.Hq, s.Hkv, s.Nq, s.Nk, s.D, causal) : 0;
-        at::Tensor scratch;
-        if (n) scratch = scratch_on(stream, n, q);
+        size_t n = s.Nq < s.Nk ? lib.tk_attn_fwd_scratch_bytes(s.B, s.Hq, s.Hkv, s.Nq, s.Nk, s.D, causal) : 0;
+        const at::Tensor scratch = optional_scratch(stream, n, q);
         rc = lib.tk_attn_fwd_rect_scratch(q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(), (float*)lse.data_ptr(),
                                           s.B, s.Hq, s.Hkv, s.Nq, s.Nk, s.D, causal, scale, n ? scratch.data_ptr() : nullptr, n, stream.raw);
     }
@@ -277,9 +287,8 @@ PyObject* bwd(PyObject* const* a) {
             dv = at::empty(k.sizes(), k.options());
         }
         const size_t workspace_bytes = (size_t)workspace.numel() * workspace.element_size();
-        const size_t n = s.Hq != s.Hkv || s.Nq != s.Nk ? lib.tk_attn_bwd_scratch_bytes(s.B, s.Hq, s.Hkv, s.Nq, s.Nk, s.D, causal, workspace_bytes) : 0;
-        at::Tensor scratch;
-        if (n) scratch = scratch_on(stream, n, q);
+        size_t n = s.Hq != s.Hkv || s.Nq != s.Nk ? lib.tk_attn_bwd_scratch_bytes(s.B, s.Hq, s.Hkv, s.Nq, s.Nk, s.D, causal, workspace_bytes) : 0;
+        const at::Tensor scratch = optional_scratch(stream, n, q);
         rc = lib.tk_attn_bwd_rect_scratch(q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(), d_o.data_ptr(), (const float*)lse.data_ptr(),
                                           dq.data_ptr(), dk.data_ptr(), dv.data_ptr(), s.B, s.Hq, s.Hkv, s.Nq, s.Nk, s.D, causal, scale,
                                           workspace.data_ptr(), workspace_bytes, n ? scratch.data_ptr() : nullptr, n, stream.raw);

@@ -230,3 +230,37 @@ def test_outputs_and_workspaces_that_do_not_fit_are_refused():
     for bad in (new(16, 23), new(24, 16), new(16, 24).float(), new(16, 24).cpu(), new(24, 16).t(), new(15, 24), new(16 * 24)):
         with pytest.raises(ValueError):
             attn.gemm(a, b, out=bad)
+
+
+@pytest.mark.gpu
+def test_without_memory_for_scratch_a_call_does_without():
+    """The scratch of a split is no more than an aid: a process at its memory limit gets the unsplit results."""
+    B, Hq, Hkv, D, scale = 1, 32, 8, 64, 0.125
+    torch.cuda.empty_cache()            # (no large block of an earlier test, of which a part would be left over)
+    g = torch.Generator(device="cuda").manual_seed(5)
+    new = lambda h, n: torch.randn(B, h, n, D, generator=g, device="cuda", dtype=torch.bfloat16)
+    q, k, v = new(Hq, 1024), new(Hkv, 8192), new(Hkv, 8192)
+    q2, k2, v2, d_o = new(Hq, 2048), new(Hkv, 2048), new(Hkv, 2048), new(Hq, 2048)
+    assert attn.tk_attn_fwd_scratch_bytes(B, Hq, Hkv, 1024, 8192, D, True) > 16 << 20
+    workspace = torch.empty(attn.tk_attn_bwd_workspace_bytes(B, Hq, 2048, D), dtype=torch.uint8, device="cuda")
+    assert attn.tk_attn_bwd_scratch_bytes(B, Hq, Hkv, 2048, 2048, D, True, workspace.numel()) > 16 << 20
+    o, lse = torch.empty_like(q), torch.empty(B, Hq, 1024, device="cuda")
+    assert attn.tk_attn_fwd_rect(q, k, v, o, lse, B, Hq, Hkv, 1024, 8192, D, True, scale) == attn.TK_OK
+    o2, lse2 = attn.gqa_fwd(q2, k2, v2, True, scale)
+    grads = tuple(torch.empty_like(t) for t in (q2, k2, v2))
+    assert attn.tk_attn_bwd_rect(q2, k2, v2, o2, d_o, lse2, *grads, B, Hq, Hkv, 2048, 2048, D, True, scale, workspace, workspace.numel()) == attn.TK_OK
+    torch.cuda.synchronize()
+    keep = [torch.empty_like(t) for t in (o, lse, *grads)]      # (memory for the results, given back to the pool)
+    torch.cuda.empty_cache()
+    del keep
+    total = torch.cuda.get_device_properties(0).total_memory
+    try:
+        torch.cuda.set_per_process_memory_fraction((torch.cuda.memory_reserved() + (1 << 20)) / total)
+        with pytest.raises(torch.OutOfMemoryError):
+            torch.empty(32 << 20, dtype=torch.uint8, device="cuda")
+        got = attn.rect_fwd(q, k, v, True, scale)
+        got_grads = attn.gqa_bwd(q2, k2, v2, o2, d_o, lse2, True, scale, workspace)
+    finally:
+        torch.cuda.set_per_process_memory_fraction(1.0)
+    assert torch.equal(got[0], o) and torch.equal(got[1], lse)
+    assert all(torch.equal(x, y) for x, y in zip(got_grads, grads))
