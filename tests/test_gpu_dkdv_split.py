@@ -1,7 +1,9 @@
 """GPU: backward calls whose queries are split over several workgroups of the dK/dV kernel.
 
 The query heads of a group, the queries of a head (cross-attention) and both.  Odd and even tile counts, a length inside
-the last key tile, parts of unequal length, groups that split fully or in part, both forms of the backward.  Against the fp64 oracle, and with nothing written behind the buffers.
+the last key tile, parts of unequal length, groups that split fully or in part, more than 16 causal key tiles (a workgroup
+then takes two, one pass behind the other), both forms of the backward.  Against the fp64 oracle, and with nothing written
+behind the buffers.
 """
 import math
 
@@ -21,6 +23,7 @@ GUARD = 1024
 @pytest.mark.parametrize("B,Hq,Hkv,Nq,Nk,D,causal", [
     (1, 4, 1, 256, 256, 128, True), (2, 8, 2, 333, 333, 128, True), (1, 6, 2, 300, 1000, 64, True), (1, 8, 1, 700, 130, 128, False),
     (1, 8, 1, 513, 513, 64, True), (5, 12, 2, 257, 1500, 64, False),
+    (1, 4, 1, 2200, 2200, 128, True), (1, 8, 2, 2100, 2100, 64, True), (2, 4, 2, 300, 2500, 64, True), (1, 6, 1, 400, 2177, 128, True),
     (2, 4, 4, 1100, 300, 64, False), (1, 2, 2, 4000, 70, 64, False), (1, 3, 3, 2049, 129, 128, False), (1, 6, 3, 1090, 600, 128, False)])
 def test_split_backward(B, Hq, Hkv, Nq, Nk, D, causal, spill):
     g = torch.Generator().manual_seed(17 * Nq + Nk + D)
@@ -54,6 +57,8 @@ def test_split_backward(B, Hq, Hkv, Nq, Nk, D, causal, spill):
         assert torch.equal(a, b) and torch.equal(a, c)
     # a workspace with room for dS but not for partial sums, or no scratch: unsplit, and as good
     room = 8 * B * Hq * Nk * D if spill else 0
+    for t in (dq, dk, dv):
+        t.fill_(float("nan"))
     assert attn.tk_attn_bwd_rect(qd, kd, vd, o, dod, lse, dq, dk, dv, B, Hq, Hkv, Nq, Nk, D, causal, scale, ws, n_ws - room) == attn.TK_OK
     for name, got, ref in zip(("dq", "dk", "dv"), (dq, dk, dv), refs):
         check_grad(got.double().cpu().numpy(), ref, name)
