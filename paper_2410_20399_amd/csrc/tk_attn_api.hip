@@ -171,12 +171,30 @@ tk::DkdvSplits dkdv_splits_scratch(int B, int Hq, int Hkv, int Nq, int Nk, int D
 constexpr int kFwdSplitWgPerCu = 2;
 constexpr int kFwdSplitMinTiles = 8;
 
+// Whether it pays: with many rows and few tiles the merge costs more than the idle compute units give, and heads that
+// share no keys are bound by reading them.  A 64-key tile takes a workgroup alone on its compute unit 0.82 us at D = 64 and
+// 1.28 at D = 128; two of them on one unit take 1.55 times as long each, with up to 64 rows (half the waves idle) 1.1
+// times; K and V come in at 6 TB/s at most; the merge takes 2 us and its bytes, written and read, at 5.5 TB/s.  Of 1206
+// sizes with 1 to 2000 queries and 1024 to 16000 keys it leaves out those that lost, us (unsplit, split): B4 Hq16 Hkv2 Nq322
+// Nk1529 D128 33, 41; B1 Hq128 Hkv32 Nq160 Nk1399 D64 22, 26; B1 H232 Nq11 Nk1496 D128 30, 32; one is left (B1 Hq16 Hkv2
+// Nq1286 Nk2559 D128 50, 52), and none that would gain a tenth is left out.
+bool fwd_split_pays(int B, int Hq, int Hkv, int Nq, int Nk, int D, int n_splits, int per, int compute_units)
+{
+    const long long workgroups = (long long)B * Hq * ((Nq + kTileN - 1) / kTileN) * n_splits;
+    const double tile_us = D == 64 ? 0.82 : 1.28;
+    const double shared = workgroups <= compute_units ? 1.0 : Nq > 64 ? 1.55 : 1.1;
+    const double kv_us = 4.0 * B * Hkv * Nk * D / 6.0e6;
+    const double merge_us = 2.0 + 8.0 * n_splits * B * Hq * Nq * D / 5.5e6;
+    const double split_us = per * tile_us * shared > kv_us ? per * tile_us * shared : kv_us;
+    return split_us + merge_us < (Nk + 63) / 64 * tile_us;
+}
+
 struct FwdPlan {
     int n_splits, tiles_per_split;
 };
 
 // Nq < Nk only: with equal lengths a head's bits do not depend on how many heads the call has.
-FwdPlan plan_fwd(int B, int Hq, int Nq, int Nk, int compute_units)
+FwdPlan plan_fwd(int B, int Hq, int Hkv, int Nq, int Nk, int D, int compute_units)
 {
     const long long base = (long long)B * Hq * ((Nq + kTileN - 1) / kTileN);
     const int tiles = (Nk + 63) / 64;
@@ -185,7 +203,9 @@ FwdPlan plan_fwd(int B, int Hq, int Nq, int Nk, int compute_units)
     if (want < 1) want = 1;
     int per = (int)((tiles + want - 1) / want);
     per += per & 1;                                   // the kernel walks the tiles in pairs
-    return {(tiles + per - 1) / per, per};            // no split is empty
+    const int n_splits = (tiles + per - 1) / per;     // no split is empty
+    if (n_splits > 1 && !fwd_split_pays(B, Hq, Hkv, Nq, Nk, D, n_splits, per, compute_units)) return {1, tiles + (tiles & 1)};
+    return {n_splits, per};
 }
 
 // fp32 partial O and partial LSE of a split forward, each padded to 256 bytes
@@ -211,7 +231,7 @@ size_t tk_attn_fwd_scratch_bytes(int B, int Hq, int Hkv, int Nq, int Nk, int D, 
     if (check_lengths(B, Hq, Hkv, Nq, Nk, D, causal) != TK_OK || Nq >= Nk) return 0;
     int cus = 0;
     if (tk::compute_unit_count(&cus) != hipSuccess || cus < 1) return 0;
-    const FwdPlan p = plan_fwd(B, Hq, Nq, Nk, cus);
+    const FwdPlan p = plan_fwd(B, Hq, Hkv, Nq, Nk, D, cus);
     if (p.n_splits == 1) return 0;
     const size_t rows = (size_t)B * Hq * Nq;
     return fwd_part_bytes(p.n_splits, rows, D) + fwd_part_bytes(p.n_splits, rows, 1);
@@ -229,7 +249,7 @@ int tk_attn_fwd_rect_scratch(const void* q, const void* k, const void* v, void* 
     if (int rc = check_scale(scale)) return rc;
     int cus = 0;
     if (tk::compute_unit_count(&cus) != hipSuccess) return TK_ERR_LAUNCH;
-    const FwdPlan p = plan_fwd(B, Hq, Nq, Nk, cus);
+    const FwdPlan p = plan_fwd(B, Hq, Hkv, Nq, Nk, D, cus);
     float* lse_part = (float*)((char*)scratch + fwd_part_bytes(p.n_splits, (size_t)B * Hq * Nq, D));
     hipError_t e = tk::launch_attn_fwd_splitk(q, k, v, o, lse, (float*)scratch, lse_part, B, Hq, Hkv, Nq, Nk, D, causal != 0, scale,
                                               p.n_splits, p.tiles_per_split, (hipStream_t)stream);

@@ -56,7 +56,9 @@ def test_split_forward(B, Hq, Hkv, Nq, Nk, D, causal):
 
 def test_calls_that_are_not_split():
     for shape in ((1, 1, 1, 4096, 4096, 128, True), (1, 1, 1, 5000, 4096, 128, False), (1, 64, 64, 1024, 4096, 128, True),
-                  (1, 2, 2, 100, 900, 64, True), (1, 2, 2, 4096, 100, 64, True), (1, 2, 2, 1, 4096, 96, False)):
+                  (1, 2, 2, 100, 900, 64, True), (1, 2, 2, 4096, 100, 64, True), (1, 2, 2, 1, 4096, 96, False),
+                  # two splits of few tiles and many rows: the merge would cost more than they save
+                  (4, 16, 2, 322, 1529, 128, False), (1, 128, 32, 160, 1399, 64, False), (1, 163, 163, 86, 1380, 128, True)):
         assert attn.tk_attn_fwd_scratch_bytes(*shape) == 0, shape
 
 
