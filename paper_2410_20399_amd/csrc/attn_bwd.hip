@@ -143,7 +143,7 @@ void attn_bwd_dkdv_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K
                           const bf16* __restrict__ dO, const float* __restrict__ LSE, const float* __restrict__ Delta,
                           bf16* __restrict__ dK, bf16* __restrict__ dV,
                           int Nq, int Nk, int num_kv_tiles, int total_units, float scale, int hq, int hkv,
-                          char* __restrict__ DS, int n_qb, int pair_tiles, int n_splits, int q_splits,
+                          char* __restrict__ DS, int n_qb, int units, int n_splits, int q_splits,
                           float* __restrict__ Part)
 {
     using S = DkdvShape<D>;
@@ -161,14 +161,14 @@ void attn_bwd_dkdv_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K
 
     // Work unit: one key tile, or, when causal, the pair (u, last - u): tile u loops over the
     // query blocks from its diagonal on, so the pairs carry (nearly) the same work and the static
-    // schedule is balanced.  (Not paired where every tile can have a workgroup of its own, see pair_tiles().)  A "pass" is one key tile; (vu, half) names the pass `half` of unit vu.
+    // schedule is balanced.  (Not paired where every tile can have a workgroup of its own, see pair_tiles().)  A "pass" is
+    // one key tile; (vu, half) names the pass `half` of unit vu.  `units` per key/value head come from the host: formed here
+    // from a flag, they cost the masked step of the D = 64 kernel a wait in the middle (32 masked blocks 29.1, 31.0 us).
     // Grouped-query attention: a key/value head is shared by `group` consecutive query heads, and a
     // pass streams the query blocks of all of them, one head after the other, into the same dK, dV
     // accumulators.  bh below counts key/value heads.
     const int heads_per_kv = hq / hkv;
     const int group = SPLIT ? heads_per_kv / (n_splits / q_splits) : heads_per_kv;      // query heads of a pass
-    const bool paired = CAUSAL && (!TAIL || pair_tiles);
-    const int units = paired ? (num_kv_tiles + 1) / 2 : num_kv_tiles;
     auto q_head_row = [&](int bh, int split) {         // first row of the first query head of a pass of key/value head bh
         return (size_t)((bh / hkv) * hq + (bh % hkv) * heads_per_kv + (SPLIT ? split / q_splits * group : 0)) * Nq;
     };
@@ -199,9 +199,9 @@ void attn_bwd_dkdv_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K
     };
     // the pass after (vu, half) in this workgroup's walk; vu >= total_units means "none"
     auto next_pass = [&](int& vu, int& half) {
-        if (paired && half == 0) {
+        if (CAUSAL && half == 0) {
             const int unit = xcd_remap(vu, total_units) % units;
-            if (num_kv_tiles - 1 - unit != unit) { half = 1; return; }   // (odd tile count: the middle tile has no partner)
+            if (num_kv_tiles - 1 - unit >= units) { half = 1; return; }   // (not paired, or the middle one of an odd count: no partner)
         }
         vu += gridDim.x;
         half = 0;
@@ -786,12 +786,13 @@ static hipError_t launch_dkdv_tt(const void* q, const void* k, const void* v, co
 {
     using S = DkdvShape<D>;
     const int num_kv_tiles = (Nk + S::kTileKV - 1) / S::kTileKV;
-    const int total_units = B * Hkv * n_splits * (CAUSAL && paired ? (num_kv_tiles + 1) / 2 : num_kv_tiles);
+    const int units = CAUSAL && paired ? (num_kv_tiles + 1) / 2 : num_kv_tiles;
+    const int total_units = B * Hkv * n_splits * units;
     const int grid = total_units < resident ? total_units : resident;
     hipLaunchKernelGGL((attn_bwd_dkdv_kernel<D, CAUSAL, TAIL, SPILL, SPLIT>), dim3(grid), dim3(S::kThreads), 0, stream,
                        (const bf16*)q, (const bf16*)k, (const bf16*)v, (const bf16*)d_o, lse, delta,
                        (bf16*)dk, (bf16*)dv, Nq, Nk, num_kv_tiles, total_units, scale, H, Hkv,
-                       (char*)ds, ds_query_blocks(Nq), paired, n_splits, q_splits, part);
+                       (char*)ds, ds_query_blocks(Nq), units, n_splits, q_splits, part);
     if (SPLIT) {
         const size_t n4 = (size_t)B * Hkv * Nk * D / 4;
         hipLaunchKernelGGL(attn_bwd_dkdv_sum_kernel, dim3((unsigned)((n4 + 255) / 256), 2), dim3(256), 0, stream,
