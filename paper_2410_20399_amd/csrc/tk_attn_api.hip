@@ -149,8 +149,7 @@ int dkdv_splits_storing(int B, int Hq, int Hkv, int Nq, int Nk, int D, int causa
     int cus = 0;
     if (dkdv_part_room(B, Hq, Nq, Nk, D) == 0 || tk::compute_unit_count(&cus) != hipSuccess) return 1;
     if (cus > kDkdvMaxWorkgroups / 2) cus = kDkdvMaxWorkgroups / 2;
-    const tk::DkdvSplits p = tk::dkdv_splits(B, Hq, Hkv, Nq, Nk, D, causal != 0, cus);
-    return p.n_splits / p.q_splits;
+    return tk::dkdv_splits(B, Hq, Hkv, Nq, Nk, D, causal != 0, cus, true).n_splits;
 }
 
 // how it splits with scratch for it
@@ -158,7 +157,7 @@ tk::DkdvSplits dkdv_splits_scratch(int B, int Hq, int Hkv, int Nq, int Nk, int D
 {
     int cus = 0;
     if (tk::compute_unit_count(&cus) != hipSuccess) return {1, 1};
-    const tk::DkdvSplits p = tk::dkdv_splits(B, Hq, Hkv, Nq, Nk, D, causal != 0, cus);
+    const tk::DkdvSplits p = tk::dkdv_splits(B, Hq, Hkv, Nq, Nk, D, causal != 0, cus, false);
     const bool storing = workspace_bytes >= delta_bytes(B, Hq, Nq) + tk::ds_spill_bytes(B, Hq, Nq, Nk);
     return storing && p.q_splits == 1 ? tk::DkdvSplits{1, 1} : p;      // (heads alone: the workspace has room)
 }

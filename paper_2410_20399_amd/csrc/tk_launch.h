@@ -74,6 +74,14 @@ inline size_t ds_spill_bytes(int B, int H, int Nq, int Nk) {
     return (size_t)B * H * (size_t)((Nk + 127) / 128) * (size_t)ds_query_blocks(Nq) * 8192;
 }
 
+// Whether the tiles of a causal backward launch are paired, long with short, for equal work per workgroup: not where
+// each has a compute unit of its own without: the longest tile alone is then the shorter way, by one tile in `tiles`
+// and a start-up.  Whole backward, us, paired and not: B2 Hq16 Hkv4 N1001 D128 100, 84; B2 H12 N700 D64 47, 37; but with
+// 32 tiles B1 H8 N4096 D128 201, 224 (half the compute units hold a higher clock) and with two workgroups to a compute
+// unit, two long ones or two short ones, B1 H16 N4096 D64 173, 227.  (A single tile has no partner either way, and counts as
+// paired: without a pair the kernels for ragged lengths are taken, B2 Hq128 Hkv16 N128 D128 52, 57.)
+inline bool pair_tiles(long long heads, int tiles, int compute_units) { return heads * tiles > compute_units || tiles > 16 || tiles == 1; }
+
 // Ways to split the queries of a key tile over workgroups of the dK/dV kernel, as far as the units still fit the compute
 // units at once (with more units the split only adds the traffic of the partial sums): n_splits in all, of which
 // q_splits share the query blocks of a head and n_splits / q_splits the query heads of a group.
@@ -85,12 +93,41 @@ inline size_t ds_spill_bytes(int B, int H, int Nq, int Nk) {
 // depend on the number of heads; with a mask the late key tiles have few blocks), down to 512 queries, and only to one
 // workgroup a compute unit.  Backward, us: B1 H4 Nq4096 Nk64 D64 91, 22; B1 H8 Nq3000 Nk200 D128 128, 42; but with two
 // workgroups to some compute units B4 H16 Nq1000 Nk300 D64 47, 53, and with 150 queries each B2 H16 Nq300 Nk128 20, 25.
+//   Whether it pays: the partial sums and their launch have to cost less than the shorter streams save (dkdv_us()).
 struct DkdvSplits {
     int n_splits, q_splits;
 };
 // blocks of a head in one of q_splits parts, an even number; the last part may be shorter
 __host__ __device__ inline int dkdv_q_chunk(int Nq, int q_splits) { return 2 * (((Nq + 63) / 64 + q_splits - 1) / q_splits); }
-inline DkdvSplits dkdv_splits(int B, int H, int Hkv, int Nq, int Nk, int D, bool causal, int compute_units) {
+
+// Microseconds of the dK/dV kernel split that way: the longest stream of blocks of a workgroup at 0.6 us a block (D = 64) or
+// 1.4 (D = 128), 1.4 times that where two workgroups share a compute unit; a split adds 3 us and its partial sums, written
+// and read, at 5 TB/s.  Fitted to 1999 backward calls with 256 to 4000 queries, each timed with and without its split: by
+// this rule five of them lose, at most 3 %; splitting wherever the units fit lost up to 20 %, us (unsplit, split): B5 Hq32
+// Hkv16 N268 D64 34, 42 (two workgroups to a compute unit); B3 Hq32 Hkv8 Nq309 Nk1060 D128 causal 95, 116 (split tiles are too
+// many to go unpaired, and the pairs are as long as the single tiles were).
+inline double dkdv_us(int B, int H, int Hkv, int Nq, int Nk, int D, bool causal, int compute_units, DkdvSplits p) {
+    const int tiles = (Nk + 127) / 128, heads = p.n_splits / p.q_splits;
+    const bool paired = causal && pair_tiles((long long)B * Hkv * p.n_splits, tiles, compute_units);
+    const int units = paired ? (tiles + 1) / 2 : tiles;
+    auto blocks_of = [&](int tile) {            // blocks of a head that a tile's pass streams
+        int first = causal ? tile * 128 - (Nk - Nq) : 0;
+        first = first > 0 ? first & ~31 : 0;
+        const int n = 2 * ((Nq - first + 63) / 64);
+        return !causal && n > dkdv_q_chunk(Nq, p.q_splits) ? dkdv_q_chunk(Nq, p.q_splits) : n;
+    };
+    int longest = blocks_of(0);
+    for (int u = 0; paired && u < units; u++) {
+        const int n = blocks_of(u) + (tiles - 1 - u >= units ? blocks_of(tiles - 1 - u) : 0);
+        if (n > longest) longest = n;
+    }
+    const double shared = D == 64 && (long long)B * Hkv * units * p.n_splits > compute_units ? 1.4 : 1.0;
+    const double sum_us = p.n_splits == 1 ? 0.0 : 3.0 + 16.0 * p.n_splits * B * Hkv * Nk * D / 5.0e6;
+    return longest * (double)(H / Hkv / heads) * (D == 64 ? 0.6 : 1.4) * shared + sum_us;
+}
+
+// heads_only: a call without memory for the partial sums of split blocks
+inline DkdvSplits dkdv_splits(int B, int H, int Hkv, int Nq, int Nk, int D, bool causal, int compute_units, bool heads_only) {
     const int tiles = (Nk + 127) / 128, group = H / Hkv;
     const long long units = (long long)B * Hkv * (causal ? (tiles + 1) / 2 : tiles);
     const long long resident = (long long)compute_units * (D == 64 ? 2 : 1);
@@ -98,25 +135,21 @@ inline DkdvSplits dkdv_splits(int B, int H, int Hkv, int Nq, int Nk, int D, bool
     int heads = group;
     while (heads > 1 && (group % heads || units * heads > resident)) heads--;
     int blocks = 1;
-    if (!causal && Nq != Nk) {
+    if (!causal && Nq != Nk && !heads_only) {
         const long long fit = compute_units / (units * heads), most = Nq / 512, ways = fit < most ? fit : most;
         blocks = ways < 1 ? 1 : (int)ways;
         const int pairs = (Nq + 63) / 64, chunk = dkdv_q_chunk(Nq, blocks) / 2;
         blocks = (pairs + chunk - 1) / chunk;           // no part is empty
     }
-    return {heads * blocks, blocks};
+    const DkdvSplits p = {heads * blocks, blocks}, unsplit = {1, 1};
+    if (p.n_splits > 1 && dkdv_us(B, H, Hkv, Nq, Nk, D, causal, compute_units, p) >= dkdv_us(B, H, Hkv, Nq, Nk, D, causal, compute_units, unsplit))
+        return unsplit;
+    return p;
 }
 // fp32 partial sums of dK and dV
 inline size_t dkdv_part_bytes(int B, int Hkv, int Nk, int D, int n_splits) {
     return (size_t)n_splits * 2 * B * Hkv * Nk * D * sizeof(float);
 }
-
-// Whether the tiles of a causal backward launch are paired, long with short, for equal work per workgroup: not where
-// each has a compute unit of its own without: the longest tile alone is then the shorter way, by one tile in `tiles`
-// and a start-up.  Whole backward, us, paired and not: B2 Hq16 Hkv4 N1001 D128 100, 84; B2 H12 N700 D64 47, 37; but with
-// 32 tiles B1 H8 N4096 D128 201, 224 (half the compute units hold a higher clock) and with two workgroups to a compute
-// unit, two long ones or two short ones, B1 H16 N4096 D64 173, 227.
-inline bool pair_tiles(long long heads, int tiles, int compute_units) { return heads * tiles > compute_units || tiles > 16; }
 
 // dK, dV (key-tile parallel).  ds != nullptr: also store the dS blocks there (ds_spill_bytes(B, H, Nq, Nk) bytes).
 // part != nullptr: n_splits > 1 ways (dkdv_splits(...)), partial sums in part (dkdv_part_bytes(...) bytes).
