@@ -118,7 +118,7 @@ template <int D> __device__ __forceinline__ int swz(int row) {
 // with the query blocks issued three blocks ahead into a four-stage ring.
 //
 // Nothing hides a workgroup's start-up and wind-down either, so the launch is persistent: the
-// resident workgroups (one per compute unit, two at D = 64) walk the key tiles v = blockIdx.x, blockIdx.x + gridDim.x, ... and
+// resident workgroups (one per compute unit, two at D = 64) walk the key tiles v = blockIdx.x, blockIdx.x + stride, ... and
 // the query-block stream never stops: the loads issued during the last blocks of one key tile
 // already fetch the first blocks of the next, and the next tile's K, V fragments are requested
 // before the current tile's results are stored.
@@ -137,12 +137,14 @@ template <int D> __device__ __forceinline__ int swz(int row) {
 // sums over its own in Part ([n_splits][2: dK, dV][B * hkv][Nk][D], unscaled) for attn_bwd_dkdv_sum_kernel.
 // For launches with fewer units than compute units: a unit's time is the length of its query stream, 1.2 us a
 // block of 32 queries, whether the other compute units are idle or not.
+//
+// stride: the number of workgroups.  (Asked of gridDim, it lay in a third cache line of the arguments, 0.3 us of every launch.)
 template <int D, bool CAUSAL, bool TAIL, bool SPILL, bool SPLIT>
 __global__ __launch_bounds__(256, D == 64 ? 2 : 1)
 void attn_bwd_dkdv_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K, const bf16* __restrict__ V,
                           const bf16* __restrict__ dO, const float* __restrict__ LSE, const float* __restrict__ Delta,
                           bf16* __restrict__ dK, bf16* __restrict__ dV,
-                          int Nq, int Nk, int num_kv_tiles, int total_units, float scale, int hq, int hkv,
+                          int Nq, int Nk, int num_kv_tiles, int total_units, float scale, int hq, int hkv, int stride,
                           char* __restrict__ DS, int n_qb, int units, int n_splits, int q_splits,
                           float* __restrict__ Part)
 {
@@ -203,7 +205,7 @@ void attn_bwd_dkdv_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K
             const int unit = xcd_remap(vu, total_units) % units;
             if (num_kv_tiles - 1 - unit >= units) { half = 1; return; }   // (not paired, or the middle one of an odd count: no partner)
         }
-        vu += gridDim.x;
+        vu += stride;
         half = 0;
     };
 
@@ -791,7 +793,7 @@ static hipError_t launch_dkdv_tt(const void* q, const void* k, const void* v, co
     const int grid = total_units < resident ? total_units : resident;
     hipLaunchKernelGGL((attn_bwd_dkdv_kernel<D, CAUSAL, TAIL, SPILL, SPLIT>), dim3(grid), dim3(S::kThreads), 0, stream,
                        (const bf16*)q, (const bf16*)k, (const bf16*)v, (const bf16*)d_o, lse, delta,
-                       (bf16*)dk, (bf16*)dv, Nq, Nk, num_kv_tiles, total_units, scale, H, Hkv,
+                       (bf16*)dk, (bf16*)dv, Nq, Nk, num_kv_tiles, total_units, scale, H, Hkv, grid,
                        (char*)ds, ds_query_blocks(Nq), units, n_splits, q_splits, part);
     if (SPLIT) {
         const size_t n4 = (size_t)B * Hkv * Nk * D / 4;
