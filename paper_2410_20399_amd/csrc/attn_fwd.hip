@@ -49,7 +49,9 @@ template <int D> __device__ __forceinline__ int swizzle_v(int row) {
 // SPLIT (implies TAIL): n_splits workgroups share one query tile, each takes tiles_per_split (even)
 // consecutive key tiles and leaves a normalised fp32 partial O and its LSE for the merge kernel below.  For
 // calls whose heads and query tiles alone cannot fill the chip: decoding, a chunk of a prompt against a long history.
-template <int D, bool CAUSAL, bool TAIL, bool SPLIT>
+//
+// SCALAR: how a tile's address is formed, see t_begin.
+template <int D, bool CAUSAL, bool TAIL, bool SPLIT, bool SCALAR>
 __global__ __launch_bounds__(256, 2)
 void attn_fwd_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K, const bf16* __restrict__ V,
                      bf16* __restrict__ O, float* __restrict__ LSE,
@@ -262,7 +264,9 @@ void attn_fwd_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K, con
     // With a known start the compiler keeps a 64-bit address per lane and load and advances each by a vector addition;
     // with an unknown one the tile's address stays scalar.  us: B16 H16 N4096 causal D64 673, 631, D128 1157, 1133;
     // B1 Hq32 Hkv8 N3001 D128 causal 90.5, 87.5; N1000 D64 without a mask 88.9, 87.5; aligned and without a mask as before.
-    if (!SPLIT && (CAUSAL || TAIL)) asm volatile("" : "+s"(t_begin));
+    // But with one workgroup on a compute unit an aligned causal tile at D = 128 is a chain that the scalar form makes
+    // longer: B4 H4 N512 13.7, 14.2; B1 H8 N2048 39.0, 40.4 (at D = 64 17.1, 15.6 for B2 Hq16 Hkv2 N1024).
+    if (SCALAR) asm volatile("" : "+s"(t_begin));
     if (SPLIT) {
         t_begin = split * tiles_per_split;
         if (t_begin + tiles_per_split < n_tiles) n_tiles = t_begin + tiles_per_split;
@@ -311,13 +315,13 @@ void attn_fwd_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K, con
     }
 }
 
-template <int D, bool CAUSAL, bool TAIL, bool SPLIT>
+template <int D, bool CAUSAL, bool TAIL, bool SPLIT, bool SCALAR = !SPLIT && (CAUSAL || TAIL)>
 static hipError_t launch_fwd_tt(const void* q, const void* k, const void* v, void* o, float* lse,
                                 int B, int H, int Hkv, int Nq, int Nk, float scale, hipStream_t stream,
                                 int n_splits = 1, int tiles_per_split = 0, float* o_part = nullptr, float* lse_part = nullptr)
 {
     using S = FwdShape<D>;
-    auto kern = attn_fwd_kernel<D, CAUSAL, TAIL, SPLIT>;
+    auto kern = attn_fwd_kernel<D, CAUSAL, TAIL, SPLIT, SCALAR>;
     const int num_q_tiles = (Nq + S::kTileQ - 1) / S::kTileQ;
     const int total = B * H * num_q_tiles * n_splits;
     hipLaunchKernelGGL(kern, dim3(total), dim3(S::kThreads), 0, stream,
@@ -331,8 +335,14 @@ static hipError_t launch_fwd_t(const void* q, const void* k, const void* v, void
                                int B, int H, int Hkv, int Nq, int Nk, float scale, hipStream_t stream)
 {
     using S = FwdShape<D>;
-    return (Nq != Nk || Nq % S::kTileQ) ? launch_fwd_tt<D, CAUSAL, true, false>(q, k, v, o, lse, B, H, Hkv, Nq, Nk, scale, stream)
-                                        : launch_fwd_tt<D, CAUSAL, false, false>(q, k, v, o, lse, B, H, Hkv, Nq, Nk, scale, stream);
+    auto launch = Nq != Nk || Nq % S::kTileQ ? launch_fwd_tt<D, CAUSAL, true, false> : launch_fwd_tt<D, CAUSAL, false, false>;
+    if constexpr (D == 128 && CAUSAL) {         // (see t_begin in the kernel)
+        int cus = 0;
+        hipError_t e = compute_unit_count(&cus);
+        if (e != hipSuccess) return e;
+        if (Nq == Nk && Nq % S::kTileQ == 0 && (long long)B * H * (Nq / S::kTileQ) <= cus) launch = launch_fwd_tt<D, CAUSAL, false, false, false>;
+    }
+    return launch(q, k, v, o, lse, B, H, Hkv, Nq, Nk, scale, stream, 1, 0, nullptr, nullptr);
 }
 
 hipError_t launch_attn_fwd(const void* q, const void* k, const void* v, void* o, float* lse,
