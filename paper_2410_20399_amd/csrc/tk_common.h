@@ -165,7 +165,8 @@ __device__ __forceinline__ void split_of(int wg, int total, int group, int tiles
 // forward left there.
 __device__ __forceinline__ void tile_of(int wg, int heads, int tiles, int group, int& head, int& tile) {
     const int per_group = group * tiles;
-    const int g = wg / per_group, r = wg - g * per_group;
+    const int g = group == heads ? 0 : wg / per_group;  // (a division is 0.1 us of a small launch)
+    const int r = wg - g * per_group;
     int in_group = heads - g * group;                   // the last group may be smaller
     if (in_group > group) in_group = group;
     const int rank = r / in_group, j = r - rank * in_group;

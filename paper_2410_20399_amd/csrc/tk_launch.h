@@ -25,20 +25,37 @@ inline hipError_t compute_unit_count(int* cus) {
 }
 
 // Heads that tile_of() walks together.  Without a mask all tiles weigh the same: one head per XCD, the best
-// reuse of its L2.  With the causal mask a tile's work grows with its index, and an XCD's 64 resident
-// workgroups (32 compute units x 2) are best given out longest first: d heads per XCD, as many as keep
-// d * tiles within one and a half times that, preferably a divisor of an XCD's share.  (One head after the
+// reuse of its L2.  With the causal mask a tile's work grows with its index, and the workgroups of an XCD (32 compute
+// units, two resident on each at D = 128) are best given out longest first: d heads per XCD, as many as keep
+// d * tiles within one and a half times the 64 that are resident, preferably a divisor of an XCD's share.  (One head after the
 // other gives a compute unit the same tile index of two heads, two long ones or two short ones:
 // B2 H16 N2048 D128 62 -> 50 us, B1 Hq32 Hkv8 N3001 111 -> 89 us; more heads than this and the L2 and the
-// balance at the end both get worse: the first of these 54 us with 6 heads, 56 us with 8.)
+// balance at the end both get worse: the first of these 54 us with 6 heads, 56 us with 8.)  At D = 64 four are resident;
+// the 96 was not fitted to that, and of 200 causal sizes with 8 to 1100 heads it makes none slower than one head per XCD.
+// Where there is none and the last group would be no more than half as large, its few heads leave the units of an XCD to
+// their short end: of six tiles and more the next divisor up to 4 * d is taken, of three or five groups of equal size.  us
+// (one head per XCD, a group that leaves a rest, this): B14 H4 N3584 D128 214, 224, 183; B4 H14 N1832 D128 78, 81, 64; B1
+// Hq104 Hkv13 N1179 D64 34, 38, 32; B10 Hq52 Hkv13 N373 D128 48, 54, 47; of 244 such sizes 16 had become slower than with one
+// head.  (Of two or four tiles, where long and short ones alternate on a unit either way, the rest does no harm: B5 Hq104
+// Hkv13 N256 D128 33, 29.5, in equal groups 32.)
 inline int tile_order_heads(int heads, int tiles, bool causal) {
     const int per_xcd = (heads + 7) / 8;
     int d = 1;
     if (causal) {
         d = 96 / tiles < per_xcd ? 96 / tiles : per_xcd;
         if (d < 1) d = 1;
-        for (int e = d; 2 * e > d; e--)
-            if (per_xcd % e == 0) { d = e; break; }
+        const int most = d;
+        bool found = false;
+        for (int e = most; 2 * e > most && !found; e--)
+            if (per_xcd % e == 0) { d = e; found = true; }
+        if (!found && heads % 8 == 0 && 2 * (per_xcd % most) <= most) {
+            if (tiles < 6 && tiles % 2) {
+                const int groups = (per_xcd + most - 1) / most;
+                d = (per_xcd + groups - 1) / groups;
+            }
+            for (int e = most + 1; tiles >= 6 && e <= 4 * most && !found; e++)
+                if (per_xcd % e == 0) { d = e; found = true; }
+        }
     }
     return 8 * d < heads ? 8 * d : heads;
 }
