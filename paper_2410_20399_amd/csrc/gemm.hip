@@ -277,20 +277,21 @@ static hipError_t launch_tile(const void* a, const void* b, void* c, int M, int 
     return hipGetLastError();
 }
 
-// The tile shapes, what their steps cost on MI355X, and the choice between them.  A call takes about
-//   3 us + (tiles on the busiest of the compute units) * (steps of a tile / KS) * us per step,
-// and the shape with the smallest sum is taken.  Measured (us per 64-wide k step of one tile; one tile on a unit /
-// several of them after or next to each other), and the time at 8192^3 that follows:
-//   256x256  8 waves   1.50 / 1.57    0.79 ms = 1.39 PFLOP/s (the best rate: least L2 and LDS traffic per flop)
+// The tile shapes, what their steps cost on MI355X, and the choice between them.  Beside a launch, the same for all, a call
+// takes about
+//   (tiles on the busiest of the compute units) * (steps of a tile / KS) * us per step,
+// and the shape with the smallest product is taken.  Measured (us per 64-wide k step of one tile; one tile on a unit /
+// several of them after or next to each other), and what that makes of 8192^3:
+//   256x256  8 waves   1.50 / 1.57    0.80 ms (measured 0.82 to 0.84 = 1.3 PFLOP/s; least L2 and LDS traffic per flop)
 //   192x256  8 waves   1.15 / 1.25    0.95 ms       64x128  4 waves  0.42 / 0.34   1.46 ms
 //   128x256  8 waves   0.88 / 0.93    0.95 ms       64x64   4 waves  0.25 / 0.24   2.05 ms (L2 bound: 16 KB per 0.5 MFLOP)
 //   256x128  8 waves   0.87 / 0.92    0.94 ms       64x64  K split in 2:  0.43 / 0.53 per two steps
-//   128x192  8 waves   0.76 / 0.735   1.04 ms       32x64  K split in 2:  0.42 / 0.42 per two steps
-//   128x128  8 waves   0.57 / 0.56    1.15 ms       32x64  K split in 4:  0.60 / 0.75 per four steps
+//   128x192  8 waves   0.76 / 0.735   1.04 ms       32x64  K split in 4:  0.60 / 0.75 per four steps
+//   128x128  8 waves   0.57 / 0.56    1.15 ms
 //   128x128  4 waves, two workgroups per compute unit: 0.68 alone, 0.95 for two   1.02 ms
-// (A single 256x256 tile with four waves of 128x128, one per SIMD, took 0.92 ms: nothing filled the gaps of a
-// wave.  With two waves per SIMD and 16x16x32 MFMAs, which move half the accumulator bits per flop of the 32x32x16
-// form, the same LDS ring gives 0.79.)
+// (A single 256x256 tile with four waves of 128x128, one per SIMD, took 0.96 ms: nothing filled the gaps of a
+// wave.  Two waves per SIMD and 16x16x32 MFMAs, which move half the accumulator bits per flop of the 32x32x16 form, do.
+// 32x64 with K split in 2 would be chosen for 65 to 128 k only, where it gains nothing: 3.7 us either way, the launch.)
 // The last three have 64-bit lane offsets and are only considered where a shape of the same rows needs them (128x256 with
 // four waves: few enough threads for the widest N): M1 N34200008 K72 1.76 ms, M250 N34500008 K64 7.0, M300 N35000000 K128
 // 15.1, M32 N8 K69400008 456.
@@ -311,7 +312,6 @@ static const GemmChoice kGemmChoices[] = {
     {launch_tile<64, 128, 2, 2, 1, 3, 2>, 256, 64, 128, 1, 0.42f, 0.34f, false},
     {launch_tile<64, 64, 2, 2, 1, 3, 2>, 256, 64, 64, 1, 0.25f, 0.24f, false},
     {launch_tile<64, 64, 2, 2, 2, 3, 2>, 512, 64, 64, 2, 0.43f, 0.53f, false},
-    {launch_tile<32, 64, 2, 2, 2, 4, 2>, 512, 32, 64, 2, 0.42f, 0.42f, false},
     {launch_tile<32, 64, 1, 4, 4, 3, 4>, 1024, 32, 64, 4, 0.60f, 0.75f, false},
     {launch_tile<256, 256, 2, 4, 1, 2, 2, true>, 512, 256, 256, 1, 1.50f, 1.57f, true},
     {launch_tile<128, 256, 2, 2, 1, 3, 1, true>, 256, 128, 256, 1, 1.01f, 1.02f, true},
