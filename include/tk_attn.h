@@ -176,7 +176,10 @@ int tk_attn_bwd_dq(const void* q, const void* k, const void* v, const void* d_o,
  *
  *   q, o, d_o, dq : bf16 [B, Hq, N, D]        k, v, dk, dv : bf16 [B, Hkv, N, D]
  *   lse, delta    : fp32 [B, Hq, N]
- *   dk, dv are summed over the query heads of each group (in fp32 and in a fixed order: no atomics).
+ *   dk, dv are summed over the query heads of each group (in fp32 and in a fixed order: no atomics).  The order may
+ *   depend on the sizes of the whole call and on the number of compute units (few key tiles: the heads of a group are
+ *   split over idle units), so with Hkv < Hq the last bits of a head's dk, dv may change with B and Hkv.  With Hkv == Hq
+ *   and equal lengths every head has the bits of the same head run alone.
  *   workspace for tk_attn_bwd_gqa: tk_attn_bwd_workspace_bytes(B, Hq, N, D) bytes.
  * TK_ERR_BAD_DIM also covers Hkv < 1, Hkv > Hq and Hq % Hkv != 0.
  */
@@ -258,7 +261,9 @@ int tk_attn_fwd_rect(const void* q, const void* k, const void* v,
  * tk_attn_fwd_rect for callers that can hand over device scratch.  With fewer queries than keys and too few
  * (head, 128-query tile) pairs to fill the chip - a chunk of a prompt against a long history - the keys are
  * split over more workgroups, which leave fp32 partial (O, LSE) pairs in the scratch, and merged.  Results equal
- * tk_attn_fwd_rect's up to fp32 rounding order of the merge, and are bit-reproducible.
+ * tk_attn_fwd_rect's up to fp32 rounding order of the merge, and are bit-reproducible; whether and how the keys are split
+ * depends on all sizes of the call and on the number of compute units, so the last bits of a head may change with B and Hq
+ * (those of tk_attn_fwd_rect do not).
  *
  *   scratch : device memory of tk_attn_fwd_scratch_bytes(...) bytes, 16-byte aligned; contents on entry are
  *             ignored.  NULL or less than that many bytes: the call is tk_attn_fwd_rect.
@@ -283,8 +288,8 @@ int tk_attn_bwd_rect(const void* q, const void* k, const void* v,
  * fill the chip the queries of a key tile are split over several workgroups - the query heads of a group, and without
  * a mask and with Nq != Nk the queries of a head - which leave fp32 partial sums of dK and dV in the scratch, added up
  * in a fixed order.  (A workspace of tk_attn_bwd_spill_workspace_bytes holds the room for a split of the heads itself.)
- * Results equal tk_attn_bwd_rect's
- * up to fp32 summation order and are bit-reproducible.
+ * Results equal tk_attn_bwd_rect's up to fp32 summation order and are bit-reproducible; as above, the order depends on all
+ * sizes of the call and on the number of compute units.
  *
  *   scratch : device memory of tk_attn_bwd_scratch_bytes(...) bytes, 16-byte aligned; contents on entry are
  *             ignored.  NULL or less than that many bytes: the call is tk_attn_bwd_rect.
@@ -343,7 +348,8 @@ int tk_attn_decode_plan(int B, int Hq, int Hkv, int Nk, int D, int compute_units
  * (TK_ERR_BAD_DIM otherwise).  The tile shape (256 x 256 down to 32 x 64, the small ones also with K split
  * inside the workgroup) is chosen by M, N and K; rows and columns past the end are not stored, the part of
  * the last K step past K contributes zeros.
- * No workspace; the result is bit-reproducible (every element is one fixed-order accumulation).
+ * No workspace; the result is bit-reproducible (every element is one fixed-order accumulation).  The order belongs to the
+ * tile shape, so the last bits of a row may change with the other sizes (M, N, the number of compute units).
  */
 int tk_gemm(const void* a, const void* b, void* c, int M, int N, int K, void* stream);
 
