@@ -28,11 +28,11 @@ MFMA_BF16_PEAK_TFLOPS = 2500.0   # MI355X dense bf16 (published: 2.5 PFLOP/s)
 # reads in the same run; the files under profiles/ give the commands and the raw counters).  The
 # live run cannot collect counters itself, so other workloads report null.
 MEASURED_TRAFFIC = {
-    "fwdbwd_causal_b16_h16_n4096_d128": {"kernel": "attn_bwd_dkdv_kernel", "bytes": 1.802e9 + 4.966e9,      # (the form that stores dS)
+    "fwdbwd_causal_b16_h16_n4096_d128": {"kernel": "attn_bwd_dkdv_kernel", "bytes": 1.713e9 + 4.966e9,      # (the form that stores dS)
                                          "source": "profiles/bench_fwdbwd_causal_b16_h16_n4096_d128.txt"},
     "fwdbwd_causal_b16_h16_n4096_d64/recompute": {"kernel": "attn_bwd_dkdv_kernel", "bytes": 0.583e9 + 0.268e9,
                                                   "source": "profiles/bench_fwdbwd_causal_b16_h16_n4096_d64.txt"},
-    "gemm_8192x8192x8192": {"kernel": "gemm_kernel", "bytes": 1.61e9 + 0.148e9, "source": "profiles/gemm_8192x8192x8192.txt"},
+    "gemm_8192x8192x8192": {"kernel": "gemm_kernel", "bytes": 1.611e9 + 0.135e9, "source": "profiles/gemm_8192x8192x8192.txt"},
     "decode_b16_hq32_hkv8_nk8192_d128": {"kernel": "attn_fwd_kernel", "bytes": 537.2e6 + 0.54e6, "source": "profiles/decode_b16_hq32_hkv8_nk8192_d128.txt"},
     "rotary_fwdbwd_causal_b16_h16_n4096_d128": {"kernel": "rotary_kernel", "bytes": 0.270e9 + 0.268e9, "source": "profiles/rotary_b16_h16_n4096_d128.txt"},
 }
