@@ -124,7 +124,7 @@ void gemm_kernel(const bf16* __restrict__ A, const bf16* __restrict__ B, bf16* _
     auto issue_stage = [&](int step, int stage_off) {
         char* base = ring + stage_off + wave * 1024;
         const int k0 = step * S::kTileK;
-        if (__builtin_expect(K - k0 >= S::kTileK, 1)) {
+        if (__builtin_expect(k0 <= K - S::kTileK, 1)) {
             const bf16* a = a_tile + k0;
             const bf16* b = b_tile + (size_t)k0 * N;
 #pragma unroll
