@@ -62,3 +62,14 @@ def test_split_backward(B, Hq, Hkv, Nq, Nk, D, causal, spill):
     assert attn.tk_attn_bwd_rect(qd, kd, vd, o, dod, lse, dq, dk, dv, B, Hq, Hkv, Nq, Nk, D, causal, scale, ws, n_ws - room) == attn.TK_OK
     for name, got, ref in zip(("dq", "dk", "dv"), (dq, dk, dv), refs):
         check_grad(got.double().cpu().numpy(), ref, name)
+
+
+def test_calls_that_are_not_split():
+    # where the partial sums cost more than the shorter streams save: few blocks, and pairs as long as the single tiles were
+    for shape in ((5, 32, 16, 268, 268, 64, False), (3, 32, 8, 309, 1060, 128, True), (8, 32, 16, 369, 369, 64, True), (1, 8, 8, 1000, 1000, 64, True),
+                  (1, 8, 2, 255, 255, 128, True), (16, 32, 8, 4096, 4096, 128, True)):
+        n = attn.tk_attn_bwd_workspace_bytes(shape[0], shape[1], shape[3], shape[5])
+        assert attn.tk_attn_bwd_scratch_bytes(*shape, n) == 0, shape
+    for shape in ((2, 16, 4, 1001, 1001, 128, True), (1, 32, 8, 2048, 2048, 64, True), (1, 4, 4, 4096, 64, 64, False)):
+        n = attn.tk_attn_bwd_workspace_bytes(shape[0], shape[1], shape[3], shape[5])
+        assert attn.tk_attn_bwd_scratch_bytes(*shape, n) > 0, shape
