@@ -144,8 +144,8 @@ def test_own_workspace_belongs_to_the_stream_of_the_call(D):
     for call in (lambda: attn.attn_bwd(q, k, v, o, d_o, lse, True, scale, stream=side),
                  lambda: attn.gqa_bwd(q, k, v, o, d_o, lse, True, scale, stream=side),
                  lambda: attn.rect_bwd(q, k, v, o, d_o, lse, True, scale, stream=side)):
-        for _ in range(20):
-            attn.gemm(a, a, out=c, stream=side)         # (about 16 ms, which the backward waits behind)
+        for _ in range(60):
+            attn.gemm(a, a, out=c, stream=side)         # (about 50 ms, which the backward waits behind)
         got = call()
         junk = [torch.full((n,), 0x5A, dtype=torch.uint8, device="cuda") for _ in range(4)]
         torch.cuda.current_stream().synchronize()
