@@ -18,6 +18,9 @@ FLAGS = [
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-Wall", "-Wno-unused-command-line-argument", "-Wno-inline-asm",
 ]
+# Kernels with more than 256 registers: the results of matrix instructions go to whichever half of the register file holds
+# them longest.  (By default all of them go to the accumulator half, and what the vector ALU reads is copied out of it.)
+SOURCE_FLAGS = {"attn_fwd.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]}
 
 
 def _newer(sources, target) -> bool:
@@ -37,7 +40,7 @@ def _build_library(extra_flags) -> None:
 
     def compile_one(source):
         obj = os.path.join(out, source + ".o")
-        subprocess.run(["hipcc", *FLAGS, *extra_flags, "-c", os.path.join(CSRC, source), "-o", obj], check=True)
+        subprocess.run(["hipcc", *FLAGS, *SOURCE_FLAGS.get(source, []), *extra_flags, "-c", os.path.join(CSRC, source), "-o", obj], check=True)
         return obj
 
     with ThreadPoolExecutor(max_workers=len(SOURCES)) as pool:

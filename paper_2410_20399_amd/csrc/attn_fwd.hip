@@ -14,6 +14,8 @@
 #include "tk_common.h"
 #include "tk_launch.h"
 
+#include <math.h>
+
 namespace tk {
 
 template <int D>
@@ -49,9 +51,7 @@ template <int D> __device__ __forceinline__ int swizzle_v(int row) {
 // SPLIT (implies TAIL): n_splits workgroups share one query tile, each takes tiles_per_split (even)
 // consecutive key tiles and leaves a normalised fp32 partial O and its LSE for the merge kernel below.  For
 // calls whose heads and query tiles alone cannot fill the chip: decoding, a chunk of a prompt against a long history.
-//
-// SCALAR: how a tile's address is formed, see t_begin.
-template <int D, bool CAUSAL, bool TAIL, bool SPLIT, bool SCALAR>
+template <int D, bool CAUSAL, bool TAIL, bool SPLIT>
 __global__ __launch_bounds__(256, 2)
 void attn_fwd_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K, const bf16* __restrict__ V,
                      bf16* __restrict__ O, float* __restrict__ LSE,
@@ -262,11 +262,8 @@ void attn_fwd_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K, con
 
     int t_begin = 0;
     // With a known start the compiler keeps a 64-bit address per lane and load and advances each by a vector addition;
-    // with an unknown one the tile's address stays scalar.  us: B16 H16 N4096 causal D64 673, 631, D128 1157, 1133;
-    // B1 Hq32 Hkv8 N3001 D128 causal 90.5, 87.5; N1000 D64 without a mask 88.9, 87.5; aligned and without a mask as before.
-    // But with one workgroup on a compute unit an aligned causal tile at D = 128 is a chain that the scalar form makes
-    // longer: B4 H4 N512 13.7, 14.2; B1 H8 N2048 39.0, 40.4 (at D = 64 17.1, 15.6 for B2 Hq16 Hkv2 N1024).
-    if (SCALAR) asm volatile("" : "+s"(t_begin));
+    // with an unknown one the tile's address stays scalar.
+    if (!SPLIT && (CAUSAL || TAIL)) asm volatile("" : "+s"(t_begin));
     if (SPLIT) {
         t_begin = split * tiles_per_split;
         if (t_begin + tiles_per_split < n_tiles) n_tiles = t_begin + tiles_per_split;
@@ -315,13 +312,470 @@ void attn_fwd_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K, con
     }
 }
 
-template <int D, bool CAUSAL, bool TAIL, bool SPLIT, bool SCALAR = !SPLIT && (CAUSAL || TAIL)>
+// ------------------------------------------------------------------------------------------
+// the forward kernel of launches that are bound by the chip's arithmetic
+// ------------------------------------------------------------------------------------------
+// A wave owns 32 query rows and goes through two phases per 64-key tile: matrix instructions (O += V P of tile t, then
+// S = K Q of tile t+1) and vector instructions (the exponentials of tile t+1).  A wave issues in order, so it uses one of
+// the two pipes at a time, and waves that are free to run drift into step with each other: both of a SIMD want the matrix
+// pipe, then both the vector ALU (3450 cycles for a tile of both at D = 128, where the matrix instructions take 2048).
+//
+// GROUPS = 2: eight waves, 256 query rows, two waves on each SIMD, kept one phase apart by a barrier per phase: the four
+// waves of one group have the matrix pipe while the other group has the vector ALU.  K and V are fetched once for 256
+// rows instead of 128 (fetching them is power that the matrix pipe does not get).
+// GROUPS = 1: four waves, 128 query rows, for launches that would leave compute units idle with 256-row tiles.  There is
+// no second wave to fill the gaps, so the wave interleaves S = K Q of the next tile with the exponentials of this one.
+// Both do the same arithmetic in the same order: a row's bits do not depend on the choice.
+//
+// The running maximum is not looked for in every tile.  The exponents are taken against the maximum of the first tile, and
+// a tile whose sum of exponentials (32 keys of a row in a lane) exceeds kMaxSum - or is not a number, or infinite - is done
+// again against its own maximum, after which O and l are scaled as usual.  Exponentials up to kMaxSum cost no precision (P
+// goes to bf16 and O and l are fp32 whatever their factor, which the final division takes out); 16 v_max3 of four cycles,
+// a sixth of the vector phase, are gone from every other tile.
+//
+// Tiles go to an LDS ring by direct loads: four stages, issued three tiles ahead, with two groups (one workgroup on a compute
+// unit); two stages with one (two or three workgroups to a unit, which cover each other's waits: four stages and one
+// workgroup were slower at every size).
+//
+// Forward, us, before (four waves, 128 rows, phases in program order) and now: B16 H16 N4096 causal D128 1140, 1013, without a
+// mask 2014, 1796, causal D64 621, 594; B16 H16 N1024 D64 79.3, 77.5; B1 H16 N8192 causal D128 302, 244; with one group
+// B1 H16 N2048 D64 27.1, 23.0, B2 Hq16 Hkv4 N1001 causal D128 24.3, 21.6.  One group or two at D = 128: see two_groups_pay().
+template <int D, int GROUPS>
+struct FwdPhaseShape {
+    static constexpr int kWaves = 4 * GROUPS, kThreads = 64 * kWaves;
+    static constexpr int kTileQ = 32 * kWaves, kTileKV = 64;
+    static constexpr int kRowBytes = D * 2, kChunksPerRow = D / 8;
+    static constexpr int kTileBytes = kTileKV * kRowBytes;
+    static constexpr int kStageBytes = 2 * kTileBytes;                  // K tile then V tile
+    static constexpr int kStages = GROUPS == 2 ? 4 : 2;
+    static constexpr int kLoads = kTileKV * kChunksPerRow / kThreads;   // per thread and tensor
+    static constexpr int kTileLoads = 2 * kLoads;
+    // waves per SIMD to compile for.  One group: two (D = 128) or three (D = 64) workgroups share a compute unit
+    static constexpr int kWavesPerSimd = D == 128 ? 2 : 3;
+};
+
+template <int D, bool CAUSAL, bool TAIL, bool SPLIT, int GROUPS>
+__global__ __launch_bounds__((FwdPhaseShape<D, GROUPS>::kThreads), (FwdPhaseShape<D, GROUPS>::kWavesPerSimd))
+void attn_fwd_phase_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K, const bf16* __restrict__ V,
+                           bf16* __restrict__ O, float* __restrict__ LSE,
+                           int Nq, int Nk, int num_q_tiles, int heads, int head_group, float scale, int hq, int hkv,
+                           int n_splits, int tiles_per_split, float* __restrict__ O_part, float* __restrict__ LSE_part)
+{
+    using S = FwdPhaseShape<D, GROUPS>;
+    __shared__ __attribute__((aligned(1024))) char smem[S::kStages * S::kStageBytes];
+
+    const int tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lane = tid & 63;
+    const int l32 = lane & 31;
+    const int h = lane >> 5;
+
+    int bh, qt, split = 0;
+    if (SPLIT) split_of(blockIdx.x, gridDim.x, hq / hkv, num_q_tiles, n_splits, bh, split, qt);
+    else if (CAUSAL) tile_of(blockIdx.x, heads, num_q_tiles, head_group, bh, qt);
+    else {
+        const int id = xcd_remap(blockIdx.x, gridDim.x);
+        bh = id / num_q_tiles;
+        qt = id - bh * num_q_tiles;
+    }
+    const size_t head = (size_t)bh * Nq * D;
+    const size_t kv_head = (size_t)((bh / hq) * hkv + (bh % hq) / (hq / hkv)) * Nk * D;
+    const bf16* Kh = K + kv_head;
+    const bf16* Vh = V + kv_head;
+    // the row blocks of the two groups alternate, so that under the causal mask both have about the same number of tiles
+    const int group = GROUPS == 2 ? wave >> 2 : 0;
+    const int q0 = qt * S::kTileQ + (GROUPS == 2 ? 2 * (wave & 3) + group : wave) * 32;
+    const int my_q = q0 + l32;
+    const int my_q_ld = (!TAIL || my_q < Nq) ? my_q : Nq - 1;
+    const int off = TAIL ? Nk - Nq : 0;          // causal: query i sees keys <= i + off
+    const float c = scale * kLog2e;
+
+    // key tiles of the workgroup, and of this wave
+    int t_begin = 0, n_tiles, n_my;
+    {
+        int n_keys = Nk;
+        if (CAUSAL && qt * S::kTileQ + S::kTileQ + off < n_keys) n_keys = qt * S::kTileQ + S::kTileQ + off;
+        n_tiles = (n_keys + S::kTileKV - 1) / S::kTileKV;
+        if (SPLIT) {
+            t_begin = split * tiles_per_split;
+            if (t_begin + tiles_per_split < n_tiles) n_tiles = t_begin + tiles_per_split;
+        }
+        n_my = n_tiles;
+        if (CAUSAL) { const int d = (q0 + 31 + off) / S::kTileKV + 1; if (d < n_my) n_my = d; }
+        if (TAIL && q0 >= Nq) n_my = t_begin;    // a wave of padding rows only
+    }
+
+    // ---- tile loads: LDS position s = it * threads + tid holds (row = s / chunks per row, physical chunk = s % chunks per row)
+    int k_src[S::kLoads], v_src[S::kLoads];
+#pragma unroll
+    for (int it = 0; it < S::kLoads; it++) {
+        const int s = it * S::kThreads + tid, row = s / S::kChunksPerRow, pc = s % S::kChunksPerRow;
+        k_src[it] = row * D + ((pc ^ swizzle_k<D>(row)) * 8);
+        v_src[it] = row * D + ((pc ^ swizzle_v<D>(row)) * 8);
+    }
+    // every call issues the same number of loads in every wave (the waits count them); beyond the last tile it fetches that
+    // one again, into a stage nobody reads any more
+    auto issue = [&](const bf16* src, const int (&lane_src)[S::kLoads], int in_stage, int tile) __attribute__((always_inline)) {
+        char* base = smem + (tile & (S::kStages - 1)) * S::kStageBytes + in_stage + wave * 1024;
+        if (tile > n_tiles - 1) tile = n_tiles - 1;
+        const int j0 = tile * S::kTileKV;
+        const bf16* first = src + (size_t)j0 * D;
+        if (!TAIL || j0 + S::kTileKV <= Nk) {
+#pragma unroll
+            for (int it = 0; it < S::kLoads; it++) load_global_to_lds16_sbase_untracked(first, lane_src[it] * 2, base + it * (S::kThreads * 16));
+        } else {                                 // rows past the last key fetch that one instead (they are masked later)
+#pragma unroll
+            for (int it = 0; it < S::kLoads; it++) {
+                const int beyond = (it * S::kThreads + tid) / S::kChunksPerRow - (Nk - 1 - j0);     // (the tile's first key is a real one)
+                load_global_to_lds16_sbase_untracked(first, (lane_src[it] - (beyond > 0 ? beyond : 0) * D) * 2, base + it * (S::kThreads * 16));
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto issue_k = [&](int tile) __attribute__((always_inline)) { issue(Kh, k_src, 0, tile); };
+    auto issue_v = [&](int tile) __attribute__((always_inline)) { issue(Vh, v_src, S::kTileBytes, tile); };
+    auto issue_tile = [&](int tile) __attribute__((always_inline)) { issue_k(tile); issue_v(tile); };
+
+    // ---- Q fragments (B operand of S^T = K Q^T): lane holds Q[my_q][16*kb + 8*h .. +7].  The compiler waits for them, and
+    // with them for everything issued before, which is what the first product needs: the first tile of K.
+    const bool any = !SPLIT || t_begin < n_tiles;    // (causal: a split may lie wholly beyond the tile's last key)
+    if (any) {
+        issue_k(t_begin);
+        if (GROUPS == 1) { issue_v(t_begin); issue_k(t_begin + 1); }
+    }
+    bf16x8 qf[D / 16];
+#pragma unroll
+    for (int kb = 0; kb < D / 16; kb++) qf[kb] = *(const bf16x8*)(Q + head + (size_t)my_q_ld * D + kb * 16 + h * 8);
+#pragma unroll
+    for (int kb = 0; kb < D / 16; kb++) asm volatile("" : "+v"(qf[kb]));
+    if (any) {
+        wait_vmcnt<0>();
+        if (GROUPS == 2) { issue_v(t_begin); issue_tile(t_begin + 1); issue_tile(t_begin + 2); }
+    }
+
+    // ---- per-lane LDS read offsets
+    // K: row 32*b + l32, logical chunk 2*kb + h.  V (transposing read): 16-lane group G = lane/16 -> (d half = G%2, key half =
+    // G/2); lane j of the group addresses row 4*(G/2) + j/4, columns 32*db + 16*(G%2) + 4*(j%4)
+    const int k_lane = l32 * S::kRowBytes + ((h ^ swizzle_k<D>(l32)) << 4);
+    const int j16 = lane & 15;
+    const int v_row = 4 * h + (j16 >> 2);
+    const int v_chunk = 2 * ((lane >> 4) & 1) + ((j16 & 3) >> 1);
+    const int v_lane = v_row * S::kRowBytes + ((v_chunk ^ swizzle_v<D>(v_row)) << 4) + ((j16 & 1) << 3);
+
+    f32x16 o_acc[D / 32];
+#pragma unroll
+    for (int db = 0; db < D / 32; db++)
+#pragma unroll
+        for (int r = 0; r < 16; r++) o_acc[db][r] = 0.f;
+    float m_run = -INFINITY;   // what the exponents are taken against (raw score, shared by both half-waves), and its multiple in
+    float mc = -INFINITY;      // base 2; -inf: exponentials against it are infinite or not a number, and the tile is done again
+    float l_run = 0.f;         // running sum, partial: this lane's 32 of the 64 keys per tile
+    bf16x8 pb[4];              // P of the tile in hand, 16 keys each
+
+    constexpr int kKSteps = D / 8, kVSteps = D / 8;      // matrix instructions of S = K Q and of O += V P
+    constexpr int kAhead = 2 * GROUPS;                   // fragments read ahead of their use (one group: more would not fit the registers)
+    bf16x8 kfr[kKSteps], vfr[kVSteps];
+    auto stage_of = [&](int tile) { return smem + (tile & (S::kStages - 1)) * S::kStageBytes; };
+    auto read_k = [&](const char* ks, int i) __attribute__((always_inline)) {        // step i: 16 columns i / 2, 32 keys i % 2
+        kfr[i] = lds_read_b128(ks, (k_lane ^ ((2 * (i >> 1)) << 4)) + (i & 1) * 32 * S::kRowBytes);
+    };
+    auto read_v = [&](const char* vs, int i) __attribute__((always_inline)) {        // step i: 16 keys i / (D/32), 32 columns i % (D/32)
+        const int row_off = 16 * (i / (D / 32)) * S::kRowBytes, db = i % (D / 32);
+        // rows 16*kk + 4*h + (0..3) and +8; the +8 flips bit 1 of swizzle_v's low field
+        vfr[i] = concat(lds_read_tr16(vs, (v_lane ^ ((4 * db) << 4)) + row_off),
+                        lds_read_tr16(vs, (v_lane ^ (((4 * db) ^ 2) << 4)) + row_off + 8 * S::kRowBytes));
+    };
+    // (the empty asm statements hold a matrix instruction in its place among the reads: the compiler keeps them in order)
+    auto multiply_k = [&](f32x16 (&s)[2], int i) __attribute__((always_inline)) {
+        const int kb = i >> 1, b = i & 1;
+        if (kb == 0) {
+            f32x16 zero;
+#pragma unroll
+            for (int r = 0; r < 16; r++) zero[r] = 0.f;
+            s[b] = mfma32(kfr[i], qf[0], zero);
+        } else {
+            s[b] = mfma32(kfr[i], qf[kb], s[b]);
+        }
+        asm volatile("" : : "v"(s[b][0]));
+    };
+    auto multiply_v = [&](int i) __attribute__((always_inline)) {
+        const int kk = i / (D / 32), db = i % (D / 32);
+        o_acc[db] = mfma32(vfr[i], pb[kk], o_acc[db]);
+        asm volatile("" : : "v"(o_acc[db][0]));
+    };
+
+    // register r of block b of the scores <-> key j0 + 32*b + 8*(r/4) + 4*h + r%4, lane <-> query my_q
+    auto mask = [&](f32x16 (&s)[2], int tile) __attribute__((always_inline)) {
+        const int j0 = tile * S::kTileKV;
+        if ((CAUSAL && j0 + S::kTileKV - 1 > q0 + off) || (TAIL && j0 + S::kTileKV > Nk)) {
+#pragma unroll
+            for (int b = 0; b < 2; b++)
+#pragma unroll
+                for (int r = 0; r < 16; r++) {
+                    const int key = j0 + 32 * b + 8 * (r >> 2) + 4 * h + (r & 3);
+                    if ((CAUSAL && key > my_q + off) || (TAIL && key >= Nk)) s[b][r] = -INFINITY;
+                }
+        }
+    };
+    // A split may hold no key that a row sees - beyond its diagonal, or with scores of -inf that the caller masks keys
+    // with: its maximum stays -inf, and its exponents are then taken against 0, so that P = 2^-inf = 0.  (Without a split
+    // every row sees key 0 under the causal mask, and a row that begins with a tile of -inf is NaN.)
+    auto finite_mc = [&]() { return SPLIT && m_run == -INFINITY ? 0.f : m_run * c; };
+    auto raise = [&](const f32x16 (&s)[2]) __attribute__((always_inline)) {
+        float mx = s[0][0];
+#pragma unroll
+        for (int r = 1; r < 16; r++) mx = __builtin_fmaxf(mx, s[0][r]);
+#pragma unroll
+        for (int r = 0; r < 16; r++) mx = __builtin_fmaxf(mx, s[1][r]);
+        const float m_old = m_run;
+        m_run = __builtin_fmaxf(m_run, half_max(mx));
+        mc = m_run * c;
+        const float corr = __builtin_amdgcn_exp2f(SPLIT && m_run == -INFINITY ? m_old : (m_old - m_run) * c);
+        l_run *= corr;
+#pragma unroll
+        for (int db = 0; db < D / 32; db++)
+#pragma unroll
+            for (int r = 0; r < 16; r++) o_acc[db][r] *= corr;
+    };
+    constexpr float kMaxSum = 65536.f;
+    // P = 2^(S*c - against): element e of 32 is register e % 16 of block e / 16.  The sum is formed in the order of the elements
+    auto exponential = [&](const f32x16 (&s)[2], int e, float against) __attribute__((always_inline)) {
+        return __builtin_amdgcn_exp2f(__builtin_fmaf(s[e >> 4][e & 15], c, -against));
+    };
+    auto exponentials = [&](const f32x16 (&s)[2], float against) __attribute__((always_inline)) {
+        float sum = 0.f;
+#pragma unroll
+        for (int kk = 0; kk < 4; kk++) {
+            float p[8];
+#pragma unroll
+            for (int r = 0; r < 8; r++) {
+                p[r] = exponential(s, 8 * kk + r, against);
+                sum += p[r];
+            }
+            pb[kk] = cvt8(p[0], p[1], p[2], p[3], p[4], p[5], p[6], p[7]);
+        }
+#pragma unroll
+        for (int kk = 0; kk < 4; kk++) asm volatile("" : "+v"(pb[kk]));
+        return sum;
+    };
+    auto too_large = [&](float sum) { return __builtin_expect(__builtin_amdgcn_ballot_w64(!(sum <= kMaxSum)) != 0, 0); };
+    auto phase_end = [&]() __attribute__((always_inline)) {
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+        asm volatile("" : : : "memory");
+    };
+    auto scores = [&](f32x16 (&s)[2], int tile) __attribute__((always_inline)) {     // S = K Q alone
+        const char* ks = stage_of(tile);
+#pragma unroll
+        for (int i = 0; i < kAhead; i++) read_k(ks, i);
+#pragma unroll
+        for (int i = 0; i < kKSteps; i++) {
+            multiply_k(s, i);
+            if (i + kAhead < kKSteps) read_k(ks, i + kAhead);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    auto read_v_ahead = [&](int tile) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < kAhead; i++) read_v(stage_of(tile) + S::kTileBytes, i);
+    };
+    auto products = [&](int tile) __attribute__((always_inline)) {                   // O += V P alone, behind read_v_ahead()
+        const char* vs = stage_of(tile) + S::kTileBytes;
+#pragma unroll
+        for (int i = 0; i < kVSteps; i++) {
+            multiply_v(i);
+            if (i + kAhead < kVSteps) read_v(vs, i + kAhead);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+
+    int t = t_begin;
+    if (any) {
+    phase_end();                                 // K of the first tile is here
+    if constexpr (GROUPS == 2) {
+        f32x16 s[2];
+        // The barriers a wave passes, two per tile and two ahead of the first, are the same in both groups; the second
+        // group's phases come one barrier later.  A stage is refilled by loads issued in the matrix phase of tile t (with
+        // tile t+3, into the stage of tile t-1, whose V the other group read at the latest one barrier ago), and every wave
+        // waits for its loads of tile t+2 at the end of that phase: both groups read tile t+2 at least one barrier later.
+        if (group == 1) phase_end();
+        if (n_my > t) scores(s, t);
+        wait_vmcnt<S::kTileLoads>();             // tiles t and t+1
+        phase_end();
+        if (n_my > t) {
+            mask(s, t);
+            raise(s);
+            l_run = exponentials(s, finite_mc());
+            read_v_ahead(t);
+        }
+        phase_end();
+#pragma unroll 1
+        for (; t < n_my - 1; t++) {
+            issue_tile(t + 3);
+            __builtin_amdgcn_s_setprio(1);       // the matrix pipe first: the other group has more instructions ready
+            const char* vs = stage_of(t) + S::kTileBytes;
+            const char* ks = stage_of(t + 1);
+#pragma unroll
+            for (int i = 0; i < kVSteps + kKSteps; i++) {
+                if (i < kVSteps) multiply_v(i); else multiply_k(s, i - kVSteps);
+                if (i + kAhead < kVSteps) read_v(vs, i + kAhead);
+                else if (i + kAhead - kVSteps < kKSteps) read_k(ks, i + kAhead - kVSteps);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            __builtin_amdgcn_s_setprio(0);
+            wait_vmcnt<S::kTileLoads>();
+            phase_end();
+            asm volatile("" : "+v"(s[0])); asm volatile("" : "+v"(s[1]));     // (the vector phase stays behind the barrier)
+            mask(s, t + 1);
+            float sum = exponentials(s, mc);
+            if (too_large(sum)) {
+                raise(s);
+                sum = exponentials(s, finite_mc());
+            }
+            l_run += sum;
+            read_v_ahead(t + 1);
+            phase_end();
+        }
+        if (t < n_my) {
+            issue_tile(t + 3);
+            products(t);
+            wait_vmcnt<S::kTileLoads>();
+            phase_end();
+            phase_end();
+            t++;
+        }
+#pragma unroll 1
+        for (; t < n_tiles; t++) {               // the others of the workgroup have more tiles
+            issue_tile(t + 3);
+            wait_vmcnt<S::kTileLoads>();
+            phase_end();
+            phase_end();
+        }
+        if (group == 0) phase_end();
+    } else {
+        f32x16 sa[2], sb[2];                     // scores of even and odd tiles (counted from the first)
+        // One tile: S of the next one, each matrix instruction with its share of this one's exponentials behind it, then O.
+        auto tile_step = [&](f32x16 (&s)[2], f32x16 (&next)[2], bool has_next, int t) __attribute__((always_inline)) {
+            issue_k(t + S::kStages);             // into the stages of K of tile t and V of tile t-1, which every wave has left
+            issue_v(t + S::kStages - 1);
+            float sum = 0.f;
+            if (has_next) {
+                const char* ks = stage_of(t + 1);
+                constexpr int kPer = 32 / kKSteps;               // exponentials per matrix instruction
+                float p[32];
+#pragma unroll
+                for (int i = 0; i < kAhead; i++) read_k(ks, i);
+#pragma unroll
+                for (int e = 0; e < kPer; e++) { p[e] = exponential(s, e, mc); asm volatile("" : : "v"(p[e])); }
+#pragma unroll
+                for (int i = 0; i < kKSteps; i++) {
+                    multiply_k(next, i);
+                    if (i + kAhead < kKSteps) read_k(ks, i + kAhead); else read_v(stage_of(t) + S::kTileBytes, i + kAhead - kKSteps);
+#pragma unroll
+                    for (int e = kPer * (i + 1); e < kPer * (i + 2) && e < 32; e++) { p[e] = exponential(s, e, mc); asm volatile("" : : "v"(p[e])); }
+#pragma unroll
+                    for (int e = kPer * i; e < kPer * (i + 1); e++) { sum += p[e]; asm volatile("" : : "v"(sum)); }
+                    if ((kPer * (i + 1)) % 8 == 0) {
+                        const int kk = kPer * (i + 1) / 8 - 1;
+                        pb[kk] = cvt8(p[8 * kk], p[8 * kk + 1], p[8 * kk + 2], p[8 * kk + 3], p[8 * kk + 4], p[8 * kk + 5], p[8 * kk + 6], p[8 * kk + 7]);
+                        asm volatile("" : : "v"(pb[kk]));
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            } else {
+                read_v_ahead(t);
+                sum = exponentials(s, mc);
+            }
+            if (too_large(sum)) {
+                raise(s);
+                sum = exponentials(s, finite_mc());
+            }
+            l_run += sum;
+            products(t);
+            if (has_next) mask(next, t + 1);
+            wait_vmcnt<(S::kStages - 2) * S::kTileLoads>();      // K of tile t+2 and V of t+1 are here
+            phase_end();
+        };
+        if (n_my > t) {
+            scores(sa, t);
+            mask(sa, t);
+            raise(sa);
+            if (SPLIT && m_run == -INFINITY) mc = 0.f;       // (the exponentials of this tile are 0 then)
+        }
+        phase_end();                             // (K of the first tile is about to be overwritten)
+#pragma unroll 1
+        for (; t + 2 < n_my; t += 2) {
+            tile_step(sa, sb, true, t);
+            tile_step(sb, sa, true, t + 1);
+        }
+        if (t + 1 < n_my) {
+            tile_step(sa, sb, true, t);
+            tile_step(sb, sa, false, t + 1);
+            t += 2;
+        } else if (t < n_my) {
+            tile_step(sa, sb, false, t);
+            t++;
+        }
+#pragma unroll 1
+        for (; t < n_tiles; t++) {
+            issue_k(t + S::kStages);
+            issue_v(t + S::kStages - 1);
+            wait_vmcnt<(S::kStages - 2) * S::kTileLoads>();
+            phase_end();
+        }
+    }
+    wait_vmcnt<0>();                             // the spare loads of the last tiles must not outlive the workgroup's LDS
+    }
+
+    // ---- epilogue: O = O / l, LSE = m*scale + ln l
+    const float l_tot = half_sum(l_run);
+    const float inv = SPLIT && l_tot == 0.f ? 0.f : 1.0f / l_tot;     // (no visible key in this split: O = 0, LSE = -inf)
+    if (SPLIT) {
+        if (my_q < Nq) {
+            const size_t prow = ((size_t)split * heads + bh) * Nq + my_q;   // [split][head][query]
+            float* Op = O_part + prow * D;
+#pragma unroll
+            for (int db = 0; db < D / 32; db++)
+#pragma unroll
+                for (int g = 0; g < 4; g++)
+                    *(f32x4*)(Op + 32 * db + 8 * g + 4 * h) = f32x4{o_acc[db][4 * g + 0] * inv, o_acc[db][4 * g + 1] * inv, o_acc[db][4 * g + 2] * inv, o_acc[db][4 * g + 3] * inv};
+            if (h == 0) LSE_part[prow] = m_run * scale + __builtin_logf(l_tot);
+        }
+    } else if (!TAIL || my_q < Nq) {
+        bf16* Oh = O + head + (size_t)my_q * D;
+#pragma unroll
+        for (int db = 0; db < D / 32; db++)
+#pragma unroll
+            for (int g = 0; g < 4; g++) {
+                bf16x2 a = cvt2(o_acc[db][4 * g + 0] * inv, o_acc[db][4 * g + 1] * inv);
+                bf16x2 b = cvt2(o_acc[db][4 * g + 2] * inv, o_acc[db][4 * g + 3] * inv);
+                *(bf16x4*)(Oh + 32 * db + 8 * g + 4 * h) = __builtin_shufflevector(a, b, 0, 1, 2, 3);
+            }
+        if (h == 0) LSE[(size_t)bh * Nq + my_q] = m_run * scale + __builtin_logf(l_tot);
+    }
+}
+
+template <int D, bool CAUSAL, bool TAIL, bool SPLIT, int GROUPS>
+static hipError_t launch_phase(const void* q, const void* k, const void* v, void* o, float* lse,
+                               int B, int H, int Hkv, int Nq, int Nk, float scale, hipStream_t stream,
+                               int n_splits = 1, int tiles_per_split = 0, float* o_part = nullptr, float* lse_part = nullptr)
+{
+    using S = FwdPhaseShape<D, GROUPS>;
+    const int num_q_tiles = (Nq + S::kTileQ - 1) / S::kTileQ;
+    hipLaunchKernelGGL((attn_fwd_phase_kernel<D, CAUSAL, TAIL, SPLIT, GROUPS>), dim3(B * H * num_q_tiles * n_splits), dim3(S::kThreads), 0, stream,
+                       (const bf16*)q, (const bf16*)k, (const bf16*)v, (bf16*)o, lse, Nq, Nk, num_q_tiles, B * H,
+                       tile_order_heads(B * H, num_q_tiles, CAUSAL), scale, H, Hkv, n_splits, tiles_per_split, o_part, lse_part);
+    return hipGetLastError();
+}
+
+template <int D, bool CAUSAL, bool TAIL, bool SPLIT>
 static hipError_t launch_fwd_tt(const void* q, const void* k, const void* v, void* o, float* lse,
                                 int B, int H, int Hkv, int Nq, int Nk, float scale, hipStream_t stream,
                                 int n_splits = 1, int tiles_per_split = 0, float* o_part = nullptr, float* lse_part = nullptr)
 {
     using S = FwdShape<D>;
-    auto kern = attn_fwd_kernel<D, CAUSAL, TAIL, SPLIT, SCALAR>;
+    auto kern = attn_fwd_kernel<D, CAUSAL, TAIL, SPLIT>;
     const int num_q_tiles = (Nq + S::kTileQ - 1) / S::kTileQ;
     const int total = B * H * num_q_tiles * n_splits;
     hipLaunchKernelGGL(kern, dim3(total), dim3(S::kThreads), 0, stream,
@@ -330,19 +784,40 @@ static hipError_t launch_fwd_tt(const void* q, const void* k, const void* v, voi
     return hipGetLastError();
 }
 
+// Whether two groups (256-row tiles) take less time than one (128-row tiles, two workgroups on a compute unit), D = 128.  us of
+// a workgroup that has its place: two groups U2 a 64-key tile and O2 around them, one group U1 and O1; a launch takes as many of
+// these one behind the other as the fullest compute unit has.
+static bool two_groups_pay(int B, int H, int Nq, int Nk, bool causal, int cus)
+{
+    const long long heads = (long long)B * H, tiles1 = heads * ((Nq + 127) / 128), tiles2 = heads * ((Nq + 255) / 256);
+    if (tiles1 <= cus) return false;
+    const double n = (Nk + 63) / 64, units1 = (double)tiles1 / (2 * cus), units2 = (double)tiles2 / cus;
+    if (!causal) return ceil(units2) * (1.7 * n + 8) < ceil(2 * units1) / 2 * (1.84 * n + 6);
+    // half the keys on average and half a tile more; the longest tiles, which come first, show in part at the end
+    return units2 * (1.5 * (n / 2 + 2) + 5) + 0.3 * (1.5 * n + 5) < units1 * (1.84 * (n / 2 + 1) + 2) + 0.3 * 0.55 * (1.84 * n + 2);
+}
+
 template <int D, bool CAUSAL>
 static hipError_t launch_fwd_t(const void* q, const void* k, const void* v, void* o, float* lse,
                                int B, int H, int Hkv, int Nq, int Nk, float scale, hipStream_t stream)
 {
-    using S = FwdShape<D>;
-    auto launch = Nq != Nk || Nq % S::kTileQ ? launch_fwd_tt<D, CAUSAL, true, false> : launch_fwd_tt<D, CAUSAL, false, false>;
-    if constexpr (D == 128 && CAUSAL) {         // (see t_begin in the kernel)
+    // Few query rows a head (decoding) are bound by reading K and V, whatever the waves do: B64 H8 Nq4 Nk4000 D128 177 us either way, and
+    // decoding takes this path with its groups as rows.  And at D = 64 a
+    // sequence of one or two tiles has nothing to overlap, and four workgroups to a compute unit instead of three are
+    // better: B16 H32 N128 7.5 us instead of 7.8, B32 H32 N100 13.1, 14.1.  Neither condition looks at the number of heads: the two kernels
+    // look for the maximum in different tiles, and a head's bits shall not depend on what else is in the call.
+    if constexpr (!CAUSAL)
+        if (Nq <= 64 && Nq != Nk) return launch_fwd_tt<D, false, true, false>(q, k, v, o, lse, B, H, Hkv, Nq, Nk, scale, stream);
+    if constexpr (D == 64)
+        if (Nk <= 128) return (Nq != Nk || Nq % 128 ? launch_fwd_tt<64, CAUSAL, true, false> : launch_fwd_tt<64, CAUSAL, false, false>)(q, k, v, o, lse, B, H, Hkv, Nq, Nk, scale, stream, 1, 0, nullptr, nullptr);
+    if constexpr (D == 128) {
         int cus = 0;
         hipError_t e = compute_unit_count(&cus);
         if (e != hipSuccess) return e;
-        if (Nq == Nk && Nq % S::kTileQ == 0 && (long long)B * H * (Nq / S::kTileQ) <= cus) launch = launch_fwd_tt<D, CAUSAL, false, false, false>;
+        if (two_groups_pay(B, H, Nq, Nk, CAUSAL, cus))
+            return (Nq != Nk || Nq % 256 ? launch_phase<128, CAUSAL, true, false, 2> : launch_phase<128, CAUSAL, false, false, 2>)(q, k, v, o, lse, B, H, Hkv, Nq, Nk, scale, stream, 1, 0, nullptr, nullptr);
     }
-    return launch(q, k, v, o, lse, B, H, Hkv, Nq, Nk, scale, stream, 1, 0, nullptr, nullptr);
+    return (Nq != Nk || Nq % 128 ? launch_phase<D, CAUSAL, true, false, 1> : launch_phase<D, CAUSAL, false, false, 1>)(q, k, v, o, lse, B, H, Hkv, Nq, Nk, scale, stream, 1, 0, nullptr, nullptr);
 }
 
 hipError_t launch_attn_fwd(const void* q, const void* k, const void* v, void* o, float* lse,
@@ -627,9 +1102,18 @@ hipError_t launch_attn_fwd_splitk(const void* q, const void* k, const void* v, v
                                   int B, int H, int Hkv, int Nq, int Nk, int D, int causal, float scale,
                                   int n_splits, int tiles_per_split, hipStream_t stream)
 {
-    auto launch = D == 128 ? (causal ? launch_fwd_tt<128, true, true, true> : launch_fwd_tt<128, false, true, true>)
-                           : (causal ? launch_fwd_tt<64, true, true, true> : launch_fwd_tt<64, false, true, true>);
-    hipError_t e = launch(q, k, v, o, lse, B, H, Hkv, Nq, Nk, scale, stream, n_splits, tiles_per_split, o_part, lse_part);
+    int cus = 0;
+    hipError_t e = compute_unit_count(&cus);
+    if (e != hipSuccess) return e;
+    // Two groups where the 128-row tiles come in pairs and would be two to a compute unit: B1 Hq32 Hkv8 Nq512 Nk8192 D128 78, 75 us
+    // with two groups, Nq387 Nk6822 61, 56 (but an odd number of tiles, B4 Hq4 Hkv1 Nq319 Nk7441, 40, 57).
+    const int tiles = (Nq + 127) / 128;
+    const bool two = tiles % 2 == 0 && (long long)B * H * tiles * n_splits > cus;
+    auto launch = !causal && Nq <= 64 ? (D == 128 ? launch_fwd_tt<128, false, true, true> : launch_fwd_tt<64, false, true, true>)     // (see launch_fwd_t)
+                : D == 64 ? (causal ? launch_phase<64, true, true, true, 1> : launch_phase<64, false, true, true, 1>)
+                : two     ? (causal ? launch_phase<128, true, true, true, 2> : launch_phase<128, false, true, true, 2>)
+                          : (causal ? launch_phase<128, true, true, true, 1> : launch_phase<128, false, true, true, 1>);
+    e = launch(q, k, v, o, lse, B, H, Hkv, Nq, Nk, scale, stream, n_splits, tiles_per_split, o_part, lse_part);
     if (e != hipSuccess) return e;
     combine(o_part, lse_part, o, lse, (size_t)B * H * Nq, D, n_splits, stream);
     return hipGetLastError();

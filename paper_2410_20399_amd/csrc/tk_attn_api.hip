@@ -163,29 +163,24 @@ tk::DkdvSplits dkdv_splits_scratch(int B, int Hq, int Hkv, int Nq, int Nk, int D
 }
 
 // Few queries against a longer history: the heads and 128-query tiles alone leave compute units idle.  The split
-// aims at the two workgroups per compute unit that are resident at once at D = 128.  Whole call, us (unsplit, then
-// 1, 2, 3, 4 per compute unit): B1 Hq32 Hkv8 Nq512 Nk8192 D128 163, 98, 84, 89, 92; Hq64 of the same 186, 164, 146,
-// 154, 155; B1 Hq8 Hkv2 Nq700 Nk9000 D64 120, 37, 34, 38, 38.  A split holds at least 8 64-key tiles: with 16
-// B2 Hq8 Hkv2 Nq100 Nk2100 takes 28 instead of 21 us (18 with 4), but with 4 B1 H16 Nq512 Nk2048 D64 23 instead of 18.5.
-constexpr int kFwdSplitWgPerCu = 2;
+// aims at one or two workgroups per compute unit, whichever the estimate below prefers.  A split holds at least 8 64-key
+// tiles (the forward kernel and its figures in an earlier form: with 16 B2 Hq8 Hkv2 Nq100 Nk2100 D128 took 28 instead of 21
+// us, but with 4 B1 H16 Nq512 Nk2048 D64 23 instead of 18.5).
 constexpr int kFwdSplitMinTiles = 8;
 
-// Whether it pays: with many rows and few tiles the merge costs more than the idle compute units give, and heads that
-// share no keys are bound by reading them.  A 64-key tile takes a workgroup alone on its compute unit 0.82 us at D = 64 and
-// 1.28 at D = 128; two of them on one unit take 1.55 times as long each, with up to 64 rows (half the waves idle) 1.1
-// times; K and V come in at 6 TB/s at most; the merge takes 2 us and its bytes, written and read, at 5.5 TB/s.  Of 1206
-// sizes with 1 to 2000 queries and 1024 to 16000 keys it leaves out those that lost, us (unsplit, split): B4 Hq16 Hkv2 Nq322
-// Nk1529 D128 33, 41; B1 Hq128 Hkv32 Nq160 Nk1399 D64 22, 26; B1 H232 Nq11 Nk1496 D128 30, 32; one is left (B1 Hq16 Hkv2
-// Nq1286 Nk2559 D128 50, 52), and none that would gain a tenth is left out.
-bool fwd_split_pays(int B, int Hq, int Hkv, int Nq, int Nk, int D, int n_splits, int per, int compute_units)
+// us of a forward call whose tiles are split that way.  A 64-key tile takes a workgroup alone on its compute unit 0.6 us at
+// D = 64 and 0.92 at D = 128; two of them on one unit take 1.7 and 2 times as long each, with up to 64 rows (half the waves
+// idle) 1.1 times; K and V come in at 6 TB/s at most; the merge takes 2 us and its bytes, written and read, at 5.5 TB/s.
+// Whole call, us (unsplit, one per unit, two): B1 Hq32 Hkv8 Nq512 Nk8192 D128 122, 87, 78; Nq192 Nk3398 D64 37, 20, 24;
+// Nq881 Nk2544 D128 43, -, 52; B1 Hq64 Hkv16 Nq36 Nk13614 D64 130, 45, 36; B2 Hq16 Hkv2 Nq900 Nk3000 D64 34, -, 40.
+double fwd_split_us(int B, int Hq, int Hkv, int Nq, int Nk, int D, int n_splits, int per, int compute_units)
 {
     const long long workgroups = (long long)B * Hq * ((Nq + kTileN - 1) / kTileN) * n_splits;
-    const double tile_us = D == 64 ? 0.82 : 1.28;
-    const double shared = workgroups <= compute_units ? 1.0 : Nq > 64 ? 1.55 : 1.1;
+    const double tile_us = D == 64 ? 0.6 : 0.92;
+    const double shared = workgroups <= compute_units ? 1.0 : Nq <= 64 ? 1.1 : D == 64 ? 1.7 : 2.0;
     const double kv_us = 4.0 * B * Hkv * Nk * D / 6.0e6;
-    const double merge_us = 2.0 + 8.0 * n_splits * B * Hq * Nq * D / 5.5e6;
-    const double split_us = per * tile_us * shared > kv_us ? per * tile_us * shared : kv_us;
-    return split_us + merge_us < (Nk + 63) / 64 * tile_us;
+    const double merge_us = n_splits == 1 ? 0.0 : 2.0 + 8.0 * n_splits * B * Hq * Nq * D / 5.5e6;
+    return (per * tile_us * shared > kv_us ? per * tile_us * shared : kv_us) + merge_us;
 }
 
 struct FwdPlan {
@@ -197,14 +192,20 @@ FwdPlan plan_fwd(int B, int Hq, int Hkv, int Nq, int Nk, int D, int compute_unit
 {
     const long long base = (long long)B * Hq * ((Nq + kTileN - 1) / kTileN);
     const int tiles = (Nk + 63) / 64;
-    long long want = Nq < Nk ? (long long)kFwdSplitWgPerCu * compute_units / base : 1;
-    if (want > tiles / kFwdSplitMinTiles) want = tiles / kFwdSplitMinTiles;
-    if (want < 1) want = 1;
-    int per = (int)((tiles + want - 1) / want);
-    per += per & 1;                                   // the kernel walks the tiles in pairs
-    const int n_splits = (tiles + per - 1) / per;     // no split is empty
-    if (n_splits > 1 && !fwd_split_pays(B, Hq, Hkv, Nq, Nk, D, n_splits, per, compute_units)) return {1, tiles + (tiles & 1)};
-    return {n_splits, per};
+    FwdPlan best = {1, tiles + (tiles & 1)};
+    if (Nq >= Nk || base > 2LL * compute_units) return best;
+    double best_us = fwd_split_us(B, Hq, Hkv, Nq, Nk, D, 1, tiles, compute_units);
+    for (int per_unit = 1; per_unit <= 2; per_unit++) {
+        long long want = (long long)per_unit * compute_units / base;
+        if (want > tiles / kFwdSplitMinTiles) want = tiles / kFwdSplitMinTiles;
+        if (want < 2) continue;
+        int per = (int)((tiles + want - 1) / want);
+        per += per & 1;                                   // (the kernel of few rows walks the tiles in pairs)
+        const int n_splits = (tiles + per - 1) / per;     // no split is empty
+        const double us = fwd_split_us(B, Hq, Hkv, Nq, Nk, D, n_splits, per, compute_units);
+        if (n_splits > 1 && us < best_us) { best = {n_splits, per}; best_us = us; }
+    }
+    return best;
 }
 
 // fp32 partial O and partial LSE of a split forward, each padded to 256 bytes
