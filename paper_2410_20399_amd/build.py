@@ -20,7 +20,7 @@ FLAGS = [
 ]
 # Kernels with more than 256 registers: the results of matrix instructions go to whichever half of the register file holds
 # them longest.  (By default all of them go to the accumulator half, and what the vector ALU reads is copied out of it.)
-SOURCE_FLAGS = {"attn_fwd.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]}
+SOURCE_FLAGS = {name: ["-mllvm", "-amdgpu-mfma-vgpr-form=1"] for name in ("attn_fwd.hip", "attn_bwd.hip")}
 
 
 def _newer(sources, target) -> bool:

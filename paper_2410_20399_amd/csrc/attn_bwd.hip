@@ -89,7 +89,7 @@ struct DkdvShape {
     static constexpr int kRowBytes = D * 2;
     static constexpr int kChunksPerRow = D / 8;
     static constexpr int kQTileBytes = kTileQ * kRowBytes;
-    static constexpr int kStageBytes = 2 * kQTileBytes + 256;      // Q, dO, LSE[32], Delta[32]; a multiple of 256
+    static constexpr int kStageBytes = 2 * kQTileBytes + kWaves * 256;     // Q, dO, and for each wave LSE[32], Delta[32]; a multiple of 256
     static constexpr int kQLoads = kTileQ * kChunksPerRow / kThreads;   // per thread, per tensor
     static constexpr int kLoadsPerBlock = 2 * kQLoads;  // per thread, of Q and dO rows (one more load fetches the statistics)
     static constexpr int kEpiPitch = kRowBytes + 8;     // row pitch of the epilogue staging tile: the odd multiple of 8 bytes spreads
@@ -111,11 +111,14 @@ template <int D> __device__ __forceinline__ int swz(int row) {
 // each other's gaps (the vector work per MFMA is twice that of D = 128 there), and the phases of a
 // block run one after the other, every MFMA operand read one phase ahead of its use:
 //     phase 1  S, dP MFMAs from row fragments already in registers; meanwhile the transposed
-//              fragments (dO^T, Q^T) and the statistics of THIS block are read from LDS
+//              fragments (dO^T, Q^T) of THIS block are read from LDS
 //     phase 2  P, dS on the vector ALU
-//     phase 3  dV^T, dK^T MFMAs from the transposed fragments; meanwhile the row fragments of the
-//              NEXT block are read from LDS
+//     phase 3  dV^T, dK^T MFMAs from the transposed fragments; meanwhile the row fragments and the
+//              statistics of the NEXT block are read from LDS
 // with the query blocks issued three blocks ahead into a four-stage ring.
+// (The statistics as starting values of the accumulators, S and dP in two sets of vector registers instead of one that is copied
+// out of accumulator registers, and no wait for the wave's LDS reads before a step's barrier, us before and after, B16 H16 N4096
+// causal: D128 2170, 2030, storing dS 2520, 2385, D64 1135, 1070.)
 //
 // Nothing hides a workgroup's start-up and wind-down either, so the launch is persistent: the
 // resident workgroups (one per compute unit, two at D = 64) walk the key tiles v = blockIdx.x, blockIdx.x + stride, ... and
@@ -135,7 +138,7 @@ template <int D> __device__ __forceinline__ int swz(int row) {
 // SPLIT (implies TAIL): the queries are dealt to n_splits workgroups - the query heads of a group to
 // n_splits / q_splits and, without a mask, the blocks of a head to q_splits - each of which leaves fp32
 // sums over its own in Part ([n_splits][2: dK, dV][B * hkv][Nk][D], unscaled) for attn_bwd_dkdv_sum_kernel.
-// For launches with fewer units than compute units: a unit's time is the length of its query stream, 1.2 us a
+// For launches with fewer units than compute units: a unit's time is the length of its query stream, 1 us a
 // block of 32 queries, whether the other compute units are idle or not.
 //
 // stride: the number of workgroups.  (Asked of gridDim, it lay in a third cache line of the arguments, 0.3 us of every launch.)
@@ -224,6 +227,7 @@ void attn_bwd_dkdv_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K
     // The lengths need not be multiples of the tile sizes: the kernel works on padded sequences.
     // Reads of rows past the end are redirected to the last row; a query row >= Nq gets LSE = +inf,
     // so its P and dS are exactly 0; key rows >= Nk are computed like any other and not stored.
+    const float* const stat_src = (lane < 32 ? LSE : Delta) + l32;
     int p_vu = blockIdx.x, p_half = 0, p_nblocks = 0, p_g = 0, p_ibegin = 0;
     size_t p_head_row = 0;                  // first row of the group's first query head of the producer's pass
     size_t p_row = 0;                       // first row of the next block to fetch (rows of all heads counted through)
@@ -290,19 +294,13 @@ void attn_bwd_dkdv_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K
             } else {
                 load_global_to_lds16_sbase_untracked(block, (uint32_t)q_src[it] * 2, dst);
             }
-        } else if (TAIL) {
-            // The statistics: every wave fetches them, to the same place (the same bytes four times over cost
-            // nothing; a branch on the wave number costs every wave a restart of its instruction stream, and
-            // the waits would have to count differently per wave).
-            // lanes 0..31 fetch LSE of the block's 32 queries, lanes 32..63 their Delta
-            const int r = e_i0 + l32;
-            const float* src = (lane < 32) ? (r < Nq ? LSE + e_head_row + r : g_lse_pad)
-                                           : Delta + e_head_row + (r < Nq ? r : Nq - 1);
-            load_global_to_lds4_untracked(src, base + 2 * S::kQTileBytes);
         } else {
-            // 8 lanes fetch LSE[row..row+31], 8 lanes Delta[row..row+31], 16 bytes each; the other lanes are masked off
-            const float* src = (lane < 8) ? (LSE + e_row + lane * 4) : (Delta + e_row + (lane - 8) * 4);
-            load_global_to_lds16_lanes16_untracked(src, base + 2 * S::kQTileBytes);
+            // The statistics: every wave fetches a copy of its own (a branch on the wave number costs every wave a
+            // restart of its instruction stream, and the waits would have to count differently per wave):
+            // lanes 0..31 LSE of the block's 32 queries, lanes 32..63 their Delta
+            const float* src = stat_src + e_row;
+            if (TAIL && e_i0 + l32 >= Nq) src = lane < 32 ? g_lse_pad : Delta + e_head_row + (Nq - 1);
+            load_global_to_lds4_untracked(src, base + 2 * S::kQTileBytes + wave * 256);
         }
     };
     auto issue_next = [&]() {
@@ -311,6 +309,13 @@ void attn_bwd_dkdv_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K
         for (int which = 0; which <= S::kLoadsPerBlock; which++) emit(which);
         prepare_turn();
     };
+
+    // A wave turns its copy of a block's statistics, once they are here, into -LSE / scale and -Delta.  The accumulators of S
+    // and dP start from these, so that scale * S - LSE takes the vector ALU one multiplication and dP - Delta nothing.
+    // (Three instructions a block instead of two more for each of a lane's 16 scores.)
+    const float stat_mul = lane < 32 ? -1.0f / scale : -1.0f;
+    auto wave_stat = [&](int stage) { return (float*)(ring + stage + 2 * S::kQTileBytes + wave * 256); };
+    auto scale_stat = [&](int stage) { float* st = wave_stat(stage) + lane; *st = *st * stat_mul; };
 
     // ---- per-lane LDS offsets
     // row operand (A of S and dP): row l32, logical chunk 2*kb + h
@@ -334,6 +339,7 @@ void attn_bwd_dkdv_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K
     int c_vu = blockIdx.x, c_half = 0;      // consumer side: the pass being computed (the grid never exceeds the unit count)
     int c_stage = 0;                        // byte offset of the ring stage of the next block to consume ...
     int c_stage1 = S::kStageBytes, c_stage2 = 2 * S::kStageBytes;      // ... and of the two blocks after it (D = 128)
+    bool first_pass = true;
     {
         int bh, kt, split;
         pass_tile(c_vu, c_half, bh, kt, split);
@@ -378,6 +384,11 @@ void attn_bwd_dkdv_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K
     wait_vmcnt<0>();
     __builtin_amdgcn_s_barrier();           // the pass's first blocks landed and visible
     __builtin_amdgcn_sched_barrier(0);
+    if (first_pass) {                       // (later passes: done by the steps before them)
+        scale_stat(c_stage);
+        if (S::kPipe) scale_stat(c_stage1);
+        first_pass = false;
+    }
 
     // register r of a score block <-> query i0 + 8*(r/4) + 4h + r%4, lane <-> key my_j
     const bool pad_key = TAIL && SPILL && my_j >= Nk;    // a padding key was computed from the last real row: its dS must not reach dQ
@@ -392,19 +403,21 @@ void attn_bwd_dkdv_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K
     // that fit in its shadow, and the work of three consecutive blocks is in flight at once:
     //     step n, first half    S, dP of block n+1 (16 MFMAs)  next to  P, dS of block n (vector ALU) and
     //                           the transposing LDS reads of block n's Q^T, dO^T fragments
-    //     step n, second half   dV^T, dK^T of block n (16 MFMAs)  next to  the LDS reads of the statistics
-    //                           of block n+1 and of the row fragments of block n+2, the dS stores and the prefetch
-    // S and dP exist twice: the matrix pipe writes one copy (accumulator registers) in the first half, the
-    // second half moves it, two registers per MFMA, to the copy the vector ALU reads in the next step.  The empty asm statements keep each group in program order: the compiler keeps them in
+    //     step n, second half   dV^T, dK^T of block n (16 MFMAs)  next to  the LDS reads of the row fragments
+    //                           and the statistics of block n+2, the dS stores and the prefetch
+    // S and dP exist twice, for blocks with an even and an odd number: a step writes one set and reads the other.  The empty asm statements keep each group in program order: the compiler keeps them in
     // order with each other and with the scheduling barriers, and each one names a value that the
     // instructions of its group produce or consume.
     // ------------------------------------------------------------------------------------------
     bf16x8 rq[kSteps], rdo[kSteps];         // row fragments: operands of the next S, dP
     bf16x8 tq[kSteps], tdo[kSteps];         // transposed fragments [ks * (D/32) + db]: operands of the next dV^T, dK^T
     bf16x8 pb[2], dsb[2];                   // bf16 P, dS of the block in hand
-    f32x4 lse4[4], dl4[4];                  // statistics of the block whose P, dS come next
-    f32x16 s_acc, dp_acc;                   // S, dP as the matrix pipe leaves them
-    float sc[16], dc[16];                   // ... and where the vector ALU reads them one step later
+    f32x16 s_even, dp_even, s_odd, dp_odd;  // S - LSE / scale, dP - Delta of blocks with an even and an odd number
+    auto read_stat = [&](f32x16& acc, const float* stat, int g) {          // four of the values that an accumulator starts from
+        const f32x4 x = ((const f32x4*)stat)[2 * g + h];
+#pragma unroll
+        for (int t = 0; t < 4; t++) acc[4 * g + t] = x[t];
+    };
 
     auto read_rows = [&](const char* qs, int kb) {
         rq[kb] = lds_read_b128(qs, row_lane ^ ((2 * kb) << 4));
@@ -429,32 +442,16 @@ void attn_bwd_dkdv_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K
     auto scores = [&](f32x16& s_out, f32x16& dp_out, auto between) {
 #pragma unroll
         for (int kb = 0; kb < kSteps; kb++) {
-            if (kb == 0) {
-                f32x16 zero;
-#pragma unroll
-                for (int r = 0; r < 16; r++) zero[r] = 0.f;
-                asm volatile("" : "+v"(rq[0]));
-                s_out = mfma32(rq[0], kf[0], zero);
-                asm volatile("" : "+a"(s_out));
-                between(kb, 0);
-                __builtin_amdgcn_sched_barrier(0);
-                asm volatile("" : "+v"(rdo[0]));
-                dp_out = mfma32(rdo[0], vf[0], zero);
-                asm volatile("" : "+a"(dp_out));
-                between(kb, 1);
-                __builtin_amdgcn_sched_barrier(0);
-            } else {
-                asm volatile("" : "+a"(s_out));
-                s_out = mfma32(rq[kb], kf[kb], s_out);
-                asm volatile("" : "+a"(s_out));
-                between(kb, 0);
-                __builtin_amdgcn_sched_barrier(0);
-                asm volatile("" : "+a"(dp_out));
-                dp_out = mfma32(rdo[kb], vf[kb], dp_out);
-                asm volatile("" : "+a"(dp_out));
-                between(kb, 1);
-                __builtin_amdgcn_sched_barrier(0);
-            }
+            asm volatile("" : "+v"(s_out));
+            s_out = mfma32(rq[kb], kf[kb], s_out);
+            asm volatile("" : "+v"(s_out));
+            between(kb, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            asm volatile("" : "+v"(dp_out));
+            dp_out = mfma32(rdo[kb], vf[kb], dp_out);
+            asm volatile("" : "+v"(dp_out));
+            between(kb, 1);
+            __builtin_amdgcn_sched_barrier(0);
         }
     };
 
@@ -464,29 +461,28 @@ void attn_bwd_dkdv_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K
     {
         const char* q0s = ring + c_stage;
         const char* q1s = ring + c_stage1;
-        const f32x4* stat0 = (const f32x4*)(q0s + 2 * S::kQTileBytes);
 #pragma unroll
         for (int kb = 0; kb < kSteps; kb++) read_rows(q0s, kb);
+#pragma unroll
+        for (int g = 0; g < 4; g++) { read_stat(s_even, wave_stat(c_stage), g); read_stat(dp_even, wave_stat(c_stage) + 32, g); }
         __builtin_amdgcn_sched_barrier(0);
-        scores(s_acc, dp_acc, [&](int kb, int which) {
+        scores(s_even, dp_even, [&](int kb, int which) {
             if (kb < 4) {
-                if (which == 0) lse4[kb] = stat0[2 * kb + h];
-                else dl4[kb] = stat0[8 + 2 * kb + h];
+                if (which == 0) read_stat(s_odd, wave_stat(c_stage1), kb);
+                else read_stat(dp_odd, wave_stat(c_stage1) + 32, kb);
             }
         });
 #pragma unroll
         for (int kb = 0; kb < kSteps; kb++) read_rows(q1s, kb);
-#pragma unroll
-        for (int r = 0; r < 16; r++) { sc[r] = s_acc[r]; dc[r] = dp_acc[r]; }
         __builtin_amdgcn_sched_barrier(0);
     }
 
-    auto step = [&](auto masked, int blk, char* ds_head) {
+    // sc, dc: S - LSE / scale, dP - Delta of this block; s_next, dp_next: of the next one
+    auto step = [&](auto masked, int blk, char* ds_head, f32x16& sc, f32x16& dc, f32x16& s_next, f32x16& dp_next) __attribute__((always_inline)) {
         const int i0 = i_begin + blk * S::kTileQ;
         const char* q0s = ring + c_stage;           // block n
-        const char* q1s = ring + c_stage1;          // block n+1
         const char* q2s = ring + c_stage2;          // block n+2
-        const f32x4* stat1 = (const f32x4*)(q1s + 2 * S::kQTileBytes);
+        const int stage2 = c_stage2;
         c_stage = c_stage1;
         c_stage1 = c_stage2;
         c_stage2 = next_stage(c_stage2);
@@ -494,26 +490,27 @@ void attn_bwd_dkdv_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K
         // ---- first half.  After each MFMA of the next block's S, dP: one element of P and dS - the
         // exponential of element r is started in one group and used in the next, so that nothing waits
         // for it - and the transposing reads of one operand of the second half.
-        float pe[16], de[16], te[16];
+        float pe[16], de[16];
+        float* const stat2 = wave_stat(stage2) + lane;      // statistics of block n+2, to be scaled
+        float st = 0.f;
         auto element_start = [&](int r) {
             const int g = r >> 2, t = r & 3;
-            float sv = sc[r], dv = dc[r];
-            asm volatile("" : "+v"(sv), "+v"(dv));
+            float sv = sc[r];
             if (decltype(masked)::value && i0 + 8 * g + 4 * h + t + off < my_j) sv = -INFINITY;
             if (pad_key) sv = -INFINITY;
-            pe[r] = __builtin_amdgcn_exp2f(__builtin_fmaf(sv, c, -lse4[g][t] * kLog2e));
-            te[r] = dv - dl4[g][t];
-            asm volatile("" : "+v"(pe[r]), "+v"(te[r]));
+            pe[r] = __builtin_amdgcn_exp2f(sv * c);
+            asm volatile("" : "+v"(pe[r]));
         };
         auto element_finish = [&](int r) {
-            de[r] = pe[r] * te[r];
+            de[r] = pe[r] * dc[r];
             asm volatile("" : "+v"(de[r]));
         };
-        scores(s_acc, dp_acc, [&](int kb, int which) {
+        scores(s_next, dp_next, [&](int kb, int which) {
             const int r = 2 * kb + which;
             element_start(r);
             if (r > 0) element_finish(r - 1);
             if (which == 0) read_tdo(q0s, kb); else read_tq(q0s, kb);
+            if (r == 2) st = *stat2;
             if (kb == kSteps / 2 + 1) {          // (elements 0..8 are done)
                 if (which == 0) {
                     pb[0] = cvt8(pe[0], pe[1], pe[2], pe[3], pe[4], pe[5], pe[6], pe[7]);
@@ -523,17 +520,11 @@ void attn_bwd_dkdv_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K
                     asm volatile("" : "+v"(dsb[0]));
                 }
             }
+            if (r == 14) { st *= stat_mul; asm volatile("" : "+v"(st)); }
         });
 
         // ---- second half: the products of this block, next to the reads of the next blocks' fragments
         element_finish(15);
-        // group g of 16 moves two registers of the next block's scores: S first (its last MFMA was issued before dP's)
-        auto move_scores = [&](int g) {
-            const int r = 2 * (g & 7);
-            float a = g < 8 ? s_acc[r] : dp_acc[r], b = g < 8 ? s_acc[r + 1] : dp_acc[r + 1];
-            asm volatile("" : "+v"(a), "+v"(b));
-            if (g < 8) { sc[r] = a; sc[r + 1] = b; } else { dc[r] = a; dc[r + 1] = b; }
-        };
 #pragma unroll
         for (int idx = 0; idx < kSteps; idx++) {
             const int ks = idx / (D / 32), db = idx % (D / 32);
@@ -541,38 +532,36 @@ void attn_bwd_dkdv_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K
                 pb[1] = cvt8(pe[8], pe[9], pe[10], pe[11], pe[12], pe[13], pe[14], pe[15]);
                 dsb[1] = cvt8(de[8], de[9], de[10], de[11], de[12], de[13], de[14], de[15]);
             }
-            asm volatile("" : "+a"(dv_acc[db]));
             dv_acc[db] = mfma32(tdo[idx], pb[ks], dv_acc[db]);
-            asm volatile("" : "+a"(dv_acc[db]));
+asm volatile("" : : "v"(dv_acc[db][0]));
             rq[idx] = lds_read_b128(q2s, row_lane ^ ((2 * idx) << 4));
-            if (idx < 4) lse4[idx] = stat1[2 * idx + h];
             if (idx == 0) asm volatile("" : "+v"(pb[1]), "+v"(dsb[1]));
             if (idx == 0) prepare();         // block n+6 goes into the stage of block n-1, which every wave has left
+            if (idx == 0) *stat2 = st;
             if (idx == S::kLoadsPerBlock + 1) emit(S::kLoadsPerBlock);
-            move_scores(2 * idx);
             __builtin_amdgcn_sched_barrier(0);
-            asm volatile("" : "+a"(dk_acc[db]));
             dk_acc[db] = mfma32(tq[idx], dsb[ks], dk_acc[db]);
-            asm volatile("" : "+a"(dk_acc[db]));
+asm volatile("" : : "v"(dk_acc[db][0]));
             rdo[idx] = lds_read_b128(q2s + S::kQTileBytes, row_lane ^ ((2 * idx) << 4));
-            if (idx < 4) dl4[idx] = stat1[8 + 2 * idx + h];
+            if (idx >= 2 && idx < 6) read_stat(sc, wave_stat(stage2), idx - 2);           // (S and dP of block n+2 start from there)
+            if (idx >= 4) read_stat(dc, wave_stat(stage2) + 32, idx - 4);
             if (idx >= 1 && idx <= S::kLoadsPerBlock) emit(idx - 1);
             if (SPILL && idx == kSteps / 2 + 2) {       // (both halves of dS exist; every step issues exactly these two stores)
                 char* dst = ds_head + ((size_t)(i0 / S::kTileQ) * 4 + wave) * 2048 + lane * 16;
                 *(bf16x8*)dst = dsb[0];
                 *(bf16x8*)(dst + 1024) = dsb[1];
             }
-            move_scores(2 * idx + 1);
             __builtin_amdgcn_sched_barrier(0);
         }
 
         // Block n+3 (issued three steps ago) must have landed before the next step reads it; the newer
         // prefetches stay in flight, and so do the dS stores issued since: the counter retires loads and stores in issue order, and the stores of the last
-        // four steps are younger than the loads waited for.  The wave's own LDS reads must have
-        // returned as well: after the barrier the next step's prefetch overwrites the stage of block n.
+        // four steps are younger than the loads waited for.  After the barrier the next step's prefetch overwrites the stage of
+        // block n: what this wave read from it (dO^T and Q^T above, rows and statistics two steps ago) has returned, since the MFMAs of this
+        // step took it; the reads still in flight are of block n+2.
         constexpr int kStores = SPILL ? 8 : 0;
         prepare_turn();
-        wait_vmcnt_lds_done<3 * (S::kLoadsPerBlock + 1) + kStores>();
+        wait_vmcnt<3 * (S::kLoadsPerBlock + 1) + kStores>();
         __builtin_amdgcn_sched_barrier(0);
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_sched_barrier(0);
@@ -585,12 +574,16 @@ void attn_bwd_dkdv_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K
         // dS blocks of (this query head, this key tile); query block 0 = queries 0..31 of the head
         char* ds_head = SPILL ? DS + ((q_head_of(g) * num_kv_tiles + kt) * n_qb) * (size_t)8192 : nullptr;
         int blk = 0;
+        auto two_steps = [&](auto masked) __attribute__((always_inline)) {         // (n_blocks and n_masked are even)
+            step(masked, blk, ds_head, s_even, dp_even, s_odd, dp_odd);
+            step(masked, blk + 1, ds_head, s_odd, dp_odd, s_even, dp_even);
+        };
         if (CAUSAL) {
 #pragma unroll 1
-            for (; blk < n_masked; blk++) step(std::true_type{}, blk, ds_head);
+            for (; blk < n_masked; blk += 2) two_steps(std::true_type{});
         }
 #pragma unroll 1
-        for (; blk < n_blocks; blk++) step(std::false_type{}, blk, ds_head);
+        for (; blk < n_blocks; blk += 2) two_steps(std::false_type{});
     }
     } else {
     // ------------------------------------------------------------------------------------------
@@ -599,8 +592,13 @@ void attn_bwd_dkdv_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K
     // ------------------------------------------------------------------------------------------
     bf16x8 rq[kSteps], rdo[kSteps];         // row fragments of the block about to be computed
     bf16x8 tq[kSteps], tdo[kSteps], pb[2], dsb[2];      // transposed fragments [ks * (D/32) + db] and bf16 P / dS of a block
-    f32x4 lse4[4], dl4[4];
+    f32x16 s, dp;                           // S - LSE / scale, dP - Delta; start from the statistics, which the step before reads
 
+    auto read_stat = [&](int stage, int g) {
+        const f32x4 l = ((const f32x4*)wave_stat(stage))[2 * g + h], d = ((const f32x4*)wave_stat(stage))[8 + 2 * g + h];
+#pragma unroll
+        for (int t = 0; t < 4; t++) { s[4 * g + t] = l[t]; dp[4 * g + t] = d[t]; }
+    };
     auto read_rows = [&](const char* qs, int kb) {
         rq[kb] = lds_read_b128(qs, row_lane ^ ((2 * kb) << 4));
         rdo[kb] = lds_read_b128(qs + S::kQTileBytes, row_lane ^ ((2 * kb) << 4));
@@ -616,30 +614,28 @@ void attn_bwd_dkdv_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K
                          lds_read_tr16(qs, (trq_lane ^ x1) + row_off + 8 * S::kRowBytes));
     };
 #pragma unroll
-    for (int kb = 0; kb < kSteps; kb++) read_rows(ring + c_stage, kb);
+    for (int kb = 0; kb < kSteps; kb++) { read_rows(ring + c_stage, kb); read_stat(c_stage, kb); }
 
     auto step = [&](auto masked, int blk, char* ds_head) {
         const int i0 = i_begin + blk * S::kTileQ;
         const char* qs = ring + c_stage;
         c_stage = next_stage(c_stage);
         const char* qs_next = ring + c_stage;
-        const f32x4* stat = (const f32x4*)(qs + 2 * S::kQTileBytes);
+        float* const stat_next = wave_stat(c_stage) + lane;
 
         issue_next();                       // into the stage of the previous block, which every wave has left
         __builtin_amdgcn_sched_barrier(0);
 
         // ---- phase 1: S = Q K^T, dP = dO V^T; read this block's transposed fragments and statistics
-        f32x16 s, dp;
-#pragma unroll
-        for (int r = 0; r < 16; r++) { s[r] = 0.f; dp[r] = 0.f; }
+        const float st = *stat_next * stat_mul;
 #pragma unroll
         for (int kb = 0; kb < kSteps; kb++) {
             s = mfma32(rq[kb], kf[kb], s);
             dp = mfma32(rdo[kb], vf[kb], dp);
             read_transposed(qs, kb);
-            if (kb < 4) { lse4[kb] = stat[2 * kb + h]; dl4[kb] = stat[8 + 2 * kb + h]; }
             __builtin_amdgcn_sched_barrier(0);
         }
+        *stat_next = st;
 
         // ---- phase 2: P, dS.  Only the first blocks of a causal tile touch the diagonal: they run as a
         // loop of their own that pushes the masked scores to -inf (P = 2^-inf = 0), so that the main
@@ -658,9 +654,9 @@ void attn_bwd_dkdv_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K
 #pragma unroll
             for (int t = 0; t < 4; t++) {
                 const int r = 4 * g + t;
-                const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(s[r], c, -lse4[g][t] * kLog2e));
+                const float p = __builtin_amdgcn_exp2f(s[r] * c);
                 s[r] = p;
-                dp[r] = p * (dp[r] - dl4[g][t]);
+                dp[r] *= p;
             }
         }
 #pragma unroll
@@ -685,15 +681,17 @@ void attn_bwd_dkdv_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K
             dv_acc[db] = mfma32(tdo[idx], pb[ks], dv_acc[db]);
             dk_acc[db] = mfma32(tq[idx], dsb[ks], dk_acc[db]);
             read_rows(qs_next, idx);
+            read_stat(c_stage, idx);
         }
 
         // the block two ahead in the stream (issued two iterations ago) must have landed before the
-        // next iteration reads its rows; the newer prefetches may stay in flight.  The wave's own LDS reads of this block's stage must have returned as
-        // well: after the barrier the next step's prefetch overwrites that stage.
+        // next iteration reads its rows; the newer prefetches may stay in flight.  After the barrier the next step's prefetch
+        // overwrites the stage of this block: what this wave read from it has returned, since MFMAs of this step and of the one before took
+        // it; the reads still in flight are of the next block.
         // (the counter retires loads and stores in issue order: the dS stores of this step and of the
         // previous one were issued after the loads waited for)
         constexpr int kStores = SPILL ? 4 : 0;
-        wait_vmcnt_lds_done<(S::kAhead - 2) * (S::kLoadsPerBlock + 1) + kStores>();
+        wait_vmcnt<(S::kAhead - 2) * (S::kLoadsPerBlock + 1) + kStores>();
         __builtin_amdgcn_sched_barrier(0);
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_sched_barrier(0);
