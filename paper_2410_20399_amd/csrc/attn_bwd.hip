@@ -4,7 +4,7 @@
 // here is the chain rule with P recomputed from the saved log-sum-exp:
 //
 //   kernel 1  Delta_i = sum_d dO_id O_id          (HBM stream)
-//   kernel 2  dK, dV: persistent workgroups walk the 128-key tiles; wave w owns keys 32w..32w+31 and keeps
+//   kernel 2  dK, dV: persistent workgroups walk the 128-key tiles (large launches at D = 128: 256-key tiles, 64 keys a wave); wave w owns keys 32w..32w+31 and keeps
 //             their dK^T, dV^T accumulators in registers while it loops over 32-query blocks:
 //               S  = Q_i K_j^T            P  = 2^(S*c - LSE_i*log2e)
 //               dP = dO_i V_j^T           dS = P (dP - Delta_i)
@@ -801,6 +801,500 @@ static hipError_t launch_dkdv_tt(const void* q, const void* k, const void* v, co
     return hipGetLastError();
 }
 
+// ------------------------------------------------------------------------------------------
+// kernel 2 at D = 128 for large launches: 64 keys a wave
+// ------------------------------------------------------------------------------------------
+// The same work in the same order (the bits of dK, dV and dS are those of the kernel above), with tiles of 256 keys: every Q, dO
+// row that comes from L2, and every fragment that is read from LDS, serves twice the matrix instructions.  One wave per SIMD:
+// the dK^T, dV^T accumulators take the whole accumulator half of the register file; K stays in registers, V in LDS.  A step is
+//     first half    S, dP of block n (32 MFMAs)  next to  the LDS reads of its rows, the fetch of block n+3, the statistics of
+//                   block n+1, the dS stores of block n-1 and the first fragments of the second half
+//     second half   dV^T, dK^T of block n-1 (32 MFMAs)  next to  P, dS of block n, one element behind each MFMA, and the first
+//                   fragments of the next step
+// What bounds it: the second half has 4.6 vector instructions to an MFMA, which a single wave issues in about 40 of the 32
+// cycles that the matrix pipe takes; and power (without its loads the kernel takes 13 % less time on normal data, on
+// constant data 5 %).  dK/dV alone, us, 128 keys and 256: B16 H16 N4096 without a mask 3680, 3303; causal 2020, 1915; causal and
+// storing dS 2385, 2344.  Two waves per SIMD in turns, as in the forward, do not fit: 256 registers a wave.
+//
+// The accumulators are only touched by inline assembly, which the compiler sees as writing them at once: results are read, and
+// copies made in front of a product, behind the waits that the hardware wants (mfma32_acc_wait, and the s_nop behind the last).
+__device__ __forceinline__ void mfma32_acc(f32x16& acc, bf16x8 a, bf16x8 b) {     // acc stays where it is from one product to the next
+    asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
+}
+// behind copies of the accumulator
+__device__ __forceinline__ void mfma32_acc_wait(f32x16& acc, bf16x8 a, bf16x8 b) {
+    asm volatile("s_nop 1\n\tv_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
+}
+struct DkdvWideShape {
+    static constexpr int D = 128;
+    static constexpr int kWaves = 4, kThreads = 256;
+    static constexpr int kTileKV = 256;                 // keys per workgroup (64 per wave)
+    static constexpr int kTileQ = 32;
+    static constexpr int kStages = 5;
+    static constexpr int kRowBytes = D * 2, kChunksPerRow = D / 8;
+    static constexpr int kQTileBytes = kTileQ * kRowBytes;
+    static constexpr int kStageBytes = 2 * kQTileBytes + kWaves * 256;
+    static constexpr int kQLoads = kTileQ * kChunksPerRow / kThreads;
+    static constexpr int kBlockLoads = 2 * kQLoads + 1;
+    static constexpr int kWaveBytes = 64 * kRowBytes;   // a wave's V tile
+    static constexpr int kEpiPitch = 128 + 8;           // the epilogue turns 32 rows x 64 columns around at a time,
+    static_assert(kWaves * 32 * kEpiPitch <= kStageBytes, "in the ring stage that is free at the end of a pass");
+};
+
+template <bool CAUSAL, bool TAIL, bool SPILL>
+__global__ __launch_bounds__(256, 1)
+void attn_bwd_dkdv_wide_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K, const bf16* __restrict__ V,
+                               const bf16* __restrict__ dO, const float* __restrict__ LSE, const float* __restrict__ Delta,
+                               bf16* __restrict__ dK, bf16* __restrict__ dV,
+                               int Nq, int Nk, int num_kv_tiles, int total_units, float scale, int hq, int hkv, int stride,
+                               char* __restrict__ DS, int n_qb, int units)
+{
+    using S = DkdvWideShape;
+    constexpr int D = S::D, kSteps = D / 16;
+    __shared__ __attribute__((aligned(1024))) char ring[S::kStages * S::kStageBytes];
+    __shared__ __attribute__((aligned(1024))) char own[S::kWaves * S::kWaveBytes];
+
+    const int tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lane = tid & 63;
+    const int l32 = lane & 31;
+    const int h = lane >> 5;
+    const int j16 = lane & 15;
+    const int ghalf = (lane >> 4) & 1;
+    const float c = scale * kLog2e;
+    const int heads_per_kv = hq / hkv;
+    const int off = TAIL ? Nk - Nq : 0;
+    char* const mine = own + wave * S::kWaveBytes;
+
+    auto q_head_row = [&](int bh) { return (size_t)((bh / hkv) * hq + (bh % hkv) * heads_per_kv) * Nq; };
+    auto pass_ibegin = [&](int kt) {
+        if (!CAUSAL) return 0;
+        const int first = kt * S::kTileKV - off;
+        return first > 0 ? first & ~(S::kTileQ - 1) : 0;
+    };
+    auto pass_nblocks = [&](int ibegin) { return 2 * ((Nq - ibegin + 2 * S::kTileQ - 1) / (2 * S::kTileQ)); };
+    auto pass_tile = [&](int vu, int half, int& bh, int& kt) {
+        const int logical = xcd_remap(vu, total_units);
+        bh = logical / units;
+        const int unit = logical % units;
+        kt = half == 0 ? unit : num_kv_tiles - 1 - unit;
+    };
+    auto next_pass = [&](int& vu, int& half) {
+        if (CAUSAL && half == 0) {
+            const int unit = xcd_remap(vu, total_units) % units;
+            if (num_kv_tiles - 1 - unit >= units) { half = 1; return; }
+        }
+        vu += stride;
+        half = 0;
+    };
+
+    // ---- query-block prefetch (the cursor of the kernel above)
+    int q_src[S::kQLoads];
+#pragma unroll
+    for (int it = 0; it < S::kQLoads; it++) {
+        int s = it * S::kThreads + tid;
+        int row = s / S::kChunksPerRow, pc = s % S::kChunksPerRow;
+        q_src[it] = row * D + ((pc ^ swz<D>(row)) * 8);
+    }
+    const float* const stat_src = (lane < 32 ? LSE : Delta) + l32;
+    int p_vu = blockIdx.x, p_half = 0, p_nblocks = 0, p_g = 0, p_ibegin = 0;
+    size_t p_head_row = 0, p_row = 0;
+    int p_i0 = 0, p_left = 0, p_advance = S::kTileQ, p_stage = 0;
+    auto next_stage = [&](int at) { return at + S::kStageBytes == S::kStages * S::kStageBytes ? 0 : at + S::kStageBytes; };
+    auto producer_head = [&]() __attribute__((always_inline)) {
+        p_row = p_head_row + (size_t)p_g * Nq + p_ibegin;
+        p_i0 = p_ibegin;
+        p_left = p_nblocks;
+    };
+    auto producer_open = [&]() __attribute__((always_inline)) {
+        int bh, kt;
+        pass_tile(p_vu, p_half, bh, kt);
+        p_ibegin = pass_ibegin(kt);
+        p_head_row = q_head_row(bh);
+        p_nblocks = pass_nblocks(p_ibegin);
+        p_g = 0;
+        producer_head();
+    };
+    auto producer_turn = [&]() __attribute__((always_inline)) {
+        if (++p_g < heads_per_kv) { producer_head(); return; }
+        next_pass(p_vu, p_half);
+        if (p_vu < total_units) { producer_open(); return; }
+        p_row -= p_advance;                 // exhausted: stay on the last block
+        p_i0 -= p_advance;
+        p_advance = 0;
+        p_left = 0x7fffffff;
+    };
+    size_t e_head_row = 0, e_row = 0;       // of the block being fetched
+    int e_i0 = 0, e_stage = 0;
+    auto prepare = [&]() __attribute__((always_inline)) {
+        e_row = p_row;
+        e_i0 = p_i0;
+        e_head_row = p_row - p_i0;
+        e_stage = p_stage;
+        p_stage = next_stage(p_stage);
+        p_row += p_advance;
+        p_i0 += p_advance;
+        --p_left;
+    };
+    auto prepare_turn = [&]() __attribute__((always_inline)) {
+        if (__builtin_expect(p_left == 0, 0)) producer_turn();
+    };
+    auto emit = [&](int which) __attribute__((always_inline)) {
+        char* base = ring + e_stage;
+        if (which < 2 * S::kQLoads) {       // Q rows, then dO rows
+            const int it = which % S::kQLoads;
+            const bf16* block = (which < S::kQLoads ? Q : dO) + e_row * D;
+            char* dst = base + (which < S::kQLoads ? 0 : S::kQTileBytes) + it * (S::kThreads * 16) + wave * 1024;
+            if (TAIL) {
+                const int r = e_i0 + (it * S::kThreads + tid) / S::kChunksPerRow;
+                load_global_to_lds16_untracked(block + q_src[it] - (r < Nq ? 0 : r - (Nq - 1)) * D, dst);
+            } else {
+                load_global_to_lds16_sbase_untracked(block, (uint32_t)q_src[it] * 2, dst);
+            }
+        } else {
+            const float* src = stat_src + e_row;
+            if (TAIL && e_i0 + l32 >= Nq) src = lane < 32 ? g_lse_pad : Delta + e_head_row + (Nq - 1);
+            load_global_to_lds4_untracked(src, base + 2 * S::kQTileBytes + wave * 256);
+        }
+    };
+    const float stat_mul = lane < 32 ? -1.0f / scale : -1.0f;
+    auto wave_stat = [&](int stage) { return (float*)(ring + stage + 2 * S::kQTileBytes + wave * 256); };
+    auto scale_stat = [&](int stage) __attribute__((always_inline)) { float* st = wave_stat(stage) + lane; *st = *st * stat_mul; };
+
+    // ---- per-lane LDS offsets
+    const int row_lane = l32 * S::kRowBytes + ((h ^ swz<D>(l32)) << 4);
+    const int trq_row = 4 * h + (j16 >> 2);
+    const int trq_lane = trq_row * S::kRowBytes + (((2 * ghalf + ((j16 & 3) >> 1)) ^ swz<D>(trq_row)) << 4) + ((j16 & 1) << 3);
+
+    bf16x8 kf[2][kSteps];                   // K fragments of the wave's two halves of 32 keys
+    f32x16 dk_acc[2][D / 32], dv_acc[2][D / 32], sc[2], dc[2], st_l, st_d;
+    struct Products { bf16x8 p[2][2], d[2][2]; };       // bf16 P, dS of a block: [half][16 queries]
+    Products even, odd;
+
+    auto load_kv = [&](int bh, int kt) __attribute__((always_inline)) {
+        const int key0 = kt * S::kTileKV + wave * 64;
+        const size_t head_row = (size_t)bh * Nk;
+        const int key_first = !TAIL || key0 < Nk ? key0 : Nk - 1, last = TAIL ? Nk - 1 - key_first : 63;
+#pragma unroll
+        for (int it = 0; it < S::kWaveBytes / 1024; it++) {
+            const int r = it * 4 + (lane >> 4);
+            load_global_to_lds16_sbase_untracked(V + (head_row + key_first) * D, (uint32_t)((TAIL && r > last ? last : r) * D + ((j16 ^ swz<D>(r)) * 8)) * 2, mine + it * 1024);
+        }
+#pragma unroll
+        for (int b = 0; b < 2; b++) {
+            const int key = key0 + 32 * b + l32;
+            const bf16* row = K + (head_row + ((!TAIL || key < Nk) ? key : Nk - 1)) * D;
+#pragma unroll
+            for (int kb = 0; kb < kSteps; kb++) kf[b][kb] = *(const bf16x8*)(row + kb * 16 + h * 8);
+        }
+    };
+    auto keep_k = [&]() __attribute__((always_inline)) {        // (the wait for K belongs here and not at its first use)
+#pragma unroll
+        for (int b = 0; b < 2; b++)
+#pragma unroll
+            for (int kb = 0; kb < kSteps; kb++) asm volatile("" : "+v"(kf[b][kb]));
+    };
+    auto step_end = [&]() __attribute__((always_inline)) {
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+        asm volatile("" : : : "memory");
+    };
+    auto read_stats = [&](int stage, int b, int g) __attribute__((always_inline)) {
+        const f32x4 x = ((const f32x4*)wave_stat(stage))[8 * b + 2 * g + h];
+#pragma unroll
+        for (int t = 0; t < 4; t++) (b == 0 ? st_l : st_d)[4 * g + t] = x[t];
+    };
+    struct Rows { bf16x8 q[kSteps], d[kSteps], v[2][kSteps]; };
+    struct Columns { bf16x8 q[kSteps], d[kSteps]; };
+    auto opaque = [](int x) __attribute__((always_inline)) { asm volatile("" : "+v"(x)); return x; };
+    auto read_row = [&](Rows& f, int rl, int stage, int kb, int part) __attribute__((always_inline)) {
+        const int at = rl ^ ((2 * kb) << 4);
+        if (part == 0) { f.q[kb] = lds_read_b128(ring + stage, at); f.d[kb] = lds_read_b128(ring + stage + S::kQTileBytes, at); }
+        else { f.v[0][kb] = lds_read_b128(mine, at); f.v[1][kb] = lds_read_b128(mine + 32 * S::kRowBytes, at); }
+    };
+    bf16x8 row_q[2], row_d[2], row_v[2][2], col_q[2], col_d[2];         // the first fragments, read half a step ahead
+    auto read_row_ahead = [&](int rl, int stage, int n) __attribute__((always_inline)) {
+        const int kb = n >> 2, at = rl ^ ((2 * kb) << 4);
+        if ((n & 3) == 0) row_q[kb] = lds_read_b128(ring + stage, at);
+        if ((n & 3) == 1) row_d[kb] = lds_read_b128(ring + stage + S::kQTileBytes, at);
+        if ((n & 3) == 2) row_v[0][kb] = lds_read_b128(mine, at);
+        if ((n & 3) == 3) row_v[1][kb] = lds_read_b128(mine + 32 * S::kRowBytes, at);
+    };
+    auto read_tr = [&](bf16x8& f, int tl, const char* rows, int idx) __attribute__((always_inline)) {
+        const int row_off = 16 * (idx / (D / 32)) * S::kRowBytes, db = idx % (D / 32);
+        f = concat(lds_read_tr16(rows, (tl ^ ((4 * db) << 4)) + row_off), lds_read_tr16(rows, (tl ^ (((4 * db) ^ 2) << 4)) + row_off + 8 * S::kRowBytes));
+    };
+
+    int c_vu = blockIdx.x, c_half = 0, c_stage = 0;
+    {
+        int bh, kt;
+        pass_tile(c_vu, c_half, bh, kt);
+        producer_open();
+#pragma unroll
+        for (int b = 0; b < 3; b++) {
+            prepare();
+#pragma unroll
+            for (int which = 0; which < S::kBlockLoads; which++) emit(which);
+            prepare_turn();
+        }
+        load_kv(bh, kt);
+    }
+    keep_k();
+    wait_vmcnt<0>();
+    scale_stat(0);
+    step_end();
+
+#pragma unroll 1
+    while (c_vu < total_units) {
+        int bh, kt;
+        pass_tile(c_vu, c_half, bh, kt);
+        const int jw0 = kt * S::kTileKV + wave * 64, my_j = jw0 + l32;
+        const int i_begin = pass_ibegin(kt), n_blocks = pass_nblocks(i_begin);
+        const int kv_tiles128 = (Nk + 127) / 128;
+        const bool stores = SPILL && (!TAIL || (jw0 >> 7) < kv_tiles128);
+        const size_t ds_head_bytes = (size_t)kv_tiles128 * n_qb * 8192;
+        int i0 = i_begin, left = n_blocks;
+        char* ds = nullptr;
+        if (SPILL) ds = DS + ((((size_t)(bh / hkv) * hq + (size_t)(bh % hkv) * heads_per_kv) * kv_tiles128 + (jw0 >> 7)) * n_qb * 4 + ((jw0 >> 5) & 3)) * 2048
+                        + lane * 16 + (size_t)(i_begin / S::kTileQ) * 8192;
+        auto advance = [&]() __attribute__((always_inline)) {
+            i0 += S::kTileQ;
+            if (SPILL) ds += 8192;
+            if (__builtin_expect(--left == 0, 0)) {     // on to the next query head
+                i0 = i_begin;
+                left = n_blocks;
+                if (SPILL) ds += ds_head_bytes - (size_t)n_blocks * 8192;
+            }
+        };
+#pragma unroll
+        for (int b = 0; b < 2; b++)
+#pragma unroll
+            for (int db = 0; db < D / 32; db++)
+#pragma unroll
+                for (int r = 0; r < 16; r++) { dk_acc[b][db][r] = 0.f; dv_acc[b][db][r] = 0.f; }
+
+        auto store_ds = [&](char* dst, const Products& x) __attribute__((always_inline)) {
+            if (SPILL && stores) {
+#pragma unroll
+                for (int b = 0; b < 2; b++)
+#pragma unroll
+                    for (int ks = 0; ks < 2; ks++) *(bf16x8*)(dst + 2048 * b + 1024 * ks) = x.d[b][ks];
+            }
+        };
+        // First half of a step: S, dP of its block (both halves of the keys, whose statistics are in sc, dc already).  Beside the
+        // matrix instructions: the fetch of the block three ahead and the statistics of the next one.
+        auto scores = [&](int stage, int stage_next, int stage_last, char* ds_last, const Products& last, bool first) __attribute__((always_inline)) {
+            Rows f;
+            const int rl = opaque(row_lane), tl = opaque(trq_lane);
+            float* const st = wave_stat(stage_next) + lane;
+            float x = 0.f;
+#pragma unroll
+            for (int kb = 0; kb < 2; kb++) { f.q[kb] = row_q[kb]; f.d[kb] = row_d[kb]; f.v[0][kb] = row_v[0][kb]; f.v[1][kb] = row_v[1][kb]; }
+#pragma unroll
+            for (int kb = 0; kb < kSteps; kb++) {
+                sc[0] = mfma32(f.q[kb], kf[0][kb], kb == 0 ? st_l : sc[0]);
+                asm volatile("" : : "v"(sc[0][0]));
+                if (kb == 0) prepare();
+                if (kb >= 1 && kb <= S::kBlockLoads) emit(kb - 1);
+                __builtin_amdgcn_sched_barrier(0);
+                sc[1] = mfma32(f.q[kb], kf[1][kb], kb == 0 ? st_l : sc[1]);
+                asm volatile("" : : "v"(sc[1][0]));
+                if (kb + 2 < kSteps) read_row(f, rl, stage, kb + 2, 0);
+                else read_tr(col_d[kb - 6 < 0 ? 0 : kb - 6], tl, ring + stage_last + S::kQTileBytes, kb - 6);
+                __builtin_amdgcn_sched_barrier(0);
+                dc[0] = mfma32(f.d[kb], f.v[0][kb], kb == 0 ? st_d : dc[0]);
+                asm volatile("" : : "v"(dc[0][0]));
+                if (kb == 2) x = *st;
+                if (kb == 5) *st = x * stat_mul;
+                if (SPILL && kb >= 6 && stores && !first) {
+                    *(bf16x8*)(ds_last + 2048 * (kb - 6)) = last.d[kb & 1][0];
+                    *(bf16x8*)(ds_last + 2048 * (kb - 6) + 1024) = last.d[kb & 1][1];
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                dc[1] = mfma32(f.d[kb], f.v[1][kb], kb == 0 ? st_d : dc[1]);
+                asm volatile("" : : "v"(dc[1][0]));
+                if (kb + 2 < kSteps) read_row(f, rl, stage, kb + 2, 1);
+                else read_tr(col_q[kb - 6 < 0 ? 0 : kb - 6], tl, ring + stage_last, kb - 6);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        };
+        auto mask = [&]() __attribute__((always_inline)) {
+            if (__builtin_expect((CAUSAL && i0 + off < jw0 + 63) || (TAIL && SPILL && jw0 + 63 >= Nk), 0)) {
+#pragma unroll
+                for (int b = 0; b < 2; b++)
+#pragma unroll
+                    for (int r = 0; r < 16; r++)
+                        if ((CAUSAL && i0 + 8 * (r >> 2) + 4 * h + (r & 3) + off < my_j + 32 * b) || (TAIL && SPILL && my_j + 32 * b >= Nk)) sc[b][r] = -INFINITY;
+            }
+        };
+        // Second half: dV^T, dK^T of the block before, and beside them P, dS of this block, one element for each matrix instruction.
+        auto products = [&](int stage_last, int stage_next, const Products& last, Products& next, auto has_last, auto has_vector) __attribute__((always_inline)) {
+            Columns f;
+            const int tl = opaque(trq_lane);
+            const char* qs = ring + stage_last;
+            const char* dos = qs + S::kQTileBytes;
+            float pe[32], de[32];
+            const int rl = opaque(row_lane);
+            if (!decltype(has_vector)::value) {
+#pragma unroll
+                for (int i = 0; i < 2; i++) { read_tr(col_d[i], tl, dos, i); read_tr(col_q[i], tl, qs, i); }
+            }
+#pragma unroll
+            for (int i = 0; i < 2; i++) { f.d[i] = col_d[i]; f.q[i] = col_q[i]; }
+            auto start = [&](int e) __attribute__((always_inline)) { pe[e] = __builtin_amdgcn_exp2f(sc[e >> 4][e & 15] * c); asm volatile("" : : "v"(pe[e])); };
+            auto finish = [&](int e) __attribute__((always_inline)) { de[e] = pe[e] * dc[e >> 4][e & 15]; asm volatile("" : : "v"(de[e])); };
+            auto pack = [&](const float (&x)[32], int e, bf16x8& to) __attribute__((always_inline)) {
+                to = cvt8(x[e], x[e + 1], x[e + 2], x[e + 3], x[e + 4], x[e + 5], x[e + 6], x[e + 7]);
+                asm volatile("" : "+v"(to));
+            };
+#pragma unroll
+            for (int i = 0; i < 32; i++) {
+                const int idx = i >> 2, j = i & 3, ks = idx / (D / 32), db = idx % (D / 32);
+                if (decltype(has_last)::value) {
+                    f32x16& acc = j < 2 ? dv_acc[j & 1][db] : dk_acc[j & 1][db];
+                    const bf16x8 a = j < 2 ? f.d[idx] : f.q[idx], b = j < 2 ? last.p[j & 1][ks] : last.d[j & 1][ks];
+                    if (decltype(has_vector)::value) mfma32_acc(acc, a, b); else mfma32_acc_wait(acc, a, b);
+                    if (j == 1 && idx + 2 < kSteps) read_tr(f.d[idx + 2], tl, dos, idx + 2);
+                    if (j == 3 && idx + 2 < kSteps) read_tr(f.q[idx + 2], tl, qs, idx + 2);
+                }
+                if (decltype(has_vector)::value) {
+                    start(i);
+                    if (i > 0) finish(i - 1);
+                    if (i % 8 == 1 && i > 8) pack(pe, i - 9, next.p[(i - 9) >> 4][((i - 9) >> 3) & 1]);
+                    if (i % 8 == 2 && i > 9) pack(de, i - 10, next.d[(i - 10) >> 4][((i - 10) >> 3) & 1]);
+                    if (i >= 18 && i < 26) read_row_ahead(rl, stage_next, i - 18);
+                    if (i >= 24) read_stats(stage_next, (i - 24) >> 2, i & 3);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            if (decltype(has_vector)::value) {
+                finish(31);
+                pack(pe, 24, next.p[1][1]);
+                pack(de, 24, next.d[1][1]);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        };
+        auto step = [&](int stage_last, const Products& last, Products& next, bool first) __attribute__((always_inline)) {
+            const int stage = c_stage, stage_next = next_stage(stage);
+            c_stage = stage_next;
+            char* const ds_last = ds;                   // of the block before
+            if (!first) advance();
+            scores(stage, stage_next, stage_last, ds_last, last, first);
+            mask();
+            products(stage_last, stage_next, last, next, std::true_type{}, std::true_type{});
+            prepare_turn();
+            // block n+2 has to be here; younger are the loads of this step and, where there are any, its stores (and those of
+            // the step before)
+            if (SPILL && stores && !first) wait_vmcnt<S::kBlockLoads + 4>(); else wait_vmcnt<S::kBlockLoads>();
+            step_end();
+        };
+        // ---- the pass, an even number of blocks.  The first step has no block before it: it adds P = dS = 0 times its own block,
+        // instead of a copy of the step without products (whose accumulators would live in other registers).
+#pragma unroll
+        for (int b = 0; b < 2; b++)
+#pragma unroll
+            for (int ks = 0; ks < 2; ks++) { odd.p[b][ks] = bf16x8{}; odd.d[b][ks] = bf16x8{}; }
+#pragma unroll
+        for (int n = 0; n < 8; n++) { read_row_ahead(row_lane, c_stage, n); read_stats(c_stage, n >> 2, n & 3); }
+        int stage_last = c_stage;
+        bool first = true;
+#pragma unroll 1
+        for (int more = heads_per_kv * n_blocks; more > 0; more -= 2) {
+            const int s0 = c_stage;
+            step(stage_last, odd, even, first);
+            stage_last = c_stage;
+            step(s0, even, odd, false);
+            first = false;
+        }
+        // K and V are done with: those of the next pass travel while this one's results are stored
+        next_pass(c_vu, c_half);
+        const bool another = c_vu < total_units;
+        if (another) {
+            int nbh, nkt;
+            pass_tile(c_vu, c_half, nbh, nkt);
+            load_kv(nbh, nkt);
+        }
+        store_ds(ds, odd);
+        products(stage_last, 0, odd, even, std::true_type{}, std::false_type{});
+        // the accumulators may be read from here on (the compiler does not know how long the products take)
+        asm volatile("s_nop 15\n\ts_nop 15" : "+a"(dv_acc[0][0]), "+a"(dv_acc[0][1]), "+a"(dv_acc[0][2]), "+a"(dv_acc[0][3]));
+        asm volatile("" : "+a"(dv_acc[1][0]), "+a"(dv_acc[1][1]), "+a"(dv_acc[1][2]), "+a"(dv_acc[1][3]));
+        asm volatile("" : "+a"(dk_acc[0][0]), "+a"(dk_acc[0][1]), "+a"(dk_acc[0][2]), "+a"(dk_acc[0][3]));
+        asm volatile("" : "+a"(dk_acc[1][0]), "+a"(dk_acc[1][1]), "+a"(dk_acc[1][2]), "+a"(dk_acc[1][3]));
+
+        // ---- the pass's results
+        const size_t head = (size_t)bh * Nk * D;
+        char* const turn = ring + p_stage + wave * (32 * S::kEpiPitch);      // (the stage the next block will be fetched into)
+        auto store_tile = [&](const f32x16 (&acc)[D / 32], float mul, bf16* dst, int key0) __attribute__((always_inline)) {
+#pragma unroll
+            for (int half = 0; half < D / 64; half++) {
+#pragma unroll
+                for (int db = 2 * half; db < 2 * half + 2; db++)
+#pragma unroll
+                    for (int q = 0; q < 4; q++) {
+                        bf16x2 a = cvt2(acc[db][4 * q] * mul, acc[db][4 * q + 1] * mul);
+                        bf16x2 b = cvt2(acc[db][4 * q + 2] * mul, acc[db][4 * q + 3] * mul);
+                        *(bf16x4*)(turn + l32 * S::kEpiPitch + (32 * (db & 1) + 8 * q + 4 * h) * 2) = __builtin_shufflevector(a, b, 0, 1, 2, 3);
+                    }
+#pragma unroll
+                for (int i = 0; i < 4; i++) {
+                    const int row = i * 8 + (lane >> 3);
+                    const char* src = turn + row * S::kEpiPitch + (lane & 7) * 16;
+                    const bf16x4 lo = *(const bf16x4*)src, hi = *(const bf16x4*)(src + 8);
+                    if (!TAIL || key0 + row < Nk) *(bf16x8*)(dst + (size_t)(key0 + row) * D + 64 * half + (lane & 7) * 8) = concat(lo, hi);
+                }
+            }
+        };
+#pragma unroll
+        for (int b = 0; b < 2; b++) {
+            store_tile(dk_acc[b], scale, dK + head, jw0 + 32 * b);
+            store_tile(dv_acc[b], 1.0f, dV + head, jw0 + 32 * b);
+        }
+        if (another) keep_k();
+        wait_vmcnt<0>();
+        step_end();                         // (no wave fetches into the stage of the last block before all are done with it)
+    }
+}
+
+// Whether tiles of 256 keys take less time than tiles of 128: us of the workgroup with most units, a block of 32 queries at
+// 1.07 (128 keys) and 1.8 us (256), 0.1 and 0.5 more where it may be masked, the ends of a pass at 4 and 8.  A unit is a key tile, or
+// a causal pair of them.  Fitted to 820 calls of 128 to 8192 queries and keys, grouped or not, with and without a mask and stored dS, both
+// ways timed: by this rule 260 take the 256-key tiles, 13 % faster on average; 13 of them lose more than 1 %, at most 6; what
+// others would gain is 0.2 % of theirs.  (Without the 3 % that a gain has to reach and the cost of masked blocks 36 lose, up to 22 %.)
+static bool dkdv_wide_pays(int B, int H, int Hkv, int Nq, int Nk, bool causal, int cus)
+{
+    auto us = [&](int keys, double block_us, double masked_us, double pass_us) {
+        const int tiles = (Nk + keys - 1) / keys;
+        const bool paired = causal && (keys == 256 || pair_tiles((long long)B * Hkv, tiles, cus));
+        const int units = paired ? (tiles + 1) / 2 : tiles, passes = paired && tiles > 1 ? 2 : 1;
+        const long long rounds = ((long long)B * Hkv * units + cus - 1) / cus;
+        // of a causal pair both passes together; otherwise the longest pass
+        double blocks = Nq / 32.0 * passes;
+        const double late = ((tiles - 1) * (double)keys - (Nk - Nq)) / 32;      // blocks that the last tile does not see
+        if (passes == 2 && late > 0) blocks -= late;
+        const double masked = causal ? (Nk < keys ? Nk : keys) / 32.0 * passes : 0;
+        return rounds * ((blocks * block_us + masked * masked_us) * (H / Hkv) + passes * pass_us);
+    };
+    return us(256, 1.8, 0.5, 8) < 0.97 * us(128, 1.07, 0.1, 4);
+}
+
+template <bool CAUSAL, bool TAIL, bool SPILL>
+static hipError_t launch_dkdv_wide(const void* q, const void* k, const void* v, const void* d_o,
+                                   const float* lse, const float* delta, void* dk, void* dv,
+                                   int B, int H, int Hkv, int Nq, int Nk, float scale, hipStream_t stream, void* ds, int cus)
+{
+    using S = DkdvWideShape;
+    const int num_kv_tiles = (Nk + S::kTileKV - 1) / S::kTileKV;
+    const int units = CAUSAL ? (num_kv_tiles + 1) / 2 : num_kv_tiles;
+    const int total_units = B * Hkv * units;
+    const int grid = total_units < cus ? total_units : cus;
+    hipLaunchKernelGGL((attn_bwd_dkdv_wide_kernel<CAUSAL, TAIL, SPILL>), dim3(grid), dim3(S::kThreads), 0, stream,
+                       (const bf16*)q, (const bf16*)k, (const bf16*)v, (const bf16*)d_o, lse, delta,
+                       (bf16*)dk, (bf16*)dv, Nq, Nk, num_kv_tiles, total_units, scale, H, Hkv, grid, (char*)ds, ds_query_blocks(Nq), units);
+    return hipGetLastError();
+}
+
 template <int D, bool CAUSAL>
 static hipError_t launch_dkdv_t(const void* q, const void* k, const void* v, const void* d_o,
                                 const float* lse, const float* delta, void* dk, void* dv,
@@ -813,6 +1307,13 @@ static hipError_t launch_dkdv_t(const void* q, const void* k, const void* v, con
     if (e != hipSuccess) return e;
     const int resident = cus * (D == 64 ? 2 : 1);               // as many workgroups as fit at once
     if (!part) n_splits = q_splits = 1;
+    if constexpr (D == 128)
+        if (!part && dkdv_wide_pays(B, H, Hkv, Nq, Nk, CAUSAL, cus)) {
+            const bool tail = Nq != Nk || Nk % DkdvWideShape::kTileKV;
+            auto launch = tail ? (ds ? launch_dkdv_wide<CAUSAL, true, true> : launch_dkdv_wide<CAUSAL, true, false>)
+                               : (ds ? launch_dkdv_wide<CAUSAL, false, true> : launch_dkdv_wide<CAUSAL, false, false>);
+            return launch(q, k, v, d_o, lse, delta, dk, dv, B, H, Hkv, Nq, Nk, scale, stream, ds, cus);
+        }
     const bool paired = CAUSAL && pair_tiles((long long)B * Hkv * n_splits, (Nk + S::kTileKV - 1) / S::kTileKV, cus);
     const bool tail = Nq != Nk || Nk % S::kTileKV || paired != CAUSAL;
     auto launch = part ? (ds ? launch_dkdv_tt<D, CAUSAL, true, true, true> : launch_dkdv_tt<D, CAUSAL, true, false, true>)
