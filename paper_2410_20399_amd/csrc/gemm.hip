@@ -13,7 +13,7 @@
 // The products are issued as D^T: v_mfma_f32_16x16x32_bf16(B fragment, A fragment), so that a lane owns one
 // ROW of C and stores 4 consecutive columns at a time.  The fragments of one half step (32 k) are read from
 // LDS while the MFMAs of the half step before it run; the barrier that frees a stage sits in the middle of a
-// step, and the load that refills it is issued right behind it.
+// step, and the loads that refill it follow one at a time between the MFMAs of the second half.
 //
 // KS > 1: KS groups of WM x WN waves in one workgroup share the K range, group g taking the steps g, g + KS, ...
 // with a ring of its own; the partial sums meet in LDS at the end, always in the same order.
@@ -168,34 +168,41 @@ void gemm_kernel(const bf16* __restrict__ A, const bf16* __restrict__ B, bf16* _
         for (int a = 0; a < MB; a++) acc[b][a] = f32x4{0.f, 0.f, 0.f, 0.f};
 
     bf16x8 af[2][MB], bfr[2][NB];       // two sets of fragments: one being multiplied, one being read
-    auto read_frags = [&](int set, const char* stage, int half) {
-#pragma unroll
-        for (int a = 0; a < MB; a++) af[set][a] = lds_read_b128(stage, (a_lane ^ (half << 6)) + a * 16 * 128);
-#pragma unroll
-        for (int b = 0; b < NB; b++) {
-            const int block = wn * NB + b;      // 16-column block of the tile
-            const int off = (block >> 2) * 8192 + half * 32 * 128, x = b_lane ^ ((block & 3) << 5);
-            bfr[set][b] = concat(lds_read_tr16(stage, x + off), lds_read_tr16(stage, x + off + 4 * 128));
-        }
+    auto read_a = [&](int set, const char* stage, int half, int a) __attribute__((always_inline)) {
+        af[set][a] = lds_read_b128(stage, (a_lane ^ (half << 6)) + a * 16 * 128);
     };
-    auto multiply = [&](int set) {
-#pragma unroll
-        for (int b = 0; b < NB; b++)
-#pragma unroll
-            for (int a = 0; a < MB; a++) acc[b][a] = mfma16(bfr[set][b], af[set][a], acc[b][a]);
+    auto read_b = [&](int set, const char* stage, int half, int b) __attribute__((always_inline)) {
+        const int block = wn * NB + b;          // 16-column block of the tile
+        const int off = (block >> 2) * 8192 + half * 32 * 128, x = b_lane ^ ((block & 3) << 5);
+        bfr[set][b] = concat(lds_read_tr16(stage, x + off), lds_read_tr16(stage, x + off + 4 * 128));
     };
-    // schedule of one half step: the fragment reads spread over its MFMAs
-    auto interleave = [&]() {
-        constexpr int kReads = MB + 2 * NB, kMfmas = MB * NB, kPer = kMfmas / kReads;
-        if constexpr (kPer > 0) {
+    // One half step: the products of a set of fragments, and between them the reads of the other set and the loads of a whole
+    // stage.  Issued in one go behind the barrier, the loads of all waves (64 KB a step with 256x256 tiles, of which a compute
+    // unit takes 64 bytes a cycle) held every wave up until they were through, and its MFMAs with it.  Spread over the half, us before
+    // and after (random data, the same tile): 8192^3 789, 760; M1000 N6144 K2048 28.7, 26.4; 2048^2 K8192 68.3, 60.5; M64 N512 K8192 in
+    // 64x128 tiles 47.3, 34.4.  The reads are done by the middle, ahead of the wait for them at the barrier (192x256 tiles, M3564 N2344
+    // K8696: 145, spread over the whole half 161).  Half steps of 32 MFMAs, whose two stages leave the loads
+    // less than a step to arrive, have theirs issued in the first three quarters (8192^3 776, 760; shorter ones lose by it).
+    auto half_step = [&](auto loads, auto set_, const char* stage, int half, const bf16* a_from, const bf16* b_from, char* to) __attribute__((always_inline)) {
+        constexpr int set = decltype(set_)::value;
+        constexpr int kMfmas = MB * NB, kReads = MB + NB, kLoads = decltype(loads)::value ? S::kLoads : 0;
+        constexpr int kLoadSpan = kMfmas >= 32 ? kMfmas * 3 / 4 : kMfmas;
+        int r = 0, l = 0;
 #pragma unroll
-            for (int i = 0; i < kReads; i++) {
-                __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);      // LDS read
-                __builtin_amdgcn_sched_group_barrier(0x008, kPer, 0);   // MFMA
+        for (int m = 0; m < kMfmas; m++) {
+#pragma unroll
+            for (; l * kLoadSpan < (m + 1) * kLoads && l < kLoads; l++) {
+                if (l < S::kALoads) load(a_from, a_src[l], to + l * (S::kGroupThreads * 16));
+                else load(b_from, b_src[l - S::kALoads], to + S::kABytes + (l - S::kALoads) * (S::kGroupThreads * 16));
             }
-            __builtin_amdgcn_sched_group_barrier(0x008, kMfmas - kPer * kReads, 0);
+#pragma unroll
+            for (; r * kMfmas < 2 * (m + 1) * kReads && r < kReads; r++) {
+                if (r < MB) read_a(set ^ 1, stage, half, r); else read_b(set ^ 1, stage, half, r - MB);
+            }
+            const int b = m / MB, a = m % MB;
+            acc[b][a] = mfma16(bfr[set][b], af[set][a], acc[b][a]);
+            __builtin_amdgcn_sched_barrier(0);
         }
-        __builtin_amdgcn_sched_barrier(0);
     };
 
     const int steps_all = (K + S::kTileK - 1) / S::kTileK;
@@ -206,26 +213,41 @@ void gemm_kernel(const bf16* __restrict__ A, const bf16* __restrict__ B, bf16* _
     if (n_steps >= S::kStages) wait_vmcnt<(S::kStages - 1) * S::kLoads>(); else wait_vmcnt<0>();
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_sched_barrier(0);
-    read_frags(0, ring, 0);
+#pragma unroll
+    for (int a = 0; a < MB; a++) read_a(0, ring, 0, a);
+#pragma unroll
+    for (int b = 0; b < NB; b++) read_b(0, ring, 0, b);
 
     int stage = 0;
+    auto next_stage = [&]() { return stage + S::kStageBytes == S::kStages * S::kStageBytes ? 0 : stage + S::kStageBytes; };
+    // Between the halves of a step: every wave's last reads of its stage have completed, so it can be refilled; the next
+    // step's stage (issued kStages - 1 steps ago) must have landed, the newer ones stay in flight.
+    int s = 0;
+    const int in_range = K / S::kTileK;                 // steps that lie within K
+    int n_full = (in_range - kg + KS - 1) / KS - S::kStages;    // steps of this group whose refill lies within K
+    if (n_full > n_steps - S::kStages) n_full = n_steps - S::kStages;
 #pragma unroll 1
-    for (int s = 0; s < n_steps; s++) {
+    for (; s < n_full; s++) {
+        const int old = stage, next = ((s + S::kStages) * KS + kg) * S::kTileK;
+        half_step(std::false_type{}, std::integral_constant<int, 0>{}, ring + stage, 1, nullptr, nullptr, nullptr);
+        stage = next_stage();
+        wait_vmcnt_lds_done<(S::kStages - 2) * S::kLoads>();
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+        half_step(std::true_type{}, std::integral_constant<int, 1>{}, ring + stage, 0, a_tile + next, b_tile + (size_t)next * N, ring + old + wave * 1024);
+    }
+#pragma unroll 1
+    for (; s < n_steps; s++) {
         const int old = stage;
-        read_frags(1, ring + stage, 1);
-        multiply(0);
-        interleave();
-        stage = stage + S::kStageBytes == S::kStages * S::kStageBytes ? 0 : stage + S::kStageBytes;
-        // Every wave's last reads of this step's stage have completed, so it can be refilled; the next
-        // step's stage (issued kStages - 1 steps ago) must have landed, the newer ones stay in flight.
+        half_step(std::false_type{}, std::integral_constant<int, 0>{}, ring + stage, 1, nullptr, nullptr, nullptr);
+        stage = next_stage();
         if (s + S::kStages <= n_steps) wait_vmcnt_lds_done<(S::kStages - 2) * S::kLoads>(); else wait_vmcnt_lds_done<0>();
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_sched_barrier(0);
         if (s + S::kStages < n_steps) issue_stage((s + S::kStages) * KS + kg, old);
         __builtin_amdgcn_sched_barrier(0);
-        read_frags(0, ring + stage, 0);         // (after the last step: a stage nobody writes, into fragments nobody uses)
-        multiply(1);
-        interleave();
+        // (after the last step: fragments of a stage nobody writes, which nobody uses)
+        half_step(std::false_type{}, std::integral_constant<int, 1>{}, ring + stage, 0, nullptr, nullptr, nullptr);
     }
 
     if constexpr (KS > 1) {
@@ -280,15 +302,16 @@ static hipError_t launch_tile(const void* a, const void* b, void* c, int M, int 
 // The tile shapes, what their steps cost on MI355X, and the choice between them.  Beside a launch, the same for all, a call
 // takes about
 //   (tiles on the busiest of the compute units) * (steps of a tile / KS) * us per step,
-// and the shape with the smallest product is taken.  Measured (us per 64-wide k step of one tile; one tile on a unit /
-// several of them after or next to each other), and what that makes of 8192^3:
-//   256x256  8 waves   1.50 / 1.57    0.80 ms (measured 0.82 to 0.84 = 1.3 PFLOP/s; least L2 and LDS traffic per flop)
-//   192x256  8 waves   1.15 / 1.25    0.95 ms       64x128  4 waves  0.42 / 0.34   1.46 ms
-//   128x256  8 waves   0.88 / 0.93    0.95 ms       64x64   4 waves  0.25 / 0.24   2.05 ms (L2 bound: 16 KB per 0.5 MFLOP)
-//   256x128  8 waves   0.87 / 0.92    0.94 ms       64x64  K split in 2:  0.43 / 0.53 per two steps
-//   128x192  8 waves   0.76 / 0.735   1.04 ms       32x64  K split in 4:  0.60 / 0.75 per four steps
-//   128x128  8 waves   0.57 / 0.56    1.15 ms
-//   128x128  4 waves, two workgroups per compute unit: 0.68 alone, 0.95 for two   1.02 ms
+// and the shape with the smallest product is taken.  Us per 64-wide k step of one tile (one tile on a unit / several of them after or
+// next to each other), fitted to 900 sizes of up to 10000 a side for which every shape was timed: the choice takes 1.8 % more than the
+// best shape, on average over the sizes of 5 us and more.  8192^3 with each:
+//   256x256  8 waves   1.40 / 1.485   0.76 ms (1.45 PFLOP/s; least L2 and LDS traffic per flop)
+//   192x256  8 waves   1.15 / 1.25    0.91 ms       64x128  4 waves  0.42 / 0.34   1.37 ms
+//   128x256  8 waves   0.88 / 0.93    0.87 ms       64x64   4 waves  0.228 / 0.24  2.5 ms (L2 bound: 16 KB per 0.5 MFLOP)
+//   256x128  8 waves   0.87 / 0.92    0.86 ms       64x64  K split in 2:  0.446 / 0.53 per two steps
+//   128x192  8 waves   0.645 / 0.846  0.99 ms       32x64  K split in 4:  0.60 / 0.75 per four steps
+//   128x128  8 waves   0.454 / 0.56   1.15 ms
+//   128x128  4 waves, two workgroups per compute unit: 0.68 alone, 1.09 for two   1.00 ms
 // (A single 256x256 tile with four waves of 128x128, one per SIMD, took 0.96 ms: nothing filled the gaps of a
 // wave.  Two waves per SIMD and 16x16x32 MFMAs, which move half the accumulator bits per flop of the 32x32x16 form, do.
 // 32x64 with K split in 2 would be chosen for 65 to 128 k only, where it gains nothing: 3.7 us either way, the launch.)
@@ -302,16 +325,16 @@ struct GemmChoice {
     bool wide;              // 64-bit lane offsets
 };
 static const GemmChoice kGemmChoices[] = {
-    {launch_tile<256, 256, 2, 4, 1, 2, 2>, 512, 256, 256, 1, 1.50f, 1.57f, false},
+    {launch_tile<256, 256, 2, 4, 1, 2, 2>, 512, 256, 256, 1, 1.40f, 1.485f, false},
     {launch_tile<192, 256, 2, 4, 1, 2, 2>, 512, 192, 256, 1, 1.15f, 1.25f, false},
     {launch_tile<256, 128, 4, 2, 1, 3, 2>, 512, 256, 128, 1, 0.87f, 0.92f, false},
     {launch_tile<128, 256, 2, 4, 1, 3, 2>, 512, 128, 256, 1, 0.88f, 0.93f, false},
-    {launch_tile<128, 192, 2, 4, 1, 3, 2>, 512, 128, 192, 1, 0.76f, 0.735f, false},
-    {launch_tile<128, 128, 2, 4, 1, 4, 2>, 512, 128, 128, 1, 0.57f, 0.56f, false},
-    {launch_tile<128, 128, 2, 2, 1, 2, 2>, 256, 128, 128, 1, 0.68f, 0.475f, false},
+    {launch_tile<128, 192, 2, 4, 1, 3, 2>, 512, 128, 192, 1, 0.645f, 0.846f, false},
+    {launch_tile<128, 128, 2, 4, 1, 4, 2>, 512, 128, 128, 1, 0.454f, 0.56f, false},
+    {launch_tile<128, 128, 2, 2, 1, 2, 2>, 256, 128, 128, 1, 0.68f, 0.547f, false},
     {launch_tile<64, 128, 2, 2, 1, 3, 2>, 256, 64, 128, 1, 0.42f, 0.34f, false},
-    {launch_tile<64, 64, 2, 2, 1, 3, 2>, 256, 64, 64, 1, 0.25f, 0.24f, false},
-    {launch_tile<64, 64, 2, 2, 2, 3, 2>, 512, 64, 64, 2, 0.43f, 0.53f, false},
+    {launch_tile<64, 64, 2, 2, 1, 3, 2>, 256, 64, 64, 1, 0.228f, 0.24f, false},
+    {launch_tile<64, 64, 2, 2, 2, 3, 2>, 512, 64, 64, 2, 0.446f, 0.53f, false},
     {launch_tile<32, 64, 1, 4, 4, 3, 4>, 1024, 32, 64, 4, 0.60f, 0.75f, false},
     {launch_tile<256, 256, 2, 4, 1, 2, 2, true>, 512, 256, 256, 1, 1.50f, 1.57f, true},
     {launch_tile<128, 256, 2, 2, 1, 3, 1, true>, 256, 128, 256, 1, 1.01f, 1.02f, true},
