@@ -162,7 +162,9 @@ void attn_bwd_dkdv_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K
     const int h = lane >> 5;
     const int j16 = lane & 15;
     const int ghalf = (lane >> 4) & 1;
-    const float c = scale * kLog2e;
+    // LSE / scale has to stay finite: scales below 1e-36 leave every score at 0 in either form
+    const float score_scale = __builtin_fmaxf(scale, 1e-36f);
+    const float c = score_scale * kLog2e;
 
     // Work unit: one key tile, or, when causal, the pair (u, last - u): tile u loops over the
     // query blocks from its diagonal on, so the pairs carry (nearly) the same work and the static
@@ -313,7 +315,7 @@ void attn_bwd_dkdv_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K
     // A wave turns its copy of a block's statistics, once they are here, into -LSE / scale and -Delta.  The accumulators of S
     // and dP start from these, so that scale * S - LSE takes the vector ALU one multiplication and dP - Delta nothing.
     // (Three instructions a block instead of two more for each of a lane's 16 scores.)
-    const float stat_mul = lane < 32 ? -1.0f / scale : -1.0f;
+    const float stat_mul = lane < 32 ? -1.0f / score_scale : -1.0f;
     auto wave_stat = [&](int stage) { return (float*)(ring + stage + 2 * S::kQTileBytes + wave * 256); };
     auto scale_stat = [&](int stage) { float* st = wave_stat(stage) + lane; *st = *st * stat_mul; };
 
@@ -861,7 +863,8 @@ void attn_bwd_dkdv_wide_kernel(const bf16* __restrict__ Q, const bf16* __restric
     const int h = lane >> 5;
     const int j16 = lane & 15;
     const int ghalf = (lane >> 4) & 1;
-    const float c = scale * kLog2e;
+    const float score_scale = __builtin_fmaxf(scale, 1e-36f);
+    const float c = score_scale * kLog2e;
     const int heads_per_kv = hq / hkv;
     const int off = TAIL ? Nk - Nq : 0;
     char* const mine = own + wave * S::kWaveBytes;
@@ -957,7 +960,7 @@ void attn_bwd_dkdv_wide_kernel(const bf16* __restrict__ Q, const bf16* __restric
             load_global_to_lds4_untracked(src, base + 2 * S::kQTileBytes + wave * 256);
         }
     };
-    const float stat_mul = lane < 32 ? -1.0f / scale : -1.0f;
+    const float stat_mul = lane < 32 ? -1.0f / score_scale : -1.0f;
     auto wave_stat = [&](int stage) { return (float*)(ring + stage + 2 * S::kQTileBytes + wave * 256); };
     auto scale_stat = [&](int stage) __attribute__((always_inline)) { float* st = wave_stat(stage) + lane; *st = *st * stat_mul; };
 
