@@ -700,8 +700,7 @@ void attn_fwd_phase_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ 
         if (n_my > t) {
             scores(sa, t);
             mask(sa, t);
-            raise(sa);
-            if (SPLIT && m_run == -INFINITY) mc = 0.f;       // (the exponentials of this tile are 0 then)
+            raise(sa);                           // (no visible key yet: mc stays -inf, and this tile and the next are done again)
         }
         phase_end();                             // (K of the first tile is about to be overwritten)
 #pragma unroll 1
