@@ -160,10 +160,9 @@ void attn_fwd_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K, con
     float m_run = -INFINITY;   // running max of raw scores (shared by both half-waves)
     float l_run = 0.f;         // running sum, partial: this lane's 32 of the 64 keys per tile
 
-    // A split may hold no key that a row sees - beyond its diagonal, or with scores of -inf that the caller masks keys
-    // with: its maximum stays -inf, and its exponents are then taken against 0, so that P = 2^-inf = 0.  (Without a split
-    // every row sees key 0 under the causal mask, and a row that begins with a tile of -inf is NaN.)
-    auto finite_max = [&](float m) { return SPLIT && m == -INFINITY ? 0.f : m; };
+    // The tiles so far may hold no key that a row sees - beyond its diagonal in a split, or with scores of -inf that the
+    // caller masks keys with: the maximum stays -inf, and the exponents are then taken against 0, so that P = 2^-inf = 0.
+    auto finite_max = [&](float m) { return m == -INFINITY ? 0.f : m; };
 
     auto compute_tile = [&](int stage, int tile) {
         const int j0 = tile * S::kTileKV;
@@ -517,10 +516,9 @@ void attn_fwd_phase_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ 
                 }
         }
     };
-    // A split may hold no key that a row sees - beyond its diagonal, or with scores of -inf that the caller masks keys
-    // with: its maximum stays -inf, and its exponents are then taken against 0, so that P = 2^-inf = 0.  (Without a split
-    // every row sees key 0 under the causal mask, and a row that begins with a tile of -inf is NaN.)
-    auto finite_mc = [&]() { return SPLIT && m_run == -INFINITY ? 0.f : m_run * c; };
+    // The tiles so far may hold no key that a row sees - beyond its diagonal in a split, or with scores of -inf that the
+    // caller masks keys with: the maximum stays -inf, and the exponents are then taken against 0, so that P = 2^-inf = 0.
+    auto finite_mc = [&]() { return m_run == -INFINITY ? 0.f : m_run * c; };
     auto raise = [&](const f32x16 (&s)[2]) __attribute__((always_inline)) {
         float mx = s[0][0];
 #pragma unroll
@@ -530,7 +528,7 @@ void attn_fwd_phase_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ 
         const float m_old = m_run;
         m_run = __builtin_fmaxf(m_run, half_max(mx));
         mc = m_run * c;
-        const float corr = __builtin_amdgcn_exp2f(SPLIT && m_run == -INFINITY ? m_old : (m_old - m_run) * c);
+        const float corr = __builtin_amdgcn_exp2f(m_run == -INFINITY ? m_old : (m_old - m_run) * c);
         l_run *= corr;
 #pragma unroll
         for (int db = 0; db < D / 32; db++)

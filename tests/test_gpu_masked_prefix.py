@@ -56,6 +56,22 @@ def test_split_calls(B, Hq, Hkv, Nq, Nk, D, causal, padding):
     check(o, lse, q, k, v, causal, 1 / math.sqrt(D))
 
 
+@pytest.mark.parametrize("padding", [64, 128, 700, "holes"])
+@pytest.mark.parametrize("B,Hq,Hkv,Nq,Nk,D,causal", [
+    (2, 16, 2, 900, 3000, 64, False), (2, 16, 2, 900, 3000, 64, True), (2, 16, 2, 1200, 3000, 128, False), (2, 16, 2, 1200, 3000, 128, True),
+    (16, 16, 16, 40, 1000, 64, False), (16, 16, 16, 40, 1000, 128, False), (4, 16, 16, 1024, 1024, 128, False), (1, 2, 2, 300, 900, 64, False),
+    (1, 4, 4, 100, 128, 64, False)])
+def test_unsplit_calls(B, Hq, Hkv, Nq, Nk, D, causal, padding):
+    """Whether a call is split depends on its sizes; what it answers does not."""
+    if padding != "holes" and padding >= Nk:
+        padding = Nk - 1
+    q, k, v = masked_inputs(B, Hq, Hkv, Nq, Nk, D, padding)
+    assert attn.tk_attn_fwd_scratch_bytes(B, Hq, Hkv, Nq, Nk, D, causal) == 0, "this shape is not meant to be split"
+    print(f"launch masked B{B} Hq{Hq} Hkv{Hkv} Nq{Nq} Nk{Nk} D{D} causal={causal} {padding}", flush=True)
+    o, lse = attn.rect_fwd(q, k, v, causal, 1 / math.sqrt(D))
+    check(o, lse, q, k, v, causal, 1 / math.sqrt(D))
+
+
 @pytest.mark.parametrize("padding", [64, 700, "holes"])
 @pytest.mark.parametrize("Hq,D", [(96, 64), (96, 128), (8, 128)])
 def test_decode(Hq, D, padding):
