@@ -333,7 +333,13 @@ void attn_fwd_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K, con
 // get no closer to the end of the number range than with a maximum that is kept within 2^8, as the kernel of few rows does.
 // What P, O and l are multiplied with has no part in their rounding, but a P that is 1 has none at all: where one key
 // dominates a row that was not done again, O is as exact as any other row's and not more (against fp64, normal data with
-// scores of sigma 1, 4 and 8: 1.78e-3, 2.16e-3, 2.05e-3, with the maximum of every tile within 2^8 1.78e-3, 2.03e-3, 1.88e-3).
+// scores of sigma 1, 4 and 8: 1.78e-3, 2.16e-3, 2.20e-3, with the maximum of every tile within 2^8 1.78e-3, 2.03e-3, 1.88e-3).
+// Where scores are that large, or grow along the keys, a tile that outgrew its maximum is followed by others: doing it again
+// leaves room, the exponents are then taken against 2^16 times its maximum.  (2^24 would do more for scores of sigma 16, but
+// values of V below 1e-36 would lose bits.)  Forward, us, with the maximum of every tile, without the room and with it: sigma
+// 8 B16 H16 N4096 causal D128 1192, 1160, 1063, D64 661, 678, 631; sigma 16 1198, 1242, 1160 and 663, 738, 668; scores that
+// grow by 2^20 from tile to tile 1197, 1327, 1182 and 681, 876, 739; the longest left, D64 B16 H16 N1024 without a mask, keys
+// that grow to sigma 30: 86, 110, 105.
 //
 // Tiles go to an LDS ring by direct loads: four stages, issued three tiles ahead, with two groups (one workgroup on a compute
 // unit); two stages with one (two or three workgroups to a unit, which cover each other's waits: four stages and one
@@ -469,7 +475,7 @@ void attn_fwd_phase_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ 
     for (int db = 0; db < D / 32; db++)
 #pragma unroll
         for (int r = 0; r < 16; r++) o_acc[db][r] = 0.f;
-    float m_run = -INFINITY;   // what the exponents are taken against (raw score, shared by both half-waves), and its multiple in
+    float m_run = -INFINITY;   // what the exponents are taken against (a raw score, shared by both half-waves), and its multiple in
     float mc = -INFINITY;      // base 2; -inf: exponentials against it are infinite or not a number, and the tile is done again
     float l_run = 0.f;         // running sum, partial: this lane's 32 of the 64 keys per tile
     bf16x8 pb[4];              // P of the tile in hand, 16 keys each
@@ -522,14 +528,14 @@ void attn_fwd_phase_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ 
     // The tiles so far may hold no key that a row sees - beyond its diagonal in a split, or with scores of -inf that the
     // caller masks keys with: the maximum stays -inf, and the exponents are then taken against 0, so that P = 2^-inf = 0.
     auto finite_mc = [&]() { return m_run == -INFINITY ? 0.f : m_run * c; };
-    auto raise = [&](const f32x16 (&s)[2]) __attribute__((always_inline)) {
+    auto raise = [&](const f32x16 (&s)[2], float above) __attribute__((always_inline)) {
         float mx = s[0][0];
 #pragma unroll
         for (int r = 1; r < 16; r++) mx = __builtin_fmaxf(mx, s[0][r]);
 #pragma unroll
         for (int r = 0; r < 16; r++) mx = __builtin_fmaxf(mx, s[1][r]);
         const float m_old = m_run;
-        m_run = __builtin_fmaxf(m_run, half_max(mx));
+        m_run = __builtin_fmaxf(m_run, half_max(mx) + above);
         mc = m_run * c;
         const float corr = __builtin_amdgcn_exp2f(m_run == -INFINITY ? m_old : (m_old - m_run) * c);
         l_run *= corr;
@@ -539,6 +545,8 @@ void attn_fwd_phase_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ 
             for (int r = 0; r < 16; r++) o_acc[db][r] *= corr;
     };
     constexpr float kMaxSum = 8192.f;
+    // 16 in the base-2 exponent, in a scalar register (finite for the smallest scales, too)
+    const float redo_above = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, __builtin_fminf(16.f / c, 1e30f))));
     // P = 2^(S*c - against): element e of 32 is register e % 16 of block e / 16.  The sum is formed in the order of the elements
     auto exponential = [&](const f32x16 (&s)[2], int e, float against) __attribute__((always_inline)) {
         return __builtin_amdgcn_exp2f(__builtin_fmaf(s[e >> 4][e & 15], c, -against));
@@ -606,7 +614,7 @@ void attn_fwd_phase_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ 
         phase_end();
         if (n_my > t) {
             mask(s, t);
-            raise(s);
+            raise(s, 0.f);
             l_run = exponentials(s, finite_mc());
             read_v_ahead(t);
         }
@@ -631,7 +639,7 @@ void attn_fwd_phase_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ 
             mask(s, t + 1);
             float sum = exponentials(s, mc);
             if (too_large(sum)) {
-                raise(s);
+                raise(s, redo_above);
                 sum = exponentials(s, finite_mc());
             }
             l_run += sum;
@@ -689,7 +697,7 @@ void attn_fwd_phase_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ 
                 sum = exponentials(s, mc);
             }
             if (too_large(sum)) {
-                raise(s);
+                raise(s, redo_above);
                 sum = exponentials(s, finite_mc());
             }
             l_run += sum;
@@ -701,7 +709,7 @@ void attn_fwd_phase_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ 
         if (n_my > t) {
             scores(sa, t);
             mask(sa, t);
-            raise(sa);                           // (no visible key yet: mc stays -inf, and this tile and the next are done again)
+            raise(sa, 0.f);                           // (no visible key yet: mc stays -inf, and this tile and the next are done again)
         }
         phase_end();                             // (K of the first tile is about to be overwritten)
 #pragma unroll 1

@@ -42,3 +42,28 @@ def test_large_values(B, H, Nq, Nk, D, causal, x):
         err = (o[b, h].double() - o_ref).abs() / ((p @ vd.abs() + o_ref.abs()) / 256 + 1e-4 * largest)
         assert err.max() <= 1, (b, h, err.max())
         assert (lse[b, h].double() - torch.logsumexp(s, -1)).abs().max() <= 1e-3, (b, h)
+
+
+@pytest.mark.parametrize("step", [5.0, 40.0])
+@pytest.mark.parametrize("B,H,Nq,Nk,D,causal", [(1, 2, 1024, 1024, 64, False), (4, 16, 1024, 1024, 128, False), (1, 2, 130, 3900, 128, True), (1, 2, 33, 700, 64, True)])
+def test_small_values(B, H, Nq, Nk, D, causal, step):
+    """Scores that grow by 2^step from tile to tile, so that tiles are done again with room above them, and the smallest V."""
+    g = torch.Generator(device="cuda").manual_seed(Nq + Nk + D)
+    q, k, v = (torch.randn(B, H, n, D, generator=g, device="cuda") for n in (Nq, Nk, Nk))
+    scale = 1 / math.sqrt(D)
+    q[..., 0] = 1.0
+    k[..., 0] = (torch.arange(Nk, device="cuda") // 64) * (step * math.log(2) / scale)
+    q, k, v = q.to(torch.bfloat16), k.to(torch.bfloat16), (v * 1e-36).to(torch.bfloat16)
+    print(f"launch forward B{B} H{H} Nq{Nq} Nk{Nk} D{D} causal={causal} step={step}", flush=True)
+    o, lse = attn.rect_fwd(q, k, v, causal, scale)
+    for b, h in {(0, 0), (B - 1, H - 1)}:
+        s = q[b, h].double() @ k[b, h].double().T * scale
+        if causal:
+            i = torch.arange(Nq, device="cuda")[:, None] + (Nk - Nq)
+            s = s.masked_fill(torch.arange(Nk, device="cuda")[None, :] > i, -math.inf)
+        p, vd = torch.softmax(s, -1), v[b, h].double()
+        o_ref = p @ vd
+        # an fp32 number of 1e-36 / 2^16 has 12 bits of its own left, 2^-13 of it is lost in each addition's rounding
+        err = (o[b, h].double() - o_ref).abs() / ((p @ vd.abs() + o_ref.abs()) / 256 + 1e-3 * 1e-36)
+        assert err.max() <= 1, (b, h, err.max())
+        assert (lse[b, h].double() - torch.logsumexp(s, -1)).abs().max() <= 1e-3 + 1e-6 * lse[b, h].abs().max(), (b, h)
