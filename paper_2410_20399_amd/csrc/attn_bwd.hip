@@ -815,8 +815,8 @@ static hipError_t launch_dkdv_tt(const void* q, const void* k, const void* v, co
 //                   fragments of the next step
 // What bounds it: the second half has 4.6 vector instructions to an MFMA, which a single wave issues in about 40 of the 32
 // cycles that the matrix pipe takes; and power (without its loads the kernel takes 13 % less time on normal data, on
-// constant data 5 %).  dK/dV alone, us, 128 keys and 256: B16 H16 N4096 without a mask 3680, 3303; causal 2020, 1915; causal and
-// storing dS 2385, 2344.  Two waves per SIMD in turns, as in the forward, do not fit: 256 registers a wave.
+// constant data 5 %).  dK/dV alone, us, 128 keys and 256: B16 H16 N4096 without a mask 3680, 3300; causal 2020, 1880; causal and
+// storing dS 2385, 2250 (with 22 and 24 registers in scratch memory 1945, 2378).  Two waves per SIMD in turns, as in the forward, do not fit: 256 registers a wave.
 //
 // The accumulators are only touched by inline assembly, which the compiler sees as writing them at once: results are read, and
 // copies made in front of a product, behind the waits that the hardware wants (mfma32_acc_wait, and the s_nop behind the last).
@@ -969,26 +969,30 @@ void attn_bwd_dkdv_wide_kernel(const bf16* __restrict__ Q, const bf16* __restric
     const int trq_row = 4 * h + (j16 >> 2);
     const int trq_lane = trq_row * S::kRowBytes + (((2 * ghalf + ((j16 & 3) >> 1)) ^ swz<D>(trq_row)) << 4) + ((j16 & 1) << 3);
 
+    // Offsets that depend on the lane alone are formed from a copy that the compiler does not see through, where they are used: it would
+    // keep them for the whole kernel otherwise, which has no registers to spare (up to 24 went to scratch memory).
+    auto opaque = [](int x) __attribute__((always_inline)) { asm volatile("" : "+v"(x)); return x; };
     bf16x8 kf[2][kSteps];                   // K fragments of the wave's two halves of 32 keys
     f32x16 dk_acc[2][D / 32], dv_acc[2][D / 32], sc[2], dc[2], st_l, st_d;
     struct Products { bf16x8 p[2][2], d[2][2]; };       // bf16 P, dS of a block: [half][16 queries]
     Products even, odd;
 
     auto load_kv = [&](int bh, int kt) __attribute__((always_inline)) {
+        const int ln = opaque(lane);
         const int key0 = kt * S::kTileKV + wave * 64;
         const size_t head_row = (size_t)bh * Nk;
         const int key_first = !TAIL || key0 < Nk ? key0 : Nk - 1, last = TAIL ? Nk - 1 - key_first : 63;
 #pragma unroll
         for (int it = 0; it < S::kWaveBytes / 1024; it++) {
-            const int r = it * 4 + (lane >> 4);
-            load_global_to_lds16_sbase_untracked(V + (head_row + key_first) * D, (uint32_t)((TAIL && r > last ? last : r) * D + ((j16 ^ swz<D>(r)) * 8)) * 2, mine + it * 1024);
+            const int r = it * 4 + (ln >> 4);
+            load_global_to_lds16_sbase_untracked(V + (head_row + key_first) * D, (uint32_t)((TAIL && r > last ? last : r) * D + (((ln & 15) ^ swz<D>(r)) * 8)) * 2, mine + it * 1024);
         }
 #pragma unroll
         for (int b = 0; b < 2; b++) {
-            const int key = key0 + 32 * b + l32;
+            const int key = key0 + 32 * b + (ln & 31);
             const bf16* row = K + (head_row + ((!TAIL || key < Nk) ? key : Nk - 1)) * D;
 #pragma unroll
-            for (int kb = 0; kb < kSteps; kb++) kf[b][kb] = *(const bf16x8*)(row + kb * 16 + h * 8);
+            for (int kb = 0; kb < kSteps; kb++) kf[b][kb] = *(const bf16x8*)(row + kb * 16 + (ln >> 5) * 8);
         }
     };
     auto keep_k = [&]() __attribute__((always_inline)) {        // (the wait for K belongs here and not at its first use)
@@ -1010,7 +1014,6 @@ void attn_bwd_dkdv_wide_kernel(const bf16* __restrict__ Q, const bf16* __restric
     };
     struct Rows { bf16x8 q[kSteps], d[kSteps], v[2][kSteps]; };
     struct Columns { bf16x8 q[kSteps], d[kSteps]; };
-    auto opaque = [](int x) __attribute__((always_inline)) { asm volatile("" : "+v"(x)); return x; };
     auto read_row = [&](Rows& f, int rl, int stage, int kb, int part) __attribute__((always_inline)) {
         const int at = rl ^ ((2 * kb) << 4);
         if (part == 0) { f.q[kb] = lds_read_b128(ring + stage, at); f.d[kb] = lds_read_b128(ring + stage + S::kQTileBytes, at); }
@@ -1123,12 +1126,23 @@ void attn_bwd_dkdv_wide_kernel(const bf16* __restrict__ Q, const bf16* __restric
             }
         };
         auto mask = [&]() __attribute__((always_inline)) {
-            if (__builtin_expect((CAUSAL && i0 + off < jw0 + 63) || (TAIL && SPILL && jw0 + 63 >= Nk), 0)) {
+            if (CAUSAL && __builtin_expect(i0 + off < jw0 + 63, 0)) {
+                // register r <-> query i0 + 4h + (a constant): one difference per lane and half.  (Sixteen offsets that the compiler formed
+                // once lay in scratch memory, and their reload waited for the fetch of block n+3 as well.)
+#pragma unroll
+                for (int b = 0; b < 2; b++) {
+                    const int first_seen = opaque(my_j + 32 * b - off - i0 - 4 * h);
+#pragma unroll
+                    for (int r = 0; r < 16; r++)
+                        if (8 * (r >> 2) + (r & 3) < first_seen) sc[b][r] = -INFINITY;
+                }
+            }
+            if (TAIL && SPILL && __builtin_expect(jw0 + 63 >= Nk, 0)) {
 #pragma unroll
                 for (int b = 0; b < 2; b++)
 #pragma unroll
                     for (int r = 0; r < 16; r++)
-                        if ((CAUSAL && i0 + 8 * (r >> 2) + 4 * h + (r & 3) + off < my_j + 32 * b) || (TAIL && SPILL && my_j + 32 * b >= Nk)) sc[b][r] = -INFINITY;
+                        if (my_j + 32 * b >= Nk) sc[b][r] = -INFINITY;
             }
         };
         // Second half: dV^T, dK^T of the block before, and beside them P, dS of this block, one element for each matrix instruction.
@@ -1230,6 +1244,7 @@ void attn_bwd_dkdv_wide_kernel(const bf16* __restrict__ Q, const bf16* __restric
         const size_t head = (size_t)bh * Nk * D;
         char* const turn = ring + p_stage + wave * (32 * S::kEpiPitch);      // (the stage the next block will be fetched into)
         auto store_tile = [&](const f32x16 (&acc)[D / 32], float mul, bf16* dst, int key0) __attribute__((always_inline)) {
+            const int ln = opaque(lane), l = ln & 31;
 #pragma unroll
             for (int half = 0; half < D / 64; half++) {
 #pragma unroll
@@ -1238,14 +1253,14 @@ void attn_bwd_dkdv_wide_kernel(const bf16* __restrict__ Q, const bf16* __restric
                     for (int q = 0; q < 4; q++) {
                         bf16x2 a = cvt2(acc[db][4 * q] * mul, acc[db][4 * q + 1] * mul);
                         bf16x2 b = cvt2(acc[db][4 * q + 2] * mul, acc[db][4 * q + 3] * mul);
-                        *(bf16x4*)(turn + l32 * S::kEpiPitch + (32 * (db & 1) + 8 * q + 4 * h) * 2) = __builtin_shufflevector(a, b, 0, 1, 2, 3);
+                        *(bf16x4*)(turn + l * S::kEpiPitch + (32 * (db & 1) + 8 * q + 4 * (ln >> 5)) * 2) = __builtin_shufflevector(a, b, 0, 1, 2, 3);
                     }
 #pragma unroll
                 for (int i = 0; i < 4; i++) {
-                    const int row = i * 8 + (lane >> 3);
-                    const char* src = turn + row * S::kEpiPitch + (lane & 7) * 16;
+                    const int row = i * 8 + (ln >> 3);
+                    const char* src = turn + row * S::kEpiPitch + (ln & 7) * 16;
                     const bf16x4 lo = *(const bf16x4*)src, hi = *(const bf16x4*)(src + 8);
-                    if (!TAIL || key0 + row < Nk) *(bf16x8*)(dst + (size_t)(key0 + row) * D + 64 * half + (lane & 7) * 8) = concat(lo, hi);
+                    if (!TAIL || key0 + row < Nk) *(bf16x8*)(dst + (size_t)(key0 + row) * D + 64 * half + (ln & 7) * 8) = concat(lo, hi);
                 }
             }
         };

@@ -358,7 +358,8 @@ struct FwdPhaseShape {
     static constexpr int kStages = GROUPS == 2 ? 4 : 2;
     static constexpr int kLoads = kTileKV * kChunksPerRow / kThreads;   // per thread and tensor
     static constexpr int kTileLoads = 2 * kLoads;
-    // waves per SIMD to compile for.  One group: two (D = 128) or three (D = 64) workgroups share a compute unit
+    // waves per SIMD to compile for.  One group: two (D = 128) or three (D = 64) workgroups share a compute unit; of the 168
+    // registers that leaves at D = 64 the ragged causal and the split kernels lack one to six (prologue, epilogue, masked tiles)
     static constexpr int kWavesPerSimd = D == 128 ? 2 : 3;
 };
 
