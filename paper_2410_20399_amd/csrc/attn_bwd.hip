@@ -806,7 +806,8 @@ static hipError_t launch_dkdv_tt(const void* q, const void* k, const void* v, co
 // ------------------------------------------------------------------------------------------
 // kernel 2 at D = 128 for large launches: 64 keys a wave
 // ------------------------------------------------------------------------------------------
-// The same work in the same order (the bits of dK, dV and dS are those of the kernel above), with tiles of 256 keys: every Q, dO
+// The same work in the same order (the bits of dK, dV and dS are those of the kernel above, except that a NaN of its masked blocks may
+// be a number here), with tiles of 256 keys: every Q, dO
 // row that comes from L2, and every fragment that is read from LDS, serves twice the matrix instructions.  One wave per SIMD:
 // the dK^T, dV^T accumulators take the whole accumulator half of the register file; K stays in registers, V in LDS.  A step is
 //     first half    S, dP of block n (32 MFMAs)  next to  the LDS reads of its rows, the fetch of block n+3, the statistics of
@@ -815,8 +816,8 @@ static hipError_t launch_dkdv_tt(const void* q, const void* k, const void* v, co
 //                   fragments of the next step
 // What bounds it: the second half has 4.6 vector instructions to an MFMA, which a single wave issues in about 40 of the 32
 // cycles that the matrix pipe takes; and power (without its loads the kernel takes 13 % less time on normal data, on
-// constant data 5 %).  dK/dV alone, us, 128 keys and 256: B16 H16 N4096 without a mask 3680, 3300; causal 2020, 1880; causal and
-// storing dS 2385, 2250 (with 22 and 24 registers in scratch memory 1945, 2378).  Two waves per SIMD in turns, as in the forward, do not fit: 256 registers a wave.
+// constant data 5 %).  dK/dV alone, us, 128 keys and 256: B16 H16 N4096 without a mask 3680, 3300; causal 2020, 1900; causal and
+// storing dS 2385, 2270 (with 22 and 24 registers in scratch memory 1945, 2378).  Two waves per SIMD in turns, as in the forward, do not fit: 256 registers a wave.
 //
 // The accumulators are only touched by inline assembly, which the compiler sees as writing them at once: results are read, and
 // copies made in front of a product, behind the waits that the hardware wants (mfma32_acc_wait, and the s_nop behind the last).
@@ -835,12 +836,17 @@ struct DkdvWideShape {
     static constexpr int kStages = 5;
     static constexpr int kRowBytes = D * 2, kChunksPerRow = D / 8;
     static constexpr int kQTileBytes = kTileQ * kRowBytes;
-    static constexpr int kStageBytes = 2 * kQTileBytes + kWaves * 256;
+    static constexpr int kStageBytes = 2 * kQTileBytes;
     static constexpr int kQLoads = kTileQ * kChunksPerRow / kThreads;
     static constexpr int kBlockLoads = 2 * kQLoads + 1;
     static constexpr int kWaveBytes = 64 * kRowBytes;   // a wave's V tile
-    static constexpr int kEpiPitch = 128 + 8;           // the epilogue turns 32 rows x 64 columns around at a time,
+    static constexpr int kEpiPitch = 128;               // the epilogue turns 32 rows x 64 columns around at a time,
     static_assert(kWaves * 32 * kEpiPitch <= kStageBytes, "in the ring stage that is free at the end of a pass");
+    // Behind the ring: rows of zeros, the rows 0, 8, 16 and 24 of a Q and of a dO block that are nothing but zeros (the reads of
+    // columns use the rows between them only through a lane's offset), and between them the statistics of the stages, 256 bytes a wave.
+    static constexpr int kZeros = kStages * kStageBytes, kZeroPitch = 8 * kRowBytes;
+    static constexpr int kRingBytes = kZeros + 7 * kZeroPitch + kRowBytes;
+    static_assert(kStages <= 7 && kRowBytes + kWaves * 256 <= kZeroPitch && kStageBytes == 8 * kZeroPitch, "the statistics of stage s lie behind the zeros of row 8 s");
 };
 
 template <bool CAUSAL, bool TAIL, bool SPILL>
@@ -853,7 +859,7 @@ void attn_bwd_dkdv_wide_kernel(const bf16* __restrict__ Q, const bf16* __restric
 {
     using S = DkdvWideShape;
     constexpr int D = S::D, kSteps = D / 16;
-    __shared__ __attribute__((aligned(1024))) char ring[S::kStages * S::kStageBytes];
+    __shared__ __attribute__((aligned(1024))) char ring[S::kRingBytes];
     __shared__ __attribute__((aligned(1024))) char own[S::kWaves * S::kWaveBytes];
 
     const int tid = threadIdx.x;
@@ -942,6 +948,7 @@ void attn_bwd_dkdv_wide_kernel(const bf16* __restrict__ Q, const bf16* __restric
     auto prepare_turn = [&]() __attribute__((always_inline)) {
         if (__builtin_expect(p_left == 0, 0)) producer_turn();
     };
+    auto wave_stat = [&](int stage) { return (float*)(ring + S::kZeros + S::kRowBytes + stage / 8 + wave * 256); };
     auto emit = [&](int which) __attribute__((always_inline)) {
         char* base = ring + e_stage;
         if (which < 2 * S::kQLoads) {       // Q rows, then dO rows
@@ -957,11 +964,10 @@ void attn_bwd_dkdv_wide_kernel(const bf16* __restrict__ Q, const bf16* __restric
         } else {
             const float* src = stat_src + e_row;
             if (TAIL && e_i0 + l32 >= Nq) src = lane < 32 ? g_lse_pad : Delta + e_head_row + (Nq - 1);
-            load_global_to_lds4_untracked(src, base + 2 * S::kQTileBytes + wave * 256);
+            load_global_to_lds4_untracked(src, (const char*)wave_stat(e_stage));
         }
     };
     const float stat_mul = lane < 32 ? -1.0f / score_scale : -1.0f;
-    auto wave_stat = [&](int stage) { return (float*)(ring + stage + 2 * S::kQTileBytes + wave * 256); };
     auto scale_stat = [&](int stage) __attribute__((always_inline)) { float* st = wave_stat(stage) + lane; *st = *st * stat_mul; };
 
     // ---- per-lane LDS offsets
@@ -1046,8 +1052,9 @@ void attn_bwd_dkdv_wide_kernel(const bf16* __restrict__ Q, const bf16* __restric
         }
         load_kv(bh, kt);
     }
+    *(uint64_t*)(ring + S::kZeros + (tid >> 5) * S::kZeroPitch + (tid & 31) * 8) = 0;
     keep_k();
-    wait_vmcnt<0>();
+    wait_vmcnt_lds_done<0>();
     scale_stat(0);
     step_end();
 
@@ -1090,9 +1097,9 @@ void attn_bwd_dkdv_wide_kernel(const bf16* __restrict__ Q, const bf16* __restric
         };
         // First half of a step: S, dP of its block (both halves of the keys, whose statistics are in sc, dc already).  Beside the
         // matrix instructions: the fetch of the block three ahead and the statistics of the next one.
-        auto scores = [&](int stage, int stage_next, int stage_last, char* ds_last, const Products& last, bool first) __attribute__((always_inline)) {
+        auto scores = [&](int stage, int stage_next, int cols, int col_lane, char* ds_last, const Products& last, bool first) __attribute__((always_inline)) {
             Rows f;
-            const int rl = opaque(row_lane), tl = opaque(trq_lane);
+            const int rl = opaque(row_lane), tl = opaque(col_lane);
             float* const st = wave_stat(stage_next) + lane;
             float x = 0.f;
 #pragma unroll
@@ -1107,7 +1114,7 @@ void attn_bwd_dkdv_wide_kernel(const bf16* __restrict__ Q, const bf16* __restric
                 sc[1] = mfma32(f.q[kb], kf[1][kb], kb == 0 ? st_l : sc[1]);
                 asm volatile("" : : "v"(sc[1][0]));
                 if (kb + 2 < kSteps) read_row(f, rl, stage, kb + 2, 0);
-                else read_tr(col_d[kb - 6 < 0 ? 0 : kb - 6], tl, ring + stage_last + S::kQTileBytes, kb - 6);
+                else read_tr(col_d[kb - 6 < 0 ? 0 : kb - 6], tl, ring + cols + S::kQTileBytes, kb - 6);
                 __builtin_amdgcn_sched_barrier(0);
                 dc[0] = mfma32(f.d[kb], f.v[0][kb], kb == 0 ? st_d : dc[0]);
                 asm volatile("" : : "v"(dc[0][0]));
@@ -1121,7 +1128,7 @@ void attn_bwd_dkdv_wide_kernel(const bf16* __restrict__ Q, const bf16* __restric
                 dc[1] = mfma32(f.d[kb], f.v[1][kb], kb == 0 ? st_d : dc[1]);
                 asm volatile("" : : "v"(dc[1][0]));
                 if (kb + 2 < kSteps) read_row(f, rl, stage, kb + 2, 1);
-                else read_tr(col_q[kb - 6 < 0 ? 0 : kb - 6], tl, ring + stage_last, kb - 6);
+                else read_tr(col_q[kb - 6 < 0 ? 0 : kb - 6], tl, ring + cols, kb - 6);
                 __builtin_amdgcn_sched_barrier(0);
             }
         };
@@ -1146,10 +1153,10 @@ void attn_bwd_dkdv_wide_kernel(const bf16* __restrict__ Q, const bf16* __restric
             }
         };
         // Second half: dV^T, dK^T of the block before, and beside them P, dS of this block, one element for each matrix instruction.
-        auto products = [&](int stage_last, int stage_next, const Products& last, Products& next, auto has_last, auto has_vector) __attribute__((always_inline)) {
+        auto products = [&](int cols, int col_lane, int stage_next, const Products& last, Products& next, auto has_last, auto has_vector) __attribute__((always_inline)) {
             Columns f;
-            const int tl = opaque(trq_lane);
-            const char* qs = ring + stage_last;
+            const int tl = opaque(col_lane);
+            const char* qs = ring + cols;
             const char* dos = qs + S::kQTileBytes;
             float pe[32], de[32];
             const int rl = opaque(row_lane);
@@ -1189,6 +1196,12 @@ void attn_bwd_dkdv_wide_kernel(const bf16* __restrict__ Q, const bf16* __restric
                 finish(31);
                 pack(pe, 24, next.p[1][1]);
                 pack(de, 24, next.d[1][1]);
+                if (CAUSAL && __builtin_expect(i0 + S::kTileQ - 1 + off < jw0, 0)) {
+#pragma unroll
+                    for (int b = 0; b < 2; b++)
+#pragma unroll
+                        for (int ks = 0; ks < 2; ks++) next.d[b][ks] = bf16x8{};
+                }
                 __builtin_amdgcn_sched_barrier(0);
             }
         };
@@ -1196,18 +1209,21 @@ void attn_bwd_dkdv_wide_kernel(const bf16* __restrict__ Q, const bf16* __restric
             const int stage = c_stage, stage_next = next_stage(stage);
             c_stage = stage_next;
             char* const ds_last = ds;                   // of the block before
+            // Where there is no block before, or the mask took it wholly, P = dS = 0 meet columns of zeros: its rows may hold an
+            // infinity or a NaN.  (A second copy of the step without products does not fit the registers.)
+            const bool none = first || (CAUSAL && i0 + S::kTileQ - 1 + off < jw0);
+            const int cols = none ? S::kZeros : stage_last, col_lane = none ? 0 : trq_lane;
             if (!first) advance();
-            scores(stage, stage_next, stage_last, ds_last, last, first);
+            scores(stage, stage_next, cols, col_lane, ds_last, last, first);
             mask();
-            products(stage_last, stage_next, last, next, std::true_type{}, std::true_type{});
+            products(cols, col_lane, stage_next, last, next, std::true_type{}, std::true_type{});
             prepare_turn();
             // block n+2 has to be here; younger are the loads of this step and, where there are any, its stores (and those of
             // the step before)
             if (SPILL && stores && !first) wait_vmcnt<S::kBlockLoads + 4>(); else wait_vmcnt<S::kBlockLoads>();
             step_end();
         };
-        // ---- the pass, an even number of blocks.  The first step has no block before it: it adds P = dS = 0 times its own block,
-        // instead of a copy of the step without products (whose accumulators would live in other registers).
+        // ---- the pass, an even number of blocks
 #pragma unroll
         for (int b = 0; b < 2; b++)
 #pragma unroll
@@ -1233,7 +1249,7 @@ void attn_bwd_dkdv_wide_kernel(const bf16* __restrict__ Q, const bf16* __restric
             load_kv(nbh, nkt);
         }
         store_ds(ds, odd);
-        products(stage_last, 0, odd, even, std::true_type{}, std::false_type{});
+        products(stage_last, trq_lane, 0, odd, even, std::true_type{}, std::false_type{});
         // the accumulators may be read from here on (the compiler does not know how long the products take)
         asm volatile("s_nop 15\n\ts_nop 15" : "+a"(dv_acc[0][0]), "+a"(dv_acc[0][1]), "+a"(dv_acc[0][2]), "+a"(dv_acc[0][3]));
         asm volatile("" : "+a"(dv_acc[1][0]), "+a"(dv_acc[1][1]), "+a"(dv_acc[1][2]), "+a"(dv_acc[1][3]));
@@ -1253,14 +1269,13 @@ void attn_bwd_dkdv_wide_kernel(const bf16* __restrict__ Q, const bf16* __restric
                     for (int q = 0; q < 4; q++) {
                         bf16x2 a = cvt2(acc[db][4 * q] * mul, acc[db][4 * q + 1] * mul);
                         bf16x2 b = cvt2(acc[db][4 * q + 2] * mul, acc[db][4 * q + 3] * mul);
-                        *(bf16x4*)(turn + l * S::kEpiPitch + (32 * (db & 1) + 8 * q + 4 * (ln >> 5)) * 2) = __builtin_shufflevector(a, b, 0, 1, 2, 3);
+                        *(bf16x4*)(turn + l * S::kEpiPitch + (((4 * (db & 1) + q) ^ (l & 7)) << 4) + 8 * (ln >> 5)) = __builtin_shufflevector(a, b, 0, 1, 2, 3);
                     }
 #pragma unroll
                 for (int i = 0; i < 4; i++) {
                     const int row = i * 8 + (ln >> 3);
-                    const char* src = turn + row * S::kEpiPitch + (ln & 7) * 16;
-                    const bf16x4 lo = *(const bf16x4*)src, hi = *(const bf16x4*)(src + 8);
-                    if (!TAIL || key0 + row < Nk) *(bf16x8*)(dst + (size_t)(key0 + row) * D + 64 * half + (ln & 7) * 8) = concat(lo, hi);
+                    const bf16x8 x = *(const bf16x8*)(turn + row * S::kEpiPitch + (((ln & 7) ^ (row & 7)) << 4));
+                    if (!TAIL || key0 + row < Nk) *(bf16x8*)(dst + (size_t)(key0 + row) * D + 64 * half + (ln & 7) * 8) = x;
                 }
             }
         };
