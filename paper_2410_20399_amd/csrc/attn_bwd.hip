@@ -816,8 +816,8 @@ static hipError_t launch_dkdv_tt(const void* q, const void* k, const void* v, co
 //                   fragments of the next step
 // What bounds it: the second half has 4.6 vector instructions to an MFMA, which a single wave issues in about 40 of the 32
 // cycles that the matrix pipe takes; and power (without its loads the kernel takes 13 % less time on normal data, on
-// constant data 5 %).  dK/dV alone, us, 128 keys and 256: B16 H16 N4096 without a mask 3680, 3300; causal 2020, 1900; causal and
-// storing dS 2385, 2270 (with 22 and 24 registers in scratch memory 1945, 2378).  Two waves per SIMD in turns, as in the forward, do not fit: 256 registers a wave.
+// constant data 5 %).  dK/dV alone, us, 128 keys and 256: B16 H16 N4096 without a mask 3680, 3300; causal 2020, 1870; causal and
+// storing dS 2385, 2255 (with 22 and 24 registers in scratch memory 1945, 2378).  Two waves per SIMD in turns, as in the forward, do not fit: 256 registers a wave.
 //
 // The accumulators are only touched by inline assembly, which the compiler sees as writing them at once: results are read, and
 // copies made in front of a product, behind the waits that the hardware wants (mfma32_acc_wait, and the s_nop behind the last).
@@ -948,7 +948,7 @@ void attn_bwd_dkdv_wide_kernel(const bf16* __restrict__ Q, const bf16* __restric
     auto prepare_turn = [&]() __attribute__((always_inline)) {
         if (__builtin_expect(p_left == 0, 0)) producer_turn();
     };
-    auto wave_stat = [&](int stage) { return (float*)(ring + S::kZeros + S::kRowBytes + stage / 8 + wave * 256); };
+    auto wave_stat = [&](int stage) { return (float*)(ring + S::kZeros + S::kRowBytes + (stage >> 3) + wave * 256); };
     auto emit = [&](int which) __attribute__((always_inline)) {
         char* base = ring + e_stage;
         if (which < 2 * S::kQLoads) {       // Q rows, then dO rows
