@@ -74,6 +74,15 @@ hipError_t launch_attn_bwd_delta(const void* o, const void* d_o, float* delta,
 // LSE stand-in for query rows past the end of a sequence: P = 2^(s - inf) = 0 for them.
 __device__ float g_lse_pad[1] = {INFINITY};
 
+// The scores are formed as scale * (S - LSE / scale), and LSE / scale has to stay finite: where the scale is smaller than this, K
+// is taken 2^64 times smaller and the scale larger.  (What that takes from elements of K below 2^-62 is less than 2^-53 of a
+// score: Q is below 2^128, the scale below 2^-119.)
+constexpr float kLeastScale = 1e-36f;
+__device__ __forceinline__ void shrink_k(bf16x8& k) {
+#pragma unroll
+    for (int i = 0; i < 8; i++) k[i] = (bf16)((float)k[i] * 0x1p-64f);
+}
+
 template <int D>
 struct DkdvShape {
     static constexpr int kWaves = 4;
@@ -162,8 +171,7 @@ void attn_bwd_dkdv_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K
     const int h = lane >> 5;
     const int j16 = lane & 15;
     const int ghalf = (lane >> 4) & 1;
-    // LSE / scale has to stay finite: scales below 1e-36 leave every score at 0 in either form
-    const float score_scale = __builtin_fmaxf(scale, 1e-36f);
+    const float score_scale = scale < kLeastScale ? scale * 0x1p64f : scale;     // (see shrink_k)
     const float c = score_scale * kLog2e;
 
     // Work unit: one key tile, or, when causal, the pair (u, last - u): tile u loops over the
@@ -371,6 +379,10 @@ void attn_bwd_dkdv_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K
 #pragma unroll
         for (int r = 0; r < 16; r++) { dk_acc[db][r] = 0.f; dv_acc[db][r] = 0.f; }
 
+    if (__builtin_expect(scale < kLeastScale, 0)) {
+#pragma unroll
+        for (int kb = 0; kb < D / 16; kb++) shrink_k(kf[kb]);
+    }
     // Every global load so far (this pass's K, V fragments, its first blocks, the previous pass's
     // stores) completes here.  The empty asm statements pin the fragment loads above this point (the
     // compiler would otherwise sink them to their first use inside the loop and wait for them there,
@@ -869,7 +881,7 @@ void attn_bwd_dkdv_wide_kernel(const bf16* __restrict__ Q, const bf16* __restric
     const int h = lane >> 5;
     const int j16 = lane & 15;
     const int ghalf = (lane >> 4) & 1;
-    const float score_scale = __builtin_fmaxf(scale, 1e-36f);
+    const float score_scale = scale < kLeastScale ? scale * 0x1p64f : scale;     // (see shrink_k)
     const float c = score_scale * kLog2e;
     const int heads_per_kv = hq / hkv;
     const int off = TAIL ? Nk - Nq : 0;
@@ -1002,6 +1014,12 @@ void attn_bwd_dkdv_wide_kernel(const bf16* __restrict__ Q, const bf16* __restric
         }
     };
     auto keep_k = [&]() __attribute__((always_inline)) {        // (the wait for K belongs here and not at its first use)
+        if (__builtin_expect(scale < kLeastScale, 0)) {
+#pragma unroll
+            for (int b = 0; b < 2; b++)
+#pragma unroll
+                for (int kb = 0; kb < kSteps; kb++) shrink_k(kf[b][kb]);
+        }
 #pragma unroll
         for (int b = 0; b < 2; b++)
 #pragma unroll
