@@ -1109,20 +1109,13 @@ static void combine(const float* o_part, const float* lse_part, void* o, float* 
 hipError_t launch_attn_fwd_splitk(const void* q, const void* k, const void* v, void* o, float* lse,
                                   float* o_part, float* lse_part,
                                   int B, int H, int Hkv, int Nq, int Nk, int D, int causal, float scale,
-                                  int n_splits, int tiles_per_split, hipStream_t stream)
+                                  int n_splits, int tiles_per_split, int groups, hipStream_t stream)
 {
-    int cus = 0;
-    hipError_t e = compute_unit_count(&cus);
-    if (e != hipSuccess) return e;
-    // Two groups where the 128-row tiles come in pairs and would be two to a compute unit: B1 Hq32 Hkv8 Nq512 Nk8192 D128 78, 75 us
-    // with two groups, Nq387 Nk6822 61, 56 (but an odd number of tiles, B4 Hq4 Hkv1 Nq319 Nk7441, 40, 57).
-    const int tiles = (Nq + 127) / 128;
-    const bool two = tiles % 2 == 0 && (long long)B * H * tiles * n_splits > cus;
     auto launch = !causal && Nq <= 64 ? (D == 128 ? launch_fwd_tt<128, false, true, true> : launch_fwd_tt<64, false, true, true>)     // (see launch_fwd_t)
                 : D == 64 ? (causal ? launch_phase<64, true, true, true, 1> : launch_phase<64, false, true, true, 1>)
-                : two     ? (causal ? launch_phase<128, true, true, true, 2> : launch_phase<128, false, true, true, 2>)
+                : groups == 2 ? (causal ? launch_phase<128, true, true, true, 2> : launch_phase<128, false, true, true, 2>)
                           : (causal ? launch_phase<128, true, true, true, 1> : launch_phase<128, false, true, true, 1>);
-    e = launch(q, k, v, o, lse, B, H, Hkv, Nq, Nk, scale, stream, n_splits, tiles_per_split, o_part, lse_part);
+    hipError_t e = launch(q, k, v, o, lse, B, H, Hkv, Nq, Nk, scale, stream, n_splits, tiles_per_split, o_part, lse_part);
     if (e != hipSuccess) return e;
     combine(o_part, lse_part, o, lse, (size_t)B * H * Nq, D, n_splits, stream);
     return hipGetLastError();

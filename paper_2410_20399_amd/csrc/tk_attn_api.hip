@@ -163,48 +163,59 @@ tk::DkdvSplits dkdv_splits_scratch(int B, int Hq, int Hkv, int Nq, int Nk, int D
 }
 
 // Few queries against a longer history: the heads and 128-query tiles alone leave compute units idle.  The split
-// aims at one or two workgroups per compute unit, whichever the estimate below prefers.  A split holds at least 8 64-key
-// tiles (the forward kernel and its figures in an earlier form: with 16 B2 Hq8 Hkv2 Nq100 Nk2100 D128 took 28 instead of 21
-// us, but with 4 B1 H16 Nq512 Nk2048 D64 23 instead of 18.5).
+// aims at one, two or (D = 64) three workgroups per compute unit, at D = 128 also at one of twice the rows, whichever the
+// estimate below prefers.  A split holds at least 8 64-key tiles.
 constexpr int kFwdSplitMinTiles = 8;
 
-// us of a forward call whose tiles are split that way.  A 64-key tile takes a workgroup alone on its compute unit 0.6 us at
-// D = 64 and 0.92 at D = 128; two of them on one unit take 1.7 and 2 times as long each, with up to 64 rows (half the waves
-// idle) 1.1 times; K and V come in at 6 TB/s at most; the merge takes 2 us and its bytes, written and read, at 5.5 TB/s.
-// Whole call, us (unsplit, one per unit, two): B1 Hq32 Hkv8 Nq512 Nk8192 D128 122, 87, 78; Nq192 Nk3398 D64 37, 20, 24;
-// Nq881 Nk2544 D128 43, -, 52; B1 Hq64 Hkv16 Nq36 Nk13614 D64 130, 45, 36; B2 Hq16 Hkv2 Nq900 Nk3000 D64 34, -, 40.
-double fwd_split_us(int B, int Hq, int Hkv, int Nq, int Nk, int D, int n_splits, int per, int compute_units)
+// us of a forward call whose tiles are split that way.  A 64-key tile takes a workgroup alone on its compute unit 0.63 us at
+// D = 64 and 1.05 at D = 128; two (three) of them on one unit take 1.6 (2.36) times as long each, 1.88 at D = 128, with up to 64
+// rows, half the waves idle, 1.15 (1.3) times; a workgroup of 256 rows takes 1.44, one on a unit at a time.  K and V come in at 7 TB/s
+// at most; the merge takes 2 us and its bytes, written and read, at 5.5 TB/s.  Fitted to 550 calls with 1 to 1600 queries and 1024 to
+// 16384 keys, each timed in all these forms, and checked on 500 others: the choice takes 0.2 % more than the best one on average, 14 % at
+// most.  Whole call, us (unsplit, one workgroup per unit, two; one of 256 rows): B1 Hq32 Hkv8 Nq512 Nk8192 D128 128, 81, 79; 75.5;
+// B6 H16 Nq164 Nk7079 D128 causal 124, -, -; 93; B4 Hq4 Hkv1 Nq319 Nk7441 D128 107, 40, 39.5; 40; B1 Hq32 Hkv8 Nq881 Nk2544 D128 46, -,
+// 53; 48.  At D = 64 (one, two, three per unit): B6 Hq32 Hkv16 Nq27 Nk11152 145, -, 80, 48; B1 H32 Nq331 Nk8022 85, -, 43.4, 41.9.
+double fwd_split_us(int B, int Hq, int Hkv, int Nq, int Nk, int D, int n_splits, int per, int groups, int compute_units)
 {
-    const long long workgroups = (long long)B * Hq * ((Nq + kTileN - 1) / kTileN) * n_splits;
-    const double tile_us = D == 64 ? 0.6 : 0.92;
-    const double shared = workgroups <= compute_units ? 1.0 : Nq <= 64 ? 1.1 : D == 64 ? 1.7 : 2.0;
-    const double kv_us = 4.0 * B * Hkv * Nk * D / 6.0e6;
+    const long long heads = (long long)B * Hq * n_splits, workgroups = heads * ((Nq + kTileN - 1) / kTileN);
+    double us;
+    if (groups == 2) {
+        const long long rounds = (heads * ((Nq + 2 * kTileN - 1) / (2 * kTileN)) + compute_units - 1) / compute_units;
+        us = 4.0 + 1.44 * per * rounds;
+    } else {
+        const bool few = Nq <= 64;
+        const double shared = workgroups <= compute_units ? 1.0 : workgroups <= 2LL * compute_units ? (few ? 1.15 : D == 64 ? 1.6 : 1.88) : few ? 1.3 : 2.36;
+        us = 2.0 + per * (D == 64 ? 0.63 : 1.05) * shared;
+    }
+    const double kv_us = 4.0 * B * Hkv * Nk * D / 7.0e6;
     const double merge_us = n_splits == 1 ? 0.0 : 2.0 + 8.0 * n_splits * B * Hq * Nq * D / 5.5e6;
-    return (per * tile_us * shared > kv_us ? per * tile_us * shared : kv_us) + merge_us;
+    return (us > kv_us ? us : kv_us) + merge_us;
 }
 
 struct FwdPlan {
-    int n_splits, tiles_per_split;
+    int n_splits, tiles_per_split, groups;
 };
 
 // Nq < Nk only: with equal lengths a head's bits do not depend on how many heads the call has.
-FwdPlan plan_fwd(int B, int Hq, int Hkv, int Nq, int Nk, int D, int compute_units)
+FwdPlan plan_fwd(int B, int Hq, int Hkv, int Nq, int Nk, int D, bool causal, int compute_units)
 {
-    const long long base = (long long)B * Hq * ((Nq + kTileN - 1) / kTileN);
+    const long long heads = (long long)B * Hq, base = heads * ((Nq + kTileN - 1) / kTileN);
     const int tiles = (Nk + 63) / 64;
-    FwdPlan best = {1, tiles + (tiles & 1)};
+    FwdPlan best = {1, tiles + (tiles & 1), 1};
     if (Nq >= Nk || base > 2LL * compute_units) return best;
-    double best_us = fwd_split_us(B, Hq, Hkv, Nq, Nk, D, 1, tiles, compute_units);
-    for (int per_unit = 1; per_unit <= 2; per_unit++) {
-        long long want = (long long)per_unit * compute_units / base;
+    double best_us = fwd_split_us(B, Hq, Hkv, Nq, Nk, D, 1, tiles, 1, compute_units);
+    auto consider = [&](int per_unit, int groups, long long row_tiles) {
+        long long want = (long long)per_unit * compute_units / row_tiles;
         if (want > tiles / kFwdSplitMinTiles) want = tiles / kFwdSplitMinTiles;
-        if (want < 2) continue;
+        if (want < 2) return;
         int per = (int)((tiles + want - 1) / want);
         per += per & 1;                                   // (the kernel of few rows walks the tiles in pairs)
         const int n_splits = (tiles + per - 1) / per;     // no split is empty
-        const double us = fwd_split_us(B, Hq, Hkv, Nq, Nk, D, n_splits, per, compute_units);
-        if (n_splits > 1 && us < best_us) { best = {n_splits, per}; best_us = us; }
-    }
+        const double us = fwd_split_us(B, Hq, Hkv, Nq, Nk, D, n_splits, per, groups, compute_units);
+        if (n_splits > 1 && us < best_us) { best = {n_splits, per, groups}; best_us = us; }
+    };
+    for (int per_unit = 1; per_unit <= (D == 64 ? 3 : 2); per_unit++) consider(per_unit, 1, base);
+    if (D == 128 && (causal || Nq > 64)) consider(1, 2, heads * ((Nq + 2 * kTileN - 1) / (2 * kTileN)));
     return best;
 }
 
@@ -231,7 +242,7 @@ size_t tk_attn_fwd_scratch_bytes(int B, int Hq, int Hkv, int Nq, int Nk, int D, 
     if (check_lengths(B, Hq, Hkv, Nq, Nk, D, causal) != TK_OK || Nq >= Nk) return 0;
     int cus = 0;
     if (tk::compute_unit_count(&cus) != hipSuccess || cus < 1) return 0;
-    const FwdPlan p = plan_fwd(B, Hq, Hkv, Nq, Nk, D, cus);
+    const FwdPlan p = plan_fwd(B, Hq, Hkv, Nq, Nk, D, causal != 0, cus);
     if (p.n_splits == 1) return 0;
     const size_t rows = (size_t)B * Hq * Nq;
     return fwd_part_bytes(p.n_splits, rows, D) + fwd_part_bytes(p.n_splits, rows, 1);
@@ -249,10 +260,10 @@ int tk_attn_fwd_rect_scratch(const void* q, const void* k, const void* v, void* 
     if (int rc = check_scale(scale)) return rc;
     int cus = 0;
     if (tk::compute_unit_count(&cus) != hipSuccess) return TK_ERR_LAUNCH;
-    const FwdPlan p = plan_fwd(B, Hq, Hkv, Nq, Nk, D, cus);
+    const FwdPlan p = plan_fwd(B, Hq, Hkv, Nq, Nk, D, causal != 0, cus);
     float* lse_part = (float*)((char*)scratch + fwd_part_bytes(p.n_splits, (size_t)B * Hq * Nq, D));
     hipError_t e = tk::launch_attn_fwd_splitk(q, k, v, o, lse, (float*)scratch, lse_part, B, Hq, Hkv, Nq, Nk, D, causal != 0, scale,
-                                              p.n_splits, p.tiles_per_split, (hipStream_t)stream);
+                                              p.n_splits, p.tiles_per_split, p.groups, (hipStream_t)stream);
     return e == hipSuccess ? TK_OK : TK_ERR_LAUNCH;
 }
 
@@ -316,7 +327,7 @@ int tk_attn_decode(const void* q, const void* k, const void* v, void* o, float* 
         e = tk::launch_attn_fwd(q, k, v, o, lse, p.b, p.h, p.hkv, p.nq, Nk, D, 0, scale, (hipStream_t)stream);
     else
         e = tk::launch_attn_fwd_splitk(q, k, v, o, lse, o_part, lse_part, p.b, p.h, p.hkv, p.nq, Nk, D, 0, scale,
-                                       p.n_splits, p.tiles_per_split, (hipStream_t)stream);
+                                       p.n_splits, p.tiles_per_split, 1, (hipStream_t)stream);
     return e == hipSuccess ? TK_OK : TK_ERR_LAUNCH;
 }
 

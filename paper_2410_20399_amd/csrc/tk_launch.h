@@ -67,11 +67,12 @@ hipError_t launch_attn_fwd(const void* q, const void* k, const void* v, void* o,
                            int B, int H, int Hkv, int Nq, int Nk, int D, int causal, float scale, hipStream_t stream);
 
 // The same forward with the keys split n_splits (>= 2) ways and a merge kernel behind it.  o_part: fp32 [n_splits][B*H][Nq][D]; lse_part: fp32 [n_splits][B*H][Nq];
-// tiles_per_split: even number of 64-key tiles per split, (n_splits - 1) * tiles_per_split * 64 < Nk.
+// tiles_per_split: even number of 64-key tiles per split, (n_splits - 1) * tiles_per_split * 64 < Nk.  groups: 2 for workgroups of
+// 256 query rows (D = 128, and more than 64 rows or the causal mask), otherwise 1.
 hipError_t launch_attn_fwd_splitk(const void* q, const void* k, const void* v, void* o, float* lse,
                                   float* o_part, float* lse_part,
                                   int B, int H, int Hkv, int Nq, int Nk, int D, int causal, float scale,
-                                  int n_splits, int tiles_per_split, hipStream_t stream);
+                                  int n_splits, int tiles_per_split, int groups, hipStream_t stream);
 
 // Decoding on a launch of at most one workgroup a compute unit: `rows` (<= kDecodeRows) query rows for each of `heads` key/value heads, the keys split n_splits (>= 1) ways as
 // above.  q, o: [heads, rows, D]; k, v: [heads, Nk, D]; lse: [heads, rows].
