@@ -609,6 +609,9 @@ void attn_fwd_phase_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ 
         // group's phases come one barrier later.  A stage is refilled by loads issued in the matrix phase of tile t (with
         // tile t+3, into the stage of tile t-1, whose V the other group read at the latest one barrier ago), and every wave
         // waits for its loads of tile t+2 at the end of that phase: both groups read tile t+2 at least one barrier later.
+        // The first tile is an exception: the first group reads its first fragments of V one barrier ahead of the second group's wait.
+        // They are the rows that its own waves have fetched.
+        static_assert((kAhead + D / 32 - 1) / (D / 32) * 16 * S::kChunksPerRow <= S::kThreads / 2, "rows that the first group's first load instruction fetches");
         if (group == 1) phase_end();
         if (n_my > t) scores(s, t);
         wait_vmcnt<S::kTileLoads>();             // tiles t and t+1
