@@ -10,6 +10,7 @@ import pytest
 import torch
 
 from paper_2410_20399_amd import attn
+from kernel_names import launched
 
 pytestmark = pytest.mark.gpu
 
@@ -38,9 +39,11 @@ def test_heads_of_a_large_call(B, H, Nq, Nk, causal, storing):
     new = lambda n: torch.randn(B, H, n, D, generator=g, device="cuda").to(torch.bfloat16)
     q, k, v, d_o = new(Nq), new(Nk), new(Nk), new(Nq)
     print(f"launch backward B{B} H{H} Nq{Nq} Nk{Nk} causal={causal} storing={storing}", flush=True)
-    grads = backward(q, k, v, d_o, causal, storing)
+    grads, names = launched(lambda: backward(q, k, v, d_o, causal, storing))
+    assert any("attn_bwd_dkdv_wide_kernel" in n for n in names), names
     for b, h in {(0, 0), (B - 1, H - 1), (B // 2, 1)}:
-        one = backward(*(t[b:b + 1, h:h + 1].contiguous() for t in (q, k, v, d_o)), causal, storing)
+        one, names = launched(lambda: backward(*(t[b:b + 1, h:h + 1].contiguous() for t in (q, k, v, d_o)), causal, storing))
+        assert any("attn_bwd_dkdv_kernel" in n for n in names), names
         for name, x, y in zip(("dq", "dk", "dv"), grads, one):
             assert torch.equal(x[b, h], y[0, 0]), (name, b, h)
 
@@ -63,10 +66,12 @@ def test_groups_of_a_large_call(B, Hq, Hkv, N, causal):
         return dk, dv
 
     print(f"launch dK/dV B{B} Hq{Hq} Hkv{Hkv} N{N} causal={causal}", flush=True)
-    all_heads = dkdv(q, k, v, d_o)
+    all_heads, names = launched(lambda: dkdv(q, k, v, d_o))
+    assert any("attn_bwd_dkdv_wide_kernel" in n for n in names), names
     group = Hq // Hkv
     for b, h in ((0, 0), (B - 1, Hkv - 1)):
         heads = slice(h * group, (h + 1) * group)
-        one = dkdv(q[b:b + 1, heads].contiguous(), k[b:b + 1, h:h + 1].contiguous(), v[b:b + 1, h:h + 1].contiguous(), d_o[b:b + 1, heads].contiguous())
+        one, names = launched(lambda: dkdv(q[b:b + 1, heads].contiguous(), k[b:b + 1, h:h + 1].contiguous(), v[b:b + 1, h:h + 1].contiguous(), d_o[b:b + 1, heads].contiguous()))
+        assert any("attn_bwd_dkdv_kernel" in n for n in names), names
         for name, x, y in zip(("dk", "dv"), all_heads, one):
             assert torch.equal(x[b, h], y[0, 0]), (name, b, h)
