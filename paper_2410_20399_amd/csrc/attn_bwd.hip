@@ -1309,11 +1309,12 @@ void attn_bwd_dkdv_wide_kernel(const bf16* __restrict__ Q, const bf16* __restric
 }
 
 // Whether tiles of 256 keys take less time than tiles of 128: us of the workgroup with most units, a block of 32 queries at
-// 1.07 (128 keys, 0.1 more where it may be masked) and 1.85 us (256), the ends of a pass at 4 and 6.  A unit is a key tile, or
-// a causal pair of them.  Fitted to 420 backward calls of 128 to 8192 queries and keys, grouped or not, with and without a mask and stored
-// dS, both ways timed, and checked on 420 others: the choice takes 0.13 % more than the better way on average; 369 take the 256-key tiles,
-// whose whole call is 9 % faster on average; 9 of them lose more than 1 %, at most 14.  (With 0.5 us for a masked block, as when those went
-// through scratch memory, 0.8 % more; us, 128 keys and 256: B9 Hq24 Hkv12 Nq160 Nk794 causal 111, 96; B12 Hq64 Hkv16 Nq143 Nk4680 1366, 1176.)
+// 1.07 (128 keys, 0.1 more where it may be masked) and 1.85 us (256), the ends of a pass at 4 and 7.  A unit is a key tile, or
+// a causal pair of them.  Fitted to 720 backward calls of 1 to 8192 queries and 128 to 16384 keys, grouped or not, with and without a mask
+// and stored dS, both ways timed, and checked on 420 others: the choice takes 0.15 % more than the better way on average; of the 840 with at
+// least 128 queries 363 take the 256-key tiles, their whole call 9 % faster on average; 17 of all lose more than 1 %, one of them 14 and one 10.
+// (With 0.5 us for a masked block, as when those went through scratch memory, 1 % more; us, 128 keys and 256: B9 Hq24 Hkv12 Nq160 Nk794
+// causal 111, 96; B12 Hq64 Hkv16 Nq143 Nk4680 1366, 1176.  With 6 us for the ends 27 of 300 calls of few queries lost up to 9 %.)
 static bool dkdv_wide_pays(int B, int H, int Hkv, int Nq, int Nk, bool causal, int cus)
 {
     auto us = [&](int keys, double block_us, double masked_us, double pass_us) {
@@ -1328,7 +1329,7 @@ static bool dkdv_wide_pays(int B, int H, int Hkv, int Nq, int Nk, bool causal, i
         const double masked = causal ? (Nk < keys ? Nk : keys) / 32.0 * passes : 0;
         return rounds * ((blocks * block_us + masked * masked_us) * (H / Hkv) + passes * pass_us);
     };
-    return us(256, 1.85, 0, 6) < us(128, 1.07, 0.1, 4);
+    return us(256, 1.85, 0, 7) < us(128, 1.07, 0.1, 4);
 }
 
 template <bool CAUSAL, bool TAIL, bool SPILL>
