@@ -104,13 +104,14 @@ inline bool pair_tiles(long long heads, int tiles, int compute_units) { return h
 // units at once (with more units the split only adds the traffic of the partial sums): n_splits in all, of which
 // q_splits share the query blocks of a head and n_splits / q_splits the query heads of a group.
 //   Heads: the largest divisor of the group that fits.  Fewer than 256 queries are not split: the stream of a unit is
-// then short next to the launch of the kernel that adds up.  Whole backward, us, unsplit and split: B2 Hq16 Hkv4 N1001
-// D128 causal 219, 112; B1 Hq32 Hkv8 N4096 642, 579 (two ways); B1 Hq64 Hkv1 N3000 6956, 686; B1 Hq8 Hkv1 N300 148, 53;
-// at D = 64 B1 Hq32 Hkv8 N2048 204, 111.
+// then short next to the launch of the kernel that adds up.  Whole causal backward, us, unsplit and split: B2 Hq16 Hkv4 N1001
+// D128 147, 80; B1 Hq32 Hkv8 N4096 573, 481 (two ways); B1 Hq64 Hkv1 N3000 5380, 640; B1 Hq8 Hkv1 N300 94, 38;
+// at D = 64 B1 Hq32 Hkv8 N2048 198, 101.
 //   Blocks: with other numbers of queries than keys and no mask (with equal lengths and no groups a head's bits do not
 // depend on the number of heads; with a mask the late key tiles have few blocks), down to 512 queries, and only to one
-// workgroup a compute unit.  Backward, us: B1 H4 Nq4096 Nk64 D64 91, 22; B1 H8 Nq3000 Nk200 D128 128, 42; but with two
-// workgroups to some compute units B4 H16 Nq1000 Nk300 D64 47, 53, and with 150 queries each B2 H16 Nq300 Nk128 20, 25.
+// workgroup a compute unit.  Backward, us: B1 H4 Nq4096 Nk64 D64 87, 24; B1 H8 Nq3000 Nk200 D128 98, 46; but with two
+// workgroups to some compute units B4 H16 Nq1000 Nk300 D64 47, 53, and with 150 queries each B2 H16 Nq300 Nk128 20, 25 (the
+// last two with an earlier form of the kernel, as such splits are not made).
 //   Whether it pays: the partial sums and their launch have to cost less than the shorter streams save (dkdv_us()).
 struct DkdvSplits {
     int n_splits, q_splits;
@@ -118,12 +119,13 @@ struct DkdvSplits {
 // blocks of a head in one of q_splits parts, an even number; the last part may be shorter
 __host__ __device__ inline int dkdv_q_chunk(int Nq, int q_splits) { return 2 * (((Nq + 63) / 64 + q_splits - 1) / q_splits); }
 
-// Microseconds of the dK/dV kernel split that way: the longest stream of blocks of a workgroup at 0.6 us a block (D = 64) or
-// 1.4 (D = 128), 1.4 times that where two workgroups share a compute unit; a split adds 3 us and its partial sums, written
-// and read, at 5 TB/s.  Fitted to 1999 backward calls with 256 to 4000 queries, each timed with and without its split: by
-// this rule five of them lose, at most 3 %; splitting wherever the units fit lost up to 20 %, us (unsplit, split): B5 Hq32
-// Hkv16 N268 D64 34, 42 (two workgroups to a compute unit); B3 Hq32 Hkv8 Nq309 Nk1060 D128 causal 95, 116 (split tiles are too
-// many to go unpaired, and the pairs are as long as the single tiles were).
+// Microseconds of the dK/dV kernel split that way: the longest stream of blocks of a workgroup at 0.7 us a block (D = 64) or
+// 1.07 (D = 128), 1.4 times that where two workgroups share a compute unit; a split adds 2 us and its partial sums, written
+// and read, at 4 TB/s.  Fitted to 437 backward calls with 256 to 4000 queries for which a split fits, each timed with and without: the choice
+// takes 0.08 % more than the better one on average, 9 lose more than 1 %, at most 8.  Splitting wherever the units fit loses up to a
+// fifth, us (unsplit, split): B5 Hq32 Hkv16 N268 D64 33, 41 (two workgroups to a compute unit); B3 Hq32 Hkv8 Nq309 Nk1060 D128 causal
+// 107, 127 (split tiles are too many to go unpaired, and the pairs are as long as the single tiles were).  The times of the kernel with
+// 128-key tiles: none of these calls would take 256-key tiles unsplit, which want more tiles than compute units.
 inline double dkdv_us(int B, int H, int Hkv, int Nq, int Nk, int D, bool causal, int compute_units, DkdvSplits p) {
     const int tiles = (Nk + 127) / 128, heads = p.n_splits / p.q_splits;
     const bool paired = causal && pair_tiles((long long)B * Hkv * p.n_splits, tiles, compute_units);
@@ -140,8 +142,8 @@ inline double dkdv_us(int B, int H, int Hkv, int Nq, int Nk, int D, bool causal,
         if (n > longest) longest = n;
     }
     const double shared = D == 64 && (long long)B * Hkv * units * p.n_splits > compute_units ? 1.4 : 1.0;
-    const double sum_us = p.n_splits == 1 ? 0.0 : 3.0 + 16.0 * p.n_splits * B * Hkv * Nk * D / 5.0e6;
-    return longest * (double)(H / Hkv / heads) * (D == 64 ? 0.6 : 1.4) * shared + sum_us;
+    const double sum_us = p.n_splits == 1 ? 0.0 : 2.0 + 16.0 * p.n_splits * B * Hkv * Nk * D / 4.0e6;
+    return longest * (double)(H / Hkv / heads) * (D == 64 ? 0.7 : 1.07) * shared + sum_us;
 }
 
 // heads_only: a call without memory for the partial sums of split blocks
