@@ -94,10 +94,11 @@ inline size_t ds_spill_bytes(int B, int H, int Nq, int Nk) {
 
 // Whether the tiles of a causal backward launch are paired, long with short, for equal work per workgroup: not where
 // each has a compute unit of its own without: the longest tile alone is then the shorter way, by one tile in `tiles`
-// and a start-up.  Whole backward, us, paired and not: B2 Hq16 Hkv4 N1001 D128 100, 84; B2 H12 N700 D64 47, 37; but with
-// 32 tiles B1 H8 N4096 D128 201, 224 (half the compute units hold a higher clock) and with two workgroups to a compute
-// unit, two long ones or two short ones, B1 H16 N4096 D64 173, 227.  (A single tile has no partner either way, and counts as
-// paired: without a pair the kernels for ragged lengths are taken, B2 Hq128 Hkv16 N128 D128 52, 57.)
+// and a start-up.  Whole backward, us, paired and not: B2 Hq16 Hkv4 N1001 D128 98, 80; B2 H12 N700 D64 45, 36; but with
+// 32 tiles B1 H8 N4096 D128 215, 223, storing dS 171, 190 (half the compute units hold a higher clock), between 17 and 26 tiles a tenth
+// either way, and with two workgroups to a compute unit, two long ones or two short ones, B1 H16 N4096 D64 148, 217.  (A single
+// tile has no partner either way, and counts as paired: without a pair the kernels for ragged lengths are taken, B2 Hq128 Hkv16
+// N128 D128 44, 51.)
 inline bool pair_tiles(long long heads, int tiles, int compute_units) { return heads * tiles > compute_units || tiles > 16 || tiles == 1; }
 
 // Ways to split the queries of a key tile over workgroups of the dK/dV kernel, as far as the units still fit the compute
