@@ -777,7 +777,7 @@ static hipError_t launch_phase(const void* q, const void* k, const void* v, void
     const int num_q_tiles = (Nq + S::kTileQ - 1) / S::kTileQ;
     hipLaunchKernelGGL((attn_fwd_phase_kernel<D, CAUSAL, TAIL, SPLIT, GROUPS>), dim3(B * H * num_q_tiles * n_splits), dim3(S::kThreads), 0, stream,
                        (const bf16*)q, (const bf16*)k, (const bf16*)v, (bf16*)o, lse, Nq, Nk, num_q_tiles, B * H,
-                       tile_order_heads(B * H, num_q_tiles, CAUSAL), scale, H, Hkv, n_splits, tiles_per_split, o_part, lse_part);
+                       tile_order_heads(B * H, num_q_tiles, CAUSAL, D), scale, H, Hkv, n_splits, tiles_per_split, o_part, lse_part);
     return hipGetLastError();
 }
 
@@ -792,7 +792,7 @@ static hipError_t launch_fwd_tt(const void* q, const void* k, const void* v, voi
     const int total = B * H * num_q_tiles * n_splits;
     hipLaunchKernelGGL(kern, dim3(total), dim3(S::kThreads), 0, stream,
                        (const bf16*)q, (const bf16*)k, (const bf16*)v, (bf16*)o, lse,
-                       Nq, Nk, num_q_tiles, B * H, tile_order_heads(B * H, num_q_tiles, CAUSAL), scale, H, Hkv, n_splits, tiles_per_split, o_part, lse_part);
+                       Nq, Nk, num_q_tiles, B * H, tile_order_heads(B * H, num_q_tiles, CAUSAL, D), scale, H, Hkv, n_splits, tiles_per_split, o_part, lse_part);
     return hipGetLastError();
 }
 

@@ -26,23 +26,26 @@ inline hipError_t compute_unit_count(int* cus) {
 
 // Heads that tile_of() walks together.  Without a mask all tiles weigh the same: one head per XCD, the best
 // reuse of its L2.  With the causal mask a tile's work grows with its index, and the workgroups of an XCD (32 compute
-// units, two resident on each at D = 128) are best given out longest first: d heads per XCD, as many as keep
-// d * tiles within one and a half times the 64 that are resident, preferably a divisor of an XCD's share.  (One head after the
-// other gives a compute unit the same tile index of two heads, two long ones or two short ones:
-// B2 H16 N2048 D128 62 -> 50 us, B1 Hq32 Hkv8 N3001 111 -> 89 us; more heads than this and the L2 and the
-// balance at the end both get worse: the first of these 54 us with 6 heads, 56 us with 8.)  At D = 64 four are resident;
-// the 96 was not fitted to that, and of 200 causal sizes with 8 to 1100 heads it makes none slower than one head per XCD.
+// units) are best given out longest first: d heads per XCD, as many as keep d * tiles within 96 at D = 128 and 256 at D = 64,
+// preferably a divisor of an XCD's share.  (One head after the other gives a compute unit the same tile index of two heads, two long
+// ones or two short ones: with the forward's kernel before the present one B2 H16 N2048 D128 62 -> 50 us, B1 Hq32 Hkv8 N3001 111 -> 89 us;
+// more heads than this and the L2 and the balance at the end both get worse: the first of these 54 us with 6 heads, 56 us with 8.)
+// The limits, timed with the present kernels: at D = 128, of 227 sizes with 128-row tiles, two workgroups to a compute unit, and 112
+// with 256-row tiles, one to a unit, 96 takes 1.6 and 1.4 % more than the best of 48 to 384, and the best single one, 160 to 192, 1.1 and
+// 1.0 %, with a twelfth of the sizes slower by 2 % and more.  At D = 64, three workgroups to a unit, of 800 sizes with 130 to 8192
+// queries 256 takes 0.5 % more than the best of 1 to 384, 96 3.7 %: of the two 256 is faster by 2 % and more in 276, slower in 9;
+// us (96, 256): B2 H13 N7808 271, 213; B7 Hq4 Hkv2 N6074 177, 144; B9 Hq26 Hkv13 N995 50, 56; 54 sizes of 8192 to 40000 gain 2.5 % on average.
 // Where there is none and the last group would be no more than half as large, its few heads leave the units of an XCD to
 // their short end: of six tiles and more the next divisor up to 4 * d is taken, of three or five groups of equal size.  us
-// (one head per XCD, a group that leaves a rest, this): B14 H4 N3584 D128 214, 224, 183; B4 H14 N1832 D128 78, 81, 64; B1
+// (one head per XCD, a group that leaves a rest, this; before the present kernels): B14 H4 N3584 D128 214, 224, 183; B4 H14 N1832 D128 78, 81, 64; B1
 // Hq104 Hkv13 N1179 D64 34, 38, 32; B10 Hq52 Hkv13 N373 D128 48, 54, 47; of 244 such sizes 16 had become slower than with one
 // head.  (Of two or four tiles, where long and short ones alternate on a unit either way, the rest does no harm: B5 Hq104
 // Hkv13 N256 D128 33, 29.5, in equal groups 32.)
-inline int tile_order_heads(int heads, int tiles, bool causal) {
-    const int per_xcd = (heads + 7) / 8;
+inline int tile_order_heads(int heads, int tiles, bool causal, int D) {
+    const int per_xcd = (heads + 7) / 8, limit = D == 64 ? 256 : 96;
     int d = 1;
     if (causal) {
-        d = 96 / tiles < per_xcd ? 96 / tiles : per_xcd;
+        d = limit / tiles < per_xcd ? limit / tiles : per_xcd;
         if (d < 1) d = 1;
         const int most = d;
         bool found = false;

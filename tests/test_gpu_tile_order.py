@@ -18,7 +18,9 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("B,H,N,D", [(1, 9, 300, 64), (3, 7, 1500, 128), (2, 13, 257, 128), (1, 70, 700, 64), (1, 24, 128, 64),
                                      (2, 20, 4000, 64),
                                      # no divisor of an XCD's heads near the group: the next one, one group and three; equal groups
-                                     (4, 14, 1832, 64), (3, 24, 4224, 64), (3, 88, 312, 64)])
+                                     (4, 14, 1832, 64), (3, 24, 4224, 64), (3, 88, 312, 64),
+                                     # the same with the larger groups of D = 64
+                                     (8, 13, 2950, 64), (8, 9, 11000, 64), (8, 89, 312, 64)])
 def test_every_tile_once(B, H, N, D, causal):
     g = torch.Generator().manual_seed(7 * N + H)
     q, k, v = (torch.randn(B, H, N, D, generator=g).to(torch.bfloat16).cuda() for _ in range(3))
