@@ -547,7 +547,7 @@ void attn_bwd_dkdv_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K
                 dsb[1] = cvt8(de[8], de[9], de[10], de[11], de[12], de[13], de[14], de[15]);
             }
             dv_acc[db] = mfma32(tdo[idx], pb[ks], dv_acc[db]);
-asm volatile("" : : "v"(dv_acc[db][0]));
+            asm volatile("" : : "v"(dv_acc[db][0]));
             rq[idx] = lds_read_b128(q2s, row_lane ^ ((2 * idx) << 4));
             if (idx == 0) asm volatile("" : "+v"(pb[1]), "+v"(dsb[1]));
             if (idx == 0) prepare();         // block n+6 goes into the stage of block n-1, which every wave has left
@@ -555,7 +555,7 @@ asm volatile("" : : "v"(dv_acc[db][0]));
             if (idx == S::kLoadsPerBlock + 1) emit(S::kLoadsPerBlock);
             __builtin_amdgcn_sched_barrier(0);
             dk_acc[db] = mfma32(tq[idx], dsb[ks], dk_acc[db]);
-asm volatile("" : : "v"(dk_acc[db][0]));
+            asm volatile("" : : "v"(dk_acc[db][0]));
             rdo[idx] = lds_read_b128(q2s + S::kQTileBytes, row_lane ^ ((2 * idx) << 4));
             if (idx >= 2 && idx < 6) read_stat(sc, wave_stat(stage2), idx - 2);           // (S and dP of block n+2 start from there)
             if (idx >= 4) read_stat(dc, wave_stat(stage2) + 32, idx - 4);
@@ -829,7 +829,9 @@ static hipError_t launch_dkdv_tt(const void* q, const void* k, const void* v, co
 // What bounds it: the second half has 4.6 vector instructions to an MFMA, which a single wave issues in about 40 of the 32
 // cycles that the matrix pipe takes; and power (without its loads the kernel takes 13 % less time on normal data, on
 // constant data 5 %).  dK/dV alone, us, 128 keys and 256: B16 H16 N4096 without a mask 3680, 3300; causal 2020, 1870; causal and
-// storing dS 2385, 2255 (with 22 and 24 registers in scratch memory 1945, 2378).  Two waves per SIMD in turns, as in the forward, do not fit: 256 registers a wave.
+// storing dS 2385, 2255 (with 22 and 24 registers in scratch memory 1945, 2378).  The matrix pipe is busy in 56 % of its cycles (128-key
+// tiles: 47 %).  From beyond L2 it reads more, 4.2 GB there instead of 1.7: the workgroups of an XCD are at four heads at once, 8 MB of Q
+// and dO, and not at two.  It stores 0.13 GB of dS more, blocks that the mask takes wholly.  Two waves per SIMD in turns, as in the forward, do not fit: 256 registers a wave.
 //
 // The accumulators are only touched by inline assembly, which the compiler sees as writing them at once: results are read, and
 // copies made in front of a product, behind the waits that the hardware wants (mfma32_acc_wait, and the s_nop behind the last).
@@ -1236,8 +1238,9 @@ void attn_bwd_dkdv_wide_kernel(const bf16* __restrict__ Q, const bf16* __restric
             mask();
             products(cols, col_lane, stage_next, last, next, std::true_type{}, std::true_type{});
             prepare_turn();
-            // block n+2 has to be here; younger are the loads of this step and, where there are any, its stores (and those of
-            // the step before)
+            // block n+2, fetched in the step before, has to be here; younger are that step's stores and this one's loads and stores.
+            // The first step of a pass has none, and the count is the one that holds behind it too: later steps wait for
+            // the stores of the step before as well.
             if (SPILL && stores && !first) wait_vmcnt<S::kBlockLoads + 4>(); else wait_vmcnt<S::kBlockLoads>();
             step_end();
         };

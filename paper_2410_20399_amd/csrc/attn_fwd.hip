@@ -1,7 +1,9 @@
 // Fused exact softmax attention, forward pass, for gfx950 (MI355X).
 //
-// One workgroup = 4 waves = 128 query rows of one (batch, head); each wave owns 32 query rows.
-// K and V are streamed in tiles of 64 keys through a two-stage LDS ring filled by direct
+// Two kernels do the same computation: attn_fwd_kernel, for few query rows per head, for decoding and for one or two key tiles at
+// D = 64, and attn_fwd_phase_kernel for all other calls, which puts the work of a tile in two phases (described there).
+// In both a wave owns 32 query rows of one (batch, head), and a workgroup of 4 waves 128 (8 waves and 256 in one form of the
+// phase kernel).  K and V are streamed in tiles of 64 keys through an LDS ring filled by direct
 // global->LDS loads.  Per tile each wave computes, with v_mfma_f32_32x32x16_bf16:
 //
 //   S^T = K Q^T          (so that a lane owns ONE query: softmax statistics are lane-local)
