@@ -28,11 +28,11 @@ MFMA_BF16_PEAK_TFLOPS = 2500.0   # MI355X dense bf16 (published: 2.5 PFLOP/s)
 # reads in the same run; the files under profiles/ give the commands and the raw counters).  The
 # live run cannot collect counters itself, so other workloads report null.
 MEASURED_TRAFFIC = {
-    "fwdbwd_causal_b16_h16_n4096_d128": {"kernel": "attn_bwd_dkdv_kernel", "bytes": 1.713e9 + 4.966e9,      # (the form that stores dS)
+    "fwdbwd_causal_b16_h16_n4096_d128": {"kernel": "attn_bwd_dkdv_wide_kernel", "bytes": 4.212e9 + 5.100e9,  # (the form that stores dS)
                                          "source": "profiles/bench_fwdbwd_causal_b16_h16_n4096_d128.txt"},
     "fwdbwd_causal_b16_h16_n4096_d64/recompute": {"kernel": "attn_bwd_dkdv_kernel", "bytes": 0.583e9 + 0.268e9,
                                                   "source": "profiles/bench_fwdbwd_causal_b16_h16_n4096_d64.txt"},
-    "gemm_8192x8192x8192": {"kernel": "gemm_kernel", "bytes": 1.611e9 + 0.135e9, "source": "profiles/gemm_8192x8192x8192.txt"},
+    "gemm_8192x8192x8192": {"kernel": "gemm_kernel", "bytes": 1.611e9 + 0.140e9, "source": "profiles/gemm_8192x8192x8192.txt"},
     "decode_b16_hq32_hkv8_nk8192_d128": {"kernel": "attn_fwd_kernel", "bytes": 537.2e6 + 0.54e6, "source": "profiles/decode_b16_hq32_hkv8_nk8192_d128.txt"},
     "rotary_fwdbwd_causal_b16_h16_n4096_d128": {"kernel": "rotary_kernel", "bytes": 0.270e9 + 0.268e9, "source": "profiles/rotary_b16_h16_n4096_d128.txt"},
 }
@@ -318,18 +318,21 @@ def main():
     # spill form: three kernels: Delta, dK/dV storing dS, dQ from the stored dS.
     dq_delta_call = lambda: attn.tk_attn_bwd_dq_delta(qd, kd, vd, o, dod, lse, delta, dq, B, H, Hkv, N, D, w.causal, w.scale, stream)
     delta_call = lambda: attn.tk_attn_bwd_delta(o, dod, delta, B, H, N, D, stream)
-    stages = [("attn_fwd_kernel", lambda: check(fwd_call(), "fwd"))]
+    # (the kernels that the library takes for these workloads)
+    fwd_name = "attn_fwd_kernel" if N <= 128 else "attn_fwd_phase_kernel"
+    dkdv_name = "attn_bwd_dkdv_wide_kernel" if D == 128 else "attn_bwd_dkdv_kernel"
+    stages = [(fwd_name, lambda: check(fwd_call(), "fwd"))]
     if w.backward and spill:
         stages += [
             ("attn_bwd_delta_kernel", lambda: check(delta_call(), "delta")),
-            ("attn_bwd_dkdv_kernel", lambda: check(attn.tk_attn_bwd_dkdv_ds(qd, kd, vd, dod, lse, delta, dk, dv, ds, B, H, Hkv, N, D,
-                                                                            w.causal, w.scale, stream), "dkdv+ds")),
+            (dkdv_name, lambda: check(attn.tk_attn_bwd_dkdv_ds(qd, kd, vd, dod, lse, delta, dk, dv, ds, B, H, Hkv, N, D,
+                                                               w.causal, w.scale, stream), "dkdv+ds")),
             ("attn_bwd_dq_from_ds_kernel", lambda: check(attn.tk_attn_bwd_dq_from_ds(kd, ds, dq, B, H, Hkv, N, D, w.causal, w.scale, stream), "dq from ds")),
         ]
     elif w.backward:
         stages += [
             ("attn_bwd_dq_kernel", lambda: check(dq_delta_call(), "dq+delta")),
-            ("attn_bwd_dkdv_kernel", lambda: check(dkdv_call(), "dkdv")),
+            (dkdv_name, lambda: check(dkdv_call(), "dkdv")),
             ("attn_bwd_delta_kernel", lambda: check(delta_call(), "delta")),
         ]
     kernel_ms = {name: 0.0 for name, _ in stages}
@@ -344,7 +347,7 @@ def main():
         for i, (name, _) in enumerate(stages):
             kernel_ms[name] += evs[s][i].elapsed_time(evs[s][i + 1]) / args.steps
 
-    fwd_tflops = flops_fwd / (kernel_ms["attn_fwd_kernel"] * 1e-3) / 1e12
+    fwd_tflops = flops_fwd / (kernel_ms[fwd_name] * 1e-3) / 1e12
     out = {
         "metric": "attention fwd+bwd TFLOPS (bf16, causal, N=4096, D=128)" if args.workload == 6 else f"attention TFLOPS ({w.name})",
         "value": round(value, 2), "unit": "TFLOP/s", "n_gpus": 1, "steps": args.steps, "warmup": args.warmup,
@@ -355,19 +358,19 @@ def main():
                    **({"bwd_form": args.bwd_form, "bwd_workspace_bytes": ws_bytes} if w.backward else {}),
                    "flop_convention": "fwd 4*B*H*N^2*D, bwd 2.5x fwd, halved when causal"},
         "frac_of_mfma_peak": round(value / MFMA_BF16_PEAK_TFLOPS, 4),
-        "fwd": {"ms": round(kernel_ms["attn_fwd_kernel"], 4), "tflops": round(fwd_tflops, 2),
+        "fwd": {"ms": round(kernel_ms[fwd_name], 4), "tflops": round(fwd_tflops, 2),
                 "frac_of_mfma_peak": round(fwd_tflops / MFMA_BF16_PEAK_TFLOPS, 4)},
         "kernel_ms": {k_: round(v_, 4) for k_, v_ in kernel_ms.items()},
     }
     if w.backward:
         # what tk_attn_bwd launches in this form
         dq_name = "attn_bwd_dq_from_ds_kernel" if spill else "attn_bwd_dq_kernel"
-        bwd_ms = kernel_ms[dq_name] + kernel_ms["attn_bwd_dkdv_kernel"] + (kernel_ms["attn_bwd_delta_kernel"] if spill else 0.0)
+        bwd_ms = kernel_ms[dq_name] + kernel_ms[dkdv_name] + (kernel_ms["attn_bwd_delta_kernel"] if spill else 0.0)
         bwd_tflops = flops_bwd / (bwd_ms * 1e-3) / 1e12
         # the dK/dV kernel executes four of the backward's five products (S, dP, dV, dK: 8*D flops per kept
         # query-key pair); the recomputing dQ kernel three (S, dP, dQ: 6*D), the dQ-from-dS kernel one (2*D)
         dkdv_flops = flops_bwd * 4.0 / 5.0
-        main_tflops = dkdv_flops / (kernel_ms["attn_bwd_dkdv_kernel"] * 1e-3) / 1e12
+        main_tflops = dkdv_flops / (kernel_ms[dkdv_name] * 1e-3) / 1e12
         dq_tflops = flops_bwd * (1.0 if spill else 3.0) / 5.0 / (kernel_ms[dq_name] * 1e-3) / 1e12
         out["bwd"] = {"ms": round(bwd_ms, 4), "tflops": round(bwd_tflops, 2),
                       "frac_of_mfma_peak": round(bwd_tflops / MFMA_BF16_PEAK_TFLOPS, 4)}
@@ -383,13 +386,13 @@ def main():
             ds_read = flops_bwd / (10.0 * D) * 2.0
             out["dq_kernel"]["algorithmic_ds_GBps"] = round(ds_read / (kernel_ms[dq_name] * 1e-3) / 1e9, 1)
             out["dq_kernel"]["frac_of_hbm_peak"] = round(ds_read / (kernel_ms[dq_name] * 1e-3) / 1e9 / HBM_PEAK_GBS, 4)
-        out["roofline"] = {"kernel": "attn_bwd_dkdv_kernel", "bound": "mfma", "achieved": round(main_tflops, 2),
+        out["roofline"] = {"kernel": dkdv_name, "bound": "mfma", "achieved": round(main_tflops, 2),
                            "peak": MFMA_BF16_PEAK_TFLOPS, "unit": "TFLOP/s",
                            "frac": round(main_tflops / MFMA_BF16_PEAK_TFLOPS, 4),
-                           **measured_traffic(w.name + ("" if spill else "/recompute"), "attn_bwd_dkdv_kernel"),
+                           **measured_traffic(w.name + ("" if spill else "/recompute"), dkdv_name),
                            "flops_per_launch": dkdv_flops}
     else:
-        out["roofline"] = {"kernel": "attn_fwd_kernel", "bound": "mfma", "achieved": round(fwd_tflops, 2),
+        out["roofline"] = {"kernel": fwd_name, "bound": "mfma", "achieved": round(fwd_tflops, 2),
                            "peak": MFMA_BF16_PEAK_TFLOPS, "unit": "TFLOP/s",
                            "frac": round(fwd_tflops / MFMA_BF16_PEAK_TFLOPS, 4), "traffic": None}
 
