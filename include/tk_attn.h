@@ -263,11 +263,11 @@ int tk_attn_fwd_rect(const void* q, const void* k, const void* v,
  * split over more workgroups, which leave fp32 partial (O, LSE) pairs in the scratch, and merged.  Results equal
  * tk_attn_fwd_rect's up to fp32 rounding order of the merge, and are bit-reproducible; whether and how the keys are split
  * depends on all sizes of the call and on the number of compute units, so the last bits of a head may change with B and Hq
- * (those of tk_attn_fwd_rect do not).
+ * (those of tk_attn_fwd_rect do not).  The same holds for a few calls that are not split but run on another kernel.
  *
  *   scratch : device memory of tk_attn_fwd_scratch_bytes(...) bytes, 16-byte aligned; contents on entry are
  *             ignored.  NULL or less than that many bytes: the call is tk_attn_fwd_rect.
- * tk_attn_fwd_scratch_bytes returns 0 where the call would not split (on the current device) or would be rejected.
+ * tk_attn_fwd_scratch_bytes returns 0 where the call would be tk_attn_fwd_rect (on the current device) or would be rejected.
  */
 size_t tk_attn_fwd_scratch_bytes(int B, int Hq, int Hkv, int Nq, int Nk, int D, int causal);
 

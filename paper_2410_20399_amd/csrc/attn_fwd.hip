@@ -1111,6 +1111,12 @@ static void combine(const float* o_part, const float* lse_part, void* o, float* 
 // Forward with the keys split n_splits ways (n_splits >= 2, every split holds at least one key:
 // (n_splits - 1) * tiles_per_split * 64 < Nk, tiles_per_split even).  o_part: fp32 [n_splits][B*H][Nq][D],
 // lse_part: fp32 [n_splits][B*H][Nq].
+hipError_t launch_attn_fwd_few_rows(const void* q, const void* k, const void* v, void* o, float* lse,
+                                    int B, int H, int Hkv, int Nq, int Nk, float scale, hipStream_t stream)
+{
+    return launch_fwd_tt<64, true, true, false>(q, k, v, o, lse, B, H, Hkv, Nq, Nk, scale, stream);
+}
+
 hipError_t launch_attn_fwd_splitk(const void* q, const void* k, const void* v, void* o, float* lse,
                                   float* o_part, float* lse_part,
                                   int B, int H, int Hkv, int Nq, int Nk, int D, int causal, float scale,

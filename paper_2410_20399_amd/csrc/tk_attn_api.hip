@@ -193,7 +193,7 @@ double fwd_split_us(int B, int Hq, int Hkv, int Nq, int Nk, int D, int n_splits,
 }
 
 struct FwdPlan {
-    int n_splits, tiles_per_split, groups;
+    int n_splits, tiles_per_split, groups;      // groups 0: launch_attn_fwd_few_rows; otherwise see launch_attn_fwd_splitk
 };
 
 // Nq < Nk only: with equal lengths a head's bits do not depend on how many heads the call has.
@@ -202,6 +202,14 @@ FwdPlan plan_fwd(int B, int Hq, int Hkv, int Nq, int Nk, int D, bool causal, int
     const long long heads = (long long)B * Hq, base = heads * ((Nq + kTileN - 1) / kTileN);
     const int tiles = (Nk + 63) / 64;
     FwdPlan best = {1, tiles + (tiles & 1), 1};
+    // Few rows under the causal mask at D = 64 and more workgroups than the phase kernel has places, three to a compute unit, but not more
+    // than the kernel of few rows has, four: that one, unsplit.  (Here and not in launch_attn_fwd, where a head has the same bits whatever
+    // the number of heads.)  Against the phase kernel, 77 calls of 769 to 1024 workgroups: up to 32 rows 23 % less on average, 33 to 64 rows 16,
+    // 65 to 128 only 4; us B13 Hq64 Hkv8 Nq2 Nk9472 183, 128.  In two parts it takes 5 to 90 % more than unsplit.
+    if (D == 64 && causal && Nq <= 64 && Nq < Nk && Nk > 128 && base > 3LL * compute_units && base <= 4LL * compute_units) {
+        best.groups = 0;
+        return best;
+    }
     if (Nq >= Nk || base > 2LL * compute_units) return best;
     double best_us = fwd_split_us(B, Hq, Hkv, Nq, Nk, D, 1, tiles, 1, compute_units);
     auto consider = [&](int per_unit, int groups, long long row_tiles) {
@@ -243,7 +251,7 @@ size_t tk_attn_fwd_scratch_bytes(int B, int Hq, int Hkv, int Nq, int Nk, int D, 
     int cus = 0;
     if (tk::compute_unit_count(&cus) != hipSuccess || cus < 1) return 0;
     const FwdPlan p = plan_fwd(B, Hq, Hkv, Nq, Nk, D, causal != 0, cus);
-    if (p.n_splits == 1) return 0;
+    if (p.n_splits == 1) return p.groups == 0 ? 256 : 0;     // (it uses none, but whoever hands over none gets tk_attn_fwd_rect's bits)
     const size_t rows = (size_t)B * Hq * Nq;
     return fwd_part_bytes(p.n_splits, rows, D) + fwd_part_bytes(p.n_splits, rows, 1);
 }
@@ -261,6 +269,10 @@ int tk_attn_fwd_rect_scratch(const void* q, const void* k, const void* v, void* 
     int cus = 0;
     if (tk::compute_unit_count(&cus) != hipSuccess) return TK_ERR_LAUNCH;
     const FwdPlan p = plan_fwd(B, Hq, Hkv, Nq, Nk, D, causal != 0, cus);
+    if (p.n_splits == 1) {
+        hipError_t e = tk::launch_attn_fwd_few_rows(q, k, v, o, lse, B, Hq, Hkv, Nq, Nk, scale, (hipStream_t)stream);
+        return e == hipSuccess ? TK_OK : TK_ERR_LAUNCH;
+    }
     float* lse_part = (float*)((char*)scratch + fwd_part_bytes(p.n_splits, (size_t)B * Hq * Nq, D));
     hipError_t e = tk::launch_attn_fwd_splitk(q, k, v, o, lse, (float*)scratch, lse_part, B, Hq, Hkv, Nq, Nk, D, causal != 0, scale,
                                               p.n_splits, p.tiles_per_split, p.groups, (hipStream_t)stream);

@@ -69,6 +69,10 @@ inline int tile_order_heads(int heads, int tiles, bool causal, int D) {
 hipError_t launch_attn_fwd(const void* q, const void* k, const void* v, void* o, float* lse,
                            int B, int H, int Hkv, int Nq, int Nk, int D, int causal, float scale, hipStream_t stream);
 
+// The same with the kernel of few query rows: D = 64, the causal mask, Nq < Nk.
+hipError_t launch_attn_fwd_few_rows(const void* q, const void* k, const void* v, void* o, float* lse,
+                                    int B, int H, int Hkv, int Nq, int Nk, float scale, hipStream_t stream);
+
 // The same forward with the keys split n_splits (>= 2) ways and a merge kernel behind it.  o_part: fp32 [n_splits][B*H][Nq][D]; lse_part: fp32 [n_splits][B*H][Nq];
 // tiles_per_split: even number of 64-key tiles per split, (n_splits - 1) * tiles_per_split * 64 < Nk.  groups: 2 for workgroups of
 // 256 query rows (D = 128, and more than 64 rows or the causal mask), otherwise 1.
